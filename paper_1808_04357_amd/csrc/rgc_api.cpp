@@ -130,6 +130,7 @@ struct CompressPlan {
   hipEvent_t uploaded = nullptr;    // recorded after the uploads
   uint32_t num_wgs = 0;
   uint32_t num_chunks = 0;                 // wave-chunks over all layers
+  uint64_t tensor_bytes = 0;               // gradients, residuals and velocities together
   uint64_t write_bytes = 0;                // what the streaming pass writes (V, and u where there is one)
   uint32_t max_k = 0;                      // the largest k of the list
   bool any_dense = false;                  // some layer is streamed by collect_kernel when it has a hint
@@ -306,6 +307,7 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
   P.num_wgs = wg;
   P.num_chunks = wc;
   P.write_bytes = 0;
+  P.tensor_bytes = 0;
   P.max_k = 0;
   P.any_dense = false;
   P.list_entries = lists;
@@ -313,6 +315,7 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
   for (int32_t l = 0; l < L; ++l) {
     P.any_dense = P.any_dense || desc[l].dense != 0;
     P.write_bytes += static_cast<uint64_t>(layers[l].n) * (layers[l].momentum ? 8u : 4u);
+    P.tensor_bytes += static_cast<uint64_t>(layers[l].n) * (layers[l].momentum ? 12u : 8u);
     P.max_k = std::max(P.max_k, static_cast<uint32_t>(layers[l].k));
   }
   P.valid = true;
@@ -560,6 +563,20 @@ uint32_t streaming_direction(const CompressPlan* plan, uint64_t call) {
   return (plan->write_bytes > kMemorySideCacheBytes) ? static_cast<uint32_t>(call & 1u) : 0u;
 }
 
+// Whether the streaming pass reads and writes V and u past the memory-side cache (nontemporal accesses, as it has always
+// read G), and in the momentum variants asks for four groups of a lane instead of two at a time.  In a training program a
+// forward and a backward pass lie between two calls, and V and u come from HBM whatever the last call left in the cache;
+// the stores' lines then only have to be evicted again.  Measured per call with a velocity, plain / past the cache:
+// three contexts taking turns 16 Mi elements (192 MB of tensors) 99 / 86 us, 48 Mi 259 / 216 us, VGG16 set 656 / 571 us;
+// 2 GB of other traffic between the calls 101 / 90, 243 / 225 us.  Below the line the caches hold the call's tensors and
+// the two are the same (8 Mi, 96 MB: 54 / 54 us; without a velocity 16 Mi, 128 MB: 59 / 63 us).  A call that will read
+// the residual again (`again`: it has no hints) leaves it in the cache if it fits there.
+constexpr uint64_t kPastCacheBytes = 128ull << 20;
+uint32_t stream_past_cache(const CompressPlan* plan, bool again) {
+  if (again && plan->write_bytes <= kMemorySideCacheBytes) return 0u;
+  return plan->tensor_bytes > kPastCacheBytes ? 1u : 0u;
+}
+
 void fill_plan_args(rgc_ctx* ctx, const CompressPlan* plan, CompressArgs& A) {
   A.layers = plan->d_layers.p;
   A.wg2layer = plan->d_wg2layer.p;
@@ -652,6 +669,7 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   // A searching call passes over the tensors four times and ends where it began; a reusing call passes once:
   // the call after it starts from the end it stopped at, whose data the memory-side cache still holds.
   const bool alternate = plan->write_bytes > kMemorySideCacheBytes;
+  A.past_cache = stream_past_cache(plan, A.search != 0u);
   A.reverse = alternate ? ctx->threshold_reverse : 0u;
   RGC_HIP(launch_threshold_compress(A, plan->num_wgs, static_cast<uint32_t>(num_layers), stream));
   if (!A.search) ctx->threshold_reverse ^= 1u;
@@ -736,6 +754,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.slots_u = ctx->d_slots_u.p;
   A.members2 = ctx->d_members2.p;
   A.shard_cnt = ctx->d_shards.p;
+  A.past_cache = stream_past_cache(plan, A.use_hints == 0u);
   A.reverse = streaming_direction(plan, ctx->compress_calls);
   ++ctx->compress_calls;
   ctx->compressed_since_decompress = true;

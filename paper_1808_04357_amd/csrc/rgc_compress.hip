@@ -157,7 +157,7 @@ __device__ __forceinline__ uint32_t zero_bin(uint32_t sign_xor, uint32_t sign_fi
 }
 
 // Streaming pass over one wave-chunk [begin, end) of a layer.
-template <bool kMom, bool kCollect, bool kNest = false>
+template <bool kNt, bool kMom, bool kCollect, bool kNest = false>
 __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin, uint32_t end,
                                              const AccumRule m, Collector& c, uint32_t* lds_hist) {
   const uint32_t lane = lane_id();
@@ -168,7 +168,7 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
     const gptr<const vf4> G4 = as_global(reinterpret_cast<const vf4*>(L.grad + begin));
     const gptr<vf4> V4 = as_global(reinterpret_cast<vf4*>(L.resid + begin));
     const gptr<vf4> U4 = as_global(kMom ? reinterpret_cast<vf4*>(L.mom + begin) : nullptr);
-    constexpr uint32_t kUnroll = kMom ? 2u : 4u;   // 16-byte loads in flight per lane: 6 or 8
+    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;   // 16-byte loads in flight per lane: 6, 8 or 12
     uint32_t g = 0;
     for (; g + kUnroll <= nfull; g += kUnroll) {
       vf4 gv[kUnroll], vv[kUnroll], uv[kUnroll];
@@ -176,8 +176,8 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
       for (uint32_t t = 0; t < kUnroll; ++t) {
         const uint32_t o = (g + t) * kWaveSize + lane;
         gv[t] = __builtin_nontemporal_load(&G4[o]);
-        vv[t] = V4[o];
-        if constexpr (kMom) uv[t] = U4[o];
+        vv[t] = stream_load<kNt>(V4 + o);
+        if constexpr (kMom) uv[t] = stream_load<kNt>(U4 + o);
       }
 #pragma unroll
       for (uint32_t t = 0; t < kUnroll; ++t) {
@@ -188,23 +188,23 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
         if constexpr (kMom) { uu[0] = uv[t].x; uu[1] = uv[t].y; uu[2] = uv[t].z; uu[3] = uv[t].w; }
         float a[4];
         accum4<kMom, kNest>(gg, vvv, uu, m, a);
-        V4[o] = vf4{a[0], a[1], a[2], a[3]};
-        if constexpr (kMom) U4[o] = vf4{uu[0], uu[1], uu[2], uu[3]};
+        stream_store<kNt>(V4 + o, vf4{a[0], a[1], a[2], a[3]});
+        if constexpr (kMom) stream_store<kNt>(U4 + o, vf4{uu[0], uu[1], uu[2], uu[3]});
         consume<kCollect>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
       }
     }
     for (; g < nfull; ++g) {
       const uint32_t o = g * kWaveSize + lane;
       const vf4 gq = __builtin_nontemporal_load(&G4[o]);
-      const vf4 vq = V4[o];
+      const vf4 vq = stream_load<kNt>(V4 + o);
       const float gg[4] = {gq.x, gq.y, gq.z, gq.w};
       const float vvv[4] = {vq.x, vq.y, vq.z, vq.w};
       float uu[4] = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (kMom) { const vf4 uq = U4[o]; uu[0] = uq.x; uu[1] = uq.y; uu[2] = uq.z; uu[3] = uq.w; }
+      if constexpr (kMom) { const vf4 uq = stream_load<kNt>(U4 + o); uu[0] = uq.x; uu[1] = uq.y; uu[2] = uq.z; uu[3] = uq.w; }
       float a[4];
       accum4<kMom, kNest>(gg, vvv, uu, m, a);
-      V4[o] = vf4{a[0], a[1], a[2], a[3]};
-      if constexpr (kMom) U4[o] = vf4{uu[0], uu[1], uu[2], uu[3]};
+      stream_store<kNt>(V4 + o, vf4{a[0], a[1], a[2], a[3]});
+      if constexpr (kMom) stream_store<kNt>(U4 + o, vf4{uu[0], uu[1], uu[2], uu[3]});
       consume<kCollect>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
     }
     base = begin + nfull * kGroupElems;
@@ -704,6 +704,7 @@ __device__ __forceinline__ unsigned long long composite(uint32_t key, uint32_t i
 }  // namespace
 
 // =================================================================== launch 1: streaming pass
+template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs A) {
   __shared__ uint32_t lds_hist[kHistBins];
   __shared__ ResolveShared sh;
@@ -741,14 +742,14 @@ __global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs 
     rule.m = A.m;
     rule.scale = A.grad_scale ? *as_global(A.grad_scale) : 1.0f;
     if (collect) {
-      if (!mom) stream_chunk<false, true>(L, begin, end, rule, c, lds_hist);
-      else if (!A.nesterov) stream_chunk<true, true>(L, begin, end, rule, c, lds_hist);
-      else stream_chunk<true, true, true>(L, begin, end, rule, c, lds_hist);
+      if (!mom) stream_chunk<kNt, false, true>(L, begin, end, rule, c, lds_hist);
+      else if (!A.nesterov) stream_chunk<kNt, true, true>(L, begin, end, rule, c, lds_hist);
+      else stream_chunk<kNt, true, true, true>(L, begin, end, rule, c, lds_hist);
       if (lane_id() == 0) st_agent(&A.cand_cnt[L.wc_first + wc_local], c.count);
     } else {
-      if (!mom) stream_chunk<false, false>(L, begin, end, rule, c, lds_hist);
-      else if (!A.nesterov) stream_chunk<true, false>(L, begin, end, rule, c, lds_hist);
-      else stream_chunk<true, false, true>(L, begin, end, rule, c, lds_hist);
+      if (!mom) stream_chunk<kNt, false, false>(L, begin, end, rule, c, lds_hist);
+      else if (!A.nesterov) stream_chunk<kNt, true, false>(L, begin, end, rule, c, lds_hist);
+      else stream_chunk<kNt, true, false, true>(L, begin, end, rule, c, lds_hist);
     }
   }
   __syncthreads();
@@ -1335,7 +1336,7 @@ __device__ __forceinline__ void list_dense(const float (&a)[4], const float (&u)
 
 // Streaming pass over one wave-chunk [begin, end) of a dense layer that has a hint: stream_chunk's loop, with the
 // candidates far above the hinted threshold masked on the way.
-template <bool kMom, bool kNest>
+template <bool kNt, bool kMom, bool kNest>
 __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t begin, uint32_t end, const AccumRule m,
                                                    bool clear_mom, Collector& c, DenseChunk& dc) {
   const uint32_t lane = lane_id();
@@ -1345,7 +1346,7 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
     const gptr<const vf4> G4 = as_global(reinterpret_cast<const vf4*>(L.grad + begin));
     const gptr<vf4> V4 = as_global(reinterpret_cast<vf4*>(L.resid + begin));
     const gptr<vf4> U4 = as_global(kMom ? reinterpret_cast<vf4*>(L.mom + begin) : nullptr);
-    constexpr uint32_t kUnroll = kMom ? 2u : 4u;
+    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;
     auto group = [&](const vf4& gq, const vf4& vq, const vf4& uq, uint32_t o) __attribute__((always_inline)) {
       const float gg[4] = {gq.x, gq.y, gq.z, gq.w};
       const float vvv[4] = {vq.x, vq.y, vq.z, vq.w};
@@ -1357,10 +1358,10 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
       uint32_t key[4];
       bool masked[4];
       masked_dense(a, 4u, c, dc, key, masked);
-      V4[o] = vf4{masked[0] ? 0.0f : a[0], masked[1] ? 0.0f : a[1], masked[2] ? 0.0f : a[2], masked[3] ? 0.0f : a[3]};
+      stream_store<kNt>(V4 + o, vf4{masked[0] ? 0.0f : a[0], masked[1] ? 0.0f : a[1], masked[2] ? 0.0f : a[2], masked[3] ? 0.0f : a[3]});
       if constexpr (kMom)
-        U4[o] = vf4{(masked[0] && clear_mom) ? 0.0f : uu[0], (masked[1] && clear_mom) ? 0.0f : uu[1],
-                    (masked[2] && clear_mom) ? 0.0f : uu[2], (masked[3] && clear_mom) ? 0.0f : uu[3]};
+        stream_store<kNt>(U4 + o, vf4{(masked[0] && clear_mom) ? 0.0f : uu[0], (masked[1] && clear_mom) ? 0.0f : uu[1],
+                                      (masked[2] && clear_mom) ? 0.0f : uu[2], (masked[3] && clear_mom) ? 0.0f : uu[3]});
       if (!dc.overflow) list_dense(a, uu, key, 4u, begin + o * 4u, c, dc);
     };
     uint32_t g = 0;
@@ -1370,8 +1371,8 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
       for (uint32_t t = 0; t < kUnroll; ++t) {
         const uint32_t o = (g + t) * kWaveSize + lane;
         gv[t] = __builtin_nontemporal_load(&G4[o]);
-        vv[t] = V4[o];
-        if constexpr (kMom) uv[t] = U4[o];
+        vv[t] = stream_load<kNt>(V4 + o);
+        if constexpr (kMom) uv[t] = stream_load<kNt>(U4 + o);
       }
 #pragma unroll
       for (uint32_t t = 0; t < kUnroll; ++t) group(gv[t], vv[t], uv[t], (g + t) * kWaveSize + lane);
@@ -1379,9 +1380,9 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
     for (; g < nfull; ++g) {
       const uint32_t o = g * kWaveSize + lane;
       const vf4 gq = __builtin_nontemporal_load(&G4[o]);
-      const vf4 vq = V4[o];
+      const vf4 vq = stream_load<kNt>(V4 + o);
       vf4 uq = vf4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (kMom) uq = U4[o];
+      if constexpr (kMom) uq = stream_load<kNt>(U4 + o);
       group(gq, vq, uq, o);
     }
     base = begin + nfull * kGroupElems;
@@ -1426,6 +1427,7 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
 }  // namespace
 
 // Launch 1 for the dense layers that have a hint (accumulate_kernel leaves exactly these out).
+template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) {
   __shared__ uint32_t lds_hist[kCoarseBins];
   __shared__ ResolveShared sh;
@@ -1471,9 +1473,9 @@ __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) 
     AccumRule rule;
     rule.m = A.m;
     rule.scale = A.grad_scale ? *as_global(A.grad_scale) : 1.0f;
-    if (!mom) stream_chunk_dense<false, false>(L, begin, end, rule, clear_mom, c, dc);
-    else if (!A.nesterov) stream_chunk_dense<true, false>(L, begin, end, rule, clear_mom, c, dc);
-    else stream_chunk_dense<true, true>(L, begin, end, rule, clear_mom, c, dc);
+    if (!mom) stream_chunk_dense<kNt, false, false>(L, begin, end, rule, clear_mom, c, dc);
+    else if (!A.nesterov) stream_chunk_dense<kNt, true, false>(L, begin, end, rule, clear_mom, c, dc);
+    else stream_chunk_dense<kNt, true, true>(L, begin, end, rule, clear_mom, c, dc);
     const uint32_t certain = wave_total(wave_incl_scan(dc.certain));
     if (lane_id() == 0) {
       // (a list that stopped early says so, and where: nothing was listed or masked after that entry)
@@ -2125,12 +2127,14 @@ hipError_t launch_message_means(const CompressArgs& a, uint32_t num_layers, uint
 }
 
 hipError_t launch_accumulate(const CompressArgs& a, uint32_t num_wgs, hipStream_t s) {
-  hipLaunchKernelGGL(accumulate_kernel, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
+  if (a.past_cache) hipLaunchKernelGGL(accumulate_kernel<true>, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
+  else hipLaunchKernelGGL(accumulate_kernel<false>, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_collect(const CompressArgs& a, uint32_t num_wgs, hipStream_t s) {
-  hipLaunchKernelGGL(collect_kernel, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
+  if (a.past_cache) hipLaunchKernelGGL(collect_kernel<true>, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
+  else hipLaunchKernelGGL(collect_kernel<false>, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -124,6 +124,17 @@ __device__ __forceinline__ uint32_t fbits(float x) { return __float_as_uint(x); 
 
 typedef float vf4 __attribute__((ext_vector_type(4)));   // one 16-byte access per lane
 
+// One access of the streaming passes to the residual and the velocity.  kNt: past the memory-side cache, for calls
+// whose tensors do not stay in it until the next call anyway (see stream_past_cache() in rgc_api.cpp).
+template <bool kNt, typename T>
+__device__ __forceinline__ T stream_load(gptr<T> p) {
+  if constexpr (kNt) return __builtin_nontemporal_load(p); else return *p;
+}
+template <bool kNt, typename T>
+__device__ __forceinline__ void stream_store(gptr<T> p, T v) {
+  if constexpr (kNt) __builtin_nontemporal_store(v, p); else *p = v;
+}
+
 // The accumulate of Algorithm 1 and its variants (Sections 2.4, 2.5): every gradient element is
 // first multiplied with the clipping coefficient (1 when there is none: an exact product), then
 //   plain:                a = V + g

@@ -110,7 +110,7 @@ __device__ __forceinline__ void read_groups(const float* generic_p, bool vec, ui
 // The accumulate of Algorithm 1 over [begin, end) of a layer (same arithmetic as the exact path:
 // accum4), handing every group of accumulated values to f.  Whole groups of an aligned layer are
 // taken four (two with a velocity) at a time, all their loads issued before the first use.
-template <bool kMom, bool kNest, typename F>
+template <bool kNt, bool kMom, bool kNest, typename F>
 __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t begin, uint32_t end, const AccumRule& rule, F&& f) {
   const gptr<const float> G = as_global(L.grad);
   const gptr<float> V = as_global(L.resid);
@@ -118,15 +118,15 @@ __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t b
   const uint32_t lane = lane_id();
   uint32_t base = begin;
   if (L.vec_ok) {
-    constexpr uint32_t kUnroll = kMom ? 2u : 4u;
+    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;
     for (; base + kUnroll * kGroupElems <= end; base += kUnroll * kGroupElems) {
       vf4 gq[kUnroll], vq[kUnroll], uq[kUnroll];
 #pragma unroll
       for (uint32_t t = 0; t < kUnroll; ++t) {
         const uint32_t idx0 = base + t * kGroupElems + lane * 4u;
         gq[t] = __builtin_nontemporal_load(reinterpret_cast<gptr<const vf4>>(G + idx0));
-        vq[t] = *reinterpret_cast<gptr<const vf4>>(V + idx0);
-        if constexpr (kMom) uq[t] = *reinterpret_cast<gptr<const vf4>>(U + idx0);
+        vq[t] = stream_load<kNt>(reinterpret_cast<gptr<vf4>>(V + idx0));
+        if constexpr (kMom) uq[t] = stream_load<kNt>(reinterpret_cast<gptr<vf4>>(U + idx0));
       }
 #pragma unroll
       for (uint32_t t = 0; t < kUnroll; ++t) {
@@ -136,8 +136,8 @@ __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t b
         float u[4] = {0.f, 0.f, 0.f, 0.f}, a[4];
         if constexpr (kMom) { u[0] = uq[t].x; u[1] = uq[t].y; u[2] = uq[t].z; u[3] = uq[t].w; }
         accum4<kMom, kNest>(g, v, u, rule, a);
-        *reinterpret_cast<gptr<vf4>>(V + idx0) = vf4{a[0], a[1], a[2], a[3]};
-        if constexpr (kMom) *reinterpret_cast<gptr<vf4>>(U + idx0) = vf4{u[0], u[1], u[2], u[3]};
+        stream_store<kNt>(reinterpret_cast<gptr<vf4>>(V + idx0), vf4{a[0], a[1], a[2], a[3]});
+        if constexpr (kMom) stream_store<kNt>(reinterpret_cast<gptr<vf4>>(U + idx0), vf4{u[0], u[1], u[2], u[3]});
         f(a, 4u, idx0);
       }
     }
@@ -155,8 +155,8 @@ __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t b
         u[0] = uq.x; u[1] = uq.y; u[2] = uq.z; u[3] = uq.w;
       }
       accum4<kMom, kNest>(g, v, u, rule, a);
-      *reinterpret_cast<gptr<vf4>>(V + idx0) = vf4{a[0], a[1], a[2], a[3]};
-      if constexpr (kMom) *reinterpret_cast<gptr<vf4>>(U + idx0) = vf4{u[0], u[1], u[2], u[3]};
+      stream_store<kNt>(reinterpret_cast<gptr<vf4>>(V + idx0), vf4{a[0], a[1], a[2], a[3]});
+      if constexpr (kMom) stream_store<kNt>(reinterpret_cast<gptr<vf4>>(U + idx0), vf4{u[0], u[1], u[2], u[3]});
       f(a, 4u, idx0);
     } else {
       const uint32_t nvalid = idx0 < end ? ((end - idx0) < 4u ? (end - idx0) : 4u) : 0u;
@@ -194,7 +194,7 @@ __device__ __forceinline__ float wave_max(float x) {
 // (rgc_exact.h) and the maximum of |a|.
 // kCount = true (the threshold is given): leaves per wave-chunk the number of |a| > threshold and, in
 // the wave-chunk's list, those elements themselves (as many as the list holds).
-template <bool kCount, bool kReverse>
+template <bool kNt, bool kCount, bool kReverse>
 __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(ThresholdArgs A) {
   __shared__ ExactShared sh;
   __shared__ float wave_mx[kWavesPerBlock];
@@ -244,9 +244,9 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
     AccumRule rule;
     rule.m = A.m;
     rule.scale = A.grad_scale ? *as_global(A.grad_scale) : 1.0f;
-    if (L.mom == nullptr) accumulate_groups<false, false>(L, p.begin, p.end, rule, take);
-    else if (!A.nesterov) accumulate_groups<true, false>(L, p.begin, p.end, rule, take);
-    else accumulate_groups<true, true>(L, p.begin, p.end, rule, take);
+    if (L.mom == nullptr) accumulate_groups<kNt, false, false>(L, p.begin, p.end, rule, take);
+    else if (!A.nesterov) accumulate_groups<kNt, true, false>(L, p.begin, p.end, rule, take);
+    else accumulate_groups<kNt, true, true>(L, p.begin, p.end, rule, take);
     if constexpr (kCount) {
       if (lane_id() == 0u) {
         A.counts[p.wc] = cnt;
@@ -497,7 +497,7 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
   // Each pass over the tensors runs against the direction of the one before it: what that one touched last
   // (still in the memory-side cache) is read first.  a.reverse turns the whole sequence round.
   if (a.search) {
-    hipLaunchKernelGGL((threshold_accumulate_kernel<false, false>), dim3(num_wgs), block, 0, s, a);
+    hipLaunchKernelGGL((threshold_accumulate_kernel<false, false, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_moments_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
@@ -511,7 +511,8 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
     RGC_LAUNCHED();
     hipLaunchKernelGGL((threshold_emit_kernel<true, false>), dim3(num_wgs), block, 0, s, a);
   } else {
-    hipLaunchKernelGGL((threshold_accumulate_kernel<true, false>), dim3(num_wgs), block, 0, s, a);
+    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, true, false>), dim3(num_wgs), block, 0, s, a);
+    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, true, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();

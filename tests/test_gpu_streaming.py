@@ -1,0 +1,46 @@
+"""GPU parity of the streaming pass at the sizes where its way through the memory changes (bit equality with the oracle)."""
+import numpy as np
+import pytest
+
+from rgc_testutil import GpuLayers, assert_layers_equal, oracle_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rgc():
+    import paper_1808_04357_amd as m
+    return m
+
+
+def _run(rgc, oracle, sizes, momentum, ppm=1000, misalign=0, steps=3, flags=0, nesterov=False, seed=11):
+    from paper_1808_04357_amd import synth
+    g = synth.rng(seed, sum(sizes) & 0xFFFF)
+    V = [synth.normal(g, n, 5e-3) for n in sizes]
+    U = [synth.normal(g, n, 1e-3) for n in sizes] if momentum else None
+    ks = [rgc.rgc_k_for_density(n, ppm) for n in sizes]
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    gl = GpuLayers(rgc, V, ks, U, misalign=misalign)
+    Vh = [v.copy() for v in V]
+    Uh = [u.copy() for u in U] if U is not None else None
+    for t in range(steps):
+        G = [synth.normal(g, n, 1e-3) for n in sizes]
+        gl.set_grads(G)
+        gl.step(ctx, 0.9, flags | (rgc.RGC_NESTEROV if nesterov else 0))
+        ref = oracle_step(oracle, G, Vh, ks, Uh, 0.9, nesterov=nesterov, threads=8)
+        assert_layers_equal("step %d" % t, ks, gl.results(), ref, Vh, Uh)
+    ctx.last_error()
+    ctx.close()
+
+
+# tensors of 128 MiB together are the line between the cached accesses and those past the memory-side cache
+@pytest.mark.parametrize("extra", [0, 1, 1025])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_both_sides_of_the_cache_line(rgc, oracle, momentum, extra):
+    n = (128 << 20) // (12 if momentum else 8)
+    _run(rgc, oracle, [n - 3000 + extra, 3000], momentum)
+
+
+@pytest.mark.parametrize("momentum,nesterov,ppm", [(True, True, 1000), (True, False, 62500), (False, False, 250000)])
+def test_past_the_cache_variants(rgc, oracle, momentum, nesterov, ppm):
+    _run(rgc, oracle, [17_000_003, 8192 * 4 + 255], momentum, ppm=ppm, nesterov=nesterov)
