@@ -75,7 +75,7 @@ typedef struct rgc_ctx rgc_ctx; /* opaque */
 /* One layer of a compression call (host struct holding device pointers).
  * Section 2, Algorithm 1: G_j is `grad`, V_j is `residual`; Section 2.5 names the
  * momentum-corrected variant, whose velocity is `momentum`.  Tensors are flat, contiguous
- * fp32; only 4-byte alignment is required (16-byte aligned tensors take the fast loads). */
+ * fp32; only 4-byte alignment is required. */
 typedef struct {
   const float* grad;      /* [n] read only                                                  */
   float*       residual;  /* [n] in/out: V on entry, masked V + G (or V + u) on return      */

@@ -233,9 +233,6 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     grp += (d.wg_count + kElectGroupHost - 1) / kElectGroupHost;
     d.mem_cap = 0;
     d.mem_first = 0;
-    const uintptr_t bits = reinterpret_cast<uintptr_t>(in.grad) | reinterpret_cast<uintptr_t>(in.residual) |
-                           reinterpret_cast<uintptr_t>(in.momentum);
-    d.vec_ok = (bits & 15u) == 0 ? 1u : 0u;
     // speed-hint policy: aim the threshold at rank 2k + margin of this call, accept up to cmax
     const uint64_t k = d.k;
     uint64_t margin = std::max<uint64_t>(k / 2, 32);
@@ -254,7 +251,6 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     d.dense = 0;
     d.list_cap = 0;
     d.list_first = 0;
-    d.pad_ = 0;
     if (!d.hintable) {
       // High densities (the warm-up period of Section 2.5): the short lists of the one-pass path cannot hold every
       // element from the threshold upwards.  Such a layer gets lists of its own, long enough for twice the number of

@@ -163,11 +163,11 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
   const uint32_t lane = lane_id();
   uint32_t zeros = 0;
   uint32_t base = begin;
-  if (L.vec_ok) {
+  {
     const uint32_t nfull = (end - begin) / kGroupElems;
-    const gptr<const vf4> G4 = as_global(reinterpret_cast<const vf4*>(L.grad + begin));
-    const gptr<vf4> V4 = as_global(reinterpret_cast<vf4*>(L.resid + begin));
-    const gptr<vf4> U4 = as_global(kMom ? reinterpret_cast<vf4*>(L.mom + begin) : nullptr);
+    const gcvf4 G4 = as_vec(L.grad + begin);
+    const gvf4 V4 = as_vec(L.resid + begin);
+    const gvf4 U4 = kMom ? as_vec(L.mom + begin) : nullptr;
     constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;   // 16-byte loads in flight per lane: 6, 8 or 12
     uint32_t g = 0;
     for (; g + kUnroll <= nfull; g += kUnroll) {
@@ -209,7 +209,7 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
     }
     base = begin + nfull * kGroupElems;
   }
-  // scalar groups: the ragged tail of an aligned layer, or every group of an unaligned one
+  // the ragged tail, a word at a time
   const gptr<const float> Gs = as_global(L.grad);
   const gptr<float> Vs = as_global(L.resid);
   const gptr<float> Us = as_global(L.mom);
@@ -244,16 +244,15 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
 // Read-only walk over one wave-chunk of the updated residual, four elements per lane per step,
 // same element order as the streaming pass.  f(a[4], nvalid, idx0) must be wave-uniform code.
 template <typename F>
-__device__ __forceinline__ void for_each_group(const float* generic_p, bool vec, uint32_t begin,
-                                               uint32_t end, F&& f) {
+__device__ __forceinline__ void for_each_group(const float* generic_p, uint32_t begin, uint32_t end, F&& f) {
   const gptr<const float> p = as_global(generic_p);
   const uint32_t lane = lane_id();
   for (uint32_t base = begin; base < end; base += kGroupElems) {
     const uint32_t idx0 = base + lane * 4u;
     float a[4] = {0.f, 0.f, 0.f, 0.f};
     uint32_t nvalid;
-    if (vec && base + kGroupElems <= end) {
-      const vf4 q = *reinterpret_cast<gptr<const vf4>>(p + idx0);
+    if (base + kGroupElems <= end) {
+      const vf4 q = *as_vec(generic_p + idx0);
       a[0] = q.x; a[1] = q.y; a[2] = q.z; a[3] = q.w;
       nvalid = 4u;
     } else {
@@ -813,7 +812,7 @@ __device__ void phase_hist(const CompressArgs& A, uint32_t l, const LayerDesc& L
     const uint32_t begin = wc_local * A.chunk;
     const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
     uint32_t zeros = 0;
-    for_each_group(L.resid, L.vec_ok != 0u, begin, end,
+    for_each_group(L.resid, begin, end,
                    [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
 #pragma unroll
                      for (int j = 0; j < 4; ++j) {
@@ -856,7 +855,7 @@ __device__ void phase_collect(const CompressArgs& A, uint32_t l, const LayerDesc
     c.sign_xor = A.sign_xor;
     c.sign_filter = A.sign_filter;
     uint32_t zeros = 0;
-    for_each_group(L.resid, L.vec_ok != 0u, begin, end,
+    for_each_group(L.resid, begin, end,
                    [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
                      consume<true>(a, nvalid, idx0, c, lds_hist, zeros);
                    });
@@ -876,7 +875,7 @@ __device__ void phase_count(const CompressArgs& A, uint32_t l, const LayerDesc& 
     const uint32_t begin = wc_local * A.chunk;
     const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
     uint32_t gt = 0, eq = 0;
-    for_each_group(L.resid, L.vec_ok != 0u, begin, end,
+    for_each_group(L.resid, begin, end,
                    [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
 #pragma unroll
                      for (int j = 0; j < 4; ++j) {
@@ -917,7 +916,7 @@ __device__ void phase_out_v(const CompressArgs& A, const LayerDesc& L, LayerStat
   const gptr<float> out_val = as_global(L.out_val);
   const gptr<float> resid = as_global(L.resid);
   const gptr<float> mom = as_global(L.mom);
-  for_each_group(L.resid, L.vec_ok != 0u, begin, end,
+  for_each_group(L.resid, begin, end,
                  [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
                    bool gt[4], eq[4];
 #pragma unroll
@@ -1341,11 +1340,11 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
                                                    bool clear_mom, Collector& c, DenseChunk& dc) {
   const uint32_t lane = lane_id();
   uint32_t base = begin;
-  if (L.vec_ok) {
+  {
     const uint32_t nfull = (end - begin) / kGroupElems;
-    const gptr<const vf4> G4 = as_global(reinterpret_cast<const vf4*>(L.grad + begin));
-    const gptr<vf4> V4 = as_global(reinterpret_cast<vf4*>(L.resid + begin));
-    const gptr<vf4> U4 = as_global(kMom ? reinterpret_cast<vf4*>(L.mom + begin) : nullptr);
+    const gcvf4 G4 = as_vec(L.grad + begin);
+    const gvf4 V4 = as_vec(L.resid + begin);
+    const gvf4 U4 = kMom ? as_vec(L.mom + begin) : nullptr;
     constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;
     auto group = [&](const vf4& gq, const vf4& vq, const vf4& uq, uint32_t o) __attribute__((always_inline)) {
       const float gg[4] = {gq.x, gq.y, gq.z, gq.w};
@@ -1387,7 +1386,7 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
     }
     base = begin + nfull * kGroupElems;
   }
-  // scalar groups: the ragged tail of an aligned layer, or every group of an unaligned one
+  // the ragged tail, a word at a time
   const gptr<const float> Gs = as_global(L.grad);
   const gptr<float> Vs = as_global(L.resid);
   const gptr<float> Us = as_global(L.mom);
@@ -1931,9 +1930,9 @@ template <bool kCareful>
 __device__ __forceinline__ void squares_of_chunk(const float* grad, uint32_t begin, uint32_t end, SquareSums& S, long long* digits) {
   const uint32_t lane = lane_id();
   uint32_t base = begin;
-  if ((reinterpret_cast<uintptr_t>(grad) & 15u) == 0u) {
+  {
     // whole groups of 64 x 4 elements, eight 16-byte loads of a lane in flight
-    const gptr<const vf4> G4 = as_global(reinterpret_cast<const vf4*>(grad + begin));
+    const gcvf4 G4 = as_vec(grad + begin);
     const uint32_t nfull = (end - begin) / kGroupElems;
     uint32_t g = 0;
     for (; g + 8u <= nfull; g += 8u) {
@@ -1950,7 +1949,7 @@ __device__ __forceinline__ void squares_of_chunk(const float* grad, uint32_t beg
     }
     base = begin + g * kGroupElems;
   }
-  for_each_group(grad, false, base, end,
+  for_each_group(grad, base, end,
                  [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
 #pragma unroll
                    for (int j = 0; j < 4; ++j) {

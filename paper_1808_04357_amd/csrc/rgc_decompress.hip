@@ -36,7 +36,7 @@ constexpr uint32_t kWords = kTile / 32;                 // words of a one-bit-pe
 
 typedef uint32_t vu2l __attribute__((ext_vector_type(2)));
 typedef uint32_t vu4l __attribute__((ext_vector_type(4)));
-typedef float vf4 __attribute__((ext_vector_type(4)));
+typedef float vf4a __attribute__((ext_vector_type(4)));
 
 struct TileGeom {          // one tile, derived arithmetically from its layer
   float* dense;            // start of the tile
@@ -237,15 +237,15 @@ __device__ __forceinline__ void write_tile(const GenericLds& S, const TileGeom& 
   const gptr<float> d = as_global(g.dense);
   const bool vec = ((reinterpret_cast<uintptr_t>(g.dense) & 15u) == 0u) && ((g.len & 3u) == 0u);
   if (vec) {
-    const gptr<vf4> d4 = as_global(reinterpret_cast<vf4*>(g.dense));
+    const gptr<vf4a> d4 = as_global(reinterpret_cast<vf4a*>(g.dense));
     for (uint32_t i = tid; i < g.len / 4u; i += kBlockThreads) {
-      vf4 o;
+      vf4a o;
       o.x = __fmul_rn(S.acc[4 * i + 0], scale);
       o.y = __fmul_rn(S.acc[4 * i + 1], scale);
       o.z = __fmul_rn(S.acc[4 * i + 2], scale);
       o.w = __fmul_rn(S.acc[4 * i + 3], scale);
       if (add_to_dst) {
-        const vf4 old = d4[i];
+        const vf4a old = d4[i];
         o.x = __fadd_rn(old.x, o.x); o.y = __fadd_rn(old.y, o.y);
         o.z = __fadd_rn(old.z, o.z); o.w = __fadd_rn(old.w, o.w);
       }
@@ -647,14 +647,14 @@ decompress_tiles_kernel(DecompressArgs A) {
             const uint32_t p = S.run_p[row];
             S.rows[row * kRowStride + S.who[p]] = S.acc[p];   // the position's first arrival (it may be there already)
           }
-          const vf4* const r4 = reinterpret_cast<const vf4*>(S.rows + row * kRowStride);
+          const vf4a* const r4 = reinterpret_cast<const vf4a*>(S.rows + row * kRowStride);
           float sum = 0.0f;
           uint32_t gi = 0;
-          vf4 c0 = r4[0], c1 = r4[1];            // the next eight slots are on their way while these are added
+          vf4a c0 = r4[0], c1 = r4[1];            // the next eight slots are on their way while these are added
           for (;;) {
             gi += 2u;
             const bool again = gi < row_groups;
-            vf4 n0 = c0, n1 = c1;
+            vf4a n0 = c0, n1 = c1;
             if (again) { n0 = r4[gi]; n1 = r4[gi + 1u]; }
             sum = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(sum, c0.x), c0.y), c0.z), c0.w);
             sum = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(sum, c1.x), c1.y), c1.z), c1.w);
@@ -666,7 +666,7 @@ decompress_tiles_kernel(DecompressArgs A) {
         __syncthreads();
         // the rows go back to +0
         for (uint32_t i = row; i < count * (kRowStride / 4u); i += kFastThreads)
-          reinterpret_cast<vf4*>(S.rows)[i] = vf4{0.0f, 0.0f, 0.0f, 0.0f};
+          reinterpret_cast<vf4a*>(S.rows)[i] = vf4a{0.0f, 0.0f, 0.0f, 0.0f};
       };
       // run f(position, value) over this lane's entries inside the tile
       auto for_my_entries = [&](auto&& f) {
@@ -761,19 +761,19 @@ decompress_tiles_kernel(DecompressArgs A) {
       const bool vec = ((reinterpret_cast<uintptr_t>(g.dense) & 15u) == 0u) && ((g.len & 3u) == 0u);
       const uint32_t out_tid = fresh_tid();
       if (vec) {
-        const gptr<vf4> d4 = as_global(reinterpret_cast<vf4*>(g.dense));
-        vf4* const acc4 = reinterpret_cast<vf4*>(S.acc);
+        const gptr<vf4a> d4 = as_global(reinterpret_cast<vf4a*>(g.dense));
+        vf4a* const acc4 = reinterpret_cast<vf4a*>(S.acc);
 #pragma unroll
         for (uint32_t j = 0; j < static_cast<uint32_t>(kTile) / (4u * kFastThreads); ++j) {
           const uint32_t i4 = out_tid + j * kFastThreads;
           if (4u * i4 < g.len) {
-            const vf4 a = acc4[i4];
-            acc4[i4] = vf4{0.0f, 0.0f, 0.0f, 0.0f};
-            vf4 o;
+            const vf4a a = acc4[i4];
+            acc4[i4] = vf4a{0.0f, 0.0f, 0.0f, 0.0f};
+            vf4a o;
             o.x = __fmul_rn(a.x, A.scale); o.y = __fmul_rn(a.y, A.scale);
             o.z = __fmul_rn(a.z, A.scale); o.w = __fmul_rn(a.w, A.scale);
             if (A.add_to_dst) {
-              const vf4 old = d4[i4];
+              const vf4a old = d4[i4];
               o.x = __fadd_rn(old.x, o.x); o.y = __fadd_rn(old.y, o.y);
               o.z = __fadd_rn(old.z, o.z); o.w = __fadd_rn(old.w, o.w);
             }

@@ -122,16 +122,25 @@ __device__ __forceinline__ bool last_block_of_layer(uint32_t* layer_done, uint32
 // ---------------------------------------------------------------- shared by every pass over a layer
 __device__ __forceinline__ uint32_t fbits(float x) { return __float_as_uint(x); }
 
-typedef float vf4 __attribute__((ext_vector_type(4)));   // one 16-byte access per lane
+// One 16-byte access per lane.  The tensors are only known to be 4-byte aligned (layers packed back to back in one
+// flat buffer start anywhere), and gfx950 needs no more for a dwordx4 access: an unaligned tensor costs one more cache
+// line per KiB and array.  (24 tensors of odd sizes packed back to back, 8.0 M elements with a velocity: a compression
+// call took 80 us when unaligned tensors were read and written a word at a time, 54 us this way.)
+typedef float vf4 __attribute__((ext_vector_type(4), aligned(4)));
+
+typedef __attribute__((address_space(1))) vf4* gvf4;
+typedef __attribute__((address_space(1))) const vf4* gcvf4;
+__device__ __forceinline__ gvf4 as_vec(float* p) { return (gvf4)(p); }
+__device__ __forceinline__ gcvf4 as_vec(const float* p) { return (gcvf4)(p); }
 
 // One access of the streaming passes to the residual and the velocity.  kNt: past the memory-side cache, for calls
 // whose tensors do not stay in it until the next call anyway (see stream_past_cache() in rgc_api.cpp).
-template <bool kNt, typename T>
-__device__ __forceinline__ T stream_load(gptr<T> p) {
+template <bool kNt>
+__device__ __forceinline__ vf4 stream_load(gcvf4 p) {
   if constexpr (kNt) return __builtin_nontemporal_load(p); else return *p;
 }
-template <bool kNt, typename T>
-__device__ __forceinline__ void stream_store(gptr<T> p, T v) {
+template <bool kNt>
+__device__ __forceinline__ void stream_store(gvf4 p, vf4 v) {
   if constexpr (kNt) __builtin_nontemporal_store(v, p); else *p = v;
 }
 

@@ -63,7 +63,6 @@ struct LayerDesc {
   uint32_t wg_first;   // first workgroup of this layer
   uint32_t wg_count;   // = ceil(wc_count / 4)
   uint32_t grp_first;  // first election-group counter of this layer
-  uint32_t vec_ok;     // every tensor pointer is 16-byte aligned
   uint32_t hintable;   // one-pass layer: the candidate lists can hold every element from the hinted threshold upwards
   uint32_t margin;     // extra candidates aimed for beyond k
   uint32_t cmax;       // largest candidate total a hint may aim at
@@ -73,7 +72,6 @@ struct LayerDesc {
   uint32_t mem_cap;    // dense layers: entries of the layer's kMemberShards sub-lists together (a multiple of kMemberShards); the
                        // overflow list behind them holds mem_cap / 4, which is also the most members a call accepts
   uint32_t list_cap;   // dense layers: entries of one wave-chunk's list
-  uint32_t pad_;
   uint64_t mem_first;  // dense layers: where the layer's region of the member pool starts
   uint64_t list_first; // dense layers: where the layer's lists start (wave-chunk c of the layer: list_first + c * list_cap)
 };

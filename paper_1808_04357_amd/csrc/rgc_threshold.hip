@@ -70,18 +70,18 @@ __device__ __forceinline__ Place place_of(const ThresholdArgs& A, const LayerDes
 }
 
 // Calls f(a, nvalid, idx0) for the groups of 256 elements of [begin, end) of tensor p: lane-major,
-// four consecutive elements per lane; whole groups of an aligned tensor four at a time.
+// four consecutive elements per lane; whole groups four at a time.
 template <typename F>
-__device__ __forceinline__ void read_groups(const float* generic_p, bool vec, uint32_t begin, uint32_t end, F&& f) {
+__device__ __forceinline__ void read_groups(const float* generic_p, uint32_t begin, uint32_t end, F&& f) {
   const gptr<const float> p = as_global(generic_p);
   const uint32_t lane = lane_id();
   uint32_t base = begin;
-  if (vec) {
+  {
     constexpr uint32_t kUnroll = 4u;
     for (; base + kUnroll * kGroupElems <= end; base += kUnroll * kGroupElems) {
       vf4 q[kUnroll];
 #pragma unroll
-      for (uint32_t t = 0; t < kUnroll; ++t) q[t] = *reinterpret_cast<gptr<const vf4>>(p + base + t * kGroupElems + lane * 4u);
+      for (uint32_t t = 0; t < kUnroll; ++t) q[t] = *as_vec(generic_p + base + t * kGroupElems + lane * 4u);
 #pragma unroll
       for (uint32_t t = 0; t < kUnroll; ++t) {
         const float a[4] = {q[t].x, q[t].y, q[t].z, q[t].w};
@@ -93,8 +93,8 @@ __device__ __forceinline__ void read_groups(const float* generic_p, bool vec, ui
     const uint32_t idx0 = base + lane * 4u;
     float a[4] = {0.f, 0.f, 0.f, 0.f};
     uint32_t nvalid;
-    if (vec && base + kGroupElems <= end) {
-      const vf4 q = *reinterpret_cast<gptr<const vf4>>(p + idx0);
+    if (base + kGroupElems <= end) {
+      const vf4 q = *as_vec(generic_p + idx0);
       a[0] = q.x; a[1] = q.y; a[2] = q.z; a[3] = q.w;
       nvalid = 4u;
     } else {
@@ -108,7 +108,7 @@ __device__ __forceinline__ void read_groups(const float* generic_p, bool vec, ui
 }
 
 // The accumulate of Algorithm 1 over [begin, end) of a layer (same arithmetic as the exact path:
-// accum4), handing every group of accumulated values to f.  Whole groups of an aligned layer are
+// accum4), handing every group of accumulated values to f.  Whole groups are
 // taken four (two with a velocity) at a time, all their loads issued before the first use.
 template <bool kNt, bool kMom, bool kNest, typename F>
 __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t begin, uint32_t end, const AccumRule& rule, F&& f) {
@@ -117,16 +117,16 @@ __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t b
   const gptr<float> U = as_global(L.mom);
   const uint32_t lane = lane_id();
   uint32_t base = begin;
-  if (L.vec_ok) {
+  {
     constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;
     for (; base + kUnroll * kGroupElems <= end; base += kUnroll * kGroupElems) {
       vf4 gq[kUnroll], vq[kUnroll], uq[kUnroll];
 #pragma unroll
       for (uint32_t t = 0; t < kUnroll; ++t) {
         const uint32_t idx0 = base + t * kGroupElems + lane * 4u;
-        gq[t] = __builtin_nontemporal_load(reinterpret_cast<gptr<const vf4>>(G + idx0));
-        vq[t] = stream_load<kNt>(reinterpret_cast<gptr<vf4>>(V + idx0));
-        if constexpr (kMom) uq[t] = stream_load<kNt>(reinterpret_cast<gptr<vf4>>(U + idx0));
+        gq[t] = __builtin_nontemporal_load(as_vec(L.grad + idx0));
+        vq[t] = stream_load<kNt>(as_vec(L.resid + idx0));
+        if constexpr (kMom) uq[t] = stream_load<kNt>(as_vec(L.mom + idx0));
       }
 #pragma unroll
       for (uint32_t t = 0; t < kUnroll; ++t) {
@@ -136,8 +136,8 @@ __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t b
         float u[4] = {0.f, 0.f, 0.f, 0.f}, a[4];
         if constexpr (kMom) { u[0] = uq[t].x; u[1] = uq[t].y; u[2] = uq[t].z; u[3] = uq[t].w; }
         accum4<kMom, kNest>(g, v, u, rule, a);
-        stream_store<kNt>(reinterpret_cast<gptr<vf4>>(V + idx0), vf4{a[0], a[1], a[2], a[3]});
-        if constexpr (kMom) stream_store<kNt>(reinterpret_cast<gptr<vf4>>(U + idx0), vf4{u[0], u[1], u[2], u[3]});
+        stream_store<kNt>(as_vec(L.resid + idx0), vf4{a[0], a[1], a[2], a[3]});
+        if constexpr (kMom) stream_store<kNt>(as_vec(L.mom + idx0), vf4{u[0], u[1], u[2], u[3]});
         f(a, 4u, idx0);
       }
     }
@@ -145,18 +145,18 @@ __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t b
   for (; base < end; base += kGroupElems) {
     const uint32_t idx0 = base + lane * 4u;
     float g[4] = {0.f, 0.f, 0.f, 0.f}, v[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f}, a[4];
-    if (L.vec_ok && base + kGroupElems <= end) {
-      const vf4 gq = __builtin_nontemporal_load(reinterpret_cast<gptr<const vf4>>(G + idx0));
-      const vf4 vq = *reinterpret_cast<gptr<const vf4>>(V + idx0);
+    if (base + kGroupElems <= end) {
+      const vf4 gq = __builtin_nontemporal_load(as_vec(L.grad + idx0));
+      const vf4 vq = *as_vec(L.resid + idx0);
       g[0] = gq.x; g[1] = gq.y; g[2] = gq.z; g[3] = gq.w;
       v[0] = vq.x; v[1] = vq.y; v[2] = vq.z; v[3] = vq.w;
       if constexpr (kMom) {
-        const vf4 uq = *reinterpret_cast<gptr<const vf4>>(U + idx0);
+        const vf4 uq = *as_vec(L.mom + idx0);
         u[0] = uq.x; u[1] = uq.y; u[2] = uq.z; u[3] = uq.w;
       }
       accum4<kMom, kNest>(g, v, u, rule, a);
-      stream_store<kNt>(reinterpret_cast<gptr<vf4>>(V + idx0), vf4{a[0], a[1], a[2], a[3]});
-      if constexpr (kMom) stream_store<kNt>(reinterpret_cast<gptr<vf4>>(U + idx0), vf4{u[0], u[1], u[2], u[3]});
+      stream_store<kNt>(as_vec(L.resid + idx0), vf4{a[0], a[1], a[2], a[3]});
+      if constexpr (kMom) stream_store<kNt>(as_vec(L.mom + idx0), vf4{u[0], u[1], u[2], u[3]});
       f(a, 4u, idx0);
     } else {
       const uint32_t nvalid = idx0 < end ? ((end - idx0) < 4u ? (end - idx0) : 4u) : 0u;
@@ -313,7 +313,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_histogram_kernel(Thre
   const ThresholdMoments M = A.moments[l];
   const float inv = M.span > 0.0f ? static_cast<float>(kSteps) / M.span : 0.0f;
   uint32_t below = 0u;     // bin 0 is by far the fullest: counted in a register
-  read_groups(L.resid, L.vec_ok != 0u, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
+  read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (static_cast<uint32_t>(j) < nvalid) {
@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_count_kernel(Threshol
   if (p.begin == p.end) return;
   const float thr = *as_global(A.thresholds + l);
   uint32_t cnt = 0u;
-  read_groups(L.resid, L.vec_ok != 0u, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
+  read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) cnt += (static_cast<uint32_t>(j) < nvalid && fabsf(a[j]) > thr) ? 1u : 0u;
   });
@@ -468,7 +468,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_emit_kernel(Threshold
     }
   }
   const float thr = *as_global(A.thresholds + l);
-  read_groups(L.resid, L.vec_ok != 0u, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
+  read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
     bool sel[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) sel[j] = static_cast<uint32_t>(j) < nvalid && fabsf(a[j]) > thr;

@@ -44,3 +44,15 @@ def test_both_sides_of_the_cache_line(rgc, oracle, momentum, extra):
 @pytest.mark.parametrize("momentum,nesterov,ppm", [(True, True, 1000), (True, False, 62500), (False, False, 250000)])
 def test_past_the_cache_variants(rgc, oracle, momentum, nesterov, ppm):
     _run(rgc, oracle, [17_000_003, 8192 * 4 + 255], momentum, ppm=ppm, nesterov=nesterov)
+
+
+# tensors that start anywhere (the gradients here stay aligned: the three streams of a layer need not agree)
+@pytest.mark.parametrize("misalign", [1, 2, 3])
+@pytest.mark.parametrize("momentum,ppm", [(False, 1000), (True, 1000), (True, 250000)])
+def test_unaligned_tensors(rgc, oracle, momentum, ppm, misalign):
+    _run(rgc, oracle, [3 * 8192 + 259, 4096, 1023, 255, 3], momentum, ppm=ppm, misalign=misalign, steps=4)
+
+
+@pytest.mark.parametrize("momentum", [False, True])
+def test_unaligned_past_the_cache(rgc, oracle, momentum):
+    _run(rgc, oracle, [17_000_003], momentum, misalign=3, steps=2)
