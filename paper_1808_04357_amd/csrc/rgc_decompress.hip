@@ -11,7 +11,7 @@
 // the sequential sum over the workers bit for bit, independent of scheduling; no floating-point
 // atomics are used.
 //
-// The fast kernel (up to kBatchWorkers workers) is persistent and XCD-aware: every XCD gets one
+// The fast kernel (up to kFastWorkersMax workers) is persistent and XCD-aware: every XCD gets one
 // contiguous range of tiles and every workgroup a contiguous piece of it, which it walks through
 // once.  Four lanes serve one worker and keep a window of its (sorted) message in registers, so
 // a message is read once, front to back, in 64-byte pieces, and no table of per-tile offsets is
@@ -20,10 +20,12 @@
 // are loaded while the current tile is being finished.
 //
 // A tile with more colliding positions than the kernel has rows (rare) takes them a row-set at a
-// time.  With more than kBatchWorkers workers a second kernel does the job instead: workers in
+// time.  With more than kFastWorkersMax workers a second kernel does the job instead: workers in
 // batches, colliding entries sorted by their rank in a per-position worker bitmask, entry ranges
 // from a table of per-tile offsets that a third kernel builds first.
 #include "rgc_device.h"
+
+#include <atomic>
 
 namespace rgc {
 
@@ -362,15 +364,20 @@ __device__ void tile_generic(const DecompressArgs& A, GenericLds& S, const TileG
 }
 
 // =================================================================== fast tiles
-constexpr uint32_t kFastShift = 9;
-constexpr uint32_t kFastThreads = 1u << kFastShift;   // 8 waves per tile
 constexpr uint32_t kRows = 48;                  // positions hit more than once in one tile
-constexpr uint32_t kRowStride = kBatchWorkers + 4;   // floats; the +4 spreads the rows over the LDS banks
+
+// The fast kernel for up to kMaxWorkers workers: four lanes a worker.
+template <uint32_t kMaxWorkers>
+struct FastGeom {
+  static constexpr uint32_t kThreads = 4u * kMaxWorkers;
+  static constexpr uint32_t kRowStride = kMaxWorkers + 4u;   // floats; the +4 spreads the rows over the LDS banks
+};
 
 // seen / cb / nq exist twice: tile i uses set i & 1 while the other set is being cleared.
+template <uint32_t kMaxWorkers>
 struct alignas(16) FastLds {
   float acc[kTile];                          // the tile; all zero between tiles
-  float rows[kRows * kRowStride];            // per colliding position one slot per worker; all +0 between tiles
+  float rows[kRows * FastGeom<kMaxWorkers>::kRowStride];   // per colliding position one slot per worker; all +0 between tiles
   uint32_t seen[2][kWords];                  // positions hit at all
   uint32_t cb[2][kWords];                    // positions hit more than once
   uint32_t nq[2];                            // how many of those
@@ -379,7 +386,8 @@ struct alignas(16) FastLds {
   uint8_t qmap[kTile];                       // the row of a colliding position (valid where cb is set)
   uint8_t who[kTile];                        // the worker whose entry reached a position first (valid where seen is set)
 };
-static_assert(sizeof(FastLds) <= 80 * 1024, "two 8-wave workgroups per CU");
+static_assert(sizeof(FastLds<kFastWorkers>) <= 80 * 1024, "two 8-wave workgroups per CU");
+static_assert(sizeof(FastLds<kFastWorkersMax>) <= 160 * 1024 && kFastWorkersMax <= 256u, "one 16-wave workgroup per CU; worker numbers are bytes");
 static_assert(kWords % 64u == 0u, "a wave scans the colliding-position bitmap, a whole number of words per lane");
 static_assert(kRows <= 64 && kRows < 256, "one wave adds the rows; row numbers are bytes");
 
@@ -448,12 +456,13 @@ __device__ __forceinline__ uint32_t quad_lane0(uint32_t v) {
 // blocks starting at the one that holds entry E, and the blocks that enter it are loaded while
 // the tile is being finished.  There is no per-tile offset table: E starts from a binary search
 // at the first tile of a layer and then advances by what each tile consumes.
-template <bool kStreamMsgs, bool kOneValue>
-__global__ void __launch_bounds__(kFastThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <uint32_t kMaxWorkers, bool kStreamMsgs, bool kOneValue>
+__global__ void __launch_bounds__(FastGeom<kMaxWorkers>::kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 decompress_tiles_kernel(DecompressArgs A) {
-  __shared__ FastLds S;
+  constexpr uint32_t kFastThreads = FastGeom<kMaxWorkers>::kThreads, kRowStride = FastGeom<kMaxWorkers>::kRowStride;
+  __shared__ FastLds<kMaxWorkers> S;
   const uint32_t tid = threadIdx.x;
-  const uint32_t N = A.num_workers;                    // 1 .. kBatchWorkers (the host checks)
+  const uint32_t N = A.num_workers;                    // 1 .. kMaxWorkers (the host checks)
   // this workgroup's tiles: a contiguous piece of its XCD's contiguous range
   uint32_t t_first, t_last;
   {
@@ -836,7 +845,7 @@ hipError_t launch_decompress_validate(const DecompressArgs& a, uint32_t* status,
 
 hipError_t launch_decompress_table(const DecompressArgs& a, hipStream_t s) {
   // only the kernel that takes any number of workers reads the table
-  if (a.num_blocks == 0 || a.num_workers <= static_cast<uint32_t>(kBatchWorkers)) return hipSuccess;
+  if (a.num_blocks == 0 || a.num_workers <= kFastWorkersMax) return hipSuccess;
   hipLaunchKernelGGL(decompress_table_kernel, dim3(a.num_blocks), dim3(kBlockThreads), 0, s, a);
   return hipGetLastError();
 }
@@ -853,26 +862,40 @@ static uint32_t resident_grid(const void* kernel, uint32_t threads, uint32_t cus
   return g < 8u ? 8u : g;
 }
 
+template <uint32_t kMaxWorkers>
+static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint32_t cus8, hipStream_t s) {
+  static std::atomic<uint32_t> per_cu{0};              // workgroups per CU; a property of the code object
+  constexpr uint32_t threads = FastGeom<kMaxWorkers>::kThreads;
+  uint32_t per = per_cu.load(std::memory_order_relaxed);
+  if (per == 0) {
+    per = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<kMaxWorkers, false, false>), threads, 8u) / 8u;
+    per_cu.store(per, std::memory_order_relaxed);
+  }
+  const uint32_t grid = want < per * cus8 ? want : per * cus8;
+  if (a.one_value) {
+    if (a.stream_msgs) hipLaunchKernelGGL((decompress_tiles_kernel<kMaxWorkers, true, true>), dim3(grid), dim3(threads), 0, s, a);
+    else hipLaunchKernelGGL((decompress_tiles_kernel<kMaxWorkers, false, true>), dim3(grid), dim3(threads), 0, s, a);
+  } else {
+    if (a.stream_msgs) hipLaunchKernelGGL((decompress_tiles_kernel<kMaxWorkers, true, false>), dim3(grid), dim3(threads), 0, s, a);
+    else hipLaunchKernelGGL((decompress_tiles_kernel<kMaxWorkers, false, false>), dim3(grid), dim3(threads), 0, s, a);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_decompress_tiles(const DecompressArgs& a, hipStream_t s) {
   if (a.num_tiles == 0) return hipSuccess;
-  static uint32_t per_cu_fast = 0, per_cu_generic = 0;   // workgroups per CU; a property of the code object
-  if (per_cu_fast == 0) {
-    per_cu_fast = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<false, false>), kFastThreads, 8u) / 8u;
-    per_cu_generic = resident_grid(reinterpret_cast<const void*>(decompress_generic_kernel), kBlockThreads, 8u) / 8u;
-  }
   const uint32_t want = ((a.num_tiles + 7u) / 8u) * 8u;
   const uint32_t cus8 = a.cus < 8u ? 8u : (a.cus / 8u) * 8u;
-  const bool fast = a.num_workers >= 1u && a.num_workers <= static_cast<uint32_t>(kBatchWorkers);
-  const uint32_t cap = (fast ? per_cu_fast : per_cu_generic) * cus8;
-  const uint32_t grid = want < cap ? want : cap;
-  if (fast && a.one_value) {
-    if (a.stream_msgs) hipLaunchKernelGGL((decompress_tiles_kernel<true, true>), dim3(grid), dim3(kFastThreads), 0, s, a);
-    else hipLaunchKernelGGL((decompress_tiles_kernel<false, true>), dim3(grid), dim3(kFastThreads), 0, s, a);
-  } else if (fast) {
-    if (a.stream_msgs) hipLaunchKernelGGL((decompress_tiles_kernel<true, false>), dim3(grid), dim3(kFastThreads), 0, s, a);
-    else hipLaunchKernelGGL((decompress_tiles_kernel<false, false>), dim3(grid), dim3(kFastThreads), 0, s, a);
+  if (a.num_workers >= 1u && a.num_workers <= kFastWorkers) return launch_fast_tiles<kFastWorkers>(a, want, cus8, s);
+  if (a.num_workers > kFastWorkers && a.num_workers <= kFastWorkersMax) return launch_fast_tiles<kFastWorkersMax>(a, want, cus8, s);
+  static std::atomic<uint32_t> per_cu_generic{0};
+  uint32_t per = per_cu_generic.load(std::memory_order_relaxed);
+  if (per == 0) {
+    per = resident_grid(reinterpret_cast<const void*>(decompress_generic_kernel), kBlockThreads, 8u) / 8u;
+    per_cu_generic.store(per, std::memory_order_relaxed);
   }
-  else hipLaunchKernelGGL(decompress_generic_kernel, dim3(grid), dim3(kBlockThreads), 0, s, a);
+  const uint32_t grid = want < per * cus8 ? want : per * cus8;
+  hipLaunchKernelGGL(decompress_generic_kernel, dim3(grid), dim3(kBlockThreads), 0, s, a);
   return hipGetLastError();
 }
 
