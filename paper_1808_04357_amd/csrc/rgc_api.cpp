@@ -67,7 +67,38 @@ uint32_t chunk_for(int64_t total) {
 }
 
 // Smallest chunk any call may use: the scratch is sized for it.
-uint32_t chunk_smallest() { return chunk_override() ? std::min(chunk_override(), kChunkSmallest) : kChunkSmallest; }
+uint32_t chunk_smallest() { return kTileChunk; }
+
+// The threshold hint of a layer of n elements that sends k: the rank it is aimed at, for lists of `cap` slots per
+// wave-chunk of `chunk` elements, and whether those lists can hold it.
+struct HintAim {
+  uint64_t margin, target, span;
+  bool hintable;
+};
+HintAim hint_aim(uint64_t n, uint64_t k, uint32_t chunk, uint32_t cap) {
+  HintAim h;
+  h.margin = std::max<uint64_t>(k / 2, 32);
+  if (n <= chunk) h.margin = std::min<uint64_t>(h.margin, std::max<uint64_t>(cap / 4, 8));   // one list holds it all
+  h.span = std::max<uint64_t>(n, chunk);
+  h.target = 2 * k + h.margin;                                             // rank the next threshold is aimed at
+  const uint64_t per_chunk = (h.target * chunk + h.span - 1) / h.span;     // expected per wave-chunk
+  // The candidates between the threshold aimed at and the k-th key fall into several hundred coarse
+  // bins, and the one bin that holds the k-th key must fit the member list: beyond about a million
+  // selected entries per layer it would not, and the hint would miss on every call.
+  h.hintable = 2 * per_chunk + 16 <= cap && k <= static_cast<uint64_t>(kMemberMax) * 256u;
+  return h;
+}
+
+// Whether finish_kernel can end every layer of the list (see rgc_internal.h).
+bool finishable(const rgc_layer* layers, int32_t L) {
+  if (chunk_override()) return false;
+  for (int32_t l = 0; l < L; ++l) {
+    if (layers[l].n <= static_cast<int64_t>(kDirectMax)) continue;
+    const HintAim h = hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileChunk, kTileChunk / kCapDiv);
+    if (!h.hintable || h.target > kFinishTargetMax) return false;
+  }
+  return true;
+}
 constexpr int kPlanCache = 8;
 constexpr uint32_t kElectGroupHost = 32;   // = kElectGroup of the kernels (workgroups per election group)
 constexpr int kLaunches = 6;               // streaming pass + at most five phase launches
@@ -120,22 +151,28 @@ struct PinnedBuf {
   }
 };
 
+// One way of cutting a layer list into wave-chunks and workgroups.
+struct Tiling {
+  uint32_t chunk = 0;                      // elements per wave-chunk
+  uint32_t wave_chunks = 0, workgroups = 0;
+  uint64_t member_entries = 0;             // of the member pool handed out to dense layers
+  uint64_t list_entries = 0;               // of their lists
+};
+
 // One cached translation of a layer list into device tables.
 struct CompressPlan {
   std::vector<rgc_layer> key;       // the caller's list this plan was built from
-  uint32_t chunk = 0;               // elements per wave-chunk of this plan
+  Tiling general, fin;              // the second one for finishable lists only
   DevBuf<LayerDesc> d_layers;
   DevBuf<uint32_t> d_wg2layer;
   PinnedBuf staging;
   hipEvent_t uploaded = nullptr;    // recorded after the uploads
-  uint32_t num_wgs = 0;
-  uint32_t num_chunks = 0;                 // wave-chunks over all layers
   uint64_t tensor_bytes = 0;               // gradients, residuals and velocities together
   uint64_t write_bytes = 0;                // what the streaming pass writes (V, and u where there is one)
   uint32_t max_k = 0;                      // the largest k of the list
+  bool finish = false;                     // finish_kernel can end every layer
+  bool finish_lists = false;               // ... and some of them from its candidate lists: those need a hint
   bool any_dense = false;                  // some layer is streamed by collect_kernel when it has a hint
-  uint64_t list_entries = 0;               // list entries of the dense layers
-  uint64_t member_entries = 0;             // entries of the member pool they own
   uint64_t last_use = 0;
   bool valid = false;
 };
@@ -159,7 +196,8 @@ struct rgc_ctx {
   int device = 0;
   int64_t max_total = 0;
   int32_t max_layers = 0;
-  uint32_t wc_max = 0;
+  uint32_t wc_max = 0;                     // wave-chunks a call can have
+  uint32_t wg_max = 0;                     // and workgroups
   uint32_t cus = 0;                        // compute units of the device (sizes the persistent decompression grids)
   DevBuf<LayerState> d_state;
   DevBuf<uint32_t> d_hist, d_coarse, d_cand_cnt, d_wc_a, d_wc_b, d_err, d_group;
@@ -195,26 +233,13 @@ struct rgc_ctx {
 
 namespace {
 
-int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, int32_t L,
-                        hipStream_t stream) {
-  if (P.uploaded) RGC_HIP(hipEventSynchronize(P.uploaded));   // an older upload may still read staging
-  else RGC_HIP(hipEventCreateWithFlags(&P.uploaded, hipEventDisableTiming));
-  P.valid = false;
-  // workgroups are handed out largest layer first so that the long per-layer tails start early
-  std::vector<int32_t> order(L);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int32_t a, int32_t b) { return layers[a].n > layers[b].n; });
-  std::vector<LayerDesc> desc(L);
-  int64_t total_elems = 0;
-  for (int32_t l = 0; l < L; ++l) total_elems += layers[l].n;
-  const uint32_t kChunk = chunk_for(total_elems), kCap = kChunk / kCapDiv;
-  P.chunk = kChunk;
+// Fills `desc` (one entry per layer); the workgroups are handed out in the given order of the layers.
+Tiling tile_layers(const rgc_layer* layers, const std::vector<int32_t>& order, uint32_t kChunk, bool finish, LayerDesc* desc) {
+  const uint32_t kCap = kChunk / kCapDiv;
   uint32_t wc = 0, wg = 0, grp = 0;
   uint64_t mem = 0;                        // entries of the member pool handed out to dense layers
   uint64_t lists = 0;                      // list entries handed out to them
-  for (int32_t o = 0; o < L; ++o) {
-    const int32_t l = order[o];
+  for (const int32_t l : order) {
     const rgc_layer& in = layers[l];
     LayerDesc& d = desc[l];
     d.grad = in.grad;
@@ -235,23 +260,18 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     d.mem_first = 0;
     // speed-hint policy: aim the threshold at rank 2k + margin of this call, accept up to cmax
     const uint64_t k = d.k;
-    uint64_t margin = std::max<uint64_t>(k / 2, 32);
-    if (d.n <= kChunk) margin = std::min<uint64_t>(margin, std::max<uint64_t>(kCap / 4, 8));   // one list holds it all
-    const uint64_t span = std::max<uint64_t>(d.n, kChunk);
-    const uint64_t target = 2 * k + margin;   // rank the next threshold is aimed at
-    const uint64_t per_chunk = (target * kChunk + span - 1) / span;         // expected per wave-chunk
-    d.hintable = (2 * per_chunk + 16 <= kCap) ? 1u : 0u;
-    // The candidates between the threshold aimed at and the k-th key fall into several hundred coarse
-    // bins, and the one bin that holds the k-th key must fit the member list: beyond about a million
-    // selected entries per layer it would not, and the hint would miss on every call.
-    if (k > static_cast<uint64_t>(kMemberMax) * 256u) d.hintable = 0u;
+    const HintAim aim = hint_aim(d.n, k, kChunk, kCap);
+    const uint64_t margin = aim.margin, span = aim.span, target = aim.target;
+    d.hintable = aim.hintable ? 1u : 0u;
+    d.direct = finish && d.n <= kDirectMax ? 1u : 0u;
+    d.pad_ = 0;
     d.margin = static_cast<uint32_t>(margin);
     uint64_t cmax = std::min<uint64_t>(2 * target, (kCap / 2) * (span / kChunk));
     d.target = static_cast<uint32_t>(std::min<uint64_t>(target, 0xFFFFFFFFu));
     d.dense = 0;
     d.list_cap = 0;
     d.list_first = 0;
-    if (!d.hintable) {
+    if (!d.hintable && !finish) {
       // High densities (the warm-up period of Section 2.5): the short lists of the one-pass path cannot hold every
       // element from the threshold upwards.  Such a layer gets lists of its own, long enough for twice the number of
       // candidates aimed at, and its hint is aimed at rank k + margin and accepted from rank k to rank k + 2 margin.
@@ -278,17 +298,44 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     wc += d.wc_count;
     wg += d.wg_count;
   }
-  if (wc > ctx->wc_max) return RGC_ENOMEM;
-  const size_t bytes_layers = sizeof(LayerDesc) * static_cast<size_t>(L);
-  const size_t bytes_map = sizeof(uint32_t) * static_cast<size_t>(wg);
+  Tiling t;
+  t.chunk = kChunk;
+  t.wave_chunks = wc;
+  t.workgroups = wg;
+  t.member_entries = mem;
+  t.list_entries = lists;
+  return t;
+}
+
+int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, int32_t L,
+                        hipStream_t stream) {
+  if (P.uploaded) RGC_HIP(hipEventSynchronize(P.uploaded));   // an older upload may still read staging
+  else RGC_HIP(hipEventCreateWithFlags(&P.uploaded, hipEventDisableTiming));
+  P.valid = false;
+  // workgroups are handed out largest layer first so that the long per-layer tails start early
+  std::vector<int32_t> order(L);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int32_t a, int32_t b) { return layers[a].n > layers[b].n; });
+  int64_t total_elems = 0;
+  for (int32_t l = 0; l < L; ++l) total_elems += layers[l].n;
+  P.finish = finishable(layers, L);
+  // the general tiling, and behind it in the same tables the one a finishable call uses
+  std::vector<LayerDesc> desc(static_cast<size_t>(L) * (P.finish ? 2u : 1u));
+  const Tiling general = tile_layers(layers, order, chunk_for(total_elems), false, desc.data());
+  const Tiling fin = P.finish ? tile_layers(layers, order, kTileChunk, true, desc.data() + L) : Tiling{};
+  if (general.wave_chunks > ctx->wc_max || fin.wave_chunks > ctx->wc_max) return RGC_ENOMEM;
+  const size_t wgs = static_cast<size_t>(general.workgroups) + fin.workgroups;
+  const size_t bytes_layers = sizeof(LayerDesc) * desc.size();
+  const size_t bytes_map = sizeof(uint32_t) * wgs;
   RGC_HIP(P.staging.ensure(bytes_layers + bytes_map));
-  if (P.d_layers.n < static_cast<size_t>(L)) RGC_HIP(P.d_layers.alloc(static_cast<size_t>(L)));
-  if (P.d_wg2layer.n < wg) RGC_HIP(P.d_wg2layer.alloc(wg));
+  if (P.d_layers.n < desc.size()) RGC_HIP(P.d_layers.alloc(desc.size()));
+  if (P.d_wg2layer.n < wgs) RGC_HIP(P.d_wg2layer.alloc(wgs));
   std::memcpy(P.staging.p, desc.data(), bytes_layers);
   uint32_t* map = reinterpret_cast<uint32_t*>(static_cast<char*>(P.staging.p) + bytes_layers);
-  for (int32_t o = 0; o < L; ++o) {
-    const int32_t l = order[o];
-    for (uint32_t i = 0; i < desc[l].wg_count; ++i) map[desc[l].wg_first + i] = static_cast<uint32_t>(l);
+  for (size_t d = 0; d < desc.size(); ++d) {
+    uint32_t* const own = map + (d < static_cast<size_t>(L) ? 0u : general.workgroups) + desc[d].wg_first;
+    std::fill_n(own, desc[d].wg_count, static_cast<uint32_t>(d % static_cast<size_t>(L)));
   }
   RGC_HIP(hipMemcpyAsync(P.d_layers.p, P.staging.p, bytes_layers, hipMemcpyHostToDevice, stream));
   RGC_HIP(hipMemcpyAsync(P.d_wg2layer.p, map, bytes_map, hipMemcpyHostToDevice, stream));
@@ -300,16 +347,16 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     c.k = layers[l].k; c.out_idx = layers[l].out_idx; c.out_val = layers[l].out_val; c.out_count = layers[l].out_count;
     P.key[l] = c;
   }
-  P.num_wgs = wg;
-  P.num_chunks = wc;
+  P.general = general;
+  P.fin = fin;
   P.write_bytes = 0;
   P.tensor_bytes = 0;
   P.max_k = 0;
   P.any_dense = false;
-  P.list_entries = lists;
-  P.member_entries = mem;
+  P.finish_lists = false;
   for (int32_t l = 0; l < L; ++l) {
     P.any_dense = P.any_dense || desc[l].dense != 0;
+    P.finish_lists = P.finish_lists || (P.finish && desc[L + l].direct == 0);
     P.write_bytes += static_cast<uint64_t>(layers[l].n) * (layers[l].momentum ? 8u : 4u);
     P.tensor_bytes += static_cast<uint64_t>(layers[l].n) * (layers[l].momentum ? 12u : 8u);
     P.max_k = std::max(P.max_k, static_cast<uint32_t>(layers[l].k));
@@ -388,6 +435,7 @@ int rgc_create(rgc_ctx** out, int device_id, int64_t max_total_elems, int32_t ma
   const uint64_t wc_max = static_cast<uint64_t>((max_total_elems + kChunk - 1) / kChunk) + static_cast<uint64_t>(max_layers);
   if (wc_max > 0x7FFFFFFFull) return RGC_ENOMEM;
   c->wc_max = static_cast<uint32_t>(wc_max);
+  c->wg_max = static_cast<uint32_t>(wc_max / kWavesPerBlock + static_cast<uint64_t>(max_layers) + 1);
   const size_t L = static_cast<size_t>(max_layers);
   hipError_t e = hipSuccess;
   auto chk = [&](hipError_t r) { if (e == hipSuccess && r != hipSuccess) e = r; };
@@ -405,14 +453,14 @@ int rgc_create(rgc_ctx** out, int device_id, int64_t max_total_elems, int32_t ma
     (void)kCap;
     chk(c->d_slots.alloc(static_cast<uint64_t>(max_total_elems) / kCapDiv + (static_cast<uint64_t>(max_layers) + 1) * (largest / kCapDiv)));
   }
-  chk(c->d_err.alloc(2));                  // [0] internal inconsistencies of compression, [1] status of the message checks
+  chk(c->d_err.alloc(5));                  // [0] internal inconsistencies of compression, [1] status of the message checks, [2..4] fallback_kernel
   const uint64_t grp_max = wc_max / (kWavesPerBlock * kElectGroupHost) + 2 * L + 2;
   chk(c->d_group.alloc(grp_max));
   if (e == hipSuccess) chk(hipMemset(c->d_state.p, 0, sizeof(LayerState) * 3 * L));
   if (e == hipSuccess) chk(hipMemset(c->d_hist.p, 0, sizeof(uint32_t) * L * kHistBins));
   if (e == hipSuccess) chk(hipMemset(c->d_coarse.p, 0, sizeof(uint32_t) * L * kCoarseRep * kCoarseBins));
   if (e == hipSuccess) chk(hipMemset(c->d_cand_cnt.p, 0, sizeof(uint32_t) * wc_max));
-  if (e == hipSuccess) chk(hipMemset(c->d_err.p, 0, 2 * sizeof(uint32_t)));
+  if (e == hipSuccess) chk(hipMemset(c->d_err.p, 0, 5 * sizeof(uint32_t)));
   if (e == hipSuccess) chk(hipMemset(c->d_group.p, 0, sizeof(uint32_t) * grp_max));
   if (e == hipSuccess) chk(hipDeviceSynchronize());
   if (e != hipSuccess) {
@@ -585,8 +633,8 @@ uint32_t stream_past_cache(const CompressPlan* plan, bool again) {
 void fill_plan_args(rgc_ctx* ctx, const CompressPlan* plan, CompressArgs& A) {
   A.layers = plan->d_layers.p;
   A.wg2layer = plan->d_wg2layer.p;
-  A.chunk = plan->chunk;
-  A.norm_parts = exact_parts_at(ctx->d_norm_part.p, ctx->wc_max);
+  A.chunk = plan->general.chunk;
+  A.norm_parts = exact_parts_at(ctx->d_norm_part.p, ctx->wg_max);
 }
 
 }  // namespace
@@ -603,13 +651,13 @@ int rgc_clip_coefficient(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_laye
   CompressPlan* plan = nullptr;
   const int rc = plan_for_layers(ctx, layers, num_layers, stream, &plan);
   if (rc != RGC_OK) return rc;
-  if (ctx->d_norm_part.n < ctx->wc_max * kExactWordsPerPart)                              // first use only
-    RGC_HIP(ctx->d_norm_part.alloc(ctx->wc_max * kExactWordsPerPart));                    // (no more workgroups than wave-chunks)
+  if (ctx->d_norm_part.n < ctx->wg_max * kExactWordsPerPart)                              // first use only
+    RGC_HIP(ctx->d_norm_part.alloc(ctx->wg_max * kExactWordsPerPart));
   CompressArgs A{};
   fill_plan_args(ctx, plan, A);
   A.reverse = streaming_direction(plan, ctx->compress_calls) ^ 1u;   // against the direction of the compression call to come
   const float threshold = static_cast<float>(static_cast<double>(max_norm) / std::sqrt(static_cast<double>(num_workers)));
-  RGC_HIP(launch_clip_coefficient(A, plan->num_wgs, threshold, coefficient, stream));
+  RGC_HIP(launch_clip_coefficient(A, plan->general.workgroups, threshold, coefficient, stream));
   return RGC_OK;
 }
 
@@ -648,8 +696,8 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   CompressPlan* plan = nullptr;
   const int rc = plan_for_layers(ctx, layers, num_layers, stream, &plan);
   if (rc != RGC_OK) return rc;
-  if (ctx->d_norm_part.n < ctx->wc_max * kExactWordsPerPart)                              // first use only
-    RGC_HIP(ctx->d_norm_part.alloc(ctx->wc_max * kExactWordsPerPart));
+  if (ctx->d_norm_part.n < ctx->wg_max * kExactWordsPerPart)                              // first use only
+    RGC_HIP(ctx->d_norm_part.alloc(ctx->wg_max * kExactWordsPerPart));
   if (ctx->d_moments.n < static_cast<size_t>(ctx->max_layers))
     RGC_HIP(ctx->d_moments.alloc(static_cast<size_t>(ctx->max_layers)));
   ThresholdArgs A{};
@@ -658,15 +706,15 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   A.thresholds = thresholds;
   A.nnz = nnz;
   A.grad_scale = grad_scale;
-  A.sum_parts = exact_parts_at(ctx->d_norm_part.p, ctx->wc_max);
+  A.sum_parts = exact_parts_at(ctx->d_norm_part.p, ctx->wg_max);
   A.part_max = reinterpret_cast<float*>(ctx->d_wc_b.p);
   A.counts = ctx->d_wc_a.p;
   A.listed = ctx->d_cand_cnt.p;
   A.slots = ctx->d_slots.p;
-  A.cap = plan->chunk / kCapDiv;
+  A.cap = plan->general.chunk / kCapDiv;
   A.hist = ctx->d_hist.p;
   A.moments = ctx->d_moments.p;
-  A.chunk = plan->chunk;
+  A.chunk = plan->general.chunk;
   A.search = (flags & RGC_THRESHOLD_SEARCH) ? 1u : 0u;
   A.mask_momentum = (flags & RGC_NO_MOMENTUM_MASK) ? 0u : 1u;
   A.nesterov = (flags & RGC_NESTEROV) ? 1u : 0u;
@@ -676,7 +724,7 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   const bool alternate = plan->write_bytes > kMemorySideCacheBytes;
   A.past_cache = stream_past_cache(plan, A.search != 0u);
   A.reverse = alternate ? ctx->threshold_reverse : 0u;
-  RGC_HIP(launch_threshold_compress(A, plan->num_wgs, static_cast<uint32_t>(num_layers), stream));
+  RGC_HIP(launch_threshold_compress(A, plan->general.workgroups, static_cast<uint32_t>(num_layers), stream));
   if (!A.search) ctx->threshold_reverse ^= 1u;
   ctx->compressed_since_decompress = true;
   return RGC_OK;
@@ -712,12 +760,18 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   }
   const bool no_hints = (flags & RGC_NO_HINTS) != 0;
 
+  // A finishable call takes two launches, and one more for the layers whose hint misses if it has layers that need one;
+  // without hints for those it goes the general way.
+  const bool use_hints = sig_same && !no_hints;
+  const bool finish = plan->finish && (use_hints || !plan->finish_lists);
+  const Tiling& tiling = finish ? plan->fin : plan->general;
+  const uint32_t num_wgs = tiling.workgroups;
   CompressArgs A{};
-  A.layers = plan->d_layers.p;
+  A.layers = plan->d_layers.p + (finish ? num_layers : 0);
   A.state = ctx->d_state.p + static_cast<size_t>(bank) * ctx->max_layers;
   A.sign_filter = bank ? 0xFFFFFFFFu : 0u;
   A.sign_xor = bank == 2 ? 0x80000000u : 0u;
-  A.wg2layer = plan->d_wg2layer.p;
+  A.wg2layer = plan->d_wg2layer.p + (finish ? plan->general.workgroups : 0u);
   A.hist = ctx->d_hist.p;
   A.coarse = ctx->d_coarse.p;
   A.members = ctx->d_members.p;
@@ -727,21 +781,21 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.wc_b = ctx->d_wc_b.p;
   A.errflag = ctx->d_err.p;
   A.group_done = ctx->d_group.p;
-  A.chunk = plan->chunk;
+  A.chunk = tiling.chunk;
   A.cap = A.chunk / kCapDiv;
-  A.use_hints = (sig_same && !no_hints) ? 1u : 0u;
+  A.use_hints = use_hints ? 1u : 0u;
   A.update_hints = no_hints ? 0u : 1u;
   A.mask_momentum = (flags & RGC_NO_MOMENTUM_MASK) ? 0u : 1u;
   // The lists of dense layers are allocated by the first call that shows the context a plan with such layers (or one
   // that needs longer lists; hipFree waits for the kernels that may still use the old ones).  Without them (the device
   // is short of memory) those layers simply take the hint-free path, as they would on a first call.
-  bool dense_ok = plan->any_dense;
-  if (plan->any_dense && (ctx->d_slots2.n < plan->list_entries || ctx->d_members2.n < plan->member_entries || !ctx->d_shards.p)) {
-    const uint64_t want = plan->list_entries * (sizeof(uint2) + sizeof(float)) + plan->member_entries * sizeof(unsigned long long);
+  bool dense_ok = plan->any_dense && !plan->finish;     // (a finishable list needs them neither with hints nor without)
+  if (dense_ok && (ctx->d_slots2.n < plan->general.list_entries || ctx->d_members2.n < plan->general.member_entries || !ctx->d_shards.p)) {
+    const uint64_t want = plan->general.list_entries * (sizeof(uint2) + sizeof(float)) + plan->general.member_entries * sizeof(unsigned long long);
     const bool capped = ctx->optional_scratch_cap >= 0 && want > static_cast<uint64_t>(ctx->optional_scratch_cap);
-    hipError_t e = capped ? hipErrorOutOfMemory : ctx->d_slots2.alloc(plan->list_entries);
-    if (e == hipSuccess) e = ctx->d_slots_u.alloc(plan->list_entries);
-    if (e == hipSuccess) e = ctx->d_members2.alloc(plan->member_entries);
+    hipError_t e = capped ? hipErrorOutOfMemory : ctx->d_slots2.alloc(plan->general.list_entries);
+    if (e == hipSuccess) e = ctx->d_slots_u.alloc(plan->general.list_entries);
+    if (e == hipSuccess) e = ctx->d_members2.alloc(plan->general.member_entries);
     if (e == hipSuccess && !ctx->d_shards.p) e = ctx->d_shards.alloc(static_cast<size_t>(ctx->max_layers) * kMemberLists * kShardStride);
     if (e != hipSuccess) {
       ctx->d_slots2.release();
@@ -765,7 +819,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   ctx->compressed_since_decompress = true;
   A.nesterov = (flags & RGC_NESTEROV) ? 1u : 0u;
   // a call that leaves most of the device idle spreads its candidate lists over as many workgroups as it has
-  A.list_group = plan->num_wgs <= kSmallCallWorkgroups ? 1u : kListGroup;
+  A.list_group = num_wgs <= kSmallCallWorkgroups ? 1u : kListGroup;
   A.grad_scale = grad_scale;
   A.m = momentum;
   A.launch = 1;
@@ -773,14 +827,29 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   // decide from the same state, which neither changes before its layer is done).  They are ranked at launch 2 and
   // written at launch 3 by lists_kernel; one whose hint misses has its residual put right at launch 2, where it
   // also starts on the five passes.
+  A.late = ctx->d_err.p + 2;
+  if (A.use_hints) {
+    A.late_first = finish ? 3u : kFirstLateLaunch;
+    A.late_last = A.late_first + (finish ? 4u : 2u);
+  }
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));
-  RGC_HIP(launch_accumulate(A, plan->num_wgs, stream));
-  if (dense) RGC_HIP(launch_collect(A, plan->num_wgs, stream));
+  if (finish) RGC_HIP(launch_tiles(A, num_wgs, stream));
+  else RGC_HIP(launch_accumulate(A, num_wgs, stream));
+  if (dense) RGC_HIP(launch_collect(A, num_wgs, stream));
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));
-  for (int launch = 2; launch <= kLaunches; ++launch) {
-    A.launch = static_cast<uint32_t>(launch);
-    RGC_HIP(launch_phase(A, plan->num_wgs, stream));
-    if (dense && launch <= 3) RGC_HIP(launch_lists(A, plan->num_wgs, stream));
+  if (finish) {
+    RGC_HIP(launch_finish(A, static_cast<uint32_t>(num_layers), stream));
+    if (plan->finish_lists) RGC_HIP(launch_fallback(A, num_wgs, ctx->cus, stream));
+  } else {
+    for (int launch = 2; launch <= kLaunches; ++launch) {
+      if (A.use_hints && launch == static_cast<int>(kFirstLateLaunch)) {
+        RGC_HIP(launch_fallback(A, num_wgs, ctx->cus, stream));
+        break;
+      }
+      A.launch = static_cast<uint32_t>(launch);
+      RGC_HIP(launch_phase(A, num_wgs, stream));
+      if (dense && launch <= 3) RGC_HIP(launch_lists(A, num_wgs, stream));
+    }
   }
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));
   if (!no_hints) {

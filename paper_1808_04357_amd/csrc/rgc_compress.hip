@@ -107,18 +107,27 @@ __device__ __forceinline__ uint32_t mask_key_for(uint32_t T, uint32_t tn, uint32
 // entries it had listed by then (as a count that is beyond every capacity, so the layer's hint counts as missed).
 constexpr uint32_t kListStopped = 0x80000000u;
 
+// What the streaming pass does with the accumulated values.
+enum Take : int {
+  kTakeDigit = 0,    // first digit's histogram (hint-free)
+  kTakeCoarse = 1,   // candidate lists and the coarse histogram of the candidates
+  kTakeList = 2,     // candidate lists only (finish_kernel makes the histogram)
+  kTakeNothing = 3,  // finish_kernel reads the residual itself
+};
+
 // Consume the four accumulated values a lane holds (elements idx0 .. idx0+3, the first
 // `nvalid` of which exist).  Element order inside the wave is lane-major.
-template <bool kCollect>
+template <Take kTake>
 __device__ __forceinline__ void consume(const float (&a)[4], uint32_t nvalid, uint32_t idx0,
                                         Collector& c, uint32_t* lds_hist, uint32_t& zeros) {
+  if constexpr (kTake == kTakeNothing) return;
   uint32_t bits[4], key[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     bits[j] = fbits(a[j]);
     key[j] = key_of(bits[j], c.sign_xor, c.sign_filter);
   }
-  if constexpr (kCollect) {
+  if constexpr (kTake == kTakeCoarse || kTake == kTakeList) {
     bool f[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) f[j] = (static_cast<uint32_t>(j) < nvalid) && (key[j] >= c.tau);
@@ -132,7 +141,7 @@ __device__ __forceinline__ void consume(const float (&a)[4], uint32_t nvalid, ui
         if (f[j]) {
           if (pos < c.cap) {
             c.slot[pos] = vu2{bits[j], idx0 + j};
-            atomicAdd(&c.coarse[coarse_bin(key[j], c.tau, c.shift)], 1u);
+            if constexpr (kTake == kTakeCoarse) atomicAdd(&c.coarse[coarse_bin(key[j], c.tau, c.shift)], 1u);
           }
           ++pos;
         }
@@ -157,7 +166,7 @@ __device__ __forceinline__ uint32_t zero_bin(uint32_t sign_xor, uint32_t sign_fi
 }
 
 // Streaming pass over one wave-chunk [begin, end) of a layer.
-template <bool kNt, bool kMom, bool kCollect, bool kNest = false>
+template <bool kNt, bool kMom, Take kTake, bool kNest = false>
 __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin, uint32_t end,
                                              const AccumRule m, Collector& c, uint32_t* lds_hist) {
   const uint32_t lane = lane_id();
@@ -168,7 +177,7 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
     const gcvf4 G4 = as_vec(L.grad + begin);
     const gvf4 V4 = as_vec(L.resid + begin);
     const gvf4 U4 = kMom ? as_vec(L.mom + begin) : nullptr;
-    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;   // 16-byte loads in flight per lane: 6, 8 or 12
+    constexpr uint32_t kUnroll = kMom && !kNt && kTake < kTakeList ? 2u : 4u;   // 16-byte loads in flight per lane: 6, 8 or 12
     uint32_t g = 0;
     for (; g + kUnroll <= nfull; g += kUnroll) {
       vf4 gv[kUnroll], vv[kUnroll], uv[kUnroll];
@@ -190,7 +199,7 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
         accum4<kMom, kNest>(gg, vvv, uu, m, a);
         stream_store<kNt>(V4 + o, vf4{a[0], a[1], a[2], a[3]});
         if constexpr (kMom) stream_store<kNt>(U4 + o, vf4{uu[0], uu[1], uu[2], uu[3]});
-        consume<kCollect>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
+        consume<kTake>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
       }
     }
     for (; g < nfull; ++g) {
@@ -205,7 +214,7 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
       accum4<kMom, kNest>(gg, vvv, uu, m, a);
       stream_store<kNt>(V4 + o, vf4{a[0], a[1], a[2], a[3]});
       if constexpr (kMom) stream_store<kNt>(U4 + o, vf4{uu[0], uu[1], uu[2], uu[3]});
-      consume<kCollect>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
+      consume<kTake>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
     }
     base = begin + nfull * kGroupElems;
   }
@@ -234,9 +243,9 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
         if constexpr (kMom) Us[idx0 + j] = uu[j];
       }
     }
-    consume<kCollect>(a, nvalid, idx0, c, lds_hist, zeros);
+    consume<kTake>(a, nvalid, idx0, c, lds_hist, zeros);
   }
-  if constexpr (!kCollect) {
+  if constexpr (kTake == kTakeDigit) {
     if (zeros) atomicAdd(&lds_hist[zero_bin(c.sign_xor, c.sign_filter)], zeros);
   }
 }
@@ -308,11 +317,43 @@ __device__ __forceinline__ uint32_t drifted_tau(uint32_t tau_rank, uint32_t T, u
   return static_cast<uint32_t>(t);
 }
 
+// Whether a layer takes the streaming pass with its hint.  (With a sign filter a threshold of 0 would let the elements
+// that key_of() ranks last and equal into the lists.)
+__device__ __forceinline__ bool hint_usable(const CompressArgs& A, const LayerState* st) {
+  return A.use_hints && st->hint_valid != 0u && !(A.sign_filter != 0u && st->tau == 0u);
+}
+
+// The next call's threshold before drift: the coarse bin `hbin` that holds rank `target` of this call's candidates, or,
+// where the lists end above that rank, an extrapolation with the key density seen between rank k (in bin `bstar`)
+// and the end of the lists (it grows further down, so this errs towards more candidates).
+__device__ __forceinline__ uint32_t next_threshold(uint32_t tau, uint32_t shift, uint32_t bstar, uint32_t hbin, uint32_t total,
+                                                   uint32_t k, uint32_t target) {
+  if (hbin != 0xFFFFFFFFu) {
+    const unsigned long long tn = static_cast<unsigned long long>(tau) + (static_cast<unsigned long long>(hbin) << shift);
+    return tn > kKeyMask ? kKeyMask : static_cast<uint32_t>(tn);
+  }
+  const unsigned long long d = (static_cast<unsigned long long>(bstar) + 1ull) << shift;
+  const unsigned long long have = total > k ? total - k : 1u;
+  const unsigned long long need = target - total;
+  const unsigned long long delta = (d * need + have - 1ull) / have + 1ull;
+  return delta < tau ? static_cast<uint32_t>(tau - delta) : 0u;
+}
+
+// The next call's hint from this call's k-th key T and the threshold `tau_next` derived above.
+__device__ __forceinline__ void next_hint(LayerState* st, uint32_t T, uint32_t tau_next) {
+  const uint32_t tn = tau_next <= T ? tau_next : T;
+  st->tau = drifted_tau(tn, T, st->T_prev, st->has_prev != 0u);
+  st->shift = shift_for(T, tn);
+  st->hint_valid = 1u;               // (a hint-free call that collected after its first digit gets its hint here)
+  st->T_prev = T;
+  st->has_prev = 1u;
+}
+
 constexpr uint32_t kOffsetGroup = 64;   // wave-chunks whose output offsets one wave of PH_OUT_C derives by itself
 static_assert(kOffsetGroup == kWaveSize, "one lane per wave-chunk of the group");
 
 struct ResolveShared {
-  uint32_t scan[4];
+  uint32_t scan[kFinishWaves];
   uint32_t flag;
   uint32_t bin, above, cnt;     // bin holding the k-th key, keys above it, keys in it
   uint32_t hbin, hcum, hcnt;    // bin where the cumulative count reaches the hint's target rank
@@ -357,10 +398,11 @@ __device__ __forceinline__ void stage_hist(uint32_t* g, uint32_t* lds) {
 // count first reaches want_k and want_h.  Results go to sh.{bin,above,cnt} and
 // sh.{hbin,hcum,hcnt} (bin = ~0 when the total stays below the wanted count); returns the total.
 // Kept light on registers: this code shares a kernel with the streaming loop.
+template <uint32_t kThreads = kBlockThreads>
 __device__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t want_k, uint32_t want_h,
                                     ResolveShared& sh) {
   const uint32_t t = threadIdx.x;
-  const uint32_t per = bins >= static_cast<uint32_t>(kBlockThreads) ? bins / kBlockThreads : 1u;
+  const uint32_t per = bins >= kThreads ? bins / kThreads : 1u;
   const bool active = t * per < bins;
   uint32_t s = 0;
   if (active) {
@@ -369,7 +411,7 @@ __device__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t
   }
   if (t == 0) { sh.bin = 0xFFFFFFFFu; sh.hbin = 0xFFFFFFFFu; sh.above = 0; sh.cnt = 0; sh.hcum = 0; sh.hcnt = 0; }
   uint32_t total;
-  const uint32_t ex = block_excl_scan(s, sh.scan, total);   // barriers inside: the init is visible
+  const uint32_t ex = block_excl_scan<kThreads / kWaveSize>(s, sh.scan, total);   // barriers inside: the init is visible
   if (active && ((ex < want_k && want_k <= ex + s) || (ex < want_h && want_h <= ex + s))) {
     uint32_t cum = ex;
 #pragma unroll 1
@@ -383,6 +425,12 @@ __device__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t
   }
   __syncthreads();
   return total;
+}
+
+// The layer's next phase runs at this launch number; fallback_kernel is told if that is the first of those it stands for.
+__device__ __forceinline__ void schedule_launch(const CompressArgs& A, LayerState* st, uint32_t launch) {
+  st->next_launch = launch;
+  if (launch == A.late_first) st_agent(A.late, 1u);
 }
 
 // Multi-pass path, one radix digit: the layer's histogram of this digit is complete.  Find the
@@ -480,7 +528,7 @@ __device__ void resolve_digit(const CompressArgs& A, uint32_t l, const LayerDesc
       }
     }
     st->hint_pending = pend;
-    st->next_launch = cur_launch + 1u;
+    schedule_launch(A, st, cur_launch + 1u);
   }
 }
 
@@ -545,21 +593,7 @@ __device__ void resolve_collect(const CompressArgs& A, uint32_t l, const LayerDe
       st->nmembers = 0u;
       if (!after_first_digit) st->path = 0u;
       st->next_phase = dense ? PH_SEL2 : PH_SEL;
-      unsigned long long tn;
-      if (sh.hbin != 0xFFFFFFFFu) {
-        tn = static_cast<unsigned long long>(tau) + (static_cast<unsigned long long>(sh.hbin) << shift);
-        if (tn > kKeyMask) tn = kKeyMask;
-      } else {
-        // the lists end above rank 2k + margin: extend tau downwards assuming the key density
-        // seen between rank k and the end of the lists (it grows further down, so this errs
-        // towards more candidates)
-        const unsigned long long d = (static_cast<unsigned long long>(sh.bin) + 1ull) << shift;
-        const unsigned long long have = cand_total > k ? cand_total - k : 1u;
-        const unsigned long long need = target - cand_total;
-        const unsigned long long delta = (d * need + have - 1ull) / have + 1ull;
-        tn = delta < tau ? tau - delta : 0ull;
-      }
-      st->tau_next = static_cast<uint32_t>(tn);
+      st->tau_next = next_threshold(tau, shift, sh.bin, sh.hbin, cand_total, k, target);
     } else if (after_first_digit) {
       st->next_phase = PH_HIST2;          // prefix and k_rem are still those of the first digit
     } else if (dense) {
@@ -572,7 +606,7 @@ __device__ void resolve_collect(const CompressArgs& A, uint32_t l, const LayerDe
       st->stat_misses += 1u;
       st->next_phase = PH_HIST1;
     }
-    st->next_launch = cur_launch + 1u;
+    schedule_launch(A, st, cur_launch + 1u);
   }
 }
 
@@ -626,12 +660,13 @@ __device__ void scan_chunks(uint32_t* a, uint32_t* b, uint32_t count, uint32_t r
 // sort of the same values took 55 dependent LDS round trips.)  All threads of the workgroup call
 // it; hist holds 3 * 256 words.
 static_assert(kBlockThreads == 256, "one thread per histogram bin");   // (PH_SEL also counts on hist holding 3 * kBlockThreads words)
+template <uint32_t kThreads = kBlockThreads>
 __device__ unsigned long long select_kth_largest(const unsigned long long* v, uint32_t m, uint32_t kk,
                                                  uint32_t* hist, ResolveShared& sh) {
   const uint32_t t = threadIdx.x, lane = lane_id();
   const unsigned long long v0 = v[0];
   unsigned long long diff = 0ull;
-  for (uint32_t i = t; i < m; i += kBlockThreads) diff |= v[i] ^ v0;
+  for (uint32_t i = t; i < m; i += kThreads) diff |= v[i] ^ v0;
   int top = diff ? 63 - __clzll(static_cast<long long>(diff)) : -1;   // highest differing bit this thread saw
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -639,12 +674,13 @@ __device__ unsigned long long select_kth_largest(const unsigned long long* v, ui
     top = other > top ? other : top;
   }
   if (lane == 0) sh.scan[t >> 6] = static_cast<uint32_t>(top + 1);
-  hist[t] = 0u; hist[256u + t] = 0u; hist[512u + t] = 0u;
+  if (t < 256u) { hist[t] = 0u; hist[256u + t] = 0u; hist[512u + t] = 0u; }
   __syncthreads();
   {
-    const uint32_t a = sh.scan[0], b = sh.scan[1], c = sh.scan[2], d = sh.scan[3];
-    const uint32_t ab = a > b ? a : b, cd = c > d ? c : d;
-    top = static_cast<int>(ab > cd ? ab : cd) - 1;
+    uint32_t m1 = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < kThreads / kWaveSize; ++w) m1 = sh.scan[w] > m1 ? sh.scan[w] : m1;
+    top = static_cast<int>(m1) - 1;
   }
   if (top < 0) return v0;                                   // a single value
   int shift = (top >> 3) << 3;
@@ -652,12 +688,12 @@ __device__ unsigned long long select_kth_largest(const unsigned long long* v, ui
   for (uint32_t pass = 0;; ++pass, shift -= 8) {
     uint32_t* const H = hist + (pass % 3u) * 256u;
     const unsigned long long himask = shift == 56 ? 0ull : (~0ull << (shift + 8));
-    for (uint32_t i = t; i < m; i += kBlockThreads) {
+    for (uint32_t i = t; i < m; i += kThreads) {
       const unsigned long long x = v[i];
       if ((x & himask) == prefix) atomicAdd(&H[static_cast<uint32_t>(x >> shift) & 255u], 1u);
     }
     __syncthreads();
-    hist[((pass + 2u) % 3u) * 256u + t] = 0u;
+    if (t < 256u) hist[((pass + 2u) % 3u) * 256u + t] = 0u;
     // each wave for itself: lane L holds bins 4L .. 4L+3
     const uint32_t h0 = H[4u * lane], h1 = H[4u * lane + 1u], h2 = H[4u * lane + 2u], h3 = H[4u * lane + 3u];
     const uint32_t mine = h0 + h1 + h2 + h3;
@@ -686,7 +722,7 @@ __device__ unsigned long long select_kth_largest(const unsigned long long* v, ui
   }
   // one value is left under these leading bytes: whoever holds it tells the others
   const unsigned long long lomask = ~0ull << shift;
-  for (uint32_t i = t; i < m; i += kBlockThreads) {
+  for (uint32_t i = t; i < m; i += kThreads) {
     const unsigned long long x = v[i];
     if ((x & lomask) == prefix) { sh.hbin = static_cast<uint32_t>(x); sh.hcum = static_cast<uint32_t>(x >> 32); }
   }
@@ -714,8 +750,7 @@ __global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs 
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   LayerState* st = A.state + l;
-  // (with a sign filter a threshold of 0 would let the elements that key_of() ranks last and equal into the lists)
-  const bool hinted = A.use_hints && (st->hint_valid != 0u) && !(A.sign_filter != 0u && st->tau == 0u);
+  const bool hinted = hint_usable(A, st);
   if (A.dense_ok && L.dense && hinted && st->dense_skip == 0u) return;     // collect_kernel has this layer
   const bool collect = hinted && L.hintable;
   // the same LDS array serves as 4096-bin digit histogram (hint-free) or 1024-bin coarse one
@@ -741,14 +776,14 @@ __global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs 
     rule.m = A.m;
     rule.scale = A.grad_scale ? *as_global(A.grad_scale) : 1.0f;
     if (collect) {
-      if (!mom) stream_chunk<kNt, false, true>(L, begin, end, rule, c, lds_hist);
-      else if (!A.nesterov) stream_chunk<kNt, true, true>(L, begin, end, rule, c, lds_hist);
-      else stream_chunk<kNt, true, true, true>(L, begin, end, rule, c, lds_hist);
+      if (!mom) stream_chunk<kNt, false, kTakeCoarse>(L, begin, end, rule, c, lds_hist);
+      else if (!A.nesterov) stream_chunk<kNt, true, kTakeCoarse>(L, begin, end, rule, c, lds_hist);
+      else stream_chunk<kNt, true, kTakeCoarse, true>(L, begin, end, rule, c, lds_hist);
       if (lane_id() == 0) st_agent(&A.cand_cnt[L.wc_first + wc_local], c.count);
     } else {
-      if (!mom) stream_chunk<kNt, false, false>(L, begin, end, rule, c, lds_hist);
-      else if (!A.nesterov) stream_chunk<kNt, true, false>(L, begin, end, rule, c, lds_hist);
-      else stream_chunk<kNt, true, false, true>(L, begin, end, rule, c, lds_hist);
+      if (!mom) stream_chunk<kNt, false, kTakeDigit>(L, begin, end, rule, c, lds_hist);
+      else if (!A.nesterov) stream_chunk<kNt, true, kTakeDigit>(L, begin, end, rule, c, lds_hist);
+      else stream_chunk<kNt, true, kTakeDigit, true>(L, begin, end, rule, c, lds_hist);
     }
   }
   __syncthreads();
@@ -857,7 +892,7 @@ __device__ void phase_collect(const CompressArgs& A, uint32_t l, const LayerDesc
     uint32_t zeros = 0;
     for_each_group(L.resid, begin, end,
                    [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
-                     consume<true>(a, nvalid, idx0, c, lds_hist, zeros);
+                     consume<kTakeCoarse>(a, nvalid, idx0, c, lds_hist, zeros);
                    });
     if (lane_id() == 0) st_agent(&A.cand_cnt[L.wc_first + wc_local], c.count);
   }
@@ -899,7 +934,7 @@ __device__ void phase_count(const CompressArgs& A, uint32_t l, const LayerDesc& 
     if (threadIdx.x == 0) {
       if (sh.cnt != L.k) atomicOr(A.errflag, 2u);
       st->next_phase = PH_OUT_V;
-      st->next_launch = A.launch + 1u;
+      schedule_launch(A, st, A.launch + 1u);
     }
   }
 }
@@ -1092,16 +1127,9 @@ __device__ void phase_sel(const CompressArgs& A, uint32_t l, const LayerDesc& L,
     const uint32_t T = static_cast<uint32_t>(thr >> 32);
     st->thr = thr;
     st->T = T;
-    if (A.update_hints) {
-      const uint32_t tn = st->tau_next <= T ? st->tau_next : T;
-      st->tau = drifted_tau(tn, T, st->T_prev, st->has_prev != 0u);
-      st->shift = shift_for(T, tn);
-      st->hint_valid = 1u;               // (a hint-free call that collected after its first digit gets its hint here)
-      st->T_prev = T;
-      st->has_prev = 1u;
-    }
+    if (A.update_hints) next_hint(st, T, st->tau_next);
     st->next_phase = PH_OUT_C;
-    st->next_launch = A.launch + 1u;
+    schedule_launch(A, st, A.launch + 1u);
   }
 }
 
@@ -1207,7 +1235,6 @@ __global__ void __launch_bounds__(kBlockThreads) phase_kernel(CompressArgs A) {
 // collected its candidates in launch 2, and in steady state they meet nothing at
 // all.  They get a kernel of their own that needs next to no LDS: twice as many of its
 // workgroups fit on the device at once, so the launches that find nothing to do are over sooner.
-constexpr uint32_t kFirstLateLaunch = 4;
 __global__ void __launch_bounds__(kBlockThreads) phase_late_kernel(CompressArgs A) {
   __shared__ uint32_t hist[256];   // the last digit: 7 or 8 bits
   __shared__ ResolveShared sh;
@@ -1223,6 +1250,385 @@ __global__ void __launch_bounds__(kBlockThreads) phase_late_kernel(CompressArgs 
     case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
     case PH_OUT_C: phase_out_c(A, L, st, wg); break;                  // a hint-free call that collected after its first digit
     default: if (threadIdx.x == 0) atomicOr(A.errflag, 16u); break;   // no other phase can be due this late
+  }
+}
+
+// =================================================================== finishable calls: two launches
+// Launch 1: the streaming pass alone.  A wave takes 1024 elements with all its loads in flight at once and nothing to wait
+// for after its stores (a wave that loops waits for the stores of one round with the loads of the next: they share a
+// counter), leaves the candidates of a layer with a hint in the wave-chunk's list, and that is all: no histogram, no election.
+// ResNet-50 set: 52 us, 5.9 TB/s, where accumulate_kernel takes 71 us; the copy rate is 4.9 TB/s.
+template <bool kNt>
+__global__ void __launch_bounds__(kBlockThreads) tile_kernel(CompressArgs A) {
+  const uint32_t wg = blockIdx.x;
+  const uint32_t l = A.wg2layer[wg];
+  const LayerDesc L = A.layers[l];
+  const LayerState* st = A.state + l;
+  const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
+  if (wc_local >= L.wc_count) return;
+  const uint32_t begin = wc_local * A.chunk;
+  const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
+  Collector c;
+  c.slot = as_global(reinterpret_cast<vu2*>(A.slots + static_cast<size_t>(L.wc_first + wc_local) * A.cap));
+  c.coarse = nullptr;
+  c.cap = A.cap;
+  c.count = 0;
+  c.tau = st->tau;
+  c.shift = 0u;
+  c.sign_xor = A.sign_xor;
+  c.sign_filter = A.sign_filter;
+  const bool mom = (L.mom != nullptr);
+  AccumRule rule;
+  rule.m = A.m;
+  rule.scale = A.grad_scale ? *as_global(A.grad_scale) : 1.0f;
+  if (!L.direct && hint_usable(A, st)) {
+    if (!mom) stream_chunk<kNt, false, kTakeList>(L, begin, end, rule, c, nullptr);
+    else if (!A.nesterov) stream_chunk<kNt, true, kTakeList>(L, begin, end, rule, c, nullptr);
+    else stream_chunk<kNt, true, kTakeList, true>(L, begin, end, rule, c, nullptr);
+    if (lane_id() == 0) A.cand_cnt[L.wc_first + wc_local] = c.count;
+  } else {
+    if (!mom) stream_chunk<kNt, false, kTakeNothing>(L, begin, end, rule, c, nullptr);
+    else if (!A.nesterov) stream_chunk<kNt, true, kTakeNothing>(L, begin, end, rule, c, nullptr);
+    else stream_chunk<kNt, true, kTakeNothing, true>(L, begin, end, rule, c, nullptr);
+  }
+}
+
+namespace {
+
+struct FinishShared {
+  union {
+    float vals[kDirectMax];                                  // a direct layer's residual
+    struct {
+      vu2 cand[kFinishCand];                                 // a layer's candidates, in index order
+      unsigned long long members[kMemberMax];                // those of the coarse bin that holds the k-th key
+    } list;
+  } u;
+  unsigned long long few[kFinishThreads];                    // direct layers: the elements left to rank
+  uint32_t hist[kHistBins];
+  uint32_t sel_hist[3 * 256];
+  uint32_t nfew, bad;
+  ResolveShared sh;
+};
+static_assert(sizeof(FinishShared) <= 160 * 1024, "one workgroup per CU");
+
+// The message of an exactly selected layer is written by waves that each own a consecutive range: sel(i) says whether
+// entry i is sent, put(i, pos) writes it.  Returns the number of entries sent.
+template <typename Sel, typename Put>
+__device__ __forceinline__ uint32_t emit_ordered(uint32_t count, FinishShared& S, Sel&& sel, Put&& put) {
+  const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+  const uint32_t per = ((count + kFinishWaves - 1u) / kFinishWaves + kWaveSize - 1u) / kWaveSize * kWaveSize;
+  const uint32_t first = wave * per < count ? wave * per : count;
+  const uint32_t last = first + per < count ? first + per : count;
+  uint32_t mine = 0u;
+  for (uint32_t b = first; b < last; b += kWaveSize) mine += popc64(__ballot(b + lane < last && sel(b + lane)));
+  __syncthreads();
+  if (lane == 0) S.sh.scan[wave] = mine;
+  __syncthreads();
+  uint32_t at = 0u, total = 0u;
+#pragma unroll
+  for (uint32_t w = 0; w < kFinishWaves; ++w) {
+    at += w < wave ? S.sh.scan[w] : 0u;
+    total += S.sh.scan[w];
+  }
+  for (uint32_t b = first; b < last; b += kWaveSize) {
+    const bool s = b + lane < last && sel(b + lane);
+    const unsigned long long m = __ballot(s);
+    if (s) put(b + lane, at + rank_below(m));
+    at += popc64(m);
+  }
+  return total;
+}
+
+// A layer of at most kDirectMax elements, any density, no hint: radix selection over the composites
+// (key, then lower index first) in LDS, 12 bits at a time from the top, until the elements that share the bits fixed
+// so far are few enough to be ranked at once (after the first digit, usually).
+__device__ void finish_direct(const CompressArgs& A, const LayerDesc& L, LayerState* st, FinishShared& S) {
+  const uint32_t t = threadIdx.x, n = L.n;
+  constexpr uint32_t kLoads = kDirectMax / (4u * kFinishThreads);
+  {
+    vf4 q[kLoads];
+#pragma unroll
+    for (uint32_t i = 0; i < kLoads; ++i) {
+      const uint32_t e = 4u * (i * kFinishThreads + t);
+      if (e + 4u <= n) q[i] = *as_vec(static_cast<const float*>(L.resid) + e);
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kLoads; ++i) {
+      const uint32_t e = 4u * (i * kFinishThreads + t);
+      if (e + 4u <= n) {
+        S.u.vals[e] = q[i].x; S.u.vals[e + 1u] = q[i].y; S.u.vals[e + 2u] = q[i].z; S.u.vals[e + 3u] = q[i].w;
+      } else {
+        for (uint32_t j = e; j < n && j < e + 4u; ++j) S.u.vals[j] = as_global(static_cast<const float*>(L.resid))[j];
+      }
+    }
+  }
+  const uint32_t up = A.sign_filter ? 0u : 1u;               // the magnitude key has 31 bits, the ordered one 32
+  auto comp = [&](uint32_t i) -> unsigned long long {
+    const uint32_t key = ordered_key(fbits(S.u.vals[i]), A.sign_xor, A.sign_filter) << up;
+    return (static_cast<unsigned long long>(key) << kDirectMaxLog2) | (kDirectMax - 1u - i);
+  };
+  const uint32_t zero_key = ordered_key(0u, A.sign_xor, A.sign_filter) << up;
+  uint32_t shift = 32u + kDirectMaxLog2, rem = L.k;
+  unsigned long long prefix = 0ull, thr = 0ull;
+  for (uint32_t level = 0; level < 4u; ++level) {
+    const uint32_t bits = level < 3u ? 12u : 32u + kDirectMaxLog2 - 36u, mask = (1u << bits) - 1u;
+    shift -= bits;
+    for (uint32_t b = t; b <= mask; b += kFinishThreads) S.hist[b] = 0u;
+    if (t == 0) S.nfew = 0u;
+    __syncthreads();
+    uint32_t zeros = 0u;                                     // (the zeros of a sparse tensor would all hit one bin)
+    for (uint32_t i = t; i < n; i += kFinishThreads) {
+      const unsigned long long c = comp(i);
+      if ((c >> (shift + bits)) != prefix) continue;
+      if (level < 2u && static_cast<uint32_t>(c >> kDirectMaxLog2) == zero_key) ++zeros;
+      else atomicAdd(&S.hist[static_cast<uint32_t>(c >> shift) & mask], 1u);
+    }
+    if (level < 2u) {
+      const uint32_t z = wave_total(wave_incl_scan(zeros));
+      if (z != 0u && lane_id() == 0) atomicAdd(&S.hist[static_cast<uint32_t>((static_cast<unsigned long long>(zero_key) << kDirectMaxLog2) >> shift) & mask], z);
+    }
+    __syncthreads();
+    (void)locate_from_top<kFinishThreads>(S.hist, mask + 1u, rem, 0xFFFFFFFFu, S.sh);
+    const uint32_t bin = S.sh.bin, cnt = S.sh.cnt;
+    if (bin == 0xFFFFFFFFu) {                                // cannot happen: k <= n
+      if (t == 0) atomicOr(A.errflag, 128u);
+      return;
+    }
+    rem -= S.sh.above;
+    prefix = (prefix << bits) | bin;
+    if (level == 3u) { thr = prefix; break; }                // every bit is fixed: the element itself
+    if (cnt <= kFinishThreads) {
+      for (uint32_t i = t; i < n; i += kFinishThreads) {
+        const unsigned long long c = comp(i);
+        if ((c >> shift) == prefix) S.few[atomicAdd(&S.nfew, 1u)] = c;
+      }
+      __syncthreads();
+      thr = select_kth_largest<kFinishThreads>(S.few, cnt, rem, S.sel_hist, S.sh);
+      break;
+    }
+    __syncthreads();                                         // everyone has read sh before the next digit's init
+  }
+  const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
+  const gptr<int32_t> out_idx = as_global(L.out_idx);
+  const gptr<float> out_val = as_global(L.out_val);
+  const gptr<float> resid = as_global(L.resid);
+  const gptr<float> mom = as_global(L.mom);
+  const uint32_t sent = emit_ordered(n, S, [&](uint32_t i) { return comp(i) >= thr; },
+                                     [&](uint32_t i, uint32_t pos) {
+                                       if (pos >= L.k) return;         // never when the selection is right
+                                       out_idx[pos] = static_cast<int32_t>(i);
+                                       out_val[pos] = S.u.vals[i];
+                                       resid[i] = 0.0f;
+                                       if (clear_mom) mom[i] = 0.0f;
+                                     });
+  if (t == 0) {
+    if (sent != L.k) atomicOr(A.errflag, 128u);
+    *as_global(L.out_count) = static_cast<int32_t>(L.k);
+    st->T = static_cast<uint32_t>(thr >> kDirectMaxLog2) >> up;
+    st->path = 1u;
+    st->stat_candidates = 0u;
+    st->stat_members = 0u;
+    st->next_phase = PH_NONE;
+    st->next_launch = 0u;
+  }
+}
+
+// A larger layer, from the lists its streaming pass left: they are copied into LDS in index order, the coarse histogram
+// and the ranking of the members are those of the one-pass path (resolve_collect, phase_sel), and the message is written
+// from LDS.  A hint that misses (or none) sends the layer through the digits in fallback_kernel.
+__device__ void finish_lists(const CompressArgs& A, const LayerDesc& L, LayerState* st, FinishShared& S) {
+  const uint32_t t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+  const bool hinted = hint_usable(A, st);
+  const uint32_t tau = st->tau, hshift = st->shift, k = L.k, target = L.target;
+  constexpr uint32_t kFirst = 4u;                            // entries of a list asked for together with its length
+  uint32_t total = 0u;
+  bool ok = hinted;
+  if (hinted) {
+    for (uint32_t b = t; b < kCoarseBins; b += kFinishThreads) S.hist[b] = 0u;
+    if (t == 0) { S.bad = 0u; S.nfew = 0u; }
+    __syncthreads();
+    // rounds of 1024 lists, one a thread: lengths and first entries together, then a scan
+    uint32_t base = 0u;
+    for (uint32_t c0 = 0; c0 < L.wc_count; c0 += kFinishThreads) {
+      const uint32_t c = c0 + t;
+      const bool have = c < L.wc_count;
+      const size_t list = static_cast<size_t>(L.wc_first + (have ? c : 0u)) * A.cap;
+      const gptr<const vu2> slot = as_global(reinterpret_cast<const vu2*>(A.slots + list));
+      vu2 first[kFirst];
+#pragma unroll
+      for (uint32_t j = 0; j < kFirst; ++j) first[j] = slot[j];
+      uint32_t cnt = have ? A.cand_cnt[L.wc_first + c] : 0u;
+      if (cnt > A.cap) { S.bad = 1u; cnt = 0u; }
+      uint32_t round;
+      const uint32_t at = base + block_excl_scan<kFinishWaves>(cnt, S.sh.scan, round);
+      if (at + cnt <= kFinishCand) {
+#pragma unroll
+        for (uint32_t j = 0; j < kFirst; ++j)
+          if (j < cnt) S.u.list.cand[at + j] = first[j];
+        if (cnt > kFirst) {                                  // the rest of a longer list: a wave takes it whole, below
+          const uint32_t qn = atomicAdd(&S.nfew, 1u);
+          if (qn < kFinishThreads) S.few[qn] = (static_cast<unsigned long long>(at) << 32) | (c << 8) | cnt;
+          else for (uint32_t j = kFirst; j < cnt; ++j) S.u.list.cand[at + j] = slot[j];
+        }
+      }
+      base += round;
+    }
+    total = base;
+    __syncthreads();
+    const uint32_t queued = S.nfew < kFinishThreads ? S.nfew : kFinishThreads;
+    constexpr uint32_t kBatch = 4u;                          // lists of a wave on their way at a time
+    for (uint32_t i0 = wave; i0 < queued; i0 += kBatch * kFinishWaves) {
+      vu2 e[kBatch];
+      unsigned long long item[kBatch];
+#pragma unroll
+      for (uint32_t b = 0; b < kBatch; ++b) {
+        const uint32_t i = i0 + b * kFinishWaves;
+        item[b] = i < queued ? S.few[i] : 0ull;
+        const uint32_t cnt = static_cast<uint32_t>(item[b]) & 0xFFu, c = (static_cast<uint32_t>(item[b]) >> 8);
+        if (lane >= kFirst && lane < cnt) e[b] = as_global(reinterpret_cast<const vu2*>(A.slots + static_cast<size_t>(L.wc_first + c) * A.cap))[lane];
+      }
+#pragma unroll
+      for (uint32_t b = 0; b < kBatch; ++b) {
+        const uint32_t cnt = static_cast<uint32_t>(item[b]) & 0xFFu;
+        if (lane >= kFirst && lane < cnt) S.u.list.cand[static_cast<uint32_t>(item[b] >> 32) + lane] = e[b];
+      }
+    }
+    __syncthreads();
+    ok = S.bad == 0u && total >= k && total <= kFinishCand;
+  }
+  auto key_at = [&](uint32_t i) { return key_of(S.u.list.cand[i].x, A.sign_xor, A.sign_filter); };
+  if (ok) {
+    for (uint32_t i = t; i < total; i += kFinishThreads) atomicAdd(&S.hist[coarse_bin(key_at(i), tau, hshift)], 1u);
+    __syncthreads();
+    (void)locate_from_top<kFinishThreads>(S.hist, kCoarseBins, k, target, S.sh);
+    ok = S.sh.bin != 0xFFFFFFFFu && S.sh.cnt <= static_cast<uint32_t>(kMemberMax);
+  }
+  if (!ok) {
+    if (t == 0) {
+      st->path = hinted ? 2u : 1u;
+      st->stat_misses += hinted ? 1u : 0u;
+      st->stat_candidates = total;
+      st->stat_members = 0u;
+      st->next_phase = PH_HIST1;
+      schedule_launch(A, st, 3u);
+    }
+    return;
+  }
+  const uint32_t bstar = S.sh.bin, above = S.sh.above, m = S.sh.cnt, hbin = S.sh.hbin;
+  if (t == 0) S.nfew = 0u;
+  __syncthreads();
+  for (uint32_t i = t; i < total; i += kFinishThreads) {
+    const uint32_t key = key_at(i);
+    if (coarse_bin(key, tau, hshift) == bstar) S.u.list.members[atomicAdd(&S.nfew, 1u)] = composite(key, S.u.list.cand[i].y);
+  }
+  __syncthreads();
+  const unsigned long long thr = select_kth_largest<kFinishThreads>(S.u.list.members, m, k - above, S.sel_hist, S.sh);
+  const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
+  const gptr<int32_t> out_idx = as_global(L.out_idx);
+  const gptr<float> out_val = as_global(L.out_val);
+  const gptr<float> resid = as_global(L.resid);
+  const gptr<float> mom = as_global(L.mom);
+  const uint32_t sent = emit_ordered(total, S, [&](uint32_t i) { return composite(key_at(i), S.u.list.cand[i].y) >= thr; },
+                                     [&](uint32_t i, uint32_t pos) {
+                                       const vu2 e = S.u.list.cand[i];
+                                       if (pos >= k || e.y >= L.n) return;     // never when the lists are right
+                                       out_idx[pos] = static_cast<int32_t>(e.y);
+                                       out_val[pos] = __uint_as_float(e.x);
+                                       mask_store(&resid[e.y]);
+                                       if (clear_mom) mask_store(&mom[e.y]);
+                                     });
+  if (t == 0) {
+    if (sent != k) atomicOr(A.errflag, 256u);
+    *as_global(L.out_count) = static_cast<int32_t>(k);
+    const uint32_t T = static_cast<uint32_t>(thr >> 32);
+    st->thr = thr;
+    st->T = T;
+    st->path = 0u;
+    st->stat_candidates = total;
+    st->stat_members = m;
+    if (A.update_hints) {
+      const uint32_t tn = next_threshold(tau, hshift, bstar, hbin, total, k, target);
+      next_hint(st, T, tn);
+    }
+    st->next_phase = PH_NONE;
+    st->next_launch = 0u;
+  }
+}
+
+}  // namespace
+
+// Launch 2: one workgroup ends one layer.  A chain of memory round trips and barriers, not of bytes: 12 us for one layer of
+// 2^20 elements, 27 us for the ResNet-50 set (its 32768-element layers).  Whole calls, six launches before and three now:
+// three layers of 50,000, 8,205 and 300 elements 26.9 -> 17.4 us, 2^20 elements 28.6 -> 17.1 us, ResNet-50 set 91 -> 82 us.
+__global__ void __launch_bounds__(kFinishThreads) finish_kernel(CompressArgs A) {
+  __shared__ FinishShared S;
+  const uint32_t l = blockIdx.x;
+  const LayerDesc L = A.layers[l];
+  LayerState* st = A.state + l;
+  if (L.direct) finish_direct(A, L, st, S);
+  else finish_lists(A, L, st, S);
+}
+
+// The last launch of a call that uses hints: the launches A.late_first .. A.late_last in one, for the layers whose hint
+// missed.  Nothing is due in steady state, and one launch that finds that out is cheaper than three (VGG16 set: 571 us per
+// call with three, 565 us with one).
+// Otherwise a grid of one workgroup per CU takes the workgroup numbers in turn, with a barrier over the grid between two
+// launch numbers: its release and acquire make plain stores visible across the XCDs, as a kernel boundary would.
+// The workgroups (256 threads, 17 KB of LDS) all fit on the device at once beside three more such kernels; the wait at the
+// barrier is bounded all the same, and running out of it is reported as an internal error.
+namespace {
+
+__device__ bool grid_barrier(uint32_t* word, uint32_t target, uint32_t* lds_flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    atomicAdd(word, 1u);
+    uint32_t spins = 0;
+    while (ld_agent(word) < target && spins < (1u << 23)) { __builtin_amdgcn_s_sleep(8); ++spins; }
+    *lds_flag = spins < (1u << 23) ? 1u : 0u;
+    __threadfence();
+  }
+  __syncthreads();
+  const bool ok = *lds_flag != 0u;
+  __syncthreads();
+  return ok;
+}
+
+}  // namespace
+
+__global__ void __launch_bounds__(kBlockThreads) fallback_kernel(CompressArgs A, uint32_t num_wgs) {
+  __shared__ uint32_t hist[kHistBins];
+  __shared__ ResolveShared sh;
+  if (ld_agent(A.late) == 0u) return;               // (all workgroups see the same: the word is reset by the last to leave)
+  for (uint32_t launch = A.late_first; launch <= A.late_last; ++launch) {
+    if (launch != A.late_first && !grid_barrier(A.late + 1, (launch - A.late_first) * gridDim.x, &sh.flag)) {
+      if (threadIdx.x == 0) atomicOr(A.errflag, 512u);
+      break;
+    }
+    A.launch = launch;
+    for (uint32_t wg = blockIdx.x; wg < num_wgs; wg += gridDim.x) {
+      const uint32_t l = A.wg2layer[wg];
+      LayerState* st = A.state + l;
+      if (st->next_launch != launch) continue;
+      const LayerDesc L = A.layers[l];
+      const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
+      switch (st->next_phase) {
+        case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, hist, sh); break;
+        case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, hist, sh); break;
+        case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, hist, sh); break;
+        case PH_COUNT: phase_count(A, l, L, st, wg, wc_local, sh); break;
+        case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
+        case PH_OUT_C: phase_out_c(A, L, st, wg); break;
+        default: if (threadIdx.x == 0) atomicOr(A.errflag, 16u); break;
+      }
+      __syncthreads();                               // the next workgroup number uses the same LDS
+    }
+  }
+  if (threadIdx.x == 0 && atomicAdd(A.late + 2, 1u) + 1u == gridDim.x) {
+    st_agent(A.late + 1, 0u);
+    st_agent(A.late + 2, 0u);
+    st_agent(A.late, 0u);
   }
 }
 
@@ -1437,8 +1843,7 @@ __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) 
   const LayerDesc L = A.layers[l];
   if (!L.dense) return;
   LayerState* st = A.state + l;
-  // the same condition as in accumulate_kernel
-  const bool hinted = A.use_hints && (st->hint_valid != 0u) && !(A.sign_filter != 0u && st->tau == 0u);
+  const bool hinted = hint_usable(A, st);            // the same condition as in accumulate_kernel
   if (!hinted || st->dense_skip != 0u) return;
   for (uint32_t b = threadIdx.x; b < static_cast<uint32_t>(kCoarseBins); b += kBlockThreads) lds_hist[b] = 0u;
   __syncthreads();
@@ -1769,7 +2174,7 @@ __device__ void dense_rank(const CompressArgs& A, uint32_t l, const LayerDesc& L
       st->has_prev = 1u;
     }
     st->next_phase = PH_EMIT;
-    st->next_launch = A.launch + 1u;
+    schedule_launch(A, st, A.launch + 1u);
   }
 }
 
@@ -2145,6 +2550,22 @@ hipError_t launch_lists(const CompressArgs& a, uint32_t num_wgs, hipStream_t s) 
 hipError_t launch_phase(const CompressArgs& a, uint32_t num_wgs, hipStream_t s) {
   if (a.launch >= kFirstLateLaunch) hipLaunchKernelGGL(phase_late_kernel, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
   else hipLaunchKernelGGL(phase_kernel, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_tiles(const CompressArgs& a, uint32_t num_wgs, hipStream_t s) {
+  if (a.past_cache) hipLaunchKernelGGL(tile_kernel<true>, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
+  else hipLaunchKernelGGL(tile_kernel<false>, dim3(num_wgs), dim3(kBlockThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_finish(const CompressArgs& a, uint32_t num_layers, hipStream_t s) {
+  hipLaunchKernelGGL(finish_kernel, dim3(num_layers), dim3(kFinishThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_fallback(const CompressArgs& a, uint32_t num_wgs, uint32_t cus, hipStream_t s) {
+  hipLaunchKernelGGL(fallback_kernel, dim3(num_wgs < cus ? num_wgs : cus), dim3(kBlockThreads), 0, s, a, num_wgs);
   return hipGetLastError();
 }
 

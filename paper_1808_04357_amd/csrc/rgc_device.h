@@ -55,8 +55,9 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t incl) {
   return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
 }
 
-// Exclusive prefix sum over the 256 threads of a workgroup.  `lds` holds >= 4 words.
+// Exclusive prefix sum over the threads of a workgroup of kWaves waves.  `lds` holds >= kWaves words.
 // Contains barriers: every thread of the workgroup must call it.
+template <uint32_t kWaves = kWavesPerBlock>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds, uint32_t& total) {
   const uint32_t incl = wave_incl_scan(v);
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -65,7 +66,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds, u
   __syncthreads();
   uint32_t off = 0, tot = 0;
 #pragma unroll
-  for (uint32_t w = 0; w < kWavesPerBlock; ++w) {
+  for (uint32_t w = 0; w < kWaves; ++w) {
     const uint32_t t = lds[w];
     off += (w < wave) ? t : 0u;
     tot += t;

@@ -39,6 +39,7 @@ enum Phase : uint32_t {
 // doubles with every further miss, up to this many.
 // Workgroups' worth of candidate lists one workgroup of PH_SEL / PH_OUT_C takes (CompressArgs::list_group:
 // kListGroup, or 1 for a call whose workgroups all fit on the device at once, where spreading the lists wins).
+constexpr uint32_t kFirstLateLaunch = 4;          // launches 4 .. 6 only meet the last phases
 constexpr uint32_t kListGroupLog2 = 2, kListGroup = 1u << kListGroupLog2;
 constexpr uint32_t kDenseBackoffMax = 64;
 // Dense layers: the members of the k-th key's coarse bin are appended to this many sub-lists, each with a counter
@@ -47,6 +48,16 @@ constexpr uint32_t kDenseBackoffMax = 64;
 constexpr uint32_t kMemberShards = 16;
 constexpr uint32_t kMemberLists = kMemberShards + 1;
 constexpr uint32_t kShardStride = 64;    // words between two counters: atomics on one cache line take their turns like atomics on one word
+
+// Calls whose layers are all small ("finishable") take two launches, a one-shot streaming pass and finish_kernel, which
+// ends a layer in one workgroup: a layer of at most kDirectMax elements from the residual itself (in LDS), a larger one
+// from its candidate lists, as long as the LDS has room for twice the rank its hint is aimed at (with room for half as many
+// more only, a layer whose residual was still building up missed on every call).
+constexpr uint32_t kFinishThreads = 1024, kFinishWaves = kFinishThreads / kWaveSize;
+constexpr uint32_t kDirectMaxLog2 = 15, kDirectMax = 1u << kDirectMaxLog2;
+constexpr uint32_t kFinishCand = 12288;            // candidates of a layer in LDS
+constexpr uint32_t kFinishTargetMax = kFinishCand / 2;   // largest target rank of such a layer (2.4 M elements at 0.1 %)
+constexpr uint32_t kTileChunk = 1024;              // elements per wave-chunk of such calls: one group of loads per wave
 
 // Per call, per layer descriptor (device copy of the caller's rgc_layer plus the tiling).
 struct LayerDesc {
@@ -72,6 +83,8 @@ struct LayerDesc {
   uint32_t mem_cap;    // dense layers: entries of the layer's kMemberShards sub-lists together (a multiple of kMemberShards); the
                        // overflow list behind them holds mem_cap / 4, which is also the most members a call accepts
   uint32_t list_cap;   // dense layers: entries of one wave-chunk's list
+  uint32_t direct;     // finishable calls: at most kDirectMax elements, selected from the residual itself
+  uint32_t pad_;
   uint64_t mem_first;  // dense layers: where the layer's region of the member pool starts
   uint64_t list_first; // dense layers: where the layer's lists start (wave-chunk c of the layer: list_first + c * list_cap)
 };
@@ -155,6 +168,9 @@ struct CompressArgs {
   uint32_t mask_momentum;
   float m;
   uint32_t launch;       // launch number of the phase kernel (2..6)
+  uint32_t* late;        // [3] fallback_kernel: layers are due, workgroups at the barrier, workgroups that have left
+  uint32_t late_first;   // the launch numbers fallback_kernel stands for (0: they are launches of their own)
+  uint32_t late_last;
   uint32_t sign_xor;     // selection key: see key_of() (0 / 0x80000000: which sign bit keeps an element in the ranking)
   uint32_t sign_filter;  // 0: every element ranks by magnitude; ~0: elements of the other sign rank last (key 0)
   uint32_t reverse;      // the streaming pass takes its workgroups in descending order
@@ -258,6 +274,9 @@ hipError_t launch_accumulate(const CompressArgs& a, uint32_t num_wgs, hipStream_
 hipError_t launch_collect(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);   // streaming pass of the dense layers
 hipError_t launch_lists(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);     // their ranking and output steps
 hipError_t launch_phase(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);
+hipError_t launch_tiles(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);        // streaming pass of a finishable call
+hipError_t launch_finish(const CompressArgs& a, uint32_t num_layers, hipStream_t s);
+hipError_t launch_fallback(const CompressArgs& a, uint32_t num_wgs, uint32_t cus, hipStream_t s);
 constexpr uint32_t kMeanPartsMax = 128;    // parts per layer at most (rgc_message_means)
 hipError_t launch_message_means(const CompressArgs& a, uint32_t num_layers, uint32_t max_k, const ExactParts& parts,
                                 float* d_means, hipStream_t s);

@@ -1,0 +1,164 @@
+"""GPU parity of the calls whose layers are all small enough to be ended by one workgroup each (bit equality): layers
+selected from the residual itself (up to 32768 elements), layers selected from their candidate lists, and the launch
+that takes the layers whose hint missed."""
+import numpy as np
+import pytest
+
+from rgc_testutil import GpuLayers, assert_layers_equal, oracle_step, u32
+from test_gpu_compress import run_iterations
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rgc():
+    import paper_1808_04357_amd as m
+    return m
+
+
+DIRECT = [1, 2, 3, 4, 5, 63, 64, 65, 1023, 1024, 1025, 4095, 4097, 16385, 32767, 32768]
+
+
+@pytest.mark.parametrize("law", ["normal", "ties", "sparse", "constant", "special"])
+@pytest.mark.parametrize("share", ["one", "permille", "quarter", "all"])
+def test_direct_layers(rgc, oracle, law, share):
+    g = np.random.default_rng(5)
+
+    def draw(n, s):
+        a = (g.standard_normal(n) * s).astype(np.float32)
+        if law == "ties":
+            a = (np.round(a / s * 3) / 3).astype(np.float32)
+        elif law == "sparse":
+            a[g.random(n) < 0.95] = 0.0
+        elif law == "constant":
+            a[:] = -1.5
+        elif law == "special" and n > 3:
+            a[g.integers(0, n, 3)] = [np.nan, np.inf, -np.inf]
+            a[: n // 3] = g.integers(-5, 5, n // 3) * np.float32(1.4e-45)
+        return a
+
+    ks = [{"one": 1, "permille": rgc.rgc_k_for_density(n), "quarter": max(1, n // 4), "all": n}[share] for n in DIRECT]
+    V = [draw(n, 1.0) for n in DIRECT]
+    G_list = [[draw(n, 0.25) if law != "constant" else np.zeros(n, np.float32) for n in DIRECT] for _ in range(2)]
+    run_iterations(rgc, oracle, V, G_list, ks, misalign=1, tag="direct %s %s" % (law, share))
+
+
+def test_direct_layers_with_momentum_and_without_hints(rgc, oracle):
+    g = np.random.default_rng(6)
+    V = [(g.standard_normal(n)).astype(np.float32) for n in DIRECT]
+    U = [(g.standard_normal(n)).astype(np.float32) for n in DIRECT]
+    G_list = [[(g.standard_normal(n)).astype(np.float32) for n in DIRECT] for _ in range(3)]
+    ks = [max(1, n // 50) for n in DIRECT]
+    for flags in (0, rgc.RGC_NESTEROV, rgc.RGC_NO_MOMENTUM_MASK | rgc.RGC_NO_HINTS):
+        run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9, flags=flags, tag="direct momentum %x" % flags)
+
+
+# 32769 is the smallest layer taken from its lists; 2457 entries sent (rank 6142 aimed at) the most
+@pytest.mark.parametrize("sizes,ks", [([32769, 32768, 100], None), ([65536 + 1023, 40_000], None), ([1 << 20], None),
+                                      ([2_457_000, 1_000_003, 33_000], None), ([400_000], [2457]), ([400_000], [2458]),
+                                      ([700_000, 500_000, 300], [1, 2, 3])])
+def test_layers_from_their_lists(rgc, oracle, sizes, ks):
+    g = np.random.default_rng(7)
+    ks = ks or [rgc.rgc_k_for_density(n) for n in sizes]
+    V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    U = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(5)]
+    paths = run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9, threads=8, tag="lists")
+    assert any(p[0] == 0 for p in paths[1:]), paths
+
+
+def test_long_lists_and_more_of_them_than_the_queue_holds(rgc, oracle):
+    """The large values sit in 1,100 of 2,930 wave-chunks, in a few of them far more than in the others."""
+    g = np.random.default_rng(8)
+    n, k = 3_000_000, 2457
+    scale = np.full(n, 1e-3, np.float32)
+    scale[: 1100 * 1024] = 1.0
+    scale[5 * 1024:6 * 1024] = 1.6
+    V = [(g.standard_normal(n).astype(np.float32) * scale)]
+    G_list = [[(g.standard_normal(n).astype(np.float32) * scale * 0.2)] for _ in range(4)]
+    paths = run_iterations(rgc, oracle, V, G_list, [k], threads=8, tag="queue")
+    assert any(p == [0] for p in paths[1:]), paths
+
+
+def test_missed_hints_take_the_fallback(rgc, oracle):
+    """Hints too high, too low and random, heavy ties, an overflowing list, zeros: several layers at once go through the
+    digits in the last launch, others do not."""
+    g = np.random.default_rng(9)
+    sizes = [300_000, 1_500_000, 40_001, 90_000, 200_000, 5000]
+    V = [(g.standard_normal(n) * 1e-2).astype(np.float32) for n in sizes]
+    V[2] = (np.round(V[2] * 300) / 300).astype(np.float32)
+    V[3][:] = 0.0
+    V[4][1000:2000] *= 100.0                                   # one list of 64 slots for 200 of the largest
+    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(8)]
+    for G in G_list:
+        G[2] = (np.round(G[2] * 300) / 300).astype(np.float32)
+        G[3][:] = 0.0
+        G[4][1000:2000] *= 100.0
+    ks = [rgc.rgc_k_for_density(n) for n in sizes]
+    paths = run_iterations(rgc, oracle, V, G_list, ks, poison=[0, 1, 2, 2, 0, 1, 2], threads=8, tag="fallback")
+    assert any(p[0] == 2 for p in paths) and any(p[1] == 2 for p in paths), paths
+
+
+def test_alternating_selection(rgc, oracle):
+    g = np.random.default_rng(10)
+    sizes = [120_000, 33_000, 32_768, 700, 9]
+    V0 = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    V0[1][:] = np.abs(V0[1])                                    # no negative elements at first
+    V0[2][:] = 0.0
+    ks = [rgc.rgc_k_for_density(n) for n in sizes[:3]] + [200, 9]
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    dev = GpuLayers(rgc, V0, ks)
+    Vh = [v.copy() for v in V0]
+    for t in range(6):
+        G = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+        dev.set_grads(G)
+        dev.step(ctx, 0.0, rgc.RGC_SELECT_SMALLEST if t % 2 else rgc.RGC_SELECT_LARGEST)
+        idx, val, cnt, V, _ = dev.results()
+        for l, n in enumerate(sizes):
+            a = (Vh[l] + G[l]).astype(np.float32)
+            order = np.argsort(a if t % 2 else -a, kind="stable")[: ks[l]]
+            want = np.sort(order)
+            assert np.array_equal(idx[l], want), "step %d layer %d" % (t, l)
+            assert np.array_equal(u32(val[l]), u32(a[want])) and int(cnt[l]) == ks[l]
+            a[want] = 0.0
+            assert np.array_equal(u32(V[l]), u32(a))
+            Vh[l] = a
+    ctx.last_error()
+    ctx.close()
+
+
+def test_replayed_from_a_graph_with_misses(rgc, oracle):
+    """The call recorded once and replayed; between the replays the hints are spoilt, so the fallback runs in some."""
+    import torch
+    g = np.random.default_rng(11)
+    sizes = [200_000, 50_000, 1000]
+    ks = [rgc.rgc_k_for_density(n) for n in sizes]
+    V0 = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    dev = GpuLayers(rgc, V0, ks)
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    Vh = [v.copy() for v in V0]
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        graph = None
+        for t in range(7):
+            G = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+            dev.set_grads(G)
+            if t in (3, 5):
+                ctx.poison_hints(t % 3, s)
+            if t < 2:
+                rgc.rgc_compress_layers(ctx, dev.layers, 0.0, 0, s)
+            else:
+                if graph is None:
+                    s.synchronize()
+                    graph = torch.cuda.CUDAGraph()
+                    with torch.cuda.graph(graph, stream=s):
+                        rgc.rgc_compress_layers(ctx, dev.layers, 0.0, 0, s)
+                graph.replay()
+            s.synchronize()
+            msgs = oracle_step(oracle, G, Vh, ks)
+            assert_layers_equal("step %d" % t, ks, dev.results(), msgs, Vh)
+            if t in (3, 5):
+                assert 2 in ctx.last_paths(len(sizes), s)
+    ctx.last_error(s)
+    ctx.close()
