@@ -511,9 +511,9 @@ def main():
                                                  "step_with_fill_in_place_of_decompress_ms": ms_step_fill,
                                                  "bytes": 4 * vgg.total}
         del fill_out
-    k_ms = step_ms4[0] / max(step_calls[0], 1)          # accumulate_kernel inside the timed steps
+    k_ms = step_ms4[0] / max(step_calls[0], 1)          # the streaming pass inside the timed steps
     achieved = vgg.alg_bytes_stream / (k_ms * 1e-3) / 1e9
-    roofline = {"bound": "hbm", "kernel": "accumulate_kernel (fused residual/momentum accumulate + candidate collect)",
+    roofline = {"bound": "hbm", "kernel": "tile_kernel (fused residual/momentum accumulate + candidate collect)",
                 "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
                 "traffic": None, "bytes_per_launch": vgg.alg_bytes_stream, "avg_launch_ms": k_ms}
     # HBM bytes per launch of that kernel as counted by rocprofv3 (FETCH_SIZE + WRITE_SIZE, scaled by a

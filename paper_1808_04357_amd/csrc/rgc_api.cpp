@@ -67,7 +67,7 @@ uint32_t chunk_for(int64_t total) {
 }
 
 // Smallest chunk any call may use: the scratch is sized for it.
-uint32_t chunk_smallest() { return kTileChunk; }
+uint32_t chunk_smallest() { return chunk_override() ? std::min(chunk_override(), kChunkSmallest) : kChunkSmallest; }
 
 // The threshold hint of a layer of n elements that sends k: the rank it is aimed at, for lists of `cap` slots per
 // wave-chunk of `chunk` elements, and whether those lists can hold it.
@@ -89,13 +89,12 @@ HintAim hint_aim(uint64_t n, uint64_t k, uint32_t chunk, uint32_t cap) {
   return h;
 }
 
-// Whether finish_kernel can end every layer of the list (see rgc_internal.h).
-bool finishable(const rgc_layer* layers, int32_t L) {
-  if (chunk_override()) return false;
+// Whether a call on this list can be a tiled one (see tile_kernel): every layer either is small enough to need no hint
+// or has one that its lists (as many slots per element as those of the general tiling's smallest chunk) can hold.
+bool tileable(const rgc_layer* layers, int32_t L) {
   for (int32_t l = 0; l < L; ++l) {
     if (layers[l].n <= static_cast<int64_t>(kDirectMax)) continue;
-    const HintAim h = hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileChunk, kTileChunk / kCapDiv);
-    if (!h.hintable || h.target > kFinishTargetMax) return false;
+    if (!hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileElems, kTileElems / kCapDiv).hintable) return false;
   }
   return true;
 }
@@ -155,6 +154,7 @@ struct PinnedBuf {
 struct Tiling {
   uint32_t chunk = 0;                      // elements per wave-chunk
   uint32_t wave_chunks = 0, workgroups = 0;
+  uint32_t parts = 0, big_parts = 0;       // tiled calls: workgroups of select_kernel, and how many of them belong to larger layers
   uint64_t member_entries = 0;             // of the member pool handed out to dense layers
   uint64_t list_entries = 0;               // of their lists
 };
@@ -162,16 +162,17 @@ struct Tiling {
 // One cached translation of a layer list into device tables.
 struct CompressPlan {
   std::vector<rgc_layer> key;       // the caller's list this plan was built from
-  Tiling general, fin;              // the second one for finishable lists only
+  Tiling general, tiled;            // the second one only for lists a tiled call can take
   DevBuf<LayerDesc> d_layers;
-  DevBuf<uint32_t> d_wg2layer;
+  DevBuf<uint32_t> d_wg2layer;      // [general.workgroups][tiled.workgroups], then from parts_at on the parts of tiled calls
+  size_t parts_at = 0;
   PinnedBuf staging;
   hipEvent_t uploaded = nullptr;    // recorded after the uploads
   uint64_t tensor_bytes = 0;               // gradients, residuals and velocities together
   uint64_t write_bytes = 0;                // what the streaming pass writes (V, and u where there is one)
   uint32_t max_k = 0;                      // the largest k of the list
-  bool finish = false;                     // finish_kernel can end every layer
-  bool finish_lists = false;               // ... and some of them from its candidate lists: those need a hint
+  bool tileable = false;                   // a call on this list can be a tiled one ...
+  bool tiled_needs_hints = false;          // ... if there are hints
   bool any_dense = false;                  // some layer is streamed by collect_kernel when it has a hint
   uint64_t last_use = 0;
   bool valid = false;
@@ -234,8 +235,10 @@ struct rgc_ctx {
 namespace {
 
 // Fills `desc` (one entry per layer); the workgroups are handed out in the given order of the layers.
-Tiling tile_layers(const rgc_layer* layers, const std::vector<int32_t>& order, uint32_t kChunk, bool finish, LayerDesc* desc) {
-  const uint32_t kCap = kChunk / kCapDiv;
+Tiling cut_layers(const rgc_layer* layers, const std::vector<int32_t>& order, uint32_t kChunk, bool tiled, LayerDesc* desc) {
+  const uint32_t kCap = (tiled ? kTileElems : kChunk) / kCapDiv;
+  const uint32_t list_span = tiled ? kTileElems : kChunk;     // elements one candidate list stands for
+  uint32_t parts = 0;
   uint32_t wc = 0, wg = 0, grp = 0;
   uint64_t mem = 0;                        // entries of the member pool handed out to dense layers
   uint64_t lists = 0;                      // list entries handed out to them
@@ -260,18 +263,20 @@ Tiling tile_layers(const rgc_layer* layers, const std::vector<int32_t>& order, u
     d.mem_first = 0;
     // speed-hint policy: aim the threshold at rank 2k + margin of this call, accept up to cmax
     const uint64_t k = d.k;
-    const HintAim aim = hint_aim(d.n, k, kChunk, kCap);
+    const HintAim aim = hint_aim(d.n, k, list_span, kCap);
     const uint64_t margin = aim.margin, span = aim.span, target = aim.target;
     d.hintable = aim.hintable ? 1u : 0u;
-    d.direct = finish && d.n <= kDirectMax ? 1u : 0u;
-    d.pad_ = 0;
+    d.kind = d.n <= kDirectMax ? kLayerDirect
+             : aim.target <= kListsTargetMax && d.wg_count <= kPartTilesMax ? kLayerLists : kLayerBig;
+    d.part_first = parts;
+    parts += d.kind == kLayerBig ? (d.wg_count + kPartTiles - 1) / kPartTiles : 1u;
     d.margin = static_cast<uint32_t>(margin);
-    uint64_t cmax = std::min<uint64_t>(2 * target, (kCap / 2) * (span / kChunk));
+    uint64_t cmax = std::min<uint64_t>(2 * target, (kCap / 2) * (span / list_span));
     d.target = static_cast<uint32_t>(std::min<uint64_t>(target, 0xFFFFFFFFu));
     d.dense = 0;
     d.list_cap = 0;
     d.list_first = 0;
-    if (!d.hintable && !finish) {
+    if (!d.hintable && !tiled) {
       // High densities (the warm-up period of Section 2.5): the short lists of the one-pass path cannot hold every
       // element from the threshold upwards.  Such a layer gets lists of its own, long enough for twice the number of
       // candidates aimed at, and its hint is aimed at rank k + margin and accepted from rank k to rank k + 2 margin.
@@ -302,6 +307,7 @@ Tiling tile_layers(const rgc_layer* layers, const std::vector<int32_t>& order, u
   t.chunk = kChunk;
   t.wave_chunks = wc;
   t.workgroups = wg;
+  t.parts = parts;
   t.member_entries = mem;
   t.list_entries = lists;
   return t;
@@ -319,24 +325,38 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
                    [&](int32_t a, int32_t b) { return layers[a].n > layers[b].n; });
   int64_t total_elems = 0;
   for (int32_t l = 0; l < L; ++l) total_elems += layers[l].n;
-  P.finish = finishable(layers, L);
-  // the general tiling, and behind it in the same tables the one a finishable call uses
-  std::vector<LayerDesc> desc(static_cast<size_t>(L) * (P.finish ? 2u : 1u));
-  const Tiling general = tile_layers(layers, order, chunk_for(total_elems), false, desc.data());
-  const Tiling fin = P.finish ? tile_layers(layers, order, kTileChunk, true, desc.data() + L) : Tiling{};
-  if (general.wave_chunks > ctx->wc_max || fin.wave_chunks > ctx->wc_max) return RGC_ENOMEM;
-  const size_t wgs = static_cast<size_t>(general.workgroups) + fin.workgroups;
+  P.tileable = tileable(layers, L);
+  // the general tiling, and behind it in the same tables the one of tiled calls
+  std::vector<LayerDesc> desc(static_cast<size_t>(L) * (P.tileable ? 2u : 1u));
+  Tiling general = cut_layers(layers, order, chunk_for(total_elems), false, desc.data());
+  Tiling tiled = P.tileable ? cut_layers(layers, order, kTileChunk, true, desc.data() + L) : Tiling{};
+  if (general.wave_chunks > ctx->wc_max || tiled.workgroups > ctx->wc_max) return RGC_ENOMEM;
+  const size_t wgs = static_cast<size_t>(general.workgroups) + tiled.workgroups;
+  const size_t map_words = (wgs + 1u) / 2u * 2u;                          // the table of parts behind it holds pairs of words
   const size_t bytes_layers = sizeof(LayerDesc) * desc.size();
-  const size_t bytes_map = sizeof(uint32_t) * wgs;
+  const size_t bytes_map = sizeof(uint32_t) * (map_words + 2u * tiled.parts);
   RGC_HIP(P.staging.ensure(bytes_layers + bytes_map));
   if (P.d_layers.n < desc.size()) RGC_HIP(P.d_layers.alloc(desc.size()));
-  if (P.d_wg2layer.n < wgs) RGC_HIP(P.d_wg2layer.alloc(wgs));
+  if (P.d_wg2layer.n < map_words + 2u * tiled.parts) RGC_HIP(P.d_wg2layer.alloc(map_words + 2u * tiled.parts));
   std::memcpy(P.staging.p, desc.data(), bytes_layers);
   uint32_t* map = reinterpret_cast<uint32_t*>(static_cast<char*>(P.staging.p) + bytes_layers);
   for (size_t d = 0; d < desc.size(); ++d) {
     uint32_t* const own = map + (d < static_cast<size_t>(L) ? 0u : general.workgroups) + desc[d].wg_first;
     std::fill_n(own, desc[d].wg_count, static_cast<uint32_t>(d % static_cast<size_t>(L)));
   }
+  if (P.tileable) {
+    uint32_t* at = map + map_words;
+    for (const bool big : {true, false}) {
+      for (const int32_t l : order) {
+        const LayerDesc& d = desc[static_cast<size_t>(L) + l];
+        if ((d.kind == kLayerBig) != big) continue;
+        const uint32_t parts = big ? (d.wg_count + kPartTiles - 1) / kPartTiles : 1u;
+        for (uint32_t i = 0; i < parts; ++i) { *at++ = static_cast<uint32_t>(l); *at++ = i; }
+        if (big) tiled.big_parts += parts;
+      }
+    }
+  }
+  P.parts_at = map_words;
   RGC_HIP(hipMemcpyAsync(P.d_layers.p, P.staging.p, bytes_layers, hipMemcpyHostToDevice, stream));
   RGC_HIP(hipMemcpyAsync(P.d_wg2layer.p, map, bytes_map, hipMemcpyHostToDevice, stream));
   RGC_HIP(hipEventRecord(P.uploaded, stream));
@@ -348,15 +368,15 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     P.key[l] = c;
   }
   P.general = general;
-  P.fin = fin;
+  P.tiled = tiled;
   P.write_bytes = 0;
   P.tensor_bytes = 0;
   P.max_k = 0;
   P.any_dense = false;
-  P.finish_lists = false;
+  P.tiled_needs_hints = false;
   for (int32_t l = 0; l < L; ++l) {
     P.any_dense = P.any_dense || desc[l].dense != 0;
-    P.finish_lists = P.finish_lists || (P.finish && desc[L + l].direct == 0);
+    P.tiled_needs_hints = P.tiled_needs_hints || (P.tileable && desc[L + l].kind != kLayerDirect);
     P.write_bytes += static_cast<uint64_t>(layers[l].n) * (layers[l].momentum ? 8u : 4u);
     P.tensor_bytes += static_cast<uint64_t>(layers[l].n) * (layers[l].momentum ? 12u : 8u);
     P.max_k = std::max(P.max_k, static_cast<uint32_t>(layers[l].k));
@@ -760,18 +780,17 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   }
   const bool no_hints = (flags & RGC_NO_HINTS) != 0;
 
-  // A finishable call takes two launches, and one more for the layers whose hint misses if it has layers that need one;
-  // without hints for those it goes the general way.
   const bool use_hints = sig_same && !no_hints;
-  const bool finish = plan->finish && (use_hints || !plan->finish_lists);
-  const Tiling& tiling = finish ? plan->fin : plan->general;
+  const bool is_tiled = plan->tileable && (use_hints || !plan->tiled_needs_hints);
+  const Tiling& tiling = is_tiled ? plan->tiled : plan->general;
   const uint32_t num_wgs = tiling.workgroups;
   CompressArgs A{};
-  A.layers = plan->d_layers.p + (finish ? num_layers : 0);
+  A.layers = plan->d_layers.p + (is_tiled ? num_layers : 0);
   A.state = ctx->d_state.p + static_cast<size_t>(bank) * ctx->max_layers;
   A.sign_filter = bank ? 0xFFFFFFFFu : 0u;
   A.sign_xor = bank == 2 ? 0x80000000u : 0u;
-  A.wg2layer = plan->d_wg2layer.p + (finish ? plan->general.workgroups : 0u);
+  A.wg2layer = plan->d_wg2layer.p + (is_tiled ? plan->general.workgroups : 0u);
+  A.parts = reinterpret_cast<const uint2*>(plan->d_wg2layer.p + plan->parts_at);
   A.hist = ctx->d_hist.p;
   A.coarse = ctx->d_coarse.p;
   A.members = ctx->d_members.p;
@@ -782,14 +801,14 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.errflag = ctx->d_err.p;
   A.group_done = ctx->d_group.p;
   A.chunk = tiling.chunk;
-  A.cap = A.chunk / kCapDiv;
+  A.cap = (is_tiled ? kTileElems : A.chunk) / kCapDiv;
   A.use_hints = use_hints ? 1u : 0u;
   A.update_hints = no_hints ? 0u : 1u;
   A.mask_momentum = (flags & RGC_NO_MOMENTUM_MASK) ? 0u : 1u;
   // The lists of dense layers are allocated by the first call that shows the context a plan with such layers (or one
   // that needs longer lists; hipFree waits for the kernels that may still use the old ones).  Without them (the device
   // is short of memory) those layers simply take the hint-free path, as they would on a first call.
-  bool dense_ok = plan->any_dense && !plan->finish;     // (a finishable list needs them neither with hints nor without)
+  bool dense_ok = plan->any_dense && !plan->tileable;   // (such a list needs them neither with hints nor without)
   if (dense_ok && (ctx->d_slots2.n < plan->general.list_entries || ctx->d_members2.n < plan->general.member_entries || !ctx->d_shards.p)) {
     const uint64_t want = plan->general.list_entries * (sizeof(uint2) + sizeof(float)) + plan->general.member_entries * sizeof(unsigned long long);
     const bool capped = ctx->optional_scratch_cap >= 0 && want > static_cast<uint64_t>(ctx->optional_scratch_cap);
@@ -829,17 +848,24 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   // also starts on the five passes.
   A.late = ctx->d_err.p + 2;
   if (A.use_hints) {
-    A.late_first = finish ? 3u : kFirstLateLaunch;
-    A.late_last = A.late_first + (finish ? 4u : 2u);
+    A.late_first = is_tiled ? kTiledLateLaunch : kFirstLateLaunch;
+    A.late_last = A.late_first + (is_tiled ? 4u : 2u);
   }
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));
-  if (finish) RGC_HIP(launch_tiles(A, num_wgs, stream));
+  if (is_tiled) RGC_HIP(launch_tiles(A, num_wgs, stream));
   else RGC_HIP(launch_accumulate(A, num_wgs, stream));
   if (dense) RGC_HIP(launch_collect(A, num_wgs, stream));
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));
-  if (finish) {
-    RGC_HIP(launch_finish(A, static_cast<uint32_t>(num_layers), stream));
-    if (plan->finish_lists) RGC_HIP(launch_fallback(A, num_wgs, ctx->cus, stream));
+  if (is_tiled) {
+    RGC_HIP(launch_select(A, tiling.parts, stream));
+    if (tiling.big_parts) RGC_HIP(launch_emit(A, tiling.big_parts, stream));
+    if (A.use_hints && plan->tiled_needs_hints) {
+      A.layers = plan->d_layers.p;                   // what is left to do, in the general tiling: fewer, larger wave-chunks
+      A.wg2layer = plan->d_wg2layer.p;
+      A.chunk = plan->general.chunk;
+      A.cap = A.chunk / kCapDiv;
+      RGC_HIP(launch_fallback(A, plan->general.workgroups, ctx->cus, stream));
+    }
   } else {
     for (int launch = 2; launch <= kLaunches; ++launch) {
       if (A.use_hints && launch == static_cast<int>(kFirstLateLaunch)) {

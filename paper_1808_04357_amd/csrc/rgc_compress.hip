@@ -36,6 +36,7 @@ namespace rgc {
 namespace {
 
 typedef uint32_t vu2 __attribute__((ext_vector_type(2))); // a candidate: (float bits, index)
+typedef float vf4a __attribute__((ext_vector_type(4)));   // 16-byte aligned (LDS)
 
 struct Collector {
   gptr<vu2> slot;    // this wave-chunk's candidate list
@@ -111,8 +112,6 @@ constexpr uint32_t kListStopped = 0x80000000u;
 enum Take : int {
   kTakeDigit = 0,    // first digit's histogram (hint-free)
   kTakeCoarse = 1,   // candidate lists and the coarse histogram of the candidates
-  kTakeList = 2,     // candidate lists only (finish_kernel makes the histogram)
-  kTakeNothing = 3,  // finish_kernel reads the residual itself
 };
 
 // Consume the four accumulated values a lane holds (elements idx0 .. idx0+3, the first
@@ -120,14 +119,13 @@ enum Take : int {
 template <Take kTake>
 __device__ __forceinline__ void consume(const float (&a)[4], uint32_t nvalid, uint32_t idx0,
                                         Collector& c, uint32_t* lds_hist, uint32_t& zeros) {
-  if constexpr (kTake == kTakeNothing) return;
   uint32_t bits[4], key[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     bits[j] = fbits(a[j]);
     key[j] = key_of(bits[j], c.sign_xor, c.sign_filter);
   }
-  if constexpr (kTake == kTakeCoarse || kTake == kTakeList) {
+  if constexpr (kTake == kTakeCoarse) {
     bool f[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) f[j] = (static_cast<uint32_t>(j) < nvalid) && (key[j] >= c.tau);
@@ -141,7 +139,7 @@ __device__ __forceinline__ void consume(const float (&a)[4], uint32_t nvalid, ui
         if (f[j]) {
           if (pos < c.cap) {
             c.slot[pos] = vu2{bits[j], idx0 + j};
-            if constexpr (kTake == kTakeCoarse) atomicAdd(&c.coarse[coarse_bin(key[j], c.tau, c.shift)], 1u);
+            atomicAdd(&c.coarse[coarse_bin(key[j], c.tau, c.shift)], 1u);
           }
           ++pos;
         }
@@ -177,7 +175,7 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
     const gcvf4 G4 = as_vec(L.grad + begin);
     const gvf4 V4 = as_vec(L.resid + begin);
     const gvf4 U4 = kMom ? as_vec(L.mom + begin) : nullptr;
-    constexpr uint32_t kUnroll = kMom && !kNt && kTake < kTakeList ? 2u : 4u;   // 16-byte loads in flight per lane: 6, 8 or 12
+    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;   // 16-byte loads in flight per lane: 6, 8 or 12
     uint32_t g = 0;
     for (; g + kUnroll <= nfull; g += kUnroll) {
       vf4 gv[kUnroll], vv[kUnroll], uv[kUnroll];
@@ -1253,121 +1251,264 @@ __global__ void __launch_bounds__(kBlockThreads) phase_late_kernel(CompressArgs 
   }
 }
 
-// =================================================================== finishable calls: two launches
-// Launch 1: the streaming pass alone.  A wave takes 1024 elements with all its loads in flight at once and nothing to wait
-// for after its stores (a wave that loops waits for the stores of one round with the loads of the next: they share a
-// counter), leaves the candidates of a layer with a hint in the wave-chunk's list, and that is all: no histogram, no election.
-// ResNet-50 set: 52 us, 5.9 TB/s, where accumulate_kernel takes 71 us; the copy rate is 4.9 TB/s.
+// =================================================================== tiled calls
+// Calls whose layers all have a hint, or none of whose other layers has more than kDirectMax elements, take
+//   1. tile_kernel: the streaming pass, one workgroup per 4096 elements, candidates to the tile's list
+//   2. select_kernel: a layer of at most kDirectMax elements is ended from the residual itself, a layer with few candidates
+//      from its lists, each by one workgroup; of a larger layer one workgroup per 256 tiles counts its candidates above the
+//      k-th key's coarse bin and appends that bin's members, which the last of them ranks
+//   3. emit_kernel, if there are such larger layers: their messages
+//   4. fallback_kernel, if any layer needs a hint: the layers whose hint missed.
+//
+// A wave of the streaming pass has all its loads in flight at once and nothing to wait for after its stores (a wave that
+// loops waits for the stores of one round with the loads of the next: they share a counter).  There is no election and no
+// histogram in LDS.  ResNet-50 set: 52 us, 5.9 TB/s, where accumulate_kernel takes 71 us; the copy rate is 4.9 TB/s.
+template <bool kNt, bool kMom, bool kNest, bool kList>
+__device__ __forceinline__ void stream_tile(const CompressArgs& A, uint32_t l, const LayerDesc& L, uint32_t wg, const AccumRule rule,
+                                            uint32_t tau, uint32_t shift, uint32_t* lds_count) {
+  constexpr uint32_t kGroups = kTileChunk / kGroupElems;     // of a wave
+  const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+  const uint32_t base = (wg - L.wg_first) * kTileElems + wave * kTileChunk;
+  const float* const G = L.grad;
+  float* const V = L.resid;
+  float* const U = L.mom;
+  float a[kGroups][4];
+  uint32_t valid = 0u;                                       // elements of this lane's last group that exist, where it is ragged
+  if (base + kTileChunk <= L.n) {
+    vf4 gv[kGroups], vv[kGroups], uv[kGroups];
+#pragma unroll
+    for (uint32_t g = 0; g < kGroups; ++g) {
+      const uint32_t o = base + g * kGroupElems + lane * 4u;
+      gv[g] = __builtin_nontemporal_load(as_vec(G + o));
+      vv[g] = stream_load<kNt>(as_vec(V + o));
+      if constexpr (kMom) uv[g] = stream_load<kNt>(as_vec(U + o));
+    }
+#pragma unroll
+    for (uint32_t g = 0; g < kGroups; ++g) {
+      const uint32_t o = base + g * kGroupElems + lane * 4u;
+      const float gg[4] = {gv[g].x, gv[g].y, gv[g].z, gv[g].w};
+      const float vvv[4] = {vv[g].x, vv[g].y, vv[g].z, vv[g].w};
+      float uu[4] = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (kMom) { uu[0] = uv[g].x; uu[1] = uv[g].y; uu[2] = uv[g].z; uu[3] = uv[g].w; }
+      accum4<kMom, kNest>(gg, vvv, uu, rule, a[g]);
+      stream_store<kNt>(as_vec(V + o), vf4{a[g][0], a[g][1], a[g][2], a[g][3]});
+      if constexpr (kMom) stream_store<kNt>(as_vec(U + o), vf4{uu[0], uu[1], uu[2], uu[3]});
+    }
+    valid = 4u * kGroups;
+  } else {
+    // the layer ends in this wave's elements (or before them): a word at a time
+    const gptr<const float> Gs = as_global(G);
+    const gptr<float> Vs = as_global(V);
+    const gptr<float> Us = as_global(U);
+#pragma unroll
+    for (uint32_t g = 0; g < kGroups; ++g) {
+      const uint32_t o = base + g * kGroupElems + lane * 4u;
+      const uint32_t nvalid = o < L.n ? (L.n - o < 4u ? L.n - o : 4u) : 0u;
+      float gg[4] = {0.f, 0.f, 0.f, 0.f}, vvv[4] = {0.f, 0.f, 0.f, 0.f}, uu[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j) {
+        if (j < nvalid) {
+          gg[j] = Gs[o + j];
+          vvv[j] = Vs[o + j];
+          if constexpr (kMom) uu[j] = Us[o + j];
+        }
+      }
+      accum4<kMom, kNest>(gg, vvv, uu, rule, a[g]);
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j) {
+        if (j < nvalid) {
+          Vs[o + j] = a[g][j];
+          if constexpr (kMom) Us[o + j] = uu[j];
+        }
+      }
+      valid += nvalid;                                       // (the groups of a lane fill up in order)
+    }
+  }
+  if constexpr (kList) {
+    // the tile's candidates, in index order: every wave counts its own, then writes behind those of the waves before it
+    bool f[kGroups][4];
+    uint32_t count = 0u;
+#pragma unroll
+    for (uint32_t g = 0; g < kGroups; ++g) {
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j) {
+        f[g][j] = 4u * g + j < valid && key_of(fbits(a[g][j]), A.sign_xor, A.sign_filter) >= tau;
+        count += popc64(__ballot(f[g][j]));
+      }
+    }
+    if (lane == 0) lds_count[wave] = count;
+    __syncthreads();
+    uint32_t at = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < kWavesPerBlock; ++w) at += w < wave ? lds_count[w] : 0u;
+    if (wave == kWavesPerBlock - 1 && lane == 0) A.cand_cnt[wg] = at + count;
+    if (count != 0u) {
+      const gptr<vu2> slot = as_global(reinterpret_cast<vu2*>(A.slots + static_cast<size_t>(wg) * A.cap));
+      uint32_t* const coarse = A.coarse + (static_cast<size_t>(l) * kCoarseRep + (wg & (kCoarseRep - 1))) * kCoarseBins;
+      const bool big = L.kind == kLayerBig;
+#pragma unroll
+      for (uint32_t g = 0; g < kGroups; ++g) {
+        const unsigned long long m0 = __ballot(f[g][0]), m1 = __ballot(f[g][1]), m2 = __ballot(f[g][2]), m3 = __ballot(f[g][3]);
+        if ((m0 | m1 | m2 | m3) == 0ull) continue;
+        uint32_t pos = at + rank_below(m0) + rank_below(m1) + rank_below(m2) + rank_below(m3);
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+          if (f[g][j]) {
+            if (pos < A.cap) {
+              const uint32_t bits = fbits(a[g][j]);
+              slot[pos] = vu2{bits, base + g * kGroupElems + lane * 4u + j};
+              // (a few candidates per wave, at its very end: nothing waits for these)
+              if (big) atomicAdd(&coarse[coarse_bin(key_of(bits, A.sign_xor, A.sign_filter), tau, shift)], 1u);
+            }
+            ++pos;
+          }
+        }
+        at += popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
+      }
+    }
+  }
+}
+
 template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) tile_kernel(CompressArgs A) {
-  const uint32_t wg = blockIdx.x;
+  __shared__ uint32_t lds_count[kWavesPerBlock];
+  const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;     // (see accumulate_kernel)
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
-  const LayerState* st = A.state + l;
-  const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
-  if (wc_local >= L.wc_count) return;
-  const uint32_t begin = wc_local * A.chunk;
-  const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
-  Collector c;
-  c.slot = as_global(reinterpret_cast<vu2*>(A.slots + static_cast<size_t>(L.wc_first + wc_local) * A.cap));
-  c.coarse = nullptr;
-  c.cap = A.cap;
-  c.count = 0;
-  c.tau = st->tau;
-  c.shift = 0u;
-  c.sign_xor = A.sign_xor;
-  c.sign_filter = A.sign_filter;
-  const bool mom = (L.mom != nullptr);
+  LayerState* st = A.state + l;
   AccumRule rule;
   rule.m = A.m;
   rule.scale = A.grad_scale ? *as_global(A.grad_scale) : 1.0f;
-  if (!L.direct && hint_usable(A, st)) {
-    if (!mom) stream_chunk<kNt, false, kTakeList>(L, begin, end, rule, c, nullptr);
-    else if (!A.nesterov) stream_chunk<kNt, true, kTakeList>(L, begin, end, rule, c, nullptr);
-    else stream_chunk<kNt, true, kTakeList, true>(L, begin, end, rule, c, nullptr);
-    if (lane_id() == 0) A.cand_cnt[L.wc_first + wc_local] = c.count;
+  const bool mom = (L.mom != nullptr);
+  if (L.kind != kLayerDirect && hint_usable(A, st)) {
+    const uint32_t tau = st->tau, shift = st->shift;
+    if (wg == L.wg_first && threadIdx.x == 0) st->nmembers = 0u;                // select_kernel counts in it
+    if (!mom) stream_tile<kNt, false, false, true>(A, l, L, wg, rule, tau, shift, lds_count);
+    else if (!A.nesterov) stream_tile<kNt, true, false, true>(A, l, L, wg, rule, tau, shift, lds_count);
+    else stream_tile<kNt, true, true, true>(A, l, L, wg, rule, tau, shift, lds_count);
   } else {
-    if (!mom) stream_chunk<kNt, false, kTakeNothing>(L, begin, end, rule, c, nullptr);
-    else if (!A.nesterov) stream_chunk<kNt, true, kTakeNothing>(L, begin, end, rule, c, nullptr);
-    else stream_chunk<kNt, true, kTakeNothing, true>(L, begin, end, rule, c, nullptr);
+    if (!mom) stream_tile<kNt, false, false, false>(A, l, L, wg, rule, 0u, 0u, lds_count);
+    else if (!A.nesterov) stream_tile<kNt, true, false, false>(A, l, L, wg, rule, 0u, 0u, lds_count);
+    else stream_tile<kNt, true, true, false>(A, l, L, wg, rule, 0u, 0u, lds_count);
   }
 }
 
 namespace {
 
-struct FinishShared {
+struct SelectShared {
   union {
-    float vals[kDirectMax];                                  // a direct layer's residual
+    vf4a vals[kDirectMax / 4];                               // a direct layer's residual
     struct {
-      vu2 cand[kFinishCand];                                 // a layer's candidates, in index order
+      vu2 cand[kFinishCand];                                 // candidates, in index order
       unsigned long long members[kMemberMax];                // those of the coarse bin that holds the k-th key
     } list;
   } u;
   unsigned long long few[kFinishThreads];                    // direct layers: the elements left to rank
   uint32_t hist[kHistBins];
-  uint32_t sel_hist[3 * 256];
+  uint32_t sel_hist[3 * 256 + kFinishThreads];               // the ranking's histograms; behind them a direct layer's bitmap
   uint32_t nfew, bad;
   ResolveShared sh;
 };
-static_assert(sizeof(FinishShared) <= 160 * 1024, "one workgroup per CU");
+static_assert(sizeof(SelectShared) <= 160 * 1024, "one workgroup per CU");
 
-// The message of an exactly selected layer is written by waves that each own a consecutive range: sel(i) says whether
-// entry i is sent, put(i, pos) writes it.  Returns the number of entries sent.
-template <typename Sel, typename Put>
-__device__ __forceinline__ uint32_t emit_ordered(uint32_t count, FinishShared& S, Sel&& sel, Put&& put) {
-  const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
-  const uint32_t per = ((count + kFinishWaves - 1u) / kFinishWaves + kWaveSize - 1u) / kWaveSize * kWaveSize;
-  const uint32_t first = wave * per < count ? wave * per : count;
-  const uint32_t last = first + per < count ? first + per : count;
-  uint32_t mine = 0u;
-  for (uint32_t b = first; b < last; b += kWaveSize) mine += popc64(__ballot(b + lane < last && sel(b + lane)));
+// Where a wave's consecutive share of `count` entries begins, in steps of kStep, when every wave counts the entries it
+// is going to write (`mine`) first; returns its first output position.  Holds barriers.
+__device__ __forceinline__ uint32_t wave_offset(uint32_t mine, ResolveShared& sh, uint32_t& total) {
+  const uint32_t wave = threadIdx.x >> 6;
   __syncthreads();
-  if (lane == 0) S.sh.scan[wave] = mine;
+  if (lane_id() == 0) sh.scan[wave] = mine;
   __syncthreads();
-  uint32_t at = 0u, total = 0u;
+  uint32_t at = 0u;
+  total = 0u;
 #pragma unroll
   for (uint32_t w = 0; w < kFinishWaves; ++w) {
-    at += w < wave ? S.sh.scan[w] : 0u;
-    total += S.sh.scan[w];
+    at += w < wave ? sh.scan[w] : 0u;
+    total += sh.scan[w];
   }
+  return at;
+}
+
+template <uint32_t kStep>
+__device__ __forceinline__ void wave_range(uint32_t count, uint32_t& first, uint32_t& last) {
+  const uint32_t per = ((count + kFinishWaves - 1u) / kFinishWaves + kStep - 1u) / kStep * kStep;
+  const uint32_t wave = threadIdx.x >> 6;
+  first = wave * per < count ? wave * per : count;
+  last = first + per < count ? first + per : count;
+}
+
+// The message from candidates in LDS: those whose composite is not below thr, from output position `base` on.
+__device__ __forceinline__ uint32_t emit_candidates(const CompressArgs& A, const LayerDesc& L, const vu2* cand, uint32_t count,
+                                                    unsigned long long thr, uint32_t base, ResolveShared& sh) {
+  const uint32_t lane = lane_id();
+  const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
+  const gptr<int32_t> out_idx = as_global(L.out_idx);
+  const gptr<float> out_val = as_global(L.out_val);
+  const gptr<float> resid = as_global(L.resid);
+  const gptr<float> mom = as_global(L.mom);
+  auto sel = [&](uint32_t i, uint32_t last, vu2& e) {
+    if (i >= last) return false;
+    e = cand[i];
+    return composite(key_of(e.x, A.sign_xor, A.sign_filter), e.y) >= thr;
+  };
+  uint32_t first, last, mine = 0u, total;
+  wave_range<kWaveSize>(count, first, last);
+  vu2 e = vu2{0u, 0u};
+  for (uint32_t b = first; b < last; b += kWaveSize) mine += popc64(__ballot(sel(b + lane, last, e)));
+  uint32_t at = base + wave_offset(mine, sh, total);
   for (uint32_t b = first; b < last; b += kWaveSize) {
-    const bool s = b + lane < last && sel(b + lane);
+    const bool s = sel(b + lane, last, e);
     const unsigned long long m = __ballot(s);
-    if (s) put(b + lane, at + rank_below(m));
+    const uint32_t pos = at + rank_below(m);
+    if (s && pos < L.k && e.y < L.n) {                       // the bounds always hold when the lists are right
+      out_idx[pos] = static_cast<int32_t>(e.y);
+      out_val[pos] = __uint_as_float(e.x);
+      mask_store(&resid[e.y]);
+      if (clear_mom) mask_store(&mom[e.y]);
+    }
     at += popc64(m);
   }
   return total;
 }
 
-// A layer of at most kDirectMax elements, any density, no hint: radix selection over the composites
-// (key, then lower index first) in LDS, 12 bits at a time from the top, until the elements that share the bits fixed
-// so far are few enough to be ranked at once (after the first digit, usually).
-__device__ void finish_direct(const CompressArgs& A, const LayerDesc& L, LayerState* st, FinishShared& S) {
-  const uint32_t t = threadIdx.x, n = L.n;
-  constexpr uint32_t kLoads = kDirectMax / (4u * kFinishThreads);
-  {
-    vf4 q[kLoads];
-#pragma unroll
-    for (uint32_t i = 0; i < kLoads; ++i) {
-      const uint32_t e = 4u * (i * kFinishThreads + t);
-      if (e + 4u <= n) q[i] = *as_vec(static_cast<const float*>(L.resid) + e);
+// A layer of at most kDirectMax elements, any density, no hint.  Every thread holds up to 32 elements in registers.  The
+// k-th largest of the threads' own largest keys bounds the k-th key of the layer from below; the few elements that reach the
+// bound are ranked at once, and a bitmap of the sent ones gives their order.  (Vector instructions are what this costs, four
+// cycles each for every wave of the one CU: 21 us for 32768 elements with the values in LDS and three passes over them,
+// 12 us this way.)  Where too many reach the bound (a large share is sent, long ties), radix selection takes over.
+__device__ __forceinline__ void direct_done(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t sent, uint32_t T) {
+  if (threadIdx.x != 0) return;
+  if (sent != L.k) atomicOr(A.errflag, 128u);
+  *as_global(L.out_count) = static_cast<int32_t>(L.k);
+  st->T = T;
+  st->path = 1u;
+  st->stat_candidates = 0u;
+  st->stat_members = 0u;
+  st->next_phase = PH_NONE;
+  st->next_launch = 0u;
+}
+
+__device__ __forceinline__ unsigned long long direct_composite(uint32_t key, uint32_t i) {
+  return (static_cast<unsigned long long>(key) << kDirectMaxLog2) | (kDirectMax - 1u - i);
+}
+
+// Radix selection over the composites (key, then lower index first) of the values in S.u.vals, 12 bits at a time from the
+// top, until few enough share the bits fixed so far to be ranked at once; then the message, by waves that own
+// consecutive elements.
+__device__ __forceinline__ void finish_direct_radix(const CompressArgs& A, const LayerDesc& L, LayerState* st, SelectShared& S) {
+  const uint32_t t = threadIdx.x, lane = lane_id(), n = L.n;
+  const uint32_t up = A.sign_filter ? 0u : 1u;
+  auto key32 = [&](float x) { return ordered_key(fbits(x), A.sign_xor, A.sign_filter) << up; };
+  // f(key, index) over the elements
+  auto for_each = [&](auto&& f) {
+    for (uint32_t e = 4u * t; e < n; e += 4u * kFinishThreads) {
+      const vf4a q = S.u.vals[e / 4u];
+      f(key32(q.x), e);
+      if (e + 1u < n) f(key32(q.y), e + 1u);
+      if (e + 2u < n) f(key32(q.z), e + 2u);
+      if (e + 3u < n) f(key32(q.w), e + 3u);
     }
-#pragma unroll
-    for (uint32_t i = 0; i < kLoads; ++i) {
-      const uint32_t e = 4u * (i * kFinishThreads + t);
-      if (e + 4u <= n) {
-        S.u.vals[e] = q[i].x; S.u.vals[e + 1u] = q[i].y; S.u.vals[e + 2u] = q[i].z; S.u.vals[e + 3u] = q[i].w;
-      } else {
-        for (uint32_t j = e; j < n && j < e + 4u; ++j) S.u.vals[j] = as_global(static_cast<const float*>(L.resid))[j];
-      }
-    }
-  }
-  const uint32_t up = A.sign_filter ? 0u : 1u;               // the magnitude key has 31 bits, the ordered one 32
-  auto comp = [&](uint32_t i) -> unsigned long long {
-    const uint32_t key = ordered_key(fbits(S.u.vals[i]), A.sign_xor, A.sign_filter) << up;
-    return (static_cast<unsigned long long>(key) << kDirectMaxLog2) | (kDirectMax - 1u - i);
   };
-  const uint32_t zero_key = ordered_key(0u, A.sign_xor, A.sign_filter) << up;
+  const uint32_t zero_key = key32(0.0f);
   uint32_t shift = 32u + kDirectMaxLog2, rem = L.k;
   unsigned long long prefix = 0ull, thr = 0ull;
   for (uint32_t level = 0; level < 4u; ++level) {
@@ -1377,15 +1518,15 @@ __device__ void finish_direct(const CompressArgs& A, const LayerDesc& L, LayerSt
     if (t == 0) S.nfew = 0u;
     __syncthreads();
     uint32_t zeros = 0u;                                     // (the zeros of a sparse tensor would all hit one bin)
-    for (uint32_t i = t; i < n; i += kFinishThreads) {
-      const unsigned long long c = comp(i);
-      if ((c >> (shift + bits)) != prefix) continue;
-      if (level < 2u && static_cast<uint32_t>(c >> kDirectMaxLog2) == zero_key) ++zeros;
+    for_each([&](uint32_t key, uint32_t i) {
+      const unsigned long long c = direct_composite(key, i);
+      if ((c >> (shift + bits)) != prefix) return;
+      if (level < 2u && key == zero_key) ++zeros;
       else atomicAdd(&S.hist[static_cast<uint32_t>(c >> shift) & mask], 1u);
-    }
+    });
     if (level < 2u) {
       const uint32_t z = wave_total(wave_incl_scan(zeros));
-      if (z != 0u && lane_id() == 0) atomicAdd(&S.hist[static_cast<uint32_t>((static_cast<unsigned long long>(zero_key) << kDirectMaxLog2) >> shift) & mask], z);
+      if (z != 0u && lane == 0) atomicAdd(&S.hist[static_cast<uint32_t>(direct_composite(zero_key, 0u) >> shift) & mask], z);
     }
     __syncthreads();
     (void)locate_from_top<kFinishThreads>(S.hist, mask + 1u, rem, 0xFFFFFFFFu, S.sh);
@@ -1398,120 +1539,278 @@ __device__ void finish_direct(const CompressArgs& A, const LayerDesc& L, LayerSt
     prefix = (prefix << bits) | bin;
     if (level == 3u) { thr = prefix; break; }                // every bit is fixed: the element itself
     if (cnt <= kFinishThreads) {
-      for (uint32_t i = t; i < n; i += kFinishThreads) {
-        const unsigned long long c = comp(i);
+      for_each([&](uint32_t key, uint32_t i) {
+        const unsigned long long c = direct_composite(key, i);
         if ((c >> shift) == prefix) S.few[atomicAdd(&S.nfew, 1u)] = c;
-      }
+      });
       __syncthreads();
       thr = select_kth_largest<kFinishThreads>(S.few, cnt, rem, S.sel_hist, S.sh);
       break;
     }
     __syncthreads();                                         // everyone has read sh before the next digit's init
   }
+  const uint32_t T = static_cast<uint32_t>(thr >> kDirectMaxLog2);                       // the k-th entry's key ...
+  const uint32_t ti = kDirectMax - 1u - (static_cast<uint32_t>(thr) & (kDirectMax - 1u));  // ... and index
   const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
   const gptr<int32_t> out_idx = as_global(L.out_idx);
   const gptr<float> out_val = as_global(L.out_val);
   const gptr<float> resid = as_global(L.resid);
   const gptr<float> mom = as_global(L.mom);
-  const uint32_t sent = emit_ordered(n, S, [&](uint32_t i) { return comp(i) >= thr; },
-                                     [&](uint32_t i, uint32_t pos) {
-                                       if (pos >= L.k) return;         // never when the selection is right
-                                       out_idx[pos] = static_cast<int32_t>(i);
-                                       out_val[pos] = S.u.vals[i];
-                                       resid[i] = 0.0f;
-                                       if (clear_mom) mom[i] = 0.0f;
-                                     });
-  if (t == 0) {
-    if (sent != L.k) atomicOr(A.errflag, 128u);
-    *as_global(L.out_count) = static_cast<int32_t>(L.k);
-    st->T = static_cast<uint32_t>(thr >> kDirectMaxLog2) >> up;
-    st->path = 1u;
-    st->stat_candidates = 0u;
-    st->stat_members = 0u;
-    st->next_phase = PH_NONE;
-    st->next_launch = 0u;
+  uint32_t first, last, mine = 0u, sent;
+  wave_range<kGroupElems>(n, first, last);
+  auto flags = [&](uint32_t e, float (&x)[4], bool (&f)[4]) {
+    const vf4a q = e < last ? S.u.vals[e / 4u] : vf4a{0.f, 0.f, 0.f, 0.f};
+    x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j) {
+      const uint32_t key = key32(x[j]);
+      f[j] = e + j < last && (key > T || (key == T && e + j <= ti));
+    }
+  };
+  for (uint32_t b = first; b < last; b += kGroupElems) {
+    float x[4];
+    bool f[4];
+    flags(b + 4u * lane, x, f);
+    if (__ballot(f[0] | f[1] | f[2] | f[3]) == 0ull) continue;
+    mine += popc64(__ballot(f[0])) + popc64(__ballot(f[1])) + popc64(__ballot(f[2])) + popc64(__ballot(f[3]));
   }
+  uint32_t at = wave_offset(mine, S.sh, sent);
+  for (uint32_t b = first; b < last; b += kGroupElems) {
+    const uint32_t e = b + 4u * lane;
+    float x[4];
+    bool f[4];
+    flags(e, x, f);
+    const unsigned long long m0 = __ballot(f[0]), m1 = __ballot(f[1]), m2 = __ballot(f[2]), m3 = __ballot(f[3]);
+    if ((m0 | m1 | m2 | m3) == 0ull) continue;
+    uint32_t pos = at + rank_below(m0) + rank_below(m1) + rank_below(m2) + rank_below(m3);
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j) {
+      if (f[j]) {
+        if (pos < L.k) {                                     // always, when the selection is right
+          out_idx[pos] = static_cast<int32_t>(e + j);
+          out_val[pos] = x[j];
+          resid[e + j] = 0.0f;
+          if (clear_mom) mom[e + j] = 0.0f;
+        }
+        ++pos;
+      }
+    }
+    at += popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
+  }
+  direct_done(A, L, st, sent, T >> up);
 }
 
-// A larger layer, from the lists its streaming pass left: they are copied into LDS in index order, the coarse histogram
-// and the ranking of the members are those of the one-pass path (resolve_collect, phase_sel), and the message is written
-// from LDS.  A hint that misses (or none) sends the layer through the digits in fallback_kernel.
-__device__ void finish_lists(const CompressArgs& A, const LayerDesc& L, LayerState* st, FinishShared& S) {
-  const uint32_t t = threadIdx.x, lane = lane_id(), wave = t >> 6;
-  const bool hinted = hint_usable(A, st);
-  const uint32_t tau = st->tau, hshift = st->shift, k = L.k, target = L.target;
-  constexpr uint32_t kFirst = 4u;                            // entries of a list asked for together with its length
-  uint32_t total = 0u;
-  bool ok = hinted;
-  if (hinted) {
-    for (uint32_t b = t; b < kCoarseBins; b += kFinishThreads) S.hist[b] = 0u;
-    if (t == 0) { S.bad = 0u; S.nfew = 0u; }
+template <bool kSigned>
+__device__ __forceinline__ void finish_direct(const CompressArgs& A, const LayerDesc& L, LayerState* st, SelectShared& S) {
+  const uint32_t t = threadIdx.x, n = L.n;
+  constexpr uint32_t kLoads = kDirectMax / (4u * kFinishThreads);
+  // the magnitude key has 31 bits, the ordered one 32
+  auto key32 = [&](float x) -> uint32_t {
+    if constexpr (kSigned) return ordered_key(fbits(x), A.sign_xor, A.sign_filter); else return fbits(x) << 1;
+  };
+  float x[kLoads][4];
+#pragma unroll
+  for (uint32_t i = 0; i < kLoads; ++i) {
+    const uint32_t e = 4u * (i * kFinishThreads + t);
+    if (i * 4u * kFinishThreads < n) {                       // (the same for every thread)
+      if (e + 4u <= n) {
+        const vf4 q = *as_vec(static_cast<const float*>(L.resid) + e);
+        x[i][0] = q.x; x[i][1] = q.y; x[i][2] = q.z; x[i][3] = q.w;
+      } else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) x[i][j] = e + j < n ? as_global(static_cast<const float*>(L.resid))[e + j] : 0.0f;
+      }
+    }
+  }
+  for (uint32_t b = t; b < kHistBins; b += kFinishThreads) S.hist[b] = 0u;
+  static_assert(kDirectMax / 32u == kFinishThreads, "one word of the bitmap a thread");
+  uint32_t* const bitmap = S.sel_hist + 3 * 256;             // (behind the histograms of the ranking)
+  bitmap[t] = 0u;
+  if (t == 0) S.nfew = 0u;
+  uint32_t top = 0u;
+#pragma unroll
+  for (uint32_t i = 0; i < kLoads; ++i) {
+    const uint32_t e = 4u * (i * kFinishThreads + t);
+    if (i * 4u * kFinishThreads < n) {
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j) {
+        const uint32_t k = key32(x[i][j]);
+        if (e + j < n && k > top) top = k;
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t holders = (n + 3u) / 4u < kFinishThreads ? (n + 3u) / 4u : kFinishThreads;   // threads with an element
+  if (L.k <= holders) {
+    float* const val = reinterpret_cast<float*>(S.u.vals);
+    // the bound from the top 24 bits of the keys (12 are too few for a residual that has piled up just below the threshold)
+    if (t < holders) atomicAdd(&S.hist[top >> 20], 1u);
     __syncthreads();
-    // rounds of 1024 lists, one a thread: lengths and first entries together, then a scan
-    uint32_t base = 0u;
-    for (uint32_t c0 = 0; c0 < L.wc_count; c0 += kFinishThreads) {
-      const uint32_t c = c0 + t;
-      const bool have = c < L.wc_count;
-      const size_t list = static_cast<size_t>(L.wc_first + (have ? c : 0u)) * A.cap;
-      const gptr<const vu2> slot = as_global(reinterpret_cast<const vu2*>(A.slots + list));
-      vu2 first[kFirst];
+    (void)locate_from_top<kFinishThreads>(S.hist, kHistBins, L.k, 0xFFFFFFFFu, S.sh);
+    uint32_t bound = S.sh.bin << 20;                         // (k <= holders: the bin exists)
+    const uint32_t rank = L.k - S.sh.above;
+    for (uint32_t b = t; b < kHistBins; b += kFinishThreads) S.hist[b] = 0u;
+    __syncthreads();
+    if (t < holders && (top >> 20) == (bound >> 20)) atomicAdd(&S.hist[(top >> 8) & (kHistBins - 1u)], 1u);
+    __syncthreads();
+    (void)locate_from_top<kFinishThreads>(S.hist, kHistBins, rank, 0xFFFFFFFFu, S.sh);
+    bound |= S.sh.bin << 8;
+    if (t < holders && top >= bound) {
 #pragma unroll
-      for (uint32_t j = 0; j < kFirst; ++j) first[j] = slot[j];
-      uint32_t cnt = have ? A.cand_cnt[L.wc_first + c] : 0u;
-      if (cnt > A.cap) { S.bad = 1u; cnt = 0u; }
-      uint32_t round;
-      const uint32_t at = base + block_excl_scan<kFinishWaves>(cnt, S.sh.scan, round);
-      if (at + cnt <= kFinishCand) {
+      for (uint32_t i = 0; i < kLoads; ++i) {
+        const uint32_t e = 4u * (i * kFinishThreads + t);
+        if (i * 4u * kFinishThreads < n) {
 #pragma unroll
-        for (uint32_t j = 0; j < kFirst; ++j)
-          if (j < cnt) S.u.list.cand[at + j] = first[j];
-        if (cnt > kFirst) {                                  // the rest of a longer list: a wave takes it whole, below
-          const uint32_t qn = atomicAdd(&S.nfew, 1u);
-          if (qn < kFinishThreads) S.few[qn] = (static_cast<unsigned long long>(at) << 32) | (c << 8) | cnt;
-          else for (uint32_t j = kFirst; j < cnt; ++j) S.u.list.cand[at + j] = slot[j];
+          for (uint32_t j = 0; j < 4u; ++j) {
+            const uint32_t k = key32(x[i][j]);
+            if (k >= bound && e + j < n) {
+              const uint32_t at = atomicAdd(&S.nfew, 1u);
+              if (at < kFinishThreads) { S.few[at] = direct_composite(k, e + j); val[at] = x[i][j]; }
+            }
+          }
         }
       }
-      base += round;
-    }
-    total = base;
-    __syncthreads();
-    const uint32_t queued = S.nfew < kFinishThreads ? S.nfew : kFinishThreads;
-    constexpr uint32_t kBatch = 4u;                          // lists of a wave on their way at a time
-    for (uint32_t i0 = wave; i0 < queued; i0 += kBatch * kFinishWaves) {
-      vu2 e[kBatch];
-      unsigned long long item[kBatch];
-#pragma unroll
-      for (uint32_t b = 0; b < kBatch; ++b) {
-        const uint32_t i = i0 + b * kFinishWaves;
-        item[b] = i < queued ? S.few[i] : 0ull;
-        const uint32_t cnt = static_cast<uint32_t>(item[b]) & 0xFFu, c = (static_cast<uint32_t>(item[b]) >> 8);
-        if (lane >= kFirst && lane < cnt) e[b] = as_global(reinterpret_cast<const vu2*>(A.slots + static_cast<size_t>(L.wc_first + c) * A.cap))[lane];
-      }
-#pragma unroll
-      for (uint32_t b = 0; b < kBatch; ++b) {
-        const uint32_t cnt = static_cast<uint32_t>(item[b]) & 0xFFu;
-        if (lane >= kFirst && lane < cnt) S.u.list.cand[static_cast<uint32_t>(item[b] >> 32) + lane] = e[b];
-      }
     }
     __syncthreads();
-    ok = S.bad == 0u && total >= k && total <= kFinishCand;
+    const uint32_t m = S.nfew;
+    if (m <= kFinishThreads) {
+      const unsigned long long thr = select_kth_largest<kFinishThreads>(S.few, m, L.k, S.sel_hist, S.sh);
+      const unsigned long long c = t < m ? S.few[t] : 0ull;
+      const bool mine = t < m && c >= thr;
+      const uint32_t i = kDirectMax - 1u - (static_cast<uint32_t>(c) & (kDirectMax - 1u));
+      if (mine) atomicOr(&bitmap[i >> 5], 1u << (i & 31u));
+      __syncthreads();
+      const uint32_t word = bitmap[t];
+      uint32_t sent;
+      S.hist[t] = block_excl_scan<kFinishWaves>(static_cast<uint32_t>(__popc(word)), S.sh.scan, sent);
+      __syncthreads();
+      if (mine) {
+        const uint32_t pos = S.hist[i >> 5] + static_cast<uint32_t>(__popc(bitmap[i >> 5] & ((1u << (i & 31u)) - 1u)));
+        if (pos < L.k) {                                     // always, when the selection is right
+          as_global(L.out_idx)[pos] = static_cast<int32_t>(i);
+          as_global(L.out_val)[pos] = val[t];
+          as_global(L.resid)[i] = 0.0f;
+          if (L.mom != nullptr && A.mask_momentum) as_global(L.mom)[i] = 0.0f;
+        }
+      }
+      direct_done(A, L, st, sent, static_cast<uint32_t>(thr >> kDirectMaxLog2) >> (kSigned ? 0u : 1u));
+      return;
+    }
+    __syncthreads();
   }
+#pragma unroll
+  for (uint32_t i = 0; i < kLoads; ++i) {
+    const uint32_t e = 4u * (i * kFinishThreads + t);
+    if (e < n) S.u.vals[e / 4u] = vf4a{x[i][0], x[i][1], x[i][2], x[i][3]};
+  }
+  __syncthreads();
+  finish_direct_radix(A, L, st, S);
+}
+
+// Copies the lists of the tiles first .. first + count - 1 (count <= 1024) into S.u.list.cand, one after the other: in
+// index order.  Returns how many candidates there are; S.bad says whether a list ran over or they do not fit.
+__device__ __forceinline__ uint32_t gather_lists(const CompressArgs& A, uint32_t first, uint32_t count, SelectShared& S) {
+  constexpr uint32_t kLanes = 8u, kEach = 2u;                // lanes a list, entries a lane: asked for together with its length
+  constexpr uint32_t kPerRound = kFinishThreads / kLanes, kRounds = kPartTilesMax / kPerRound;
+  typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
+  uint32_t* const start = S.hist + kCoarseBins;              // [count + 1] where each list goes
+  uint32_t* const queue = start + kPartTilesMax + 1;         // [count] lists with more than kLanes * kEach entries
+  static_assert(kCoarseBins + 2 * kPartTilesMax + 1 <= kHistBins, "the coarse histogram, the list starts and the queue share hist");
+  const uint32_t t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+  vu4 e[kRounds];
+#pragma unroll
+  for (uint32_t r = 0; r < kRounds; ++r) {
+    const uint32_t i = r * kPerRound + t / kLanes;
+    if (r * kPerRound < count && i < count)
+      e[r] = *as_global(reinterpret_cast<const vu4*>(A.slots + static_cast<size_t>(first + i) * A.cap + (t % kLanes) * kEach));
+  }
+  uint32_t len = t < count ? A.cand_cnt[first + t] : 0u;
+  if (t == 0) { S.bad = 0u; S.nfew = 0u; }
+  __syncthreads();
+  if (len > A.cap) { S.bad = 1u; len = 0u; }
+  uint32_t total;
+  const uint32_t at = block_excl_scan<kFinishWaves>(len, S.sh.scan, total);
+  if (t < count) start[t] = at;
+  if (t == 0) {
+    start[count] = total;
+    if (total > kFinishCand) S.bad = 1u;
+  }
+  __syncthreads();
+  if (S.bad != 0u) return total;
+#pragma unroll
+  for (uint32_t r = 0; r < kRounds; ++r) {
+    const uint32_t i = r * kPerRound + t / kLanes;
+    if (r * kPerRound < count && i < count) {
+      const uint32_t s0 = start[i], c = start[i + 1u] - s0, j = (t % kLanes) * kEach;
+      if (j < c) S.u.list.cand[s0 + j] = vu2{e[r].x, e[r].y};
+      if (j + 1u < c) S.u.list.cand[s0 + j + 1u] = vu2{e[r].z, e[r].w};
+      if (j == 0u && c > kLanes * kEach) queue[atomicAdd(&S.nfew, 1u)] = i;
+    }
+  }
+  __syncthreads();
+  const uint32_t queued = S.nfew;
+  for (uint32_t qi = wave; qi < queued; qi += kFinishWaves) {
+    const uint32_t i = queue[qi], s0 = start[i], c = start[i + 1u] - s0;
+    const gptr<const vu2> slot = as_global(reinterpret_cast<const vu2*>(A.slots + static_cast<size_t>(first + i) * A.cap));
+    constexpr uint32_t kTail = (kTileElems / 16u + kWaveSize - 1u) / kWaveSize;     // a list has kTileElems / 16 slots
+    vu2 x[kTail];
+#pragma unroll
+    for (uint32_t b = 0; b < kTail; ++b) {
+      const uint32_t j = kLanes * kEach + b * kWaveSize + lane;
+      if (j < c) x[b] = slot[j];
+    }
+#pragma unroll
+    for (uint32_t b = 0; b < kTail; ++b) {
+      const uint32_t j = kLanes * kEach + b * kWaveSize + lane;
+      if (j < c) S.u.list.cand[s0 + j] = x[b];
+    }
+  }
+  __syncthreads();
+  return total;
+}
+
+__device__ __forceinline__ void hint_missed(const CompressArgs& A, LayerState* st, bool hinted, uint32_t total) {
+  st->path = hinted ? 2u : 1u;
+  st->stat_misses += hinted ? 1u : 0u;
+  st->stat_candidates = total;
+  st->stat_members = 0u;
+  st->next_phase = PH_HIST1;
+  schedule_launch(A, st, kTiledLateLaunch);
+}
+
+__device__ __forceinline__ void hint_hit(const CompressArgs& A, const LayerDesc& L, LayerState* st, unsigned long long thr, uint32_t tau,
+                                         uint32_t shift, uint32_t bstar, uint32_t hbin, uint32_t total, uint32_t members) {
+  const uint32_t T = static_cast<uint32_t>(thr >> 32);
+  st->thr = thr;
+  st->T = T;
+  st->path = 0u;
+  st->stat_candidates = total;
+  st->stat_members = members;
+  if (A.update_hints) next_hint(st, T, next_threshold(tau, shift, bstar, hbin, total, L.k, L.target));
+}
+
+// A layer with few candidates: the coarse histogram and the ranking of the members are those of the one-pass path
+// (resolve_collect, phase_sel), all of it in LDS, and the message follows at once.
+__device__ __forceinline__ void finish_lists(const CompressArgs& A, const LayerDesc& L, LayerState* st, SelectShared& S) {
+  const uint32_t t = threadIdx.x;
+  const bool hinted = hint_usable(A, st);
+  const uint32_t tau = st->tau, shift = st->shift, k = L.k;
+  uint32_t total = 0u;
+  bool ok = hinted;
   auto key_at = [&](uint32_t i) { return key_of(S.u.list.cand[i].x, A.sign_xor, A.sign_filter); };
   if (ok) {
-    for (uint32_t i = t; i < total; i += kFinishThreads) atomicAdd(&S.hist[coarse_bin(key_at(i), tau, hshift)], 1u);
+    for (uint32_t b = t; b < kCoarseBins; b += kFinishThreads) S.hist[b] = 0u;
+    total = gather_lists(A, L.wg_first, L.wg_count, S);
+    ok = S.bad == 0u && total >= k;
+  }
+  if (ok) {
+    for (uint32_t i = t; i < total; i += kFinishThreads) atomicAdd(&S.hist[coarse_bin(key_at(i), tau, shift)], 1u);
     __syncthreads();
-    (void)locate_from_top<kFinishThreads>(S.hist, kCoarseBins, k, target, S.sh);
+    (void)locate_from_top<kFinishThreads>(S.hist, kCoarseBins, k, L.target, S.sh);
     ok = S.sh.bin != 0xFFFFFFFFu && S.sh.cnt <= static_cast<uint32_t>(kMemberMax);
   }
   if (!ok) {
-    if (t == 0) {
-      st->path = hinted ? 2u : 1u;
-      st->stat_misses += hinted ? 1u : 0u;
-      st->stat_candidates = total;
-      st->stat_members = 0u;
-      st->next_phase = PH_HIST1;
-      schedule_launch(A, st, 3u);
-    }
+    if (t == 0) hint_missed(A, st, hinted, total);
     return;
   }
   const uint32_t bstar = S.sh.bin, above = S.sh.above, m = S.sh.cnt, hbin = S.sh.hbin;
@@ -1519,58 +1818,166 @@ __device__ void finish_lists(const CompressArgs& A, const LayerDesc& L, LayerSta
   __syncthreads();
   for (uint32_t i = t; i < total; i += kFinishThreads) {
     const uint32_t key = key_at(i);
-    if (coarse_bin(key, tau, hshift) == bstar) S.u.list.members[atomicAdd(&S.nfew, 1u)] = composite(key, S.u.list.cand[i].y);
+    if (coarse_bin(key, tau, shift) == bstar) S.u.list.members[atomicAdd(&S.nfew, 1u)] = composite(key, S.u.list.cand[i].y);
   }
   __syncthreads();
   const unsigned long long thr = select_kth_largest<kFinishThreads>(S.u.list.members, m, k - above, S.sel_hist, S.sh);
-  const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
-  const gptr<int32_t> out_idx = as_global(L.out_idx);
-  const gptr<float> out_val = as_global(L.out_val);
-  const gptr<float> resid = as_global(L.resid);
-  const gptr<float> mom = as_global(L.mom);
-  const uint32_t sent = emit_ordered(total, S, [&](uint32_t i) { return composite(key_at(i), S.u.list.cand[i].y) >= thr; },
-                                     [&](uint32_t i, uint32_t pos) {
-                                       const vu2 e = S.u.list.cand[i];
-                                       if (pos >= k || e.y >= L.n) return;     // never when the lists are right
-                                       out_idx[pos] = static_cast<int32_t>(e.y);
-                                       out_val[pos] = __uint_as_float(e.x);
-                                       mask_store(&resid[e.y]);
-                                       if (clear_mom) mask_store(&mom[e.y]);
-                                     });
+  const uint32_t sent = emit_candidates(A, L, S.u.list.cand, total, thr, 0u, S.sh);
   if (t == 0) {
     if (sent != k) atomicOr(A.errflag, 256u);
     *as_global(L.out_count) = static_cast<int32_t>(k);
-    const uint32_t T = static_cast<uint32_t>(thr >> 32);
-    st->thr = thr;
-    st->T = T;
-    st->path = 0u;
-    st->stat_candidates = total;
-    st->stat_members = m;
-    if (A.update_hints) {
-      const uint32_t tn = next_threshold(tau, hshift, bstar, hbin, total, k, target);
-      next_hint(st, T, tn);
-    }
+    hint_hit(A, L, st, thr, tau, shift, bstar, hbin, total, m);
     st->next_phase = PH_NONE;
     st->next_launch = 0u;
   }
 }
 
+// One part (kPartTiles tiles) of a larger layer.  The tiles have left the layer's coarse histogram in global memory, and every
+// part finds the k-th key's bin for itself; what it contributes goes through device-scope stores and atomics, as everything that
+// the last workgroup of a layer reads.  Its candidates are left in one piece where its first list began.
+constexpr uint32_t kPartBad = 0x80000000u;
+__device__ __forceinline__ void select_part(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t part, SelectShared& S) {
+  const uint32_t t = threadIdx.x;
+  const uint32_t parts = (L.wg_count + kPartTiles - 1u) / kPartTiles;
+  if (!hint_usable(A, st)) {
+    if (part == 0u && t == 0) hint_missed(A, st, false, 0u);
+    return;
+  }
+  const uint32_t tau = st->tau, shift = st->shift, k = L.k;
+  uint32_t* const coarse = A.coarse + static_cast<size_t>(l) * kCoarseRep * kCoarseBins;
+  unsigned long long* const members = A.members + static_cast<size_t>(l) * kMemberMax;
+  static_assert(kCoarseBins == kFinishThreads, "one thread per coarse bin");
+  {
+    uint32_t v[kCoarseRep], sum = 0u;
+#pragma unroll
+    for (uint32_t r = 0; r < static_cast<uint32_t>(kCoarseRep); ++r) v[r] = coarse[r * kCoarseBins + t];
+#pragma unroll
+    for (uint32_t r = 0; r < static_cast<uint32_t>(kCoarseRep); ++r) sum += v[r];
+    S.hist[t] = sum;
+  }
+  const uint32_t tile0 = part * kPartTiles;
+  const uint32_t tiles = L.wg_count - tile0 < kPartTiles ? L.wg_count - tile0 : kPartTiles;
+  const uint32_t total = gather_lists(A, L.wg_first + tile0, tiles, S);
+  const uint32_t cand_total = locate_from_top<kFinishThreads>(S.hist, kCoarseBins, k, L.target, S.sh);
+  const uint32_t bstar = S.sh.bin, above = S.sh.above, m = S.sh.cnt, hbin = S.sh.hbin;
+  const bool ok = S.bad == 0u && bstar != 0xFFFFFFFFu && m <= static_cast<uint32_t>(kMemberMax);
+  uint32_t hi = 0u;
+  if (t == 0) S.nfew = 0u;
+  __syncthreads();
+  if (ok) {
+    vu2* const packed = reinterpret_cast<vu2*>(A.slots + static_cast<size_t>(L.wg_first + tile0) * A.cap);
+    for (uint32_t i = t; i < total; i += kFinishThreads) {
+      const vu2 e = S.u.list.cand[i];
+      as_global(packed)[i] = e;
+      const uint32_t key = key_of(e.x, A.sign_xor, A.sign_filter), bin = coarse_bin(key, tau, shift);
+      hi += bin > bstar ? 1u : 0u;
+      if (bin == bstar) S.u.list.members[atomicAdd(&S.nfew, 1u)] = composite(key, e.y);   // (m of them in the whole layer)
+    }
+    if (t == 0) A.cand_cnt[L.wg_first + tile0] = total;
+  }
+  uint32_t hi_all;
+  (void)block_excl_scan<kFinishWaves>(hi, S.sh.scan, hi_all);
+  const uint32_t mine = S.nfew;
+  if (t == 0) {
+    st_agent(&A.wc_a[L.part_first + part], ok ? hi_all : kPartBad);
+    S.bad = mine != 0u ? atomicAdd(&st->nmembers, mine) : 0u;
+  }
+  __syncthreads();
+  const uint32_t where = S.bad;
+  for (uint32_t i = t; i < mine; i += kFinishThreads)
+    if (where + i < static_cast<uint32_t>(kMemberMax)) __hip_atomic_store(&members[where + i], S.u.list.members[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // ---- the last part of the layer to get here goes on
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (t == 0) S.sh.flag = atomicAdd(&st->done, 1u) + 1u == parts ? 1u : 0u;
+  __syncthreads();
+  if (S.sh.flag == 0u) return;
+  if (t == 0) st_agent(&st->done, 0u);
+#pragma unroll
+  for (uint32_t r = 0; r < static_cast<uint32_t>(kCoarseRep); ++r) coarse[r * kCoarseBins + t] = 0u;   // (every part has read it)
+  static_assert(kPartsMax == 2u * kFinishThreads, "two parts a thread");
+  uint32_t v[2], bad = 0u;
+#pragma unroll
+  for (uint32_t j = 0; j < 2u; ++j) {
+    v[j] = 2u * t + j < parts ? ld_agent(&A.wc_a[L.part_first + 2u * t + j]) : 0u;
+    bad |= v[j] & kPartBad;
+  }
+  const uint32_t all = ld_agent(&st->nmembers);
+  if (__syncthreads_or(static_cast<int>(bad)) != 0) {
+    if (t == 0) hint_missed(A, st, true, cand_total);
+    return;
+  }
+  const uint32_t k_rem = k - above;
+  if (all != m || k_rem == 0u || k_rem > m) {                // cannot happen when the histogram and the lists agree
+    if (t == 0) { atomicOr(A.errflag, 4u); st->next_launch = 0u; }
+    return;
+  }
+  for (uint32_t i = t; i < m; i += kFinishThreads)
+    S.u.list.members[i] = __hip_atomic_load(&members[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  S.hist[t] = 0u;
+  S.hist[kFinishThreads + t] = 0u;
+  __syncthreads();
+  const unsigned long long thr = select_kth_largest<kFinishThreads>(S.u.list.members, m, k_rem, S.sel_hist, S.sh);
+  for (uint32_t i = t; i < m; i += kFinishThreads) {         // the selected members are credited to their parts
+    if (S.u.list.members[i] >= thr) {
+      const uint32_t idx = 0xFFFFFFFFu - static_cast<uint32_t>(S.u.list.members[i]);
+      atomicAdd(&S.hist[idx / (kTileElems * kPartTiles)], 1u);
+    }
+  }
+  __syncthreads();
+  v[0] += S.hist[2u * t];
+  v[1] += S.hist[2u * t + 1u];
+  uint32_t sent;
+  const uint32_t at = block_excl_scan<kFinishWaves>(v[0] + v[1], S.sh.scan, sent);
+  if (2u * t < parts) A.wc_b[L.part_first + 2u * t] = at;
+  if (2u * t + 1u < parts) A.wc_b[L.part_first + 2u * t + 1u] = at + v[0];
+  if (t == 0) {
+    if (sent != k) atomicOr(A.errflag, 8u);
+    hint_hit(A, L, st, thr, tau, shift, bstar, hbin, cand_total, m);
+    st->next_phase = PH_EMIT_PART;
+    st->next_launch = kEmitLaunch;
+  }
+}
+
 }  // namespace
 
-// Launch 2: one workgroup ends one layer.  A chain of memory round trips and barriers, not of bytes: 12 us for one layer of
-// 2^20 elements, 27 us for the ResNet-50 set (its 32768-element layers).  Whole calls, six launches before and three now:
-// three layers of 50,000, 8,205 and 300 elements 26.9 -> 17.4 us, 2^20 elements 28.6 -> 17.1 us, ResNet-50 set 91 -> 82 us.
-__global__ void __launch_bounds__(kFinishThreads) finish_kernel(CompressArgs A) {
-  __shared__ FinishShared S;
-  const uint32_t l = blockIdx.x;
+// A chain of memory round trips and barriers, not of bytes: 6 us for one layer of 300 elements, 13 us for one of 32768, 10 us
+// for one of 2^20, 15 us for the ResNet-50 set, 16 us for the VGG16 set's 134 parts and small layers.  Everything it calls is
+// inlined: with calls left in it the kernel took 12 us more.  Whole calls, three contexts taking turns, with the six launches of
+// the general path before: layers of 50,000, 8,205 and 300 elements 26.9 -> 15.4 us, 2^20 elements 28.6 -> 15.6 us, ResNet-50
+// set 91 -> 72 us, VGG16 set 571 -> 518 us.
+__global__ void __launch_bounds__(kFinishThreads) select_kernel(CompressArgs A) {
+  __shared__ SelectShared S;
+  const uint2 where = A.parts[blockIdx.x];                   // (layer, part of it)
+  const uint32_t l = where.x;
   const LayerDesc L = A.layers[l];
   LayerState* st = A.state + l;
-  if (L.direct) finish_direct(A, L, st, S);
-  else finish_lists(A, L, st, S);
+  if (L.kind == kLayerDirect) {
+    if (A.sign_filter) finish_direct<true>(A, L, st, S); else finish_direct<false>(A, L, st, S);
+  }
+  else if (L.kind == kLayerLists) finish_lists(A, L, st, S);
+  else select_part(A, l, L, st, where.y, S);
+}
+
+// The messages of the larger layers (their parts come first in the table): a part's candidates are read in one piece.
+__global__ void __launch_bounds__(kFinishThreads) emit_kernel(CompressArgs A) {
+  __shared__ vu2 cand[kFinishCand];
+  __shared__ ResolveShared sh;
+  const uint2 where = A.parts[blockIdx.x];
+  const LayerDesc L = A.layers[where.x];
+  const LayerState* st = A.state + where.x;
+  if (st->next_launch != kEmitLaunch) return;                // the hint missed: fallback_kernel has this layer
+  const uint32_t tile0 = L.wg_first + where.y * kPartTiles;
+  const uint32_t count = A.cand_cnt[tile0] < kFinishCand ? A.cand_cnt[tile0] : kFinishCand;
+  const gptr<const vu2> packed = as_global(reinterpret_cast<const vu2*>(A.slots + static_cast<size_t>(tile0) * A.cap));
+  for (uint32_t i = threadIdx.x; i < count; i += kFinishThreads) cand[i] = packed[i];
+  __syncthreads();
+  (void)emit_candidates(A, L, cand, count, st->thr, A.wc_b[L.part_first + where.y], sh);
+  if (where.y == 0u && threadIdx.x == 0) *as_global(L.out_count) = static_cast<int32_t>(L.k);
 }
 
 // The last launch of a call that uses hints: the launches A.late_first .. A.late_last in one, for the layers whose hint
-// missed.  Nothing is due in steady state, and one launch that finds that out is cheaper than three (VGG16 set: 571 us per
+// missed (a tiled call hands it the general tiling).  Nothing is due in steady state, and one launch that finds that out is cheaper than three (VGG16 set: 571 us per
 // call with three, 565 us with one).
 // Otherwise a grid of one workgroup per CU takes the workgroup numbers in turn, with a barrier over the grid between two
 // launch numbers: its release and acquire make plain stores visible across the XCDs, as a kernel boundary would.
@@ -2559,8 +2966,13 @@ hipError_t launch_tiles(const CompressArgs& a, uint32_t num_wgs, hipStream_t s) 
   return hipGetLastError();
 }
 
-hipError_t launch_finish(const CompressArgs& a, uint32_t num_layers, hipStream_t s) {
-  hipLaunchKernelGGL(finish_kernel, dim3(num_layers), dim3(kFinishThreads), 0, s, a);
+hipError_t launch_select(const CompressArgs& a, uint32_t num_parts, hipStream_t s) {
+  hipLaunchKernelGGL(select_kernel, dim3(num_parts), dim3(kFinishThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_emit(const CompressArgs& a, uint32_t num_parts, hipStream_t s) {
+  hipLaunchKernelGGL(emit_kernel, dim3(num_parts), dim3(kFinishThreads), 0, s, a);
   return hipGetLastError();
 }
 

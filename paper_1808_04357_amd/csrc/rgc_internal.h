@@ -32,6 +32,7 @@ enum Phase : uint32_t {
   PH_RESTORE = 9,  // dense layers whose hint missed: the entries masked on the strength of the hint go back into residual and
                    // velocity, then PH_HIST1 in the same launch
   PH_EMIT = 10,    // dense layers: the message from the lists, with the k-th entry known
+  PH_EMIT_PART = 12,   // tiled calls, larger layers: emit_kernel
   PH_SEL2 = 11,    // dense layers: PH_SEL on the layer's own lists (lists_kernel)
 };
 
@@ -49,15 +50,25 @@ constexpr uint32_t kMemberShards = 16;
 constexpr uint32_t kMemberLists = kMemberShards + 1;
 constexpr uint32_t kShardStride = 64;    // words between two counters: atomics on one cache line take their turns like atomics on one word
 
-// Calls whose layers are all small ("finishable") take two launches, a one-shot streaming pass and finish_kernel, which
-// ends a layer in one workgroup: a layer of at most kDirectMax elements from the residual itself (in LDS), a larger one
-// from its candidate lists, as long as the LDS has room for twice the rank its hint is aimed at (with room for half as many
-// more only, a layer whose residual was still building up missed on every call).
+// Tiled calls (see tile_kernel): what select_kernel does with a layer.
 constexpr uint32_t kFinishThreads = 1024, kFinishWaves = kFinishThreads / kWaveSize;
 constexpr uint32_t kDirectMaxLog2 = 15, kDirectMax = 1u << kDirectMaxLog2;
-constexpr uint32_t kFinishCand = 12288;            // candidates of a layer in LDS
-constexpr uint32_t kFinishTargetMax = kFinishCand / 2;   // largest target rank of such a layer (2.4 M elements at 0.1 %)
-constexpr uint32_t kTileChunk = 1024;              // elements per wave-chunk of such calls: one group of loads per wave
+constexpr uint32_t kTileChunk = 1024;              // elements per wave
+constexpr uint32_t kTileElems = kTileChunk * kWavesPerBlock;
+constexpr uint32_t kFinishCand = 12288;            // candidates in LDS
+constexpr uint32_t kPartTilesMax = 1024;           // lists gather_lists() can take
+// A larger layer's parts: 2^20 elements, 2,600 candidates at 0.1 %.  All tiles of the largest layer make at most kPartsMax.
+constexpr uint32_t kPartTiles = 256, kPartsMax = 2048;
+static_assert(static_cast<uint64_t>(kPartsMax) * kPartTiles * kTileElems >= (1ull << 31), "any layer has at most kPartsMax parts");
+enum LayerKind : uint32_t {
+  kLayerBig = 0,       // several workgroups, a message launch of its own
+  kLayerLists = 1,     // ended by one workgroup from its lists: the rank its hint is aimed at leaves room in the LDS for twice as many
+                       // (with room for half as many more only, a layer whose residual was still building up missed on every call)
+  kLayerDirect = 2,    // at most kDirectMax elements: ended by one workgroup from the residual itself, needs no hint
+};
+constexpr uint32_t kListsTargetMax = kFinishCand / 2;
+constexpr uint32_t kEmitLaunch = 3;                // tile_kernel is 1, select_kernel 2
+constexpr uint32_t kTiledLateLaunch = 4;           // a missed hint: the first digit, in fallback_kernel
 
 // Per call, per layer descriptor (device copy of the caller's rgc_layer plus the tiling).
 struct LayerDesc {
@@ -83,8 +94,8 @@ struct LayerDesc {
   uint32_t mem_cap;    // dense layers: entries of the layer's kMemberShards sub-lists together (a multiple of kMemberShards); the
                        // overflow list behind them holds mem_cap / 4, which is also the most members a call accepts
   uint32_t list_cap;   // dense layers: entries of one wave-chunk's list
-  uint32_t direct;     // finishable calls: at most kDirectMax elements, selected from the residual itself
-  uint32_t pad_;
+  uint32_t kind;       // LayerKind (tiled calls)
+  uint32_t part_first; // tiled calls: where the layer's parts start in the per-part arrays
   uint64_t mem_first;  // dense layers: where the layer's region of the member pool starts
   uint64_t list_first; // dense layers: where the layer's lists start (wave-chunk c of the layer: list_first + c * list_cap)
 };
@@ -168,6 +179,7 @@ struct CompressArgs {
   uint32_t mask_momentum;
   float m;
   uint32_t launch;       // launch number of the phase kernel (2..6)
+  const uint2* parts;    // tiled calls: (layer, part of it) of every workgroup of select_kernel, those of the larger layers first
   uint32_t* late;        // [3] fallback_kernel: layers are due, workgroups at the barrier, workgroups that have left
   uint32_t late_first;   // the launch numbers fallback_kernel stands for (0: they are launches of their own)
   uint32_t late_last;
@@ -274,8 +286,9 @@ hipError_t launch_accumulate(const CompressArgs& a, uint32_t num_wgs, hipStream_
 hipError_t launch_collect(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);   // streaming pass of the dense layers
 hipError_t launch_lists(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);     // their ranking and output steps
 hipError_t launch_phase(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);
-hipError_t launch_tiles(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);        // streaming pass of a finishable call
-hipError_t launch_finish(const CompressArgs& a, uint32_t num_layers, hipStream_t s);
+hipError_t launch_tiles(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);        // streaming pass of a tiled call
+hipError_t launch_select(const CompressArgs& a, uint32_t num_parts, hipStream_t s);
+hipError_t launch_emit(const CompressArgs& a, uint32_t num_parts, hipStream_t s);
 hipError_t launch_fallback(const CompressArgs& a, uint32_t num_wgs, uint32_t cus, hipStream_t s);
 constexpr uint32_t kMeanPartsMax = 128;    // parts per layer at most (rgc_message_means)
 hipError_t launch_message_means(const CompressArgs& a, uint32_t num_layers, uint32_t max_k, const ExactParts& parts,

@@ -1,6 +1,6 @@
-"""GPU parity of the calls whose layers are all small enough to be ended by one workgroup each (bit equality): layers
-selected from the residual itself (up to 32768 elements), layers selected from their candidate lists, and the launch
-that takes the layers whose hint missed."""
+"""GPU parity of the tiled calls (bit equality): layers selected from the residual itself (up to 32768 elements), layers
+ended by one workgroup from their candidate lists, larger layers in parts of 2^20 elements, and the launch that takes the
+layers whose hint missed."""
 import numpy as np
 import pytest
 
@@ -53,9 +53,12 @@ def test_direct_layers_with_momentum_and_without_hints(rgc, oracle):
         run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9, flags=flags, tag="direct momentum %x" % flags)
 
 
-# 32769 is the smallest layer taken from its lists; 2457 entries sent (rank 6142 aimed at) the most
+# 32769 is the smallest layer taken from its lists; 2457 entries sent (rank 6142 aimed at) and 1024 tiles of 4096 elements the
+# most one workgroup takes
 @pytest.mark.parametrize("sizes,ks", [([32769, 32768, 100], None), ([65536 + 1023, 40_000], None), ([1 << 20], None),
                                       ([2_457_000, 1_000_003, 33_000], None), ([400_000], [2457]), ([400_000], [2458]),
+                                      ([3 << 20], None), ([(3 << 20) - 1, 5 << 20, 70_000], None), ([(3 << 20) + 1], None),
+                                      ([1024 * 4096], [400]), ([1024 * 4096 + 1], [400]),
                                       ([700_000, 500_000, 300], [1, 2, 3])])
 def test_layers_from_their_lists(rgc, oracle, sizes, ks):
     g = np.random.default_rng(7)
@@ -84,7 +87,7 @@ def test_missed_hints_take_the_fallback(rgc, oracle):
     """Hints too high, too low and random, heavy ties, an overflowing list, zeros: several layers at once go through the
     digits in the last launch, others do not."""
     g = np.random.default_rng(9)
-    sizes = [300_000, 1_500_000, 40_001, 90_000, 200_000, 5000]
+    sizes = [300_000, 4_500_000, 40_001, 90_000, 200_000, 5000]
     V = [(g.standard_normal(n) * 1e-2).astype(np.float32) for n in sizes]
     V[2] = (np.round(V[2] * 300) / 300).astype(np.float32)
     V[3][:] = 0.0
