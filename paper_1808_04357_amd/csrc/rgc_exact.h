@@ -218,8 +218,10 @@ __device__ __forceinline__ void exact_take_parts(ExactPair& a, const ExactParts&
   }
 }
 
-// Thread 0, after exact_block_total: the sum of everything the workgroup took, rounded once.
-__device__ __noinline__ double exact_round(const ExactAcc& total, ExactShared& sh);
+// Thread 0, after exact_block_total: the sum of everything the workgroup took, rounded once.  (Inlined: as a function it gave
+// the kernels that end a sum a stack: clip_coefficient_kernel 12.8 -> 11.2 us on the LSTM set, message_means_kernel 8.2 -> 7.3 us
+// on the ResNet-50 set.)
+__device__ __forceinline__ double exact_round(const ExactAcc& total, ExactShared& sh);
 
 // Every thread brings what exact_take_parts gave it; thread 0 returns with the sum of all parts, rounded once
 // (the other threads with nothing of use).  Holds barriers.
@@ -233,7 +235,7 @@ __device__ __forceinline__ double exact_finish(const ExactPair& mine, ExactShare
   return exact_round(sums, sh);
 }
 
-__device__ __noinline__ double exact_round(const ExactAcc& total, ExactShared& sh) {
+__device__ __forceinline__ double exact_round(const ExactAcc& total, ExactShared& sh) {
   const uint32_t f = total.flags;
   if ((f & kExactNaN) || ((f & kExactPosInf) && (f & kExactNegInf))) return __longlong_as_double(0x7FF8000000000000ll);
   if (f & kExactPosInf) return __longlong_as_double(0x7FF0000000000000ll);
