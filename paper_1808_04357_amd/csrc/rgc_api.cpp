@@ -742,7 +742,7 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   // A searching call passes over the tensors four times and ends where it began; a reusing call passes once:
   // the call after it starts from the end it stopped at, whose data the memory-side cache still holds.
   const bool alternate = plan->write_bytes > kMemorySideCacheBytes;
-  A.past_cache = stream_past_cache(plan, A.search != 0u);
+  A.past_cache = stream_past_cache(plan, false);
   A.reverse = alternate ? ctx->threshold_reverse : 0u;
   RGC_HIP(launch_threshold_compress(A, plan->general.workgroups, static_cast<uint32_t>(num_layers), stream));
   if (!A.search) ctx->threshold_reverse ^= 1u;

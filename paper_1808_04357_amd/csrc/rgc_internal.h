@@ -199,6 +199,8 @@ struct ThresholdMoments {   // per layer, written by the moments kernel
   float max;                // max of |a|
   float span;               // max - mean, rounded
   uint32_t counts_taken;    // counts the bisection took (diagnostics)
+  float listed_above;       // searching call: the streaming pass has listed the elements above this magnitude (+inf: none)
+  uint32_t lists;           // ... and the lists are all the rest of the call needs
 };
 
 struct ThresholdArgs {

@@ -11,8 +11,16 @@
 // suffix sum, and the bisection runs on those sums.  T(j) is computed with the very operations
 // of the listing (fp32, every operation rounded), so the counts are the listing's counts.
 //
+// And that pass goes over lists of the layer's largest elements, not over the layer.  A sample of the accumulated values
+// (16384 of them, from 1024 places) gives a magnitude that about 4k elements exceed; the streaming pass
+// lists those.  If it has listed at least 2k of them, every count the search compares with k and 2k is known: above a
+// threshold not below that magnitude from the lists, above a lower one it is 2k or more, and that is all the search asks.
+// LSTM set: 291 us per call with three more passes over V, 212 us this way.
+// A layer whose lists do not do (too few listed, a list that ran over, a share too large to list, a search that ends below)
+// is read from V instead, in the same launches.
+//
 // Launches of one call (same workgroup -> layer -> wave-chunk decomposition as the exact path):
-//   search:  accumulate (+ partial sums and maxima of |a|)  ->  moments  ->  histogram  ->  search
+//   search:  sample  ->  accumulate (+ partial sums and maxima of |a|, lists)  ->  moments  ->  histogram  ->  search
 //            ->  count  ->  offsets  ->  emit
 //   reuse:   accumulate (+ the elements above the given threshold, listed per wave-chunk)  ->  offsets
 //            ->  emit from the lists
@@ -107,6 +115,21 @@ __device__ __forceinline__ void read_groups(const float* generic_p, uint32_t beg
   }
 }
 
+// Calls f(entry, exists) for the entries of the wave-chunk's list, 64 at a time (all lanes take part).
+template <typename F>
+__device__ __forceinline__ void for_listed(const ThresholdArgs& A, const Place& p, F&& f) {
+  if (p.begin == p.end) return;
+  const gptr<const vu2> slot = as_global(reinterpret_cast<const vu2*>(A.slots + static_cast<size_t>(p.wc) * A.cap));
+  const uint32_t lane = lane_id();
+  vu2 e = slot[lane];                               // (the slots exist whatever the length: a list has more than 64)
+  const uint32_t listed = A.listed[p.wc] < A.cap ? A.listed[p.wc] : A.cap;
+  for (uint32_t b = 0; b < listed; b += kWaveSize) {
+    const vu2 next = b + kWaveSize + lane < listed ? slot[b + kWaveSize + lane] : vu2{0u, 0u};
+    f(e, b + lane < listed);
+    e = next;
+  }
+}
+
 // The accumulate of Algorithm 1 over [begin, end) of a layer (same arithmetic as the exact path:
 // accum4), handing every group of accumulated values to f.  Whole groups are
 // taken four (two with a velocity) at a time, all their loads issued before the first use.
@@ -189,16 +212,107 @@ __device__ __forceinline__ float wave_max(float x) {
 
 }  // namespace
 
-// ------------------------------------------------------------------ accumulate (+ moments or counts)
-// kCount = false (a search follows): leaves per workgroup its part of the exactly rounded sum of |a|
-// (rgc_exact.h) and the maximum of |a|.
-// kCount = true (the threshold is given): leaves per wave-chunk the number of |a| > threshold and, in
-// the wave-chunk's list, those elements themselves (as many as the list holds).
-template <bool kNt, bool kCount, bool kReverse>
+// ------------------------------------------------------------------ sample (a search follows)
+// One workgroup per layer, one piece of 16 consecutive elements a thread, each from a stretch of the layer of its own, and the
+// magnitude that (4k of the layer's elements, and a margin for small samples) of them exceed, rounded down to 12 bits.
+// Speed only: a magnitude that turns out too high or too low costs further passes, not the result.  (Scattered cache lines
+// are what one workgroup waits for: 4096 pieces of four elements took 23 us on the LSTM set, these 14.5 us; counting only the
+// samples above a bound, a fraction of the LDS atomics, changed nothing.)
+constexpr uint32_t kSampleThreads = 1024, kPieceElems = 16;
+__global__ void __launch_bounds__(kSampleThreads) threshold_sample_kernel(ThresholdArgs A) {
+  __shared__ uint32_t hist[kHistBins];
+  __shared__ uint32_t scan[kSampleThreads / kWaveSize];
+  __shared__ uint32_t found;
+  const uint32_t l = blockIdx.x, t = threadIdx.x;
+  const LayerDesc L = A.layers[l];
+  const uint32_t groups = (L.n + kPieceElems - 1u) / kPieceElems;
+  const uint32_t pieces = groups < kSampleThreads ? groups : kSampleThreads;
+  const unsigned long long samples = static_cast<unsigned long long>(kPieceElems) * pieces;
+  // rank of the magnitude in the sample, and how many elements of the layer that stands for: lists hold one in 16, and
+  // single ones several times the average
+  const unsigned long long rank = (4ull * L.k * samples + L.n - 1u) / L.n + 24u;
+  const bool listable = 2ull * (4ull * L.k + 24ull * L.n / samples) <= L.n / 16u && rank <= samples;
+  for (uint32_t b = t; b < static_cast<uint32_t>(kHistBins); b += kSampleThreads) hist[b] = 0u;
+  if (t == 0u) found = 0xFFFFFFFFu;
+  __syncthreads();
+  if (listable && t < pieces) {
+    AccumRule rule;
+    rule.m = A.m;
+    rule.scale = A.grad_scale ? *as_global(A.grad_scale) : 1.0f;
+    constexpr uint32_t kEach = kPieceElems / 4u;
+    const uint32_t lo = static_cast<uint32_t>(static_cast<unsigned long long>(t) * groups / pieces);
+    const uint32_t hi = static_cast<uint32_t>(static_cast<unsigned long long>(t + 1u) * groups / pieces);
+    uint32_t h = (t + 1u) * 2654435761u;                     // (some place inside the stretch: rows of a matrix are not to line up)
+    h ^= h >> 15; h *= 2246822519u; h ^= h >> 13;
+    const uint32_t first = kPieceElems * (lo + static_cast<uint32_t>((static_cast<unsigned long long>(h) * (hi - lo)) >> 32));
+    const uint32_t have = L.n - first < kPieceElems ? L.n - first : kPieceElems;
+    float g[kEach][4], v[kEach][4], u[kEach][4];
+#pragma unroll
+    for (uint32_t q = 0; q < kEach; ++q) {
+      const uint32_t e = first + 4u * q;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) g[q][j] = v[q][j] = u[q][j] = 0.0f;
+      if (4u * q + 4u <= have) {
+        const vf4 gq = *as_vec(L.grad + e), vq = *as_vec(static_cast<const float*>(L.resid) + e);
+        g[q][0] = gq.x; g[q][1] = gq.y; g[q][2] = gq.z; g[q][3] = gq.w;
+        v[q][0] = vq.x; v[q][1] = vq.y; v[q][2] = vq.z; v[q][3] = vq.w;
+        if (L.mom != nullptr) {
+          const vf4 uq = *as_vec(static_cast<const float*>(L.mom) + e);
+          u[q][0] = uq.x; u[q][1] = uq.y; u[q][2] = uq.z; u[q][3] = uq.w;
+        }
+      } else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+          if (4u * q + j < have) {
+            g[q][j] = as_global(L.grad)[e + j];
+            v[q][j] = as_global(static_cast<const float*>(L.resid))[e + j];
+            if (L.mom != nullptr) u[q][j] = as_global(static_cast<const float*>(L.mom))[e + j];
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kEach; ++q) {
+      float a[4];
+      if (L.mom == nullptr) accum4<false, false>(g[q], v[q], u[q], rule, a);
+      else if (!A.nesterov) accum4<true, false>(g[q], v[q], u[q], rule, a);
+      else accum4<true, true>(g[q], v[q], u[q], rule, a);
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j)
+        if (4u * q + j < have && fabsf(a[j]) > 0.0f) atomicAdd(&hist[(fbits(a[j]) & kKeyMask) >> 19], 1u);
+    }
+  }
+  __syncthreads();
+  // four bins a thread, from the top
+  uint32_t h[4], mine = 0u;
+#pragma unroll
+  for (uint32_t j = 0; j < 4u; ++j) { h[j] = hist[kHistBins - 1u - (4u * t + j)]; mine += h[j]; }
+  uint32_t total;
+  uint32_t cum = block_excl_scan<kSampleThreads / kWaveSize>(mine, scan, total);
+  if (listable && cum < rank && rank <= cum + mine) {
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j) {
+      if (cum < rank && rank <= cum + h[j]) found = kHistBins - 1u - (4u * t + j);
+      cum += h[j];
+    }
+  }
+  __syncthreads();
+  if (t == 0u) {
+    // (fewer non-zero samples than that: a sparse layer, every non-zero element is listed if they fit)
+    const uint32_t bits = found != 0xFFFFFFFFu ? found << 19 : 0u;
+    A.moments[l].listed_above = listable ? __uint_as_float(bits) : __uint_as_float(0x7F800000u);
+  }
+}
+
+// ------------------------------------------------------------------ accumulate (+ moments, lists)
+// Leaves in the wave-chunk's list the elements above a magnitude (as many as the list holds) and per wave-chunk their number;
+// the magnitude is the threshold where it is given, and the sample's where it is searched (kSearch), in which case the pass
+// also leaves per workgroup its part of the exactly rounded sum of |a| (rgc_exact.h) and the maximum of |a|.
+template <bool kNt, bool kSearch, bool kReverse>
 __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(ThresholdArgs A) {
   __shared__ ExactShared sh;
   __shared__ float wave_mx[kWavesPerBlock];
-  if constexpr (!kCount) {
+  if constexpr (kSearch) {
     exact_shared_init(sh);
     __syncthreads();
   }
@@ -209,28 +323,11 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
   ExactAcc acc{0.0, 0.0, 0u};
   float mx = 0.0f;
   if (p.begin != p.end) {
-    const float thr = kCount ? *as_global(A.thresholds + l) : 0.0f;
-    uint32_t cnt = 0u;                      // kCount: elements above the threshold so far, the same in every lane
+    const float thr = kSearch ? A.moments[l].listed_above : *as_global(A.thresholds + l);
+    uint32_t cnt = 0u;                      // elements above it so far, the same in every lane
     const gptr<vu2> slot = as_global(reinterpret_cast<vu2*>(A.slots + static_cast<size_t>(p.wc) * A.cap));
     auto take = [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
-      if constexpr (kCount) {
-        // the elements above the threshold go to the wave-chunk's list in index order (ballot ranks);
-        // a list that is full only counts on, and the emit pass reads that wave-chunk from V instead
-        bool f[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f[j] = static_cast<uint32_t>(j) < nvalid && fabsf(a[j]) > thr;
-        const unsigned long long m0 = __ballot(f[0]), m1 = __ballot(f[1]), m2 = __ballot(f[2]), m3 = __ballot(f[3]);
-        if ((m0 | m1 | m2 | m3) == 0ull) return;
-        uint32_t pos = cnt + rank_below(m0) + rank_below(m1) + rank_below(m2) + rank_below(m3);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (f[j]) {
-            if (pos < A.cap) slot[pos] = vu2{fbits(a[j]), idx0 + static_cast<uint32_t>(j)};
-            ++pos;
-          }
-        }
-        cnt += popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
-      } else {
+      if constexpr (kSearch) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (static_cast<uint32_t>(j) < nvalid) {
@@ -240,6 +337,22 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
           }
         }
       }
+      // the elements above the magnitude go to the wave-chunk's list in index order (ballot ranks);
+      // a list that is full only counts on, and the later passes read that wave-chunk (or layer) from V instead
+      bool f[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = static_cast<uint32_t>(j) < nvalid && fabsf(a[j]) > thr;
+      const unsigned long long m0 = __ballot(f[0]), m1 = __ballot(f[1]), m2 = __ballot(f[2]), m3 = __ballot(f[3]);
+      if ((m0 | m1 | m2 | m3) == 0ull) return;
+      uint32_t pos = cnt + rank_below(m0) + rank_below(m1) + rank_below(m2) + rank_below(m3);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (f[j]) {
+          if (pos < A.cap) slot[pos] = vu2{fbits(a[j]), idx0 + static_cast<uint32_t>(j)};
+          ++pos;
+        }
+      }
+      cnt += popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
     };
     AccumRule rule;
     rule.m = A.m;
@@ -247,14 +360,12 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
     if (L.mom == nullptr) accumulate_groups<kNt, false, false>(L, p.begin, p.end, rule, take);
     else if (!A.nesterov) accumulate_groups<kNt, true, false>(L, p.begin, p.end, rule, take);
     else accumulate_groups<kNt, true, true>(L, p.begin, p.end, rule, take);
-    if constexpr (kCount) {
-      if (lane_id() == 0u) {
-        A.counts[p.wc] = cnt;
-        A.listed[p.wc] = cnt;
-      }
+    if (lane_id() == 0u) {
+      A.counts[p.wc] = cnt;
+      A.listed[p.wc] = cnt;
     }
   }
-  if constexpr (!kCount) {
+  if constexpr (kSearch) {
     const float m = wave_max(mx);
     if (lane_id() == 0u) wave_mx[threadIdx.x >> 6] = m;
     const ExactAcc total = exact_block_total(acc, sh);      // its barriers also order wave_mx
@@ -274,6 +385,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
 __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(ThresholdArgs A) {
   __shared__ ExactShared sh;
   __shared__ float redm[kBlockThreads];
+  __shared__ uint32_t scan[kWavesPerBlock];
   exact_shared_init(sh);
   __syncthreads();
   const uint32_t l = blockIdx.x;
@@ -282,6 +394,19 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(Thresh
   float mx = 0.0f;
   exact_take_parts(acc, A.sum_parts, L.wg_first, L.wg_count, sh);
   for (uint32_t i = threadIdx.x; i < L.wg_count; i += kBlockThreads) mx = fmaxf(mx, A.part_max[L.wg_first + i]);
+  // what the lists hold: all of them complete, and 2k elements or more together
+  uint32_t listed = 0u, bad = 0u;
+  constexpr uint32_t kItems = 8;          // independent loads in flight per thread
+  for (uint32_t base = threadIdx.x; base < L.wc_count; base += kItems * kBlockThreads) {
+    uint32_t v[kItems];
+#pragma unroll
+    for (uint32_t j = 0; j < kItems; ++j) v[j] = base + j * kBlockThreads < L.wc_count ? A.listed[L.wc_first + base + j * kBlockThreads] : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < kItems; ++j) { bad |= v[j] > A.cap ? 1u : 0u; listed += v[j]; }
+  }
+  uint32_t listed_all;
+  (void)block_excl_scan(listed, scan, listed_all);
+  bad = __syncthreads_or(static_cast<int>(bad)) ? 1u : 0u;
   redm[threadIdx.x] = mx;
   const double sum = exact_finish(acc, sh);                 // holds barriers
   for (uint32_t step = kBlockThreads / 2u; step >= 1u; step >>= 1) {
@@ -294,6 +419,8 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(Thresh
     M.max = redm[0];
     M.span = __fsub_rn(M.max, M.mean);
     M.counts_taken = 0u;
+    M.listed_above = A.moments[l].listed_above;
+    M.lists = !bad && listed_all >= 2u * L.k ? 1u : 0u;     // (k <= 2^30)
     A.moments[l] = M;
   }
   uint32_t* hist = A.hist + static_cast<size_t>(l) * kHistBins;
@@ -313,7 +440,12 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_histogram_kernel(Thre
   const ThresholdMoments M = A.moments[l];
   const float inv = M.span > 0.0f ? static_cast<float>(kSteps) / M.span : 0.0f;
   uint32_t below = 0u;     // bin 0 is by far the fullest: counted in a register
-  read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
+  if (M.lists) for_listed(A, p, [&](const vu2& e, bool in) {
+    const uint32_t b = in ? bin_of(fabsf(__uint_as_float(e.x)), M.mean, M.span, inv) : 0u;
+    if (b != 0u) atomicAdd(&lds_hist[b], 1u);
+    else below += in ? 1u : 0u;
+  });
+  else read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (static_cast<uint32_t>(j) < nvalid) {
@@ -380,6 +512,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_search_kernel(Thresho
     }
     *as_global(A.thresholds + l) = thr;
     A.moments[l].counts_taken = counts;
+    if (M.lists && thr < M.listed_above) A.moments[l].lists = 0u;   // (the lists know that 2k or more exceed it, not which)
   }
 }
 
@@ -393,7 +526,8 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_count_kernel(Threshol
   if (p.begin == p.end) return;
   const float thr = *as_global(A.thresholds + l);
   uint32_t cnt = 0u;
-  read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
+  if (A.moments[l].lists) for_listed(A, p, [&](const vu2& e, bool in) { cnt += in && fabsf(__uint_as_float(e.x)) > thr ? 1u : 0u; });
+  else read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) cnt += (static_cast<uint32_t>(j) < nvalid && fabsf(a[j]) > thr) ? 1u : 0u;
   });
@@ -433,9 +567,9 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_offsets_kernel(Thresh
   }
 }
 
-// kLists: the accumulate pass of this call left the elements above the threshold in the wave-chunk
+// The accumulate pass of this call left the elements above the threshold (kSearch: those and others) in the wave-chunk
 // lists; a wave-chunk whose list holds them all is written from it, without another look at V.
-template <bool kReverse, bool kLists>
+template <bool kReverse, bool kSearch>
 __global__ void __launch_bounds__(kBlockThreads) threshold_emit_kernel(ThresholdArgs A) {
   const uint32_t wg = (kReverse != (A.reverse != 0u)) ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
@@ -450,22 +584,21 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_emit_kernel(Threshold
   const gptr<float> out_val = as_global(L.out_val);
   const gptr<float> resid = as_global(L.resid);
   const gptr<float> mom = as_global(L.mom);
-  if constexpr (kLists) {
-    const uint32_t listed = A.listed[p.wc];
-    if (listed <= A.cap) {
-      const gptr<const vu2> slot = as_global(reinterpret_cast<const vu2*>(A.slots + static_cast<size_t>(p.wc) * A.cap));
-      for (uint32_t i = lane_id(); i < listed; i += kWaveSize) {
-        const uint32_t pos = out_pos + i;
-        if (pos < cap) {
-          const vu2 e = slot[i];
-          out_idx[pos] = static_cast<int32_t>(e.y);
-          out_val[pos] = __uint_as_float(e.x);
-          mask_store(resid + e.y);
-          if (clear_mom) mask_store(mom + e.y);
-        }
+  if (kSearch ? A.moments[l].lists != 0u : A.listed[p.wc] <= A.cap) {
+    const float above = *as_global(A.thresholds + l);
+    for_listed(A, p, [&](const vu2& e, bool in) {
+      const bool sel = in && fabsf(__uint_as_float(e.x)) > above;
+      const unsigned long long m = __ballot(sel);
+      const uint32_t pos = out_pos + rank_below(m);
+      if (sel && pos < cap) {
+        out_idx[pos] = static_cast<int32_t>(e.y);
+        out_val[pos] = __uint_as_float(e.x);
+        mask_store(resid + e.y);
+        if (clear_mom) mask_store(mom + e.y);
       }
-      return;
-    }
+      out_pos += popc64(m);
+    });
+    return;
   }
   const float thr = *as_global(A.thresholds + l);
   read_groups(L.resid, p.begin, p.end, [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
@@ -497,7 +630,10 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
   // Each pass over the tensors runs against the direction of the one before it: what that one touched last
   // (still in the memory-side cache) is read first.  a.reverse turns the whole sequence round.
   if (a.search) {
-    hipLaunchKernelGGL((threshold_accumulate_kernel<false, false, false>), dim3(num_wgs), block, 0, s, a);
+    hipLaunchKernelGGL(threshold_sample_kernel, dim3(num_layers), dim3(kSampleThreads), 0, s, a);
+    RGC_LAUNCHED();
+    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, true, false>), dim3(num_wgs), block, 0, s, a);
+    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, true, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_moments_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
@@ -509,14 +645,14 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
-    hipLaunchKernelGGL((threshold_emit_kernel<true, false>), dim3(num_wgs), block, 0, s, a);
+    hipLaunchKernelGGL((threshold_emit_kernel<true, true>), dim3(num_wgs), block, 0, s, a);
   } else {
-    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, true, false>), dim3(num_wgs), block, 0, s, a);
-    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, true, false>), dim3(num_wgs), block, 0, s, a);
+    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, false, false>), dim3(num_wgs), block, 0, s, a);
+    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, false, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
-    hipLaunchKernelGGL((threshold_emit_kernel<true, true>), dim3(num_wgs), block, 0, s, a);
+    hipLaunchKernelGGL((threshold_emit_kernel<true, false>), dim3(num_wgs), block, 0, s, a);
   }
 #undef RGC_LAUNCHED
   return hipGetLastError();

@@ -1,0 +1,57 @@
+"""GPU parity of a searching threshold call where its lists do, and where they do not: layers at the sizes and densities
+where the sample changes, values that fill single lists, sparse layers, searches that end below what was listed (bit equality)."""
+import numpy as np
+import pytest
+
+from test_gpu_threshold import Runner
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rgc():
+    import paper_1808_04357_amd as m
+    return m
+
+
+@pytest.mark.parametrize("ppm", [100, 1000, 7000, 9000, 100_000])
+@pytest.mark.parametrize("momentum,nesterov", [(False, False), (True, False), (True, True)])
+def test_densities_and_sample_sizes(rgc, oracle, ppm, momentum, nesterov):
+    g = np.random.default_rng(ppm)
+    sizes = [3, 4095, 16383, 16385, 65_537, 1_000_003]
+    ks = [rgc.rgc_k_for_density(n, ppm) for n in sizes]
+    V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    U = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] if momentum else None
+    r = Runner(rgc, oracle, V, ks, U0=U, m=0.9, misalign=1, tag="threshold lists")
+    for t in range(3):
+        r.step([(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes], search=t != 1, nesterov=nesterov,
+               grad_scale=0.5 if t == 2 else None)
+    r.close()
+
+
+@pytest.mark.parametrize("law", ["clustered", "row sparse", "nearly all zero", "two levels", "uniform", "one outlier"])
+def test_layers_whose_lists_may_not_do(rgc, oracle, law):
+    g = np.random.default_rng(17)
+    n = 600_000
+    k = rgc.rgc_k_for_density(n)
+
+    def draw(s):
+        a = (g.standard_normal(n) * s).astype(np.float32)
+        if law == "clustered":
+            a *= np.where((np.arange(n) > 50_000) & (np.arange(n) < 53_000), np.float32(100.0), np.float32(1.0))
+        elif law == "row sparse":
+            a.reshape(400, 1500)[g.permutation(400)[:380]] = 0.0
+        elif law == "nearly all zero":
+            a[g.permutation(n)[k // 2:]] = 0.0
+        elif law == "two levels":
+            a = np.where(g.random(n) < 0.003, np.float32(1.0), np.float32(0.25)).astype(np.float32) * np.float32(s)
+        elif law == "uniform":
+            a = (g.random(n) * s).astype(np.float32)
+        else:
+            a[7] = 1e4                                           # every threshold tried lies far above the others
+        return a
+
+    r = Runner(rgc, oracle, [draw(1.0), (g.standard_normal(200_000)).astype(np.float32)], [k, 200], tag="threshold " + law)
+    for t in range(3):
+        r.step([draw(0.05), (g.standard_normal(200_000) * 0.1).astype(np.float32)], search=True)
+    r.close()
