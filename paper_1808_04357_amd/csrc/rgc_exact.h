@@ -229,9 +229,15 @@ __device__ __forceinline__ double exact_finish(const ExactPair& mine, ExactShare
   const ExactAcc errs = exact_block_total(mine.errs, sh);
   ExactAcc sums = exact_block_total(mine.sums, sh);
   if (threadIdx.x != 0u) return 0.0;
-  if (errs.s != 0.0) exact_spill(errs.s, sh.digits);
-  if (errs.c != 0.0) exact_spill(errs.c, sh.digits);
+  double e, f;
+  two_sum(sums.c, errs.s, e, f);
+  sums.c = e;
   sums.flags |= errs.flags;
+  if (f != 0.0 || errs.c != 0.0) {
+    if (f != 0.0) exact_spill(f, sh.digits);
+    if (errs.c != 0.0) exact_spill(errs.c, sh.digits);
+    sums.flags |= kExactSpilled;
+  }
   return exact_round(sums, sh);
 }
 
@@ -240,6 +246,9 @@ __device__ __forceinline__ double exact_round(const ExactAcc& total, ExactShared
   if ((f & kExactNaN) || ((f & kExactPosInf) && (f & kExactNegInf))) return __longlong_as_double(0x7FF8000000000000ll);
   if (f & kExactPosInf) return __longlong_as_double(0x7FF0000000000000ll);
   if (f & kExactNegInf) return __longlong_as_double(static_cast<long long>(0xFFF0000000000000ull));
+  // Nothing in the digits: the sum is two doubles, and their addition rounds it once.  (Nearly every sum ends here; the walks
+  // through the digits below are chains of LDS round trips: threshold_moments_kernel 9.5 -> 7.8 us on the LSTM set.)
+  if (f == 0u && total.s != 0.0) return total.s + total.c;
   long long* dg = sh.digits;
   if (total.s != 0.0) exact_spill(total.s, dg);
   if (total.c != 0.0) exact_spill(total.c, dg);
