@@ -3,23 +3,23 @@
 //   magnitude (Section 2.1 defines the communication-set as the top 0.1 % of each layer),
 //   packing into (index, value) messages (Sections 2.2 / 2.3) and masking of the residual.
 //
-// Work decomposition: a layer is cut into wave-chunks of `chunk` consecutive elements; one
-// wave64 owns one wave-chunk, four waves form a workgroup, all layers of a call share one
-// launch (workgroup -> layer through a table).  A wave keeps everything it emits in ascending
-// index order using ballot + popcount ranks, so every list below is ordered without a sort.
+// Work decomposition: a layer is cut into wave-chunks of consecutive elements; one wave64 owns one wave-chunk, four waves form a
+// workgroup, all layers of a call share one launch (workgroup -> layer through a table).  A wave keeps everything it emits in
+// ascending index order using ballot + popcount ranks, so every list below is ordered without a sort.
 //
-// Two ways to the same result:
-//  * hinted, one pass over G/V: the streaming pass appends every element whose magnitude key
-//    is >= a cached threshold tau to its wave-chunk's candidate list and counts candidates in
-//    a coarse histogram of (key - tau).  If at least k candidates were seen and no list
-//    overflowed, the exact k-th key is found among the candidates (PH_SEL) and the message is
-//    written from the lists (PH_OUT_C).  tau only decides speed: a bad tau is detected and the
-//    layer falls back to
-//  * multi-pass radix select: three histogram passes over 12+12+7 key bits give the exact
-//    k-th key T and the number r of admitted ties, a counting pass and an ordered-compaction
-//    pass write the message (lowest indices win among keys equal to T).
-// Per layer decisions are taken by the last workgroup of the layer to finish a phase (a two-level
-// election with device-scope atomic counters; what it reads was written with device-scope stores, so no
+// Four ways to the same result:
+//  * tiled calls (tile_kernel and what follows it): one pass over G/V that lists, tile by tile, the elements whose magnitude key
+//    is >= a cached threshold tau; the exact k-th key is found among them.  Layers of up to 2^15 elements need no tau.
+//    Every layer of the call must be of one of these two kinds;
+//  * hinted, in calls with dense layers: the same lists from accumulate_kernel's looping waves, with a coarse histogram of
+//    (key - tau), ranked by PH_SEL and written by PH_OUT_C;
+//  * dense layers (warm-up densities) with a tau: collect_kernel and lists_kernel;
+//  * multi-pass radix select, without tau: three histogram passes over 12+12+7 key bits give the exact k-th key T and the
+//    number r of admitted ties, a counting pass and an ordered-compaction pass write the message (lowest indices win among
+//    keys equal to T).
+// tau only decides speed: a call notices a bad one (fewer than k candidates, a list overflow) and the layer falls back to the
+// last way on the updated residual.  In the general launches the last workgroup of the layer to finish a phase decides for the
+// layer (a two-level election with device-scope atomic counters; what it reads was written with device-scope stores, so no
 // fence, no host round trip and no spinning is needed).
 #include "rgc_exact.h"
 
@@ -1977,8 +1977,8 @@ __global__ void __launch_bounds__(kFinishThreads) emit_kernel(CompressArgs A) {
 }
 
 // The last launch of a call that uses hints: the launches A.late_first .. A.late_last in one, for the layers whose hint
-// missed (a tiled call hands it the general tiling).  Nothing is due in steady state, and one launch that finds that out is cheaper than three (VGG16 set: 571 us per
-// call with three, 565 us with one).
+// missed (a tiled call hands it the general tiling).  Nothing is due in steady state, and one launch that finds that out is
+// cheaper than three (VGG16 set: 571 us per call with three, 565 us with one).
 // Otherwise a grid of one workgroup per CU takes the workgroup numbers in turn, with a barrier over the grid between two
 // launch numbers: its release and acquire make plain stores visible across the XCDs, as a kernel boundary would.
 // The workgroups (256 threads, 17 KB of LDS) all fit on the device at once beside three more such kernels; the wait at the

@@ -219,12 +219,28 @@ struct ThresholdArgs {
   ThresholdMoments* moments;  // [layers]
   uint32_t chunk;           // elements per wave-chunk
   uint32_t search;          // 1: Algorithm 3 finds the thresholds; 0: they are given
-  uint32_t past_cache;      // a single-pass call reads and writes residual and velocity past the memory-side cache
+  uint32_t sampled;         // searching call: a sample says what the streaming pass lists (0: it lists nothing)
+  uint32_t past_cache;      // the first pass reads and writes residual and velocity past the memory-side cache
   uint32_t reverse;         // the first pass takes its workgroups in descending order (and every pass after it the other way)
   uint32_t mask_momentum;
   uint32_t nesterov;
   float m;
 };
+
+// The sample of a searching threshold call: kPieceElems elements from each of up to kSampleThreads places of a layer, and the
+// magnitude that threshold_sample_rank() of them exceed.  Lists hold one element in 16 and single ones several times the
+// average: layers with a larger share above that magnitude are not listed.
+constexpr uint32_t kSampleThreads = 1024, kPieceElems = 16;
+constexpr uint32_t threshold_sample_pieces(uint32_t n) {
+  return (n + (kPieceElems - 1u)) / kPieceElems < kSampleThreads ? (n + (kPieceElems - 1u)) / kPieceElems : kSampleThreads;
+}
+constexpr uint64_t threshold_sample_rank(uint32_t n, uint32_t k) {
+  return (4ull * k * kPieceElems * threshold_sample_pieces(n) + n - 1u) / n + 24u;
+}
+constexpr bool threshold_listable(uint32_t n, uint32_t k) {
+  const uint64_t samples = static_cast<uint64_t>(kPieceElems) * threshold_sample_pieces(n);
+  return 2ull * (4ull * k + 24ull * n / samples) <= n / 16u && threshold_sample_rank(n, k) <= samples;
+}
 
 hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, uint32_t num_layers, hipStream_t s);
 

@@ -218,7 +218,6 @@ __device__ __forceinline__ float wave_max(float x) {
 // Speed only: a magnitude that turns out too high or too low costs further passes, not the result.  (Scattered cache lines
 // are what one workgroup waits for: 4096 pieces of four elements took 23 us on the LSTM set, these 14.5 us; counting only the
 // samples above a bound, a fraction of the LDS atomics, changed nothing.)
-constexpr uint32_t kSampleThreads = 1024, kPieceElems = 16;
 __global__ void __launch_bounds__(kSampleThreads) threshold_sample_kernel(ThresholdArgs A) {
   __shared__ uint32_t hist[kHistBins];
   __shared__ uint32_t scan[kSampleThreads / kWaveSize];
@@ -226,12 +225,9 @@ __global__ void __launch_bounds__(kSampleThreads) threshold_sample_kernel(Thresh
   const uint32_t l = blockIdx.x, t = threadIdx.x;
   const LayerDesc L = A.layers[l];
   const uint32_t groups = (L.n + kPieceElems - 1u) / kPieceElems;
-  const uint32_t pieces = groups < kSampleThreads ? groups : kSampleThreads;
-  const unsigned long long samples = static_cast<unsigned long long>(kPieceElems) * pieces;
-  // rank of the magnitude in the sample, and how many elements of the layer that stands for: lists hold one in 16, and
-  // single ones several times the average
-  const unsigned long long rank = (4ull * L.k * samples + L.n - 1u) / L.n + 24u;
-  const bool listable = 2ull * (4ull * L.k + 24ull * L.n / samples) <= L.n / 16u && rank <= samples;
+  const uint32_t pieces = threshold_sample_pieces(L.n);
+  const unsigned long long rank = threshold_sample_rank(L.n, L.k);
+  const bool listable = threshold_listable(L.n, L.k);
   for (uint32_t b = t; b < static_cast<uint32_t>(kHistBins); b += kSampleThreads) hist[b] = 0u;
   if (t == 0u) found = 0xFFFFFFFFu;
   __syncthreads();
@@ -323,7 +319,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
   ExactAcc acc{0.0, 0.0, 0u};
   float mx = 0.0f;
   if (p.begin != p.end) {
-    const float thr = kSearch ? A.moments[l].listed_above : *as_global(A.thresholds + l);
+    const float thr = !kSearch ? *as_global(A.thresholds + l) : A.sampled ? A.moments[l].listed_above : __uint_as_float(0x7F800000u);
     uint32_t cnt = 0u;                      // elements above it so far, the same in every lane
     const gptr<vu2> slot = as_global(reinterpret_cast<vu2*>(A.slots + static_cast<size_t>(p.wc) * A.cap));
     auto take = [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
@@ -419,7 +415,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(Thresh
     M.max = redm[0];
     M.span = __fsub_rn(M.max, M.mean);
     M.counts_taken = 0u;
-    M.listed_above = A.moments[l].listed_above;
+    M.listed_above = A.sampled ? A.moments[l].listed_above : __uint_as_float(0x7F800000u);
     M.lists = !bad && listed_all >= 2u * L.k ? 1u : 0u;     // (k <= 2^30)
     A.moments[l] = M;
   }
@@ -630,8 +626,10 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
   // Each pass over the tensors runs against the direction of the one before it: what that one touched last
   // (still in the memory-side cache) is read first.  a.reverse turns the whole sequence round.
   if (a.search) {
-    hipLaunchKernelGGL(threshold_sample_kernel, dim3(num_layers), dim3(kSampleThreads), 0, s, a);
-    RGC_LAUNCHED();
+    if (a.sampled) {
+      hipLaunchKernelGGL(threshold_sample_kernel, dim3(num_layers), dim3(kSampleThreads), 0, s, a);
+      RGC_LAUNCHED();
+    }
     if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, true, false>), dim3(num_wgs), block, 0, s, a);
     else hipLaunchKernelGGL((threshold_accumulate_kernel<false, true, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();

@@ -14,23 +14,36 @@ def rgc():
     return m
 
 
+LINE = 8 << 20     # elements of a call from which it lists (kSampleElems)
+
+
+@pytest.fixture(scope="module")
+def filler():
+    """A layer that takes its call to the line: residual, gradient, velocity."""
+    g = np.random.default_rng(5)
+    return [(g.standard_normal(LINE, dtype=np.float32) * np.float32(s)) for s in (5e-3, 1e-3, 1e-3)]
+
+
 @pytest.mark.parametrize("ppm", [100, 1000, 7000, 9000, 100_000])
 @pytest.mark.parametrize("momentum,nesterov", [(False, False), (True, False), (True, True)])
-def test_densities_and_sample_sizes(rgc, oracle, ppm, momentum, nesterov):
+def test_densities_and_sample_sizes(rgc, oracle, filler, ppm, momentum, nesterov):
     g = np.random.default_rng(ppm)
     sizes = [3, 4095, 16383, 16385, 65_537, 1_000_003]
     ks = [rgc.rgc_k_for_density(n, ppm) for n in sizes]
     V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
-    U = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] if momentum else None
+    U = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] + [filler[2]] if momentum else None
+    V.append(filler[0])
+    ks.append(rgc.rgc_k_for_density(LINE, 1000))
     r = Runner(rgc, oracle, V, ks, U0=U, m=0.9, misalign=1, tag="threshold lists")
     for t in range(3):
-        r.step([(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes], search=t != 1, nesterov=nesterov,
+        r.step([(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] + [filler[1]], search=t != 1, nesterov=nesterov,
                grad_scale=0.5 if t == 2 else None)
     r.close()
 
 
+@pytest.mark.parametrize("listed", [True, False])
 @pytest.mark.parametrize("law", ["clustered", "row sparse", "nearly all zero", "two levels", "uniform", "one outlier"])
-def test_layers_whose_lists_may_not_do(rgc, oracle, law):
+def test_layers_whose_lists_may_not_do(rgc, oracle, filler, law, listed):
     g = np.random.default_rng(17)
     n = 600_000
     k = rgc.rgc_k_for_density(n)
@@ -51,7 +64,9 @@ def test_layers_whose_lists_may_not_do(rgc, oracle, law):
             a[7] = 1e4                                           # every threshold tried lies far above the others
         return a
 
-    r = Runner(rgc, oracle, [draw(1.0), (g.standard_normal(200_000)).astype(np.float32)], [k, 200], tag="threshold " + law)
+    more = LINE if listed else LINE - n - 200_000 - 1           # at the line, and one element below it
+    V = [draw(1.0), g.standard_normal(200_000).astype(np.float32), filler[0][:more]]
+    r = Runner(rgc, oracle, V, [k, 200, more // 1000], tag="threshold " + law)
     for t in range(3):
-        r.step([draw(0.05), (g.standard_normal(200_000) * 0.1).astype(np.float32)], search=True)
+        r.step([draw(0.05), (g.standard_normal(200_000) * 0.1).astype(np.float32), filler[1][:more]], search=True)
     r.close()
