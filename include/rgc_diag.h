@@ -30,7 +30,8 @@ int rgc_limit_optional_scratch(rgc_ctx* ctx, int64_t max_bytes);
 int rgc_selftest(rgc_ctx* ctx, void* hip_stream);
 
 /* Copies per-layer path statistics of the LAST compression call into `out` (host memory,
- * int32[num_layers]): 0 = one-pass hinted path, 1 = hint-free multi-pass path, 2 = hinted
+ * int32[num_layers]): 0 = one-pass hinted path, 1 = without a hint (multi-pass path, or a layer
+ * of at most 32768 elements ended by one workgroup), 2 = hinted
  * pass missed and the multi-pass path re-ran on the updated residual.  Synchronises
  * `hip_stream`.  Returns RGC_EINTERNAL if any kernel of an earlier call flagged an internal
  * inconsistency.  A diagnostic for tests and benchmarks. */
@@ -46,7 +47,7 @@ int rgc_last_stats(rgc_ctx* ctx, int64_t* out, int32_t num_layers, void* hip_str
  * decompression call record HIP events on the caller's stream around its kernels (a few extra
  * microseconds per call); rgc_profile_enable(ctx, 0) stops that.  rgc_profile_read synchronises
  * the recorded events and returns, summed over the calls since the last read, the milliseconds
- * spent in  out_ms[0] the streaming accumulate kernel, out_ms[1] the phase launches after it,
+ * spent in  out_ms[0] the streaming pass, out_ms[1] the selection and message launches after it,
  * out_ms[2] the decompression table kernel, out_ms[3] the decompression tile kernel, and the
  * number of compression / decompression calls in out_calls[0..1].  The record is then cleared. */
 int rgc_profile_enable(rgc_ctx* ctx, int enable);
