@@ -22,6 +22,7 @@
 // layer (a two-level election with device-scope atomic counters; what it reads was written with device-scope stores, so no
 // fence, no host round trip and no spinning is needed).
 #include "rgc_exact.h"
+#include "rgc_tickets.h"
 
 #include <mutex>
 
@@ -356,6 +357,7 @@ struct ResolveShared {
   uint32_t bin, above, cnt;     // bin holding the k-th key, keys above it, keys in it
   uint32_t hbin, hcum, hcnt;    // bin where the cumulative count reaches the hint's target rank
   uint32_t bad;
+  uint32_t publish;             // fallback_kernel: what a layer's last workgroup of a pass has to publish
 };
 
 // Copy a (possibly replicated) global histogram into LDS, summing the replicas, and clear the
@@ -425,9 +427,16 @@ __device__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t
   return total;
 }
 
-// The layer's next phase runs at this launch number; fallback_kernel is told if that is the first of those it stands for.
-__device__ __forceinline__ void schedule_launch(const CompressArgs& A, LayerState* st, uint32_t launch) {
-  st->next_launch = launch;
+// Whether this code runs in fallback_kernel, where no kernel boundary lies between a layer's phases.
+__device__ __forceinline__ bool in_fallback(const CompressArgs& A) { return A.late_first != 0u && A.launch >= A.late_first; }
+
+// The layer's next phase runs at this launch number (`last`: and is its last); fallback_kernel is told if that is the first of
+// those it stands for.  Inside fallback_kernel the number is published once everything the phase needs is visible.
+__device__ __forceinline__ void schedule_launch(const CompressArgs& A, LayerState* st, ResolveShared& sh, uint32_t launch,
+                                                bool last = false) {
+  const uint32_t word = launch | (last && A.late_first != 0u && launch >= A.late_first ? kLastPass : 0u);
+  if (in_fallback(A)) { sh.publish = word; return; }
+  st->next_launch = word;
   if (launch == A.late_first) st_agent(A.late, 1u);
 }
 
@@ -436,7 +445,7 @@ __device__ __forceinline__ void schedule_launch(const CompressArgs& A, LayerStat
 // the next call on the way, clear the histogram, schedule the next phase.
 // `lds` holds the bins of this level (kHistBins words, 128 at the last level) and is free for use.
 template <int kLevel>
-__device__ void resolve_digit(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st,
+__device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st,
                               ResolveShared& sh, uint32_t* lds, uint32_t cur_launch) {
   constexpr uint32_t kBins = (kLevel == 3) ? 256u : static_cast<uint32_t>(kHistBins);   // the last digit has 7 or 8 bits
   const uint32_t low = low_bits_of(A.sign_filter);
@@ -526,7 +535,7 @@ __device__ void resolve_digit(const CompressArgs& A, uint32_t l, const LayerDesc
       }
     }
     st->hint_pending = pend;
-    schedule_launch(A, st, cur_launch + 1u);
+    schedule_launch(A, st, sh, cur_launch + 1u);
   }
 }
 
@@ -546,7 +555,7 @@ __device__ __forceinline__ void dense_missed(LayerState* st) {
 // `dense`: the lists are those of a dense layer's streaming pass (collect_kernel), which has already masked the
 // candidates of the coarse bins from the layer's clip bin upwards: the k-th key must lie below that bin, and
 // should it not, or should anything else be off, those entries are put back first (PH_RESTORE).
-__device__ void resolve_collect(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st,
+__device__ __forceinline__ void resolve_collect(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st,
                                 ResolveShared& sh, uint32_t* lds, bool after_first_digit, uint32_t cur_launch,
                                 bool dense = false) {
   const uint32_t t = threadIdx.x;
@@ -604,14 +613,14 @@ __device__ void resolve_collect(const CompressArgs& A, uint32_t l, const LayerDe
       st->stat_misses += 1u;
       st->next_phase = PH_HIST1;
     }
-    schedule_launch(A, st, cur_launch + 1u);
+    schedule_launch(A, st, sh, cur_launch + 1u);
   }
 }
 
 // In-place exclusive scan over the per wave-chunk counters of one layer (one workgroup).
 // with_ties: a[] = keys > T, b[] = keys == T  ->  a[] = output offset of the chunk
 //            (= prefix(a) + min(prefix(b), r)), b[] = prefix(b).
-__device__ void scan_chunks(uint32_t* a, uint32_t* b, uint32_t count, uint32_t r, bool with_ties,
+__device__ __forceinline__ void scan_chunks(uint32_t* a, uint32_t* b, uint32_t count, uint32_t r, bool with_ties,
                             uint32_t* lds_scan, uint32_t* out_total) {
   constexpr uint32_t kItems = 16;   // many independent device-scope loads in flight per thread: this is a serial step
   uint32_t carry_a = 0, carry_b = 0;
@@ -810,7 +819,7 @@ namespace {
 // (keys from the expected k-th key upwards) get their accumulated value and their velocity back from the wave-chunk's
 // list; V and u are then exactly what an ordinary streaming pass leaves.  The wave goes on to the first digit's
 // histogram of the same wave-chunk at once (phase_hist<1>), which reads what it has just written.
-__device__ void dense_restore(const CompressArgs& A, const LayerDesc& L, const LayerState* st, uint32_t wc_local) {
+__device__ __forceinline__ void dense_restore(const CompressArgs& A, const LayerDesc& L, const LayerState* st, uint32_t wc_local) {
   if (wc_local < L.wc_count) {
     const uint32_t mask_key = st->cur_mask_key;
     const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
@@ -834,7 +843,7 @@ __device__ void dense_restore(const CompressArgs& A, const LayerDesc& L, const L
 }
 
 template <int kLevel>
-__device__ void phase_hist(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
+__device__ __forceinline__ void phase_hist(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                            uint32_t wc_local, uint32_t* lds_hist, ResolveShared& sh) {
   constexpr uint32_t kBins = (kLevel == 3) ? 256u : static_cast<uint32_t>(kHistBins);
   for (uint32_t b = threadIdx.x; b < kBins; b += kBlockThreads) lds_hist[b] = 0u;
@@ -867,11 +876,11 @@ __device__ void phase_hist(const CompressArgs& A, uint32_t l, const LayerDesc& L
   }
   __syncthreads();
   flush_hist(lds_hist, A.hist + static_cast<size_t>(l) * kHistBins, kBins);
-  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag)) resolve_digit<kLevel>(A, l, L, st, sh, lds_hist, A.launch);
+  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag, in_fallback(A))) resolve_digit<kLevel>(A, l, L, st, sh, lds_hist, A.launch);
 }
 
 // PH_COLLECT: the streaming pass's candidate collection, from the updated residual (see resolve_digit<1>).
-__device__ void phase_collect(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
+__device__ __forceinline__ void phase_collect(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                               uint32_t wc_local, uint32_t* lds_hist, ResolveShared& sh) {
   for (uint32_t b = threadIdx.x; b < static_cast<uint32_t>(kCoarseBins); b += kBlockThreads) lds_hist[b] = 0u;
   __syncthreads();
@@ -901,7 +910,7 @@ __device__ void phase_collect(const CompressArgs& A, uint32_t l, const LayerDesc
     resolve_collect(A, l, L, st, sh, lds_hist, true, A.launch);
 }
 
-__device__ void phase_count(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
+__device__ __forceinline__ void phase_count(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                             uint32_t wc_local, ResolveShared& sh) {
   const uint32_t T = st->T;
   if (wc_local < L.wc_count) {
@@ -926,18 +935,18 @@ __device__ void phase_count(const CompressArgs& A, uint32_t l, const LayerDesc& 
       st_agent(&A.wc_b[L.wc_first + wc_local], eq_all);
     }
   }
-  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag)) {
+  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag, in_fallback(A))) {
     scan_chunks(A.wc_a + L.wc_first, A.wc_b + L.wc_first, L.wc_count, st->r, true, sh.scan, &sh.cnt);
     __syncthreads();
     if (threadIdx.x == 0) {
       if (sh.cnt != L.k) atomicOr(A.errflag, 2u);
       st->next_phase = PH_OUT_V;
-      schedule_launch(A, st, A.launch + 1u);
+      schedule_launch(A, st, sh, A.launch + 1u, true);
     }
   }
 }
 
-__device__ void phase_out_v(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wc_local) {
+__device__ __forceinline__ void phase_out_v(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wc_local) {
   if (wc_local >= L.wc_count) return;
   const uint32_t T = st->T, r = st->r;
   const uint32_t begin = wc_local * A.chunk;
@@ -995,7 +1004,7 @@ __device__ void phase_out_v(const CompressArgs& A, const LayerDesc& L, LayerStat
 // Hinted path: every wave looks at its own candidate list; candidates of the coarse bin that
 // holds the k-th key become "members" (ranked exactly by the last workgroup), candidates of
 // higher bins are counted as certainly selected.
-__device__ void phase_sel(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
+__device__ __forceinline__ void phase_sel(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                           unsigned long long* sortbuf, uint32_t* sel_hist, ResolveShared& sh) {
   // The lists are short (a few dozen entries), so this phase is a chain of dependent loads per
   // workgroup and little else: one workgroup in A.list_group takes the lists of that many
@@ -1127,11 +1136,11 @@ __device__ void phase_sel(const CompressArgs& A, uint32_t l, const LayerDesc& L,
     st->T = T;
     if (A.update_hints) next_hint(st, T, st->tau_next);
     st->next_phase = PH_OUT_C;
-    schedule_launch(A, st, A.launch + 1u);
+    schedule_launch(A, st, sh, A.launch + 1u, true);
   }
 }
 
-__device__ void phase_out_c(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wg) {
+__device__ __forceinline__ void phase_out_c(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wg) {
   const uint32_t wgl = wg - L.wg_first;
   const uint32_t group = A.list_group;              // (1 or kListGroup)
   if ((wgl & (group - 1u)) != 0u) return;           // see phase_sel
@@ -1769,13 +1778,13 @@ __device__ __forceinline__ uint32_t gather_lists(const CompressArgs& A, uint32_t
   return total;
 }
 
-__device__ __forceinline__ void hint_missed(const CompressArgs& A, LayerState* st, bool hinted, uint32_t total) {
+__device__ __forceinline__ void hint_missed(const CompressArgs& A, LayerState* st, ResolveShared& sh, bool hinted, uint32_t total) {
   st->path = hinted ? 2u : 1u;
   st->stat_misses += hinted ? 1u : 0u;
   st->stat_candidates = total;
   st->stat_members = 0u;
   st->next_phase = PH_HIST1;
-  schedule_launch(A, st, kTiledLateLaunch);
+  schedule_launch(A, st, sh, kTiledLateLaunch);
 }
 
 __device__ __forceinline__ void hint_hit(const CompressArgs& A, const LayerDesc& L, LayerState* st, unsigned long long thr, uint32_t tau,
@@ -1810,7 +1819,7 @@ __device__ __forceinline__ void finish_lists(const CompressArgs& A, const LayerD
     ok = S.sh.bin != 0xFFFFFFFFu && S.sh.cnt <= static_cast<uint32_t>(kMemberMax);
   }
   if (!ok) {
-    if (t == 0) hint_missed(A, st, hinted, total);
+    if (t == 0) hint_missed(A, st, S.sh, hinted, total);
     return;
   }
   const uint32_t bstar = S.sh.bin, above = S.sh.above, m = S.sh.cnt, hbin = S.sh.hbin;
@@ -1840,7 +1849,7 @@ __device__ __forceinline__ void select_part(const CompressArgs& A, uint32_t l, c
   const uint32_t t = threadIdx.x;
   const uint32_t parts = (L.wg_count + kPartTiles - 1u) / kPartTiles;
   if (!hint_usable(A, st)) {
-    if (part == 0u && t == 0) hint_missed(A, st, false, 0u);
+    if (part == 0u && t == 0) hint_missed(A, st, S.sh, false, 0u);
     return;
   }
   const uint32_t tau = st->tau, shift = st->shift, k = L.k;
@@ -1904,7 +1913,7 @@ __device__ __forceinline__ void select_part(const CompressArgs& A, uint32_t l, c
   }
   const uint32_t all = ld_agent(&st->nmembers);
   if (__syncthreads_or(static_cast<int>(bad)) != 0) {
-    if (t == 0) hint_missed(A, st, true, cand_total);
+    if (t == 0) hint_missed(A, st, S.sh, true, cand_total);
     return;
   }
   const uint32_t k_rem = k - above;
@@ -1979,59 +1988,81 @@ __global__ void __launch_bounds__(kFinishThreads) emit_kernel(CompressArgs A) {
 // The last launch of a call that uses hints: the launches A.late_first .. A.late_last in one, for the layers whose hint
 // missed (a tiled call hands it the general tiling).  Nothing is due in steady state, and one launch that finds that out is
 // cheaper than three (VGG16 set: 571 us per call with three, 565 us with one).
-// Otherwise a grid of one workgroup per CU takes the workgroup numbers in turn, with a barrier over the grid between two
-// launch numbers: its release and acquire make plain stores visible across the XCDs, as a kernel boundary would.
-// The workgroups (256 threads, 17 KB of LDS) all fit on the device at once beside three more such kernels; the wait at the
-// barrier is bounded all the same, and running out of it is reported as an internal error.
+// Otherwise its workgroups take tickets (rgc_tickets.h): a workgroup number whose layer has not got to this pass yet waits for the
+// layer, which publishes every pass with an agent-scope release that the waiting side acquires, as a kernel boundary would.
+// Waiting needs no other workgroup to be on the device than those that run, so it ends on any stream and beside any kernels.
 namespace {
 
-__device__ bool grid_barrier(uint32_t* word, uint32_t target, uint32_t* lds_flag) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    atomicAdd(word, 1u);
-    uint32_t spins = 0;
-    while (ld_agent(word) < target && spins < (1u << 23)) { __builtin_amdgcn_s_sleep(8); ++spins; }
-    *lds_flag = spins < (1u << 23) ? 1u : 0u;
-    __threadfence();
+constexpr uint32_t kWaitPolls = 1u << 23;   // seconds; a pass over a layer takes milliseconds at most
+
+struct FallbackWork {
+  CompressArgs& A;
+  uint32_t* hist;
+  ResolveShared& sh;
+  uint32_t* word;                           // in the LDS: what thread 0 has found out
+
+  __device__ __forceinline__ uint32_t take() {
+    if (threadIdx.x == 0) *word = atomicAdd(A.late + 1, 1u);
+    __syncthreads();
+    const uint32_t t = *word;
+    __syncthreads();
+    return t;
   }
-  __syncthreads();
-  const bool ok = *lds_flag != 0u;
-  __syncthreads();
-  return ok;
-}
+
+  __device__ __forceinline__ bool due(const LayerState* st, uint32_t launch) {
+    if (threadIdx.x == 0) {
+      Due d = due_at(ld_agent(&st->next_launch), launch, A.late_first);
+      for (uint32_t polls = 0; d == Due::kWait && polls < kWaitPolls; ++polls) {
+        __builtin_amdgcn_s_sleep(8);
+        d = due_at(ld_agent(&st->next_launch), launch, A.late_first);
+      }
+      if (d == Due::kWait) atomicOr(A.errflag, 512u);       // a layer that never published: a bug
+      if (d == Due::kRun && launch != A.late_first) __threadfence();
+      sh.publish = 0u;
+      *word = d == Due::kRun ? 1u : 0u;
+    }
+    __syncthreads();
+    const bool run = *word != 0u;
+    __syncthreads();
+    return run;
+  }
+
+  __device__ __forceinline__ void unit(uint32_t wg, uint32_t launch) {
+    const uint32_t l = A.wg2layer[wg];
+    LayerState* st = A.state + l;
+    if (!due(st, launch)) return;
+    A.launch = launch;
+    const LayerDesc L = A.layers[l];
+    const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
+    switch (st->next_phase) {
+      case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, hist, sh); break;
+      case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, hist, sh); break;
+      case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, hist, sh); break;
+      case PH_COUNT: phase_count(A, l, L, st, wg, wc_local, sh); break;
+      case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
+      case PH_OUT_C: phase_out_c(A, L, st, wg); break;
+      default:                                       // no other phase can be due this late
+        if (threadIdx.x == 0) { atomicOr(A.errflag, 16u); st_agent(&st->next_launch, 0u); }
+        break;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                 // (the next unit uses the same LDS)
+    if (threadIdx.x == 0 && sh.publish != 0u) {
+      __threadfence();
+      st_agent(&st->next_launch, sh.publish);
+    }
+  }
+};
 
 }  // namespace
 
-__global__ void __launch_bounds__(kBlockThreads) fallback_kernel(CompressArgs A, uint32_t num_wgs) {
+__global__ void __launch_bounds__(kBlockThreads) fallback_kernel(CompressArgs A, TicketOrder order) {
   __shared__ uint32_t hist[kHistBins];
   __shared__ ResolveShared sh;
+  __shared__ uint32_t word;
   if (ld_agent(A.late) == 0u) return;               // (all workgroups see the same: the word is reset by the last to leave)
-  for (uint32_t launch = A.late_first; launch <= A.late_last; ++launch) {
-    if (launch != A.late_first && !grid_barrier(A.late + 1, (launch - A.late_first) * gridDim.x, &sh.flag)) {
-      if (threadIdx.x == 0) atomicOr(A.errflag, 512u);
-      break;
-    }
-    A.launch = launch;
-    for (uint32_t wg = blockIdx.x; wg < num_wgs; wg += gridDim.x) {
-      const uint32_t l = A.wg2layer[wg];
-      LayerState* st = A.state + l;
-      if (st->next_launch != launch) continue;
-      const LayerDesc L = A.layers[l];
-      const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
-      switch (st->next_phase) {
-        case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, hist, sh); break;
-        case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, hist, sh); break;
-        case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, hist, sh); break;
-        case PH_COUNT: phase_count(A, l, L, st, wg, wc_local, sh); break;
-        case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
-        case PH_OUT_C: phase_out_c(A, L, st, wg); break;
-        default: if (threadIdx.x == 0) atomicOr(A.errflag, 16u); break;
-      }
-      __syncthreads();                               // the next workgroup number uses the same LDS
-    }
-  }
+  FallbackWork work{A, hist, sh, &word};
+  run_tickets(order, A.late_first, work);
   if (threadIdx.x == 0 && atomicAdd(A.late + 2, 1u) + 1u == gridDim.x) {
     st_agent(A.late + 1, 0u);
     st_agent(A.late + 2, 0u);
@@ -2581,7 +2612,7 @@ __device__ void dense_rank(const CompressArgs& A, uint32_t l, const LayerDesc& L
       st->has_prev = 1u;
     }
     st->next_phase = PH_EMIT;
-    schedule_launch(A, st, A.launch + 1u);
+    schedule_launch(A, st, sh, A.launch + 1u);
   }
 }
 
@@ -3006,7 +3037,8 @@ hipError_t launch_emit(const CompressArgs& a, uint32_t num_parts, hipStream_t s)
 }
 
 hipError_t launch_fallback(const CompressArgs& a, uint32_t num_wgs, uint32_t cus, hipStream_t s) {
-  hipLaunchKernelGGL(fallback_kernel, dim3(num_wgs < cus ? num_wgs : cus), dim3(kBlockThreads), 0, s, a, num_wgs);
+  const TicketOrder order = ticket_order(num_wgs, cus, a.late_last - a.late_first + 1u);
+  hipLaunchKernelGGL(fallback_kernel, dim3(order.slices), dim3(kBlockThreads), 0, s, a, order);
   return hipGetLastError();
 }
 

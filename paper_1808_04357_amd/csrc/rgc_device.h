@@ -96,10 +96,12 @@ __device__ __forceinline__ void st_agent(uint32_t* p, uint32_t v) {
 // kElectGroup consecutive workgroups, the last of a group counts the group into the layer's
 // counter.  Thousands of workgroups finishing a short phase together otherwise queue up on one
 // address (a same-address device atomic takes ~10-25 ns, i.e. ~100 us for 4000 workgroups).
+// `again_soon`: the counters are used again before the kernel ends (fallback_kernel): a group's reset has to have arrived before
+// the layer's last workgroup can be elected, which lets the next phase begin.
 constexpr uint32_t kElectGroup = 32;
 
 __device__ __forceinline__ bool last_block_of_layer(uint32_t* layer_done, uint32_t* group_done, uint32_t wg_in_layer,
-                                                    uint32_t wg_count, uint32_t* lds_flag) {
+                                                    uint32_t wg_count, uint32_t* lds_flag, bool again_soon = false) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -109,6 +111,7 @@ __device__ __forceinline__ bool last_block_of_layer(uint32_t* layer_done, uint32
     bool last = false;
     if (atomicAdd(&group_done[grp], 1u) + 1u == in_grp) {
       st_agent(&group_done[grp], 0u);
+      if (again_soon) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       if (atomicAdd(layer_done, 1u) + 1u == groups) {
         st_agent(layer_done, 0u);
         last = true;

@@ -104,7 +104,7 @@ struct LayerDesc {
 // rewritten by every call before it is read.
 struct LayerState {
   uint32_t next_phase;   // Phase to run ...
-  uint32_t next_launch;  // ... at this launch number (2..6)
+  uint32_t next_launch;  // ... at this launch number (general calls 2..6, tiled ones 3..8), in fallback_kernel's launches with kLastPass
   uint32_t done;         // workgroups of the layer that finished the current phase
   uint32_t prefix;       // multi-pass: key bits fixed so far (digits 1 and 2)
   uint32_t k_rem;        // rank of the k-th key inside the current bin (1-based)
@@ -178,9 +178,9 @@ struct CompressArgs {
   uint32_t update_hints;
   uint32_t mask_momentum;
   float m;
-  uint32_t launch;       // launch number of the phase kernel (2..6)
+  uint32_t launch;       // launch number of the kernel (1..6; in fallback_kernel the number of the launch it stands for)
   const uint2* parts;    // tiled calls: (layer, part of it) of every workgroup of select_kernel, those of the larger layers first
-  uint32_t* late;        // [3] fallback_kernel: layers are due, workgroups at the barrier, workgroups that have left
+  uint32_t* late;        // [3] fallback_kernel: layers are due, tickets taken, workgroups that have left
   uint32_t late_first;   // the launch numbers fallback_kernel stands for (0: they are launches of their own)
   uint32_t late_last;
   uint32_t sign_xor;     // selection key: see key_of() (0 / 0x80000000: which sign bit keeps an element in the ranking)

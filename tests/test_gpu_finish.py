@@ -165,3 +165,53 @@ def test_replayed_from_a_graph_with_misses(rgc, oracle):
                 assert 2 in ctx.last_paths(len(sizes), s)
     ctx.last_error(s)
     ctx.close()
+
+
+def test_missed_hints_on_several_streams_at_once(rgc, oracle):
+    """Six contexts, a thread and a stream each, all hints spoilt before every other call: the launches that put the missed
+    layers right run beside each other and share the device."""
+    import threading
+    import torch
+    sizes = [2_500_000, 300_000, 70_001, 4000]
+    ks = [rgc.rgc_k_for_density(n) for n in sizes]
+    steps, failed = 6, []
+    inputs = []
+    for c in range(6):
+        g = np.random.default_rng(100 + c)
+        inputs.append(([(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes],
+                       [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(steps)]))
+    contexts = [rgc.Context(sum(sizes), len(sizes)) for _ in inputs]
+    devs = []
+    for V0, _ in inputs:
+        devs.append(GpuLayers(rgc, V0, ks))
+    grads = [[[torch.from_numpy(g).cuda() for g in G] for G in Gs] for _, Gs in inputs]
+    torch.cuda.synchronize()
+
+    def work(c):
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                for t in range(steps):
+                    for l in range(len(sizes)):
+                        devs[c].G[l].copy_(grads[c][t][l])
+                    if t % 2:
+                        contexts[c].poison_hints(0, s)
+                    rgc.rgc_compress_layers(contexts[c], devs[c].layers, 0.0, 0, s)
+            s.synchronize()
+            contexts[c].last_error(s)
+            assert contexts[c].last_paths(len(sizes), s)[0] == 2
+        except Exception as e:                                  # noqa: BLE001 (told to the test's own thread)
+            failed.append((c, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(c,)) for c in range(len(inputs))]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not failed, failed
+    for c, (V0, Gs) in enumerate(inputs):
+        Vh = [v.copy() for v in V0]
+        for G in Gs:
+            msgs = oracle_step(oracle, G, Vh, ks, threads=8)
+        assert_layers_equal("context %d" % c, ks, devs[c].results(), msgs, Vh)
+        contexts[c].close()
