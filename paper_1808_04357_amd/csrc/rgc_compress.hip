@@ -249,13 +249,25 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
   }
 }
 
-// Read-only walk over one wave-chunk of the updated residual, four elements per lane per step,
-// same element order as the streaming pass.  f(a[4], nvalid, idx0) must be wave-uniform code.
+// Read-only walk over one wave-chunk of the updated residual, four elements per lane per step, same element order as the
+// streaming pass, whole groups four at a time.  f(a[4], nvalid, idx0) must be wave-uniform code.
 template <typename F>
 __device__ __forceinline__ void for_each_group(const float* generic_p, uint32_t begin, uint32_t end, F&& f) {
   const gptr<const float> p = as_global(generic_p);
   const uint32_t lane = lane_id();
-  for (uint32_t base = begin; base < end; base += kGroupElems) {
+  constexpr uint32_t kUnroll = 4u;
+  uint32_t base = begin;
+  for (; base + kUnroll * kGroupElems <= end; base += kUnroll * kGroupElems) {
+    vf4 q[kUnroll];
+#pragma unroll
+    for (uint32_t t = 0; t < kUnroll; ++t) q[t] = *as_vec(generic_p + base + t * kGroupElems + lane * 4u);
+#pragma unroll
+    for (uint32_t t = 0; t < kUnroll; ++t) {
+      const float a[4] = {q[t].x, q[t].y, q[t].z, q[t].w};
+      f(a, 4u, base + t * kGroupElems + lane * 4u);
+    }
+  }
+  for (; base < end; base += kGroupElems) {
     const uint32_t idx0 = base + lane * 4u;
     float a[4] = {0.f, 0.f, 0.f, 0.f};
     uint32_t nvalid;
@@ -385,7 +397,7 @@ __device__ __forceinline__ void stage_hist(uint32_t* g, uint32_t* lds) {
 #pragma unroll
         for (uint32_t rep = 0; rep < kReps; ++rep) {
           sum += v[i][rep];
-          g[rep * kBins + b] = 0u;
+          st_agent(&g[rep * kBins + b], 0u);
         }
         lds[b] = sum;
       }
@@ -427,11 +439,12 @@ __device__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t
   return total;
 }
 
-// Whether this code runs in fallback_kernel, where no kernel boundary lies between a layer's phases.
+// Whether this code runs in fallback_kernel, where no kernel boundary lies between a layer's phases: the digits, the counts and
+// what they leave in the layer's state and scratch are written with st_agent() and read with ld_agent() for its sake.
 __device__ __forceinline__ bool in_fallback(const CompressArgs& A) { return A.late_first != 0u && A.launch >= A.late_first; }
 
 // The layer's next phase runs at this launch number (`last`: and is its last); fallback_kernel is told if that is the first of
-// those it stands for.  Inside fallback_kernel the number is published once everything the phase needs is visible.
+// those it stands for.  Inside fallback_kernel the number is published once everything the phase needs has been written.
 __device__ __forceinline__ void schedule_launch(const CompressArgs& A, LayerState* st, ResolveShared& sh, uint32_t launch,
                                                 bool last = false) {
   const uint32_t word = launch | (last && A.late_first != 0u && launch >= A.late_first ? kLastPass : 0u);
@@ -449,13 +462,13 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
                               ResolveShared& sh, uint32_t* lds, uint32_t cur_launch) {
   constexpr uint32_t kBins = (kLevel == 3) ? 256u : static_cast<uint32_t>(kHistBins);   // the last digit has 7 or 8 bits
   const uint32_t low = low_bits_of(A.sign_filter);
-  const uint32_t k_rem = (kLevel == 1) ? L.k : st->k_rem;
+  const uint32_t k_rem = (kLevel == 1) ? L.k : ld_agent(&st->k_rem);
   const uint32_t above_scope = L.k - k_rem;          // keys above the current scope
   // The k entries selected now leave the residual, so the next call's top-k come from ranks
   // k+1.. of this call: aim the next threshold at rank 2k + margin.
   const uint32_t target = L.target;
-  const uint32_t pending = (kLevel == 1) ? 1u : st->hint_pending;
-  const uint32_t prefix = (kLevel == 1) ? 0u : st->prefix;
+  const uint32_t pending = (kLevel == 1) ? 1u : ld_agent(&st->hint_pending);
+  const uint32_t prefix = (kLevel == 1) ? 0u : ld_agent(&st->prefix);
   stage_hist<kBins, 1u>(A.hist + static_cast<size_t>(l) * kHistBins, lds);
   (void)locate_from_top(lds, kBins, k_rem, target - above_scope, sh);
   if (threadIdx.x == 0) {
@@ -471,20 +484,20 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
     uint32_t pend = pending;
     if (pend == 1u) {
       if (sh.hbin == 0xFFFFFFFFu) {          // the whole layer holds fewer keys than the target rank
-        st->tau_next = 0u; pend = 2u;
+        st_agent(&st->tau_next, 0u); pend = 2u;
       } else if (hcum <= L.cmax) {
-        st->tau_next = edge(sh.hbin); pend = 2u;
+        st_agent(&st->tau_next, edge(sh.hbin)); pend = 2u;
       } else if (sh.hbin == D) {
         pend = (kLevel < 3) ? 1u : 3u;      // refine inside the same bin, or give up (heavy ties)
       } else {
-        st->tau_next = edge(sh.hbin + 1u); pend = 2u;   // one bin up: fewer keys than aimed at, still >= k
+        st_agent(&st->tau_next, edge(sh.hbin + 1u)); pend = 2u;   // one bin up: fewer keys than aimed at, still >= k
       }
     }
     const uint32_t new_rem = k_rem - sh.above;
-    st->k_rem = new_rem;
+    st_agent(&st->k_rem, new_rem);
     if (kLevel == 1) {
-      st->prefix = D;
-      st->next_phase = PH_HIST2;
+      st_agent(&st->prefix, D);
+      st_agent(&st->next_phase, PH_HIST2);
       // A hint-free call needs no further digits if the keys from the first digit's bin upwards fit the
       // candidate lists: one more pass over the residual collects them (threshold = the bin's lower edge,
       // so at least k of them exist) and the call ends like a hinted one (PH_SEL, PH_OUT_C): two passes
@@ -497,22 +510,22 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
         const uint32_t tau = (lower & kKeyMask) ? (lower & kKeyMask) : 1u;
         st->tau = tau;
         st->shift = shift_for(tau + ((1u << (low + 12u)) - 1u), tau);
-        st->next_phase = PH_COLLECT;
+        st_agent(&st->next_phase, PH_COLLECT);
       }
     } else if (kLevel == 2) {
-      st->prefix = (prefix << 12) | D;
-      st->next_phase = PH_HIST3;
+      st_agent(&st->prefix, (prefix << 12) | D);
+      st_agent(&st->next_phase, PH_HIST3);
     } else {
       const uint32_t T = (prefix << low) | D;
-      st->T = T;
-      st->r = new_rem;
-      st->next_phase = PH_COUNT;
+      st_agent(&st->T, T);
+      st_agent(&st->r, new_rem);
+      st_agent(&st->next_phase, PH_COUNT);
       if (A.update_hints && L.dense && st->dense_skip != 0u) st->dense_skip -= 1u;   // one more call without its hint
       if (A.update_hints) {
         // The hints live in the key space of the one-pass path (key_of).  With the ordered key a hint
         // exists only if the k-th key and the threshold aimed at both lie among the elements key_of()
         // ranks (top bit set); a layer short of such elements has none and stays on this path.
-        uint32_t Th = T, tn = st->tau_next;
+        uint32_t Th = T, tn = ld_agent(&st->tau_next);
         bool usable = (pend == 2u);
         if (A.sign_filter) {
           usable = usable && T > 0x80000000u && tn >= 0x80000000u;
@@ -534,7 +547,7 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
         }
       }
     }
-    st->hint_pending = pend;
+    st_agent(&st->hint_pending, pend);
     schedule_launch(A, st, sh, cur_launch + 1u);
   }
 }
@@ -643,10 +656,10 @@ __device__ __forceinline__ void scan_chunks(uint32_t* a, uint32_t* b, uint32_t c
     for (uint32_t j = 0; j < kItems; ++j) {
       if (i0 + j < count) {
         if (with_ties) {
-          a[i0 + j] = ea + (eb < r ? eb : r);
-          b[i0 + j] = eb;
+          st_agent(&a[i0 + j], ea + (eb < r ? eb : r));
+          st_agent(&b[i0 + j], eb);
         } else {
-          a[i0 + j] = ea;
+          st_agent(&a[i0 + j], ea);
         }
       }
       ea += va[j];
@@ -848,7 +861,7 @@ __device__ __forceinline__ void phase_hist(const CompressArgs& A, uint32_t l, co
   constexpr uint32_t kBins = (kLevel == 3) ? 256u : static_cast<uint32_t>(kHistBins);
   for (uint32_t b = threadIdx.x; b < kBins; b += kBlockThreads) lds_hist[b] = 0u;
   __syncthreads();
-  const uint32_t prefix = st->prefix;
+  const uint32_t prefix = ld_uniform(&st->prefix);
   const uint32_t low = low_bits_of(A.sign_filter), low_mask = (1u << low) - 1u;
   if (wc_local < L.wc_count) {
     const uint32_t begin = wc_local * A.chunk;
@@ -912,7 +925,7 @@ __device__ __forceinline__ void phase_collect(const CompressArgs& A, uint32_t l,
 
 __device__ __forceinline__ void phase_count(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                             uint32_t wc_local, ResolveShared& sh) {
-  const uint32_t T = st->T;
+  const uint32_t T = ld_uniform(&st->T);
   if (wc_local < L.wc_count) {
     const uint32_t begin = wc_local * A.chunk;
     const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
@@ -936,11 +949,11 @@ __device__ __forceinline__ void phase_count(const CompressArgs& A, uint32_t l, c
     }
   }
   if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag, in_fallback(A))) {
-    scan_chunks(A.wc_a + L.wc_first, A.wc_b + L.wc_first, L.wc_count, st->r, true, sh.scan, &sh.cnt);
+    scan_chunks(A.wc_a + L.wc_first, A.wc_b + L.wc_first, L.wc_count, ld_agent(&st->r), true, sh.scan, &sh.cnt);
     __syncthreads();
     if (threadIdx.x == 0) {
       if (sh.cnt != L.k) atomicOr(A.errflag, 2u);
-      st->next_phase = PH_OUT_V;
+      st_agent(&st->next_phase, PH_OUT_V);
       schedule_launch(A, st, sh, A.launch + 1u, true);
     }
   }
@@ -948,11 +961,11 @@ __device__ __forceinline__ void phase_count(const CompressArgs& A, uint32_t l, c
 
 __device__ __forceinline__ void phase_out_v(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wc_local) {
   if (wc_local >= L.wc_count) return;
-  const uint32_t T = st->T, r = st->r;
+  const uint32_t T = ld_uniform(&st->T), r = ld_uniform(&st->r);
   const uint32_t begin = wc_local * A.chunk;
   const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
-  uint32_t out_pos = A.wc_a[L.wc_first + wc_local];
-  uint32_t eq_seen = A.wc_b[L.wc_first + wc_local];
+  uint32_t out_pos = ld_uniform(&A.wc_a[L.wc_first + wc_local]);
+  uint32_t eq_seen = ld_uniform(&A.wc_b[L.wc_first + wc_local]);
   const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
   const gptr<int32_t> out_idx = as_global(L.out_idx);
   const gptr<float> out_val = as_global(L.out_val);
@@ -1989,8 +2002,14 @@ __global__ void __launch_bounds__(kFinishThreads) emit_kernel(CompressArgs A) {
 // missed (a tiled call hands it the general tiling).  Nothing is due in steady state, and one launch that finds that out is
 // cheaper than three (VGG16 set: 571 us per call with three, 565 us with one).
 // Otherwise its workgroups take tickets (rgc_tickets.h): a workgroup number whose layer has not got to this pass yet waits for the
-// layer, which publishes every pass with an agent-scope release that the waiting side acquires, as a kernel boundary would.
-// Waiting needs no other workgroup to be on the device than those that run, so it ends on any stream and beside any kernels.
+// layer's last workgroup of the pass before to publish it.  Waiting needs no other workgroup to be on the device than those
+// that run, so it ends on any stream and beside any kernels.
+// What a phase leaves for the next one goes through st_agent() and device-scope atomics and is read with ld_agent(), as in the
+// election: a release and an acquire at every pass (they walk the XCD's L2) cost more than the passes' own reading.  With them
+// and a workgroup per CU, one 16-byte load of a lane in flight, a call whose hints all miss took 1.18 ms on the LSTM set, 0.57
+// on the ResNet-50 set and 1.09 on 64 Mi elements; it takes 0.41, 0.21 and 0.48 with four workgroups per CU and four loads
+// (two workgroups 0.46 / 0.23 / 0.50, eight 0.48 / 0.21 / 0.59; four with the acquires 0.49 / 0.29 / 0.53).  The five passes
+// as launches of their own, behind the streaming pass of that time, took 0.45, 0.23 and 0.49.
 namespace {
 
 constexpr uint32_t kWaitPolls = 1u << 23;   // seconds; a pass over a layer takes milliseconds at most
@@ -2004,7 +2023,7 @@ struct FallbackWork {
   __device__ __forceinline__ uint32_t take() {
     if (threadIdx.x == 0) *word = atomicAdd(A.late + 1, 1u);
     __syncthreads();
-    const uint32_t t = *word;
+    const uint32_t t = __builtin_amdgcn_readfirstlane(*word);
     __syncthreads();
     return t;
   }
@@ -2017,12 +2036,11 @@ struct FallbackWork {
         d = due_at(ld_agent(&st->next_launch), launch, A.late_first);
       }
       if (d == Due::kWait) atomicOr(A.errflag, 512u);       // a layer that never published: a bug
-      if (d == Due::kRun && launch != A.late_first) __threadfence();
       sh.publish = 0u;
       *word = d == Due::kRun ? 1u : 0u;
     }
     __syncthreads();
-    const bool run = *word != 0u;
+    const bool run = __builtin_amdgcn_readfirstlane(*word) != 0u;
     __syncthreads();
     return run;
   }
@@ -2034,7 +2052,7 @@ struct FallbackWork {
     A.launch = launch;
     const LayerDesc L = A.layers[l];
     const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
-    switch (st->next_phase) {
+    switch (ld_uniform(&st->next_phase)) {
       case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, hist, sh); break;
       case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, hist, sh); break;
       case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, hist, sh); break;
@@ -2047,16 +2065,13 @@ struct FallbackWork {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();                                 // (the next unit uses the same LDS)
-    if (threadIdx.x == 0 && sh.publish != 0u) {
-      __threadfence();
-      st_agent(&st->next_launch, sh.publish);
-    }
+    if (threadIdx.x == 0 && sh.publish != 0u) st_agent(&st->next_launch, sh.publish);
   }
 };
 
 }  // namespace
 
-__global__ void __launch_bounds__(kBlockThreads) fallback_kernel(CompressArgs A, TicketOrder order) {
+__global__ void __launch_bounds__(kBlockThreads, 4) fallback_kernel(CompressArgs A, TicketOrder order) {
   __shared__ uint32_t hist[kHistBins];
   __shared__ ResolveShared sh;
   __shared__ uint32_t word;
@@ -3037,7 +3052,7 @@ hipError_t launch_emit(const CompressArgs& a, uint32_t num_parts, hipStream_t s)
 }
 
 hipError_t launch_fallback(const CompressArgs& a, uint32_t num_wgs, uint32_t cus, hipStream_t s) {
-  const TicketOrder order = ticket_order(num_wgs, cus, a.late_last - a.late_first + 1u);
+  const TicketOrder order = ticket_order(num_wgs, 4u * cus, a.late_last - a.late_first + 1u);   // (four workgroups fit on a CU)
   hipLaunchKernelGGL(fallback_kernel, dim3(order.slices), dim3(kBlockThreads), 0, s, a, order);
   return hipGetLastError();
 }

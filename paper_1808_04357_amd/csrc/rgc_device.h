@@ -79,6 +79,9 @@ __device__ __forceinline__ uint32_t ld_agent(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// ... at an address that is the same for the whole wave.
+__device__ __forceinline__ uint32_t ld_uniform(const uint32_t* p) { return __builtin_amdgcn_readfirstlane(ld_agent(p)); }
+
 __device__ __forceinline__ void st_agent(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
