@@ -236,6 +236,13 @@ struct rgc_ctx {
 
 namespace {
 
+// Tiles of a part of a larger layer whose hint is aimed at rank `target`: see kPartCand.
+uint32_t part_tiles(uint32_t tiles, uint64_t n, uint64_t target) {
+  uint32_t per = kPartTiles;
+  while (per > 1 && target * per * kTileElems > kPartCand * n && (tiles + per / 2 - 1) / (per / 2) <= kPartsMax) per /= 2;
+  return per;
+}
+
 // Fills `desc` (one entry per layer); the workgroups are handed out in the given order of the layers.
 Tiling cut_layers(const rgc_layer* layers, const std::vector<int32_t>& order, uint32_t kChunk, bool tiled, LayerDesc* desc) {
   const uint32_t kCap = (tiled ? kTileElems : kChunk) / kCapDiv;
@@ -271,7 +278,8 @@ Tiling cut_layers(const rgc_layer* layers, const std::vector<int32_t>& order, ui
     d.kind = d.n <= kDirectMax ? kLayerDirect
              : aim.target <= kListsTargetMax && d.wg_count <= kPartTilesMax ? kLayerLists : kLayerBig;
     d.part_first = parts;
-    parts += d.kind == kLayerBig ? (d.wg_count + kPartTiles - 1) / kPartTiles : 1u;
+    d.part_tiles = part_tiles(d.wg_count, d.n, aim.target);
+    parts += d.kind == kLayerBig ? (d.wg_count + d.part_tiles - 1) / d.part_tiles : 1u;
     d.margin = static_cast<uint32_t>(margin);
     uint64_t cmax = std::min<uint64_t>(2 * target, (kCap / 2) * (span / list_span));
     d.target = static_cast<uint32_t>(std::min<uint64_t>(target, 0xFFFFFFFFu));
@@ -354,7 +362,7 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
       for (const int32_t l : order) {
         const LayerDesc& d = desc[static_cast<size_t>(L) + l];
         if ((d.kind == kLayerBig) != big) continue;
-        const uint32_t parts = big ? (d.wg_count + kPartTiles - 1) / kPartTiles : 1u;
+        const uint32_t parts = big ? (d.wg_count + d.part_tiles - 1) / d.part_tiles : 1u;
         for (uint32_t i = 0; i < parts; ++i) { *at++ = static_cast<uint32_t>(l); *at++ = i; }
         if (big) tiled.big_parts += parts;
       }

@@ -57,8 +57,11 @@ constexpr uint32_t kTileChunk = 1024;              // elements per wave
 constexpr uint32_t kTileElems = kTileChunk * kWavesPerBlock;
 constexpr uint32_t kFinishCand = 12288;            // candidates in LDS
 constexpr uint32_t kPartTilesMax = 1024;           // lists gather_lists() can take
-// A larger layer's parts: 2^20 elements, 2,600 candidates at 0.1 %.  All tiles of the largest layer make at most kPartsMax.
-constexpr uint32_t kPartTiles = 256, kPartsMax = 2048;
+// A larger layer's parts: kPartTiles tiles (2^20 elements, 2,600 candidates at 0.1 %), at higher densities half as many and again
+// until about kPartCand candidates are expected of each, but never more than kPartsMax parts.  A part's candidates are one
+// workgroup's work: at 1 % the ResNet-50 set takes 97 us per call, with parts of 2^20 elements whatever the density 122 (2 Mi +
+// 0.6 Mi elements: 34 and 69; lines of 3072 and 6144 candidates: within 6 us of this one).
+constexpr uint32_t kPartTiles = 256, kPartsMax = 2048, kPartCand = 4096;
 static_assert(static_cast<uint64_t>(kPartsMax) * kPartTiles * kTileElems >= (1ull << 31), "any layer has at most kPartsMax parts");
 enum LayerKind : uint32_t {
   kLayerBig = 0,       // several workgroups, a message launch of its own
@@ -96,6 +99,7 @@ struct LayerDesc {
   uint32_t list_cap;   // dense layers: entries of one wave-chunk's list
   uint32_t kind;       // LayerKind (tiled calls)
   uint32_t part_first; // tiled calls: where the layer's parts start in the per-part arrays
+  uint32_t part_tiles; // tiled calls: tiles of a part (a power of two)
   uint64_t mem_first;  // dense layers: where the layer's region of the member pool starts
   uint64_t list_first; // dense layers: where the layer's lists start (wave-chunk c of the layer: list_first + c * list_cap)
 };

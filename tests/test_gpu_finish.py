@@ -83,6 +83,35 @@ def test_long_lists_and_more_of_them_than_the_queue_holds(rgc, oracle):
     assert any(p == [0] for p in paths[1:]), paths
 
 
+# a full part (2^20 elements) has more than the 12288 candidates of one step from about 0.47 % on; 11,700 ppm is about the most a
+# tile's list is long enough for
+@pytest.mark.parametrize("ppm", [4000, 5000, 8000, 10_000, 11_500])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_densities_up_to_one_percent_keep_their_hints(rgc, oracle, ppm, momentum):
+    g = np.random.default_rng(12)
+    sizes = [(2 << 20) + 77_777, 1 << 20, 600_000, 40_000, 3000]
+    ks = [rgc.rgc_k_for_density(n, ppm) for n in sizes]
+    V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    U = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] if momentum else None
+    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(8)]
+    paths = run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9 if momentum else 0.0, threads=8, tag="%d ppm" % ppm)
+    assert all(p[:4] == [0, 0, 0, 0] for p in paths[-4:]), paths
+
+
+def test_large_values_in_one_part_keep_their_hints(rgc, oracle):
+    """The frequent rows of an embedding come first: nearly all candidates of a layer of seven parts lie in the first of them,
+    more than one step holds, though no list runs over."""
+    g = np.random.default_rng(13)
+    n, ppm = (6 << 20) + 12_345, 1000
+    k = rgc.rgc_k_for_density(n, ppm)
+    scale = np.full(n, 1e-3, np.float32)
+    scale[: n // 10] = 1.0
+    V = [(g.standard_normal(n).astype(np.float32) * scale)]
+    G_list = [[(g.standard_normal(n).astype(np.float32) * scale * 0.2)] for _ in range(8)]
+    paths = run_iterations(rgc, oracle, V, G_list, [k], threads=8, tag="one part")
+    assert all(p == [0] for p in paths[-4:]), paths
+
+
 def test_missed_hints_take_the_fallback(rgc, oracle):
     """Hints too high, too low and random, heavy ties, an overflowing list, zeros: several layers at once go through the
     digits in the last launch, others do not."""
