@@ -170,6 +170,7 @@ struct CompressPlan {
   PinnedBuf staging;
   hipEvent_t uploaded = nullptr;    // recorded after the uploads
   uint64_t tensor_bytes = 0;               // gradients, residuals and velocities together
+  uint64_t total_elems = 0;
   uint64_t listable_elems = 0;             // elements of the layers that a searching threshold call can list the largest of
   uint64_t write_bytes = 0;                // what the streaming pass writes (V, and u where there is one)
   uint32_t max_k = 0;                      // the largest k of the list
@@ -383,6 +384,7 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
   P.write_bytes = 0;
   P.tensor_bytes = 0;
   P.listable_elems = 0;
+  P.total_elems = static_cast<uint64_t>(total_elems);
   P.max_k = 0;
   P.any_dense = false;
   P.tiled_needs_hints = false;
@@ -655,8 +657,14 @@ uint32_t streaming_direction(const CompressPlan* plan, uint64_t call) {
 // the stores' lines then only have to be evicted again.  Measured per call with a velocity, plain / past the cache:
 // three contexts taking turns 16 Mi elements (192 MB of tensors) 99 / 86 us, 48 Mi 259 / 216 us, VGG16 set 656 / 571 us;
 // 2 GB of other traffic between the calls 101 / 90, 243 / 225 us.  Below the line the caches hold the call's tensors and
-// the two are the same (8 Mi, 96 MB: 54 / 54 us; without a velocity 16 Mi, 128 MB: 59 / 63 us).  A call that will read
-// the residual again (`again`: it has no hints) leaves it in the cache if it fits there.
+// the two are the same (8 Mi, 96 MB: 54 / 54 us; without a velocity 16 Mi, 128 MB: 59 / 63 us).
+// A call that will read the residual again (`again`: it has no hints, or searches thresholds at a density too high for lists)
+// leaves it in the cache if it fits there: a search at 1 % over 32 Mi elements, contexts in turn, 183 / 193 us, over 48 Mi 256 /
+// 275; after 2 GB of other traffic 202 / 213, 277 / 295.
+// Threshold calls that list (searching) or reuse thresholds read it once, as a hinted call does: LSTM set 244 / 205 and 204 / 161
+// in turn, 235 / 214 and 192 / 174 after other traffic; VGG16 set reusing 684 / 545, 639 / 570.  Only a program that does
+// nothing between two calls of one context finds a V of up to 256 MB still cached: LSTM set 185 / 207 and 145 / 166 (nontemporal
+// loads alone or stores alone keep neither gain).
 constexpr uint64_t kPastCacheBytes = 128ull << 20;
 uint32_t stream_past_cache(const CompressPlan* plan, bool again) {
   if (again && plan->write_bytes <= kMemorySideCacheBytes) return 0u;
@@ -764,7 +772,8 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   // memory-side cache still holds.  A searching call leaves the direction as it was (where its lists do not do, it passes
   // over the residual three times more and ends where it began).
   const bool alternate = plan->write_bytes > kMemorySideCacheBytes;
-  A.past_cache = stream_past_cache(plan, false);
+  // (a search reads the residual three times more where its lists do not hold the largest elements of most of the call)
+  A.past_cache = stream_past_cache(plan, A.search != 0u && (A.sampled == 0u || 2u * plan->listable_elems < plan->total_elems));
   A.reverse = alternate ? ctx->threshold_reverse : 0u;
   RGC_HIP(launch_threshold_compress(A, plan->general.workgroups, static_cast<uint32_t>(num_layers), stream));
   if (!A.search) ctx->threshold_reverse ^= 1u;
