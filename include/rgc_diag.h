@@ -30,9 +30,9 @@ int rgc_limit_optional_scratch(rgc_ctx* ctx, int64_t max_bytes);
 int rgc_selftest(rgc_ctx* ctx, void* hip_stream);
 
 /* Copies per-layer path statistics of the LAST compression call into `out` (host memory,
- * int32[num_layers]): 0 = one-pass hinted path, 1 = without a hint (multi-pass path, or a layer
- * of at most 32768 elements ended by one workgroup), 2 = hinted
- * pass missed and the multi-pass path re-ran on the updated residual.  Synchronises
+ * int32[num_layers]): 0 = one pass over the tensors (the layer's hint held, or, in a call that uses
+ * hints, the layer is too small to need one), 1 = a call without hints, or a layer that has none
+ * (multi-pass path), 2 = hinted pass missed and the multi-pass path re-ran on the updated residual.  Synchronises
  * `hip_stream`.  Returns RGC_EINTERNAL if any kernel of an earlier call flagged an internal
  * inconsistency.  A diagnostic for tests and benchmarks. */
 int rgc_last_paths(rgc_ctx* ctx, int32_t* out, int32_t num_layers, void* hip_stream);

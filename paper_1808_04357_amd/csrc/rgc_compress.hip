@@ -1503,7 +1503,7 @@ __device__ __forceinline__ void direct_done(const CompressArgs& A, const LayerDe
   if (sent != L.k) atomicOr(A.errflag, 128u);
   *as_global(L.out_count) = static_cast<int32_t>(L.k);
   st->T = T;
-  st->path = 1u;
+  st->path = A.use_hints ? 0u : 1u;                          // (one pass over the tensors like a layer whose hint held)
   st->stat_candidates = 0u;
   st->stat_members = 0u;
   st->next_phase = PH_NONE;

@@ -83,6 +83,19 @@ def test_long_lists_and_more_of_them_than_the_queue_holds(rgc, oracle):
     assert any(p == [0] for p in paths[1:]), paths
 
 
+@pytest.mark.parametrize("sizes", [[32768, 5000, 1], [200_000, 32768, 300]])
+def test_reported_paths_of_small_layers(rgc, oracle, sizes):
+    """A layer small enough to need no hint is on the one-pass path like the others: from the first call that has hints on."""
+    g = np.random.default_rng(14)
+    ks = [rgc.rgc_k_for_density(n) for n in sizes]
+    V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(4)]
+    paths = run_iterations(rgc, oracle, V, G_list, ks, tag="paths")
+    assert paths[0] == [1] * len(sizes) and all(p[-1] == 0 and p[-2] == 0 for p in paths[1:]), paths
+    paths = run_iterations(rgc, oracle, V, G_list, ks, flags=rgc.RGC_NO_HINTS, tag="paths without hints")
+    assert all(p == [1] * len(sizes) for p in paths), paths
+
+
 # a full part (2^20 elements) has more than the 12288 candidates of one step from about 0.47 % on; 11,700 ppm is about the most a
 # tile's list is long enough for
 @pytest.mark.parametrize("ppm", [4000, 5000, 8000, 10_000, 11_500])
