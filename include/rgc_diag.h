@@ -57,9 +57,9 @@ int rgc_profile_read(rgc_ctx* ctx, double* out_ms, int64_t* out_calls);
  * correction of Section 2.5): one kernel that reads `grad`, `residual` and `velocity` (device pointers, n fp32
  * elements each, 16-byte aligned, the caller's) and writes  velocity = momentum * velocity + grad,
  * residual = residual + velocity  back in place -- the 20 bytes per element of that pass and none of its
- * selection work, with the same decomposition (one wave per 8192 consecutive elements; `reverse` != 0 walks the
- * tensors from the far end, as every other compression call does).  A benchmark times it to learn what share of
- * the HBM peak this mix of reads and writes reaches on the device at all.  Launches on the current device and
+ * selection work, with the decomposition and the accesses of a large call (one wave per 1024 consecutive elements,
+ * past the memory-side cache; `reverse` != 0 walks the tensors from the far end).  A benchmark times it to learn what
+ * share of the HBM peak this mix of reads and writes reaches on the device at all.  Launches on the current device and
  * `hip_stream`, does not synchronise, needs no context.  RGC_EINVAL: null or misaligned pointer, n < 1. */
 int rgc_stream_yardstick(const float* grad, float* residual, float* velocity, int64_t n, float momentum,
                          int reverse, void* hip_stream);

@@ -3,10 +3,10 @@
 // The compression call's streaming pass (Algorithm 1's accumulate with the momentum correction of
 // Section 2.5) reads G, V and u and writes V and u: 20 bytes per element, two fifths of them writes.
 // The kernel below does exactly that and nothing else -- no keys, no lists, no histogram -- with the
-// same decomposition (one wave per contiguous wave-chunk, 16 bytes per lane and access, consecutive
-// calls walking the tensors in opposite directions).  Its time is the yardstick a benchmark holds the
-// streaming pass against: the share of the HBM peak that this mix of reads and writes reaches on the
-// device at all.  A diagnostic (rgc_diag.h); no product call uses it.
+// decomposition and the accesses of a large call (tile_kernel: one wave per 1024 consecutive elements,
+// all its 16-byte loads in flight at once, everything past the memory-side cache).  Its time is the
+// yardstick a benchmark holds the streaming pass against: the share of the HBM peak that this mix of
+// reads and writes reaches on the device at all.  A diagnostic (rgc_diag.h); no product call uses it.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -20,8 +20,9 @@ namespace {
 typedef float yf4 __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kYardThreads = 256;      // four waves, as in the streaming pass
-constexpr uint32_t kYardChunk = 8192;       // elements per wave
-constexpr uint32_t kYardInFlight = 2;       // 16-byte accesses per lane and array in flight
+constexpr uint32_t kYardChunk = 1024;       // elements per wave
+constexpr uint32_t kYardInFlight = 4;       // 16-byte accesses per lane and array in flight
+static_assert(kYardChunk == 64u * 4u * kYardInFlight, "a wave's elements at once");
 
 __global__ void __launch_bounds__(kYardThreads) yardstick_kernel(const float* __restrict__ g, float* __restrict__ v,
                                                                  float* __restrict__ u, uint64_t n, float m,
@@ -31,27 +32,27 @@ __global__ void __launch_bounds__(kYardThreads) yardstick_kernel(const float* __
   const uint32_t lane = threadIdx.x & 63u;
   const uint64_t n4 = n / 4u;                                  // whole 16-byte groups
   const uint64_t b = wave * (kYardChunk / 4u);
-  uint64_t e = b + kYardChunk / 4u;
-  if (e > n4) e = n4;
   const yf4* g4 = reinterpret_cast<const yf4*>(g);
   yf4* v4 = reinterpret_cast<yf4*>(v);
   yf4* u4 = reinterpret_cast<yf4*>(u);
-  for (uint64_t i = b + lane; i < e; i += 64u * kYardInFlight) {
-    yf4 gg[kYardInFlight], vv[kYardInFlight], uu[kYardInFlight];
+  yf4 gg[kYardInFlight], vv[kYardInFlight], uu[kYardInFlight];
 #pragma unroll
-    for (uint32_t j = 0; j < kYardInFlight; ++j) {
-      const uint64_t p = i + 64u * j;
-      if (p < e) { gg[j] = g4[p]; vv[j] = v4[p]; uu[j] = u4[p]; }
+  for (uint32_t j = 0; j < kYardInFlight; ++j) {
+    const uint64_t p = b + lane + 64u * j;
+    if (p < n4) {
+      gg[j] = __builtin_nontemporal_load(g4 + p);
+      vv[j] = __builtin_nontemporal_load(v4 + p);
+      uu[j] = __builtin_nontemporal_load(u4 + p);
     }
+  }
 #pragma unroll
-    for (uint32_t j = 0; j < kYardInFlight; ++j) {
-      const uint64_t p = i + 64u * j;
-      if (p < e) {
-        uu[j] = m * uu[j] + gg[j];      // (no contraction: the library is built without fma fusion)
-        vv[j] = vv[j] + uu[j];
-        u4[p] = uu[j];
-        v4[p] = vv[j];
-      }
+  for (uint32_t j = 0; j < kYardInFlight; ++j) {
+    const uint64_t p = b + lane + 64u * j;
+    if (p < n4) {
+      uu[j] = m * uu[j] + gg[j];        // (no contraction: the library is built without fma fusion)
+      vv[j] = vv[j] + uu[j];
+      __builtin_nontemporal_store(uu[j], u4 + p);
+      __builtin_nontemporal_store(vv[j], v4 + p);
     }
   }
   // the up to three elements behind the last whole group
