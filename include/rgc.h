@@ -253,7 +253,8 @@ int rgc_reset_hints(rgc_ctx* ctx);
 /* Whether a kernel of any compression call enqueued so far has reported an internal inconsistency (a
  * candidate list and its histogram that disagree, a message that came out shorter than k: a bug in the
  * library, after which results are invalid).  Waits for `hip_stream`, copies one word.  Returns RGC_OK,
- * RGC_EINTERNAL (it stays set until the context is destroyed), RGC_EINVAL or RGC_EHIP. */
+ * RGC_EINTERNAL (it stays set until the context is destroyed, which is what is left to do with it: its later
+ * calls are not to be trusted either), RGC_EINVAL or RGC_EHIP. */
 int rgc_last_error(rgc_ctx* ctx, void* hip_stream);
 
 /* Text for a status code; for RGC_EHIP the text of the last HIP error seen by this thread. */

@@ -28,10 +28,6 @@
 
 #include "../../include/rgc.h"
 
-#ifndef RGC_RECOMPUTE_UNROLL
-#define RGC_RECOMPUTE_UNROLL 2
-#endif
-
 namespace rgc {
 
 namespace {
@@ -1215,10 +1211,8 @@ __device__ __forceinline__ void phase_out_c(const CompressArgs& A, const LayerDe
 
 // The phase launches always take the workgroups in ascending order, largest layers first: their
 // serial per-layer steps then start as early as possible.  (Letting consecutive launches alternate
-// like the streaming passes of consecutive calls do makes the multi-pass path 6 % faster, each pass
-// starting with what the one before touched last, but the steady state 2 us slower.)
-__device__ __forceinline__ uint32_t phase_workgroup(const CompressArgs&) { return blockIdx.x; }
-
+// makes the multi-pass path 6 % faster, each pass starting with what the one before touched last,
+// but the steady state 2 us slower.)
 __global__ void __launch_bounds__(kBlockThreads) phase_kernel(CompressArgs A) {
   __shared__ union {
     uint32_t hist[kHistBins];
@@ -1226,7 +1220,7 @@ __global__ void __launch_bounds__(kBlockThreads) phase_kernel(CompressArgs A) {
   } sm;
   __shared__ ResolveShared sh;
   __shared__ __attribute__((aligned(16))) uint32_t sel_hist[3 * 256];
-  const uint32_t wg = phase_workgroup(A);
+  const uint32_t wg = blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   LayerState* st = A.state + l;
   if (st->next_launch != A.launch) return;
@@ -1247,15 +1241,14 @@ __global__ void __launch_bounds__(kBlockThreads) phase_kernel(CompressArgs A) {
   }
 }
 
-// Launches 4..6 can only meet the last three phases of the multi-pass path (a layer that missed
-// its hint is at PH_HIST3 in launch 4 at the earliest) or the output phase of a hint-free call that
-// collected its candidates in launch 2, and in steady state they meet nothing at
-// all.  They get a kernel of their own that needs next to no LDS: twice as many of its
-// workgroups fit on the device at once, so the launches that find nothing to do are over sooner.
+// Launches 4..6 of a call without hints (in the others fallback_kernel stands for them) can only meet
+// the last three phases of the multi-pass path or the output phase of a layer that collected its
+// candidates in launch 2.  They get a kernel of their own that needs next to no LDS: twice as many of
+// its workgroups fit on the device at once, so the launches that find nothing to do are over sooner.
 __global__ void __launch_bounds__(kBlockThreads) phase_late_kernel(CompressArgs A) {
   __shared__ uint32_t hist[256];   // the last digit: 7 or 8 bits
   __shared__ ResolveShared sh;
-  const uint32_t wg = phase_workgroup(A);
+  const uint32_t wg = blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   LayerState* st = A.state + l;
   if (st->next_launch != A.launch) return;

@@ -36,12 +36,12 @@ enum Phase : uint32_t {
   PH_SEL2 = 11,    // dense layers: PH_SEL on the layer's own lists (lists_kernel)
 };
 
-// Dense layers: after a call whose hint missed, the layer goes without its hint for a number of calls that
-// doubles with every further miss, up to this many.
+constexpr uint32_t kFirstLateLaunch = 4;          // general calls: launches 4 .. 6 only meet the last phases
 // Workgroups' worth of candidate lists one workgroup of PH_SEL / PH_OUT_C takes (CompressArgs::list_group:
 // kListGroup, or 1 for a call whose workgroups all fit on the device at once, where spreading the lists wins).
-constexpr uint32_t kFirstLateLaunch = 4;          // launches 4 .. 6 only meet the last phases
 constexpr uint32_t kListGroupLog2 = 2, kListGroup = 1u << kListGroupLog2;
+// Dense layers: after a call whose hint missed, the layer goes without its hint for a number of calls that
+// doubles with every further miss, up to this many.
 constexpr uint32_t kDenseBackoffMax = 64;
 // Dense layers: the members of the k-th key's coarse bin are appended to this many sub-lists, each with a counter
 // of its own (thousands of waves appending through one counter take their turns at ~20 ns each), and what a

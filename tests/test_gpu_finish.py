@@ -70,8 +70,9 @@ def test_layers_from_their_lists(rgc, oracle, sizes, ks):
     assert any(p[0] == 0 for p in paths[1:]), paths
 
 
-def test_long_lists_and_more_of_them_than_the_queue_holds(rgc, oracle):
-    """The large values sit in 1,100 of 2,930 wave-chunks, in a few of them far more than in the others."""
+def test_long_lists_of_a_layer_ended_by_one_workgroup(rgc, oracle):
+    """The large values sit in 275 of 733 tiles, more than the 16 in each that are asked for with the list's length, and one
+    tile has far more of them than the others."""
     g = np.random.default_rng(8)
     n, k = 3_000_000, 2457
     scale = np.full(n, 1e-3, np.float32)
@@ -133,7 +134,7 @@ def test_missed_hints_take_the_fallback(rgc, oracle):
     V = [(g.standard_normal(n) * 1e-2).astype(np.float32) for n in sizes]
     V[2] = (np.round(V[2] * 300) / 300).astype(np.float32)
     V[3][:] = 0.0
-    V[4][1000:2000] *= 100.0                                   # one list of 64 slots for 200 of the largest
+    V[4][1000:2000] *= 100.0                                   # one list of 256 slots for the 500 largest, the rank aimed at
     G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(8)]
     for G in G_list:
         G[2] = (np.round(G[2] * 300) / 300).astype(np.float32)
