@@ -218,6 +218,8 @@ struct rgc_ctx {
   uint64_t tick = 0;
   int64_t optional_scratch_cap = -1;       // bytes the dense layers' lists may take (diagnostics); negative: no cap
   bool compressed_since_decompress = false;
+  uint64_t compress_calls = 0;             // its parity is the direction of the next streaming pass
+  uint32_t threshold_reverse = 0;          // direction of the next threshold-selection call's first pass
   // Speed hints are kept per selection mode (0 magnitude, 1 largest, 2 smallest: the thresholds of
   // the positive and the negative tail differ, and Alternating Signs Quantization switches between
   // them from call to call): bank b uses the layer states [b * max_layers, (b + 1) * max_layers).
@@ -639,7 +641,16 @@ int plan_for_layers(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_layers, h
   return RGC_OK;
 }
 
-constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;   // MI355X
+// Direction of the streaming pass of compression call number `call` (0: workgroups ascending).
+// Every other call goes backwards when the call writes more than the memory-side cache holds
+// (256 MB on MI355X).  While the passes went through that cache, the tail of what the previous call
+// had written was still there and was read first: a tenth of the call.  Past it a little is left of
+// that: VGG16 set, three contexts in turn, 520.4 us alternating, 522.0 always ascending.  Smaller
+// layer sets do better in ascending order (largest layers first).
+constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
+uint32_t streaming_direction(const CompressPlan* plan, uint64_t call) {
+  return (plan->write_bytes > kMemorySideCacheBytes) ? static_cast<uint32_t>(call & 1u) : 0u;
+}
 
 // Whether the streaming pass reads and writes V and u past the memory-side cache (nontemporal accesses, as it has always
 // read G), and in the momentum variants asks for four groups of a lane instead of two at a time.  In a training program a
@@ -693,6 +704,7 @@ int rgc_clip_coefficient(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_laye
     RGC_HIP(ctx->d_norm_part.alloc(ctx->wg_max * kExactWordsPerPart));
   CompressArgs A{};
   fill_plan_args(ctx, plan, A);
+  A.reverse = streaming_direction(plan, ctx->compress_calls) ^ 1u;   // against the direction of the compression call to come
   const float threshold = static_cast<float>(static_cast<double>(max_norm) / std::sqrt(static_cast<double>(num_workers)));
   RGC_HIP(launch_clip_coefficient(A, plan->general.workgroups, threshold, coefficient, stream));
   return RGC_OK;
@@ -757,9 +769,15 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   A.mask_momentum = (flags & RGC_NO_MOMENTUM_MASK) ? 0u : 1u;
   A.nesterov = (flags & RGC_NESTEROV) ? 1u : 0u;
   A.m = momentum;
+  // A reusing call passes over the tensors once, and the call after it starts from the end it stopped at, as above.  A
+  // searching call leaves the direction as it was (where its lists do not do, it passes over the residual three times more
+  // and ends where it began).
+  const bool alternate = plan->write_bytes > kMemorySideCacheBytes;
   // (a search reads the residual three times more where its lists do not hold the largest elements of most of the call)
   A.past_cache = stream_past_cache(plan, A.search != 0u && (A.sampled == 0u || 2u * plan->listable_elems < plan->total_elems));
+  A.reverse = alternate ? ctx->threshold_reverse : 0u;
   RGC_HIP(launch_threshold_compress(A, plan->general.workgroups, static_cast<uint32_t>(num_layers), stream));
+  if (!A.search) ctx->threshold_reverse ^= 1u;
   ctx->compressed_since_decompress = true;
   return RGC_OK;
 }
@@ -847,6 +865,8 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.members2 = ctx->d_members2.p;
   A.shard_cnt = ctx->d_shards.p;
   A.past_cache = stream_past_cache(plan, A.use_hints == 0u);
+  A.reverse = streaming_direction(plan, ctx->compress_calls);
+  ++ctx->compress_calls;
   ctx->compressed_since_decompress = true;
   A.nesterov = (flags & RGC_NESTEROV) ? 1u : 0u;
   // a call that leaves most of the device idle spreads its candidate lists over as many workgroups as it has

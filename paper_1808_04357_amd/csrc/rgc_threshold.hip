@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(kSampleThreads) threshold_sample_kernel(Thresh
 // Leaves in the wave-chunk's list the elements above a magnitude (as many as the list holds) and per wave-chunk their number;
 // the magnitude is the threshold where it is given, and the sample's where it is searched (kSearch), in which case the pass
 // also leaves per workgroup its part of the exactly rounded sum of |a| (rgc_exact.h) and the maximum of |a|.
-template <bool kNt, bool kSearch>
+template <bool kNt, bool kSearch, bool kReverse>
 __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(ThresholdArgs A) {
   __shared__ ExactShared sh;
   __shared__ float wave_mx[kWavesPerBlock];
@@ -312,7 +312,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
     exact_shared_init(sh);
     __syncthreads();
   }
-  const uint32_t wg = blockIdx.x;
+  const uint32_t wg = (kReverse != (A.reverse != 0u)) ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   const Place p = place_of(A, L, l, wg);
@@ -427,7 +427,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(Thresh
 template <bool kReverse>
 __global__ void __launch_bounds__(kBlockThreads) threshold_histogram_kernel(ThresholdArgs A) {
   __shared__ uint32_t lds_hist[kSteps];
-  const uint32_t wg = kReverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  const uint32_t wg = (kReverse != (A.reverse != 0u)) ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   const Place p = place_of(A, L, l, wg);
@@ -515,7 +515,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_search_kernel(Thresho
 // ------------------------------------------------------------------ count, offsets, emit
 template <bool kReverse>
 __global__ void __launch_bounds__(kBlockThreads) threshold_count_kernel(ThresholdArgs A) {
-  const uint32_t wg = kReverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  const uint32_t wg = (kReverse != (A.reverse != 0u)) ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   const Place p = place_of(A, L, l, wg);
@@ -567,7 +567,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_offsets_kernel(Thresh
 // lists; a wave-chunk whose list holds them all is written from it, without another look at V.
 template <bool kReverse, bool kSearch>
 __global__ void __launch_bounds__(kBlockThreads) threshold_emit_kernel(ThresholdArgs A) {
-  const uint32_t wg = kReverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  const uint32_t wg = (kReverse != (A.reverse != 0u)) ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   const Place p = place_of(A, L, l, wg);
@@ -624,14 +624,14 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
   const dim3 block(kBlockThreads);
 #define RGC_LAUNCHED() do { hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return e_; } while (0)
   // Each pass over the tensors runs against the direction of the one before it: what that one touched last
-  // (still in the memory-side cache) is read first.
+  // (still in the memory-side cache) is read first.  a.reverse turns the whole sequence round.
   if (a.search) {
     if (a.sampled) {
       hipLaunchKernelGGL(threshold_sample_kernel, dim3(num_layers), dim3(kSampleThreads), 0, s, a);
       RGC_LAUNCHED();
     }
-    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, true>), dim3(num_wgs), block, 0, s, a);
-    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, true>), dim3(num_wgs), block, 0, s, a);
+    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, true, false>), dim3(num_wgs), block, 0, s, a);
+    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, true, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_moments_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
@@ -645,8 +645,8 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
     RGC_LAUNCHED();
     hipLaunchKernelGGL((threshold_emit_kernel<true, true>), dim3(num_wgs), block, 0, s, a);
   } else {
-    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, false>), dim3(num_wgs), block, 0, s, a);
-    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, false>), dim3(num_wgs), block, 0, s, a);
+    if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, false, false>), dim3(num_wgs), block, 0, s, a);
+    else hipLaunchKernelGGL((threshold_accumulate_kernel<false, false, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
