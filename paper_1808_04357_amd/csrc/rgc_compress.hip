@@ -759,7 +759,8 @@ template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs A) {
   __shared__ uint32_t lds_hist[kHistBins];
   __shared__ ResolveShared sh;
-  const uint32_t wg = blockIdx.x;
+  // (every other call walks through the tensors from the end: see streaming_direction() in rgc_api.cpp)
+  const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   LayerState* st = A.state + l;
@@ -1384,7 +1385,7 @@ __device__ __forceinline__ void stream_tile(const CompressArgs& A, uint32_t l, c
 template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) tile_kernel(CompressArgs A) {
   __shared__ uint32_t lds_count[kWavesPerBlock];
-  const uint32_t wg = blockIdx.x;
+  const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;     // (see accumulate_kernel)
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   LayerState* st = A.state + l;
@@ -2304,7 +2305,7 @@ __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) 
   __shared__ ResolveShared sh;
   __shared__ vu2 stage[kWavesPerBlock][kStageEntries];
   __shared__ float stage_u[kWavesPerBlock][kStageEntries];
-  const uint32_t wg = blockIdx.x;
+  const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   if (!L.dense) return;
@@ -2848,7 +2849,7 @@ __global__ void __launch_bounds__(kBlockThreads) grad_sqnorm_kernel(CompressArgs
   // follows: what this pass reads last is what that one reads first, and finds in the memory-side
   // cache (the pair of calls is 18 us shorter on the VGG16-shaped set than with both walking the
   // same way).
-  const uint32_t wg = gridDim.x - 1u - blockIdx.x;
+  const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
