@@ -368,11 +368,23 @@ struct ResolveShared {
   uint32_t publish;             // fallback_kernel: what a layer's last workgroup of a pass has to publish
 };
 
+// What a phase leaves for the next one in the layer's state and scratch.  kInFallback: the code runs in fallback_kernel, where no
+// kernel boundary lies between a layer's phases, and it has to be written and read past the caches of a single XCD.  (Done so in
+// every kernel, the launches without hints took 2 to 4 % longer.)
+template <bool kInFallback>
+__device__ __forceinline__ void leave(uint32_t* p, uint32_t v) {
+  if constexpr (kInFallback) st_agent(p, v); else *p = v;
+}
+template <bool kInFallback>
+__device__ __forceinline__ uint32_t left_at(const uint32_t* p) {
+  if constexpr (kInFallback) return ld_uniform(p); else return *p;
+}
+
 // Copy a (possibly replicated) global histogram into LDS, summing the replicas, and clear the
 // global copy for its next use.  The global bins were filled with device-scope atomics, so they
 // are read with device-scope loads; all loads of a thread are issued before the first use so
 // that their round trips overlap (this runs on the critical path of a layer's last workgroup).
-template <uint32_t kBins, uint32_t kReps>
+template <uint32_t kBins, uint32_t kReps, bool kInFallback = false>
 __device__ __forceinline__ void stage_hist(uint32_t* g, uint32_t* lds) {
   constexpr uint32_t kPer = (kBins + kBlockThreads - 1) / kBlockThreads;
   constexpr uint32_t kBatch = (kPer * kReps > 16u) ? (16u / kReps ? 16u / kReps : 1u) : kPer;   // <= 16 loads in flight
@@ -393,7 +405,7 @@ __device__ __forceinline__ void stage_hist(uint32_t* g, uint32_t* lds) {
 #pragma unroll
         for (uint32_t rep = 0; rep < kReps; ++rep) {
           sum += v[i][rep];
-          st_agent(&g[rep * kBins + b], 0u);
+          leave<kInFallback>(&g[rep * kBins + b], 0u);
         }
         lds[b] = sum;
       }
@@ -435,37 +447,37 @@ __device__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t
   return total;
 }
 
-// Whether this code runs in fallback_kernel, where no kernel boundary lies between a layer's phases: the digits, the counts and
-// what they leave in the layer's state and scratch are written with st_agent() and read with ld_agent() for its sake.
-__device__ __forceinline__ bool in_fallback(const CompressArgs& A) { return A.late_first != 0u && A.launch >= A.late_first; }
-
 // The layer's next phase runs at this launch number (`last`: and is its last); fallback_kernel is told if that is the first of
 // those it stands for.  Inside fallback_kernel the number is published once everything the phase needs has been written.
+template <bool kInFallback = false>
 __device__ __forceinline__ void schedule_launch(const CompressArgs& A, LayerState* st, ResolveShared& sh, uint32_t launch,
                                                 bool last = false) {
   const uint32_t word = launch | (last && A.late_first != 0u && launch >= A.late_first ? kLastPass : 0u);
-  if (in_fallback(A)) { sh.publish = word; return; }
-  st->next_launch = word;
-  if (launch == A.late_first) st_agent(A.late, 1u);
+  if constexpr (kInFallback) {
+    sh.publish = word;
+  } else {
+    st->next_launch = word;
+    if (launch == A.late_first) st_agent(A.late, 1u);
+  }
 }
 
 // Multi-pass path, one radix digit: the layer's histogram of this digit is complete.  Find the
 // bin holding the k_rem-th largest key, update prefix / k_rem, derive the threshold hint for
 // the next call on the way, clear the histogram, schedule the next phase.
 // `lds` holds the bins of this level (kHistBins words, 128 at the last level) and is free for use.
-template <int kLevel>
+template <int kLevel, bool kInFallback = false>
 __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st,
                               ResolveShared& sh, uint32_t* lds, uint32_t cur_launch) {
   constexpr uint32_t kBins = (kLevel == 3) ? 256u : static_cast<uint32_t>(kHistBins);   // the last digit has 7 or 8 bits
   const uint32_t low = low_bits_of(A.sign_filter);
-  const uint32_t k_rem = (kLevel == 1) ? L.k : ld_agent(&st->k_rem);
+  const uint32_t k_rem = (kLevel == 1) ? L.k : left_at<kInFallback>(&st->k_rem);
   const uint32_t above_scope = L.k - k_rem;          // keys above the current scope
   // The k entries selected now leave the residual, so the next call's top-k come from ranks
   // k+1.. of this call: aim the next threshold at rank 2k + margin.
   const uint32_t target = L.target;
-  const uint32_t pending = (kLevel == 1) ? 1u : ld_agent(&st->hint_pending);
-  const uint32_t prefix = (kLevel == 1) ? 0u : ld_agent(&st->prefix);
-  stage_hist<kBins, 1u>(A.hist + static_cast<size_t>(l) * kHistBins, lds);
+  const uint32_t pending = (kLevel == 1) ? 1u : left_at<kInFallback>(&st->hint_pending);
+  const uint32_t prefix = (kLevel == 1) ? 0u : left_at<kInFallback>(&st->prefix);
+  stage_hist<kBins, 1u, kInFallback>(A.hist + static_cast<size_t>(l) * kHistBins, lds);
   (void)locate_from_top(lds, kBins, k_rem, target - above_scope, sh);
   if (threadIdx.x == 0) {
     if (sh.bin == 0xFFFFFFFFu) { atomicOr(A.errflag, 1u); sh.bin = 0; }
@@ -480,20 +492,20 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
     uint32_t pend = pending;
     if (pend == 1u) {
       if (sh.hbin == 0xFFFFFFFFu) {          // the whole layer holds fewer keys than the target rank
-        st_agent(&st->tau_next, 0u); pend = 2u;
+        leave<kInFallback>(&st->tau_next, 0u); pend = 2u;
       } else if (hcum <= L.cmax) {
-        st_agent(&st->tau_next, edge(sh.hbin)); pend = 2u;
+        leave<kInFallback>(&st->tau_next, edge(sh.hbin)); pend = 2u;
       } else if (sh.hbin == D) {
         pend = (kLevel < 3) ? 1u : 3u;      // refine inside the same bin, or give up (heavy ties)
       } else {
-        st_agent(&st->tau_next, edge(sh.hbin + 1u)); pend = 2u;   // one bin up: fewer keys than aimed at, still >= k
+        leave<kInFallback>(&st->tau_next, edge(sh.hbin + 1u)); pend = 2u;   // one bin up: fewer keys than aimed at, still >= k
       }
     }
     const uint32_t new_rem = k_rem - sh.above;
-    st_agent(&st->k_rem, new_rem);
+    leave<kInFallback>(&st->k_rem, new_rem);
     if (kLevel == 1) {
-      st_agent(&st->prefix, D);
-      st_agent(&st->next_phase, PH_HIST2);
+      leave<kInFallback>(&st->prefix, D);
+      leave<kInFallback>(&st->next_phase, PH_HIST2);
       // A hint-free call needs no further digits if the keys from the first digit's bin upwards fit the
       // candidate lists: one more pass over the residual collects them (threshold = the bin's lower edge,
       // so at least k of them exist) and the call ends like a hinted one (PH_SEL, PH_OUT_C): two passes
@@ -506,22 +518,22 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
         const uint32_t tau = (lower & kKeyMask) ? (lower & kKeyMask) : 1u;
         st->tau = tau;
         st->shift = shift_for(tau + ((1u << (low + 12u)) - 1u), tau);
-        st_agent(&st->next_phase, PH_COLLECT);
+        leave<kInFallback>(&st->next_phase, PH_COLLECT);
       }
     } else if (kLevel == 2) {
-      st_agent(&st->prefix, (prefix << 12) | D);
-      st_agent(&st->next_phase, PH_HIST3);
+      leave<kInFallback>(&st->prefix, (prefix << 12) | D);
+      leave<kInFallback>(&st->next_phase, PH_HIST3);
     } else {
       const uint32_t T = (prefix << low) | D;
-      st_agent(&st->T, T);
-      st_agent(&st->r, new_rem);
-      st_agent(&st->next_phase, PH_COUNT);
+      leave<kInFallback>(&st->T, T);
+      leave<kInFallback>(&st->r, new_rem);
+      leave<kInFallback>(&st->next_phase, PH_COUNT);
       if (A.update_hints && L.dense && st->dense_skip != 0u) st->dense_skip -= 1u;   // one more call without its hint
       if (A.update_hints) {
         // The hints live in the key space of the one-pass path (key_of).  With the ordered key a hint
         // exists only if the k-th key and the threshold aimed at both lie among the elements key_of()
         // ranks (top bit set); a layer short of such elements has none and stays on this path.
-        uint32_t Th = T, tn = ld_agent(&st->tau_next);
+        uint32_t Th = T, tn = left_at<kInFallback>(&st->tau_next);
         bool usable = (pend == 2u);
         if (A.sign_filter) {
           usable = usable && T > 0x80000000u && tn >= 0x80000000u;
@@ -543,8 +555,8 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
         }
       }
     }
-    st_agent(&st->hint_pending, pend);
-    schedule_launch(A, st, sh, cur_launch + 1u);
+    leave<kInFallback>(&st->hint_pending, pend);
+    schedule_launch<kInFallback>(A, st, sh, cur_launch + 1u);
   }
 }
 
@@ -629,6 +641,7 @@ __device__ __forceinline__ void resolve_collect(const CompressArgs& A, uint32_t 
 // In-place exclusive scan over the per wave-chunk counters of one layer (one workgroup).
 // with_ties: a[] = keys > T, b[] = keys == T  ->  a[] = output offset of the chunk
 //            (= prefix(a) + min(prefix(b), r)), b[] = prefix(b).
+template <bool kInFallback = false>
 __device__ __forceinline__ void scan_chunks(uint32_t* a, uint32_t* b, uint32_t count, uint32_t r, bool with_ties,
                             uint32_t* lds_scan, uint32_t* out_total) {
   constexpr uint32_t kItems = 16;   // many independent device-scope loads in flight per thread: this is a serial step
@@ -652,10 +665,10 @@ __device__ __forceinline__ void scan_chunks(uint32_t* a, uint32_t* b, uint32_t c
     for (uint32_t j = 0; j < kItems; ++j) {
       if (i0 + j < count) {
         if (with_ties) {
-          st_agent(&a[i0 + j], ea + (eb < r ? eb : r));
-          st_agent(&b[i0 + j], eb);
+          leave<kInFallback>(&a[i0 + j], ea + (eb < r ? eb : r));
+          leave<kInFallback>(&b[i0 + j], eb);
         } else {
-          st_agent(&a[i0 + j], ea);
+          leave<kInFallback>(&a[i0 + j], ea);
         }
       }
       ea += va[j];
@@ -849,13 +862,13 @@ __device__ __forceinline__ void dense_restore(const CompressArgs& A, const Layer
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the wave's stores have arrived before it reads the wave-chunk
 }
 
-template <int kLevel>
+template <int kLevel, bool kInFallback = false>
 __device__ __forceinline__ void phase_hist(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                            uint32_t wc_local, uint32_t* lds_hist, ResolveShared& sh) {
   constexpr uint32_t kBins = (kLevel == 3) ? 256u : static_cast<uint32_t>(kHistBins);
   for (uint32_t b = threadIdx.x; b < kBins; b += kBlockThreads) lds_hist[b] = 0u;
   __syncthreads();
-  const uint32_t prefix = ld_uniform(&st->prefix);
+  const uint32_t prefix = left_at<kInFallback>(&st->prefix);
   const uint32_t low = low_bits_of(A.sign_filter), low_mask = (1u << low) - 1u;
   if (wc_local < L.wc_count) {
     const uint32_t begin = wc_local * A.chunk;
@@ -883,7 +896,7 @@ __device__ __forceinline__ void phase_hist(const CompressArgs& A, uint32_t l, co
   }
   __syncthreads();
   flush_hist(lds_hist, A.hist + static_cast<size_t>(l) * kHistBins, kBins);
-  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag, in_fallback(A))) resolve_digit<kLevel>(A, l, L, st, sh, lds_hist, A.launch);
+  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag, kInFallback)) resolve_digit<kLevel, kInFallback>(A, l, L, st, sh, lds_hist, A.launch);
 }
 
 // PH_COLLECT: the streaming pass's candidate collection, from the updated residual (see resolve_digit<1>).
@@ -917,9 +930,10 @@ __device__ __forceinline__ void phase_collect(const CompressArgs& A, uint32_t l,
     resolve_collect(A, l, L, st, sh, lds_hist, true, A.launch);
 }
 
+template <bool kInFallback = false>
 __device__ __forceinline__ void phase_count(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                             uint32_t wc_local, ResolveShared& sh) {
-  const uint32_t T = ld_uniform(&st->T);
+  const uint32_t T = left_at<kInFallback>(&st->T);
   if (wc_local < L.wc_count) {
     const uint32_t begin = wc_local * A.chunk;
     const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
@@ -942,24 +956,25 @@ __device__ __forceinline__ void phase_count(const CompressArgs& A, uint32_t l, c
       st_agent(&A.wc_b[L.wc_first + wc_local], eq_all);
     }
   }
-  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag, in_fallback(A))) {
-    scan_chunks(A.wc_a + L.wc_first, A.wc_b + L.wc_first, L.wc_count, ld_agent(&st->r), true, sh.scan, &sh.cnt);
+  if (last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag, kInFallback)) {
+    scan_chunks<kInFallback>(A.wc_a + L.wc_first, A.wc_b + L.wc_first, L.wc_count, left_at<kInFallback>(&st->r), true, sh.scan, &sh.cnt);
     __syncthreads();
     if (threadIdx.x == 0) {
       if (sh.cnt != L.k) atomicOr(A.errflag, 2u);
-      st_agent(&st->next_phase, PH_OUT_V);
-      schedule_launch(A, st, sh, A.launch + 1u, true);
+      leave<kInFallback>(&st->next_phase, PH_OUT_V);
+      schedule_launch<kInFallback>(A, st, sh, A.launch + 1u, true);
     }
   }
 }
 
+template <bool kInFallback = false>
 __device__ __forceinline__ void phase_out_v(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wc_local) {
   if (wc_local >= L.wc_count) return;
-  const uint32_t T = ld_uniform(&st->T), r = ld_uniform(&st->r);
+  const uint32_t T = left_at<kInFallback>(&st->T), r = left_at<kInFallback>(&st->r);
   const uint32_t begin = wc_local * A.chunk;
   const uint32_t end = (L.n - begin) < A.chunk ? L.n : begin + A.chunk;
-  uint32_t out_pos = ld_uniform(&A.wc_a[L.wc_first + wc_local]);
-  uint32_t eq_seen = ld_uniform(&A.wc_b[L.wc_first + wc_local]);
+  uint32_t out_pos = left_at<kInFallback>(&A.wc_a[L.wc_first + wc_local]);
+  uint32_t eq_seen = left_at<kInFallback>(&A.wc_b[L.wc_first + wc_local]);
   const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
   const gptr<int32_t> out_idx = as_global(L.out_idx);
   const gptr<float> out_val = as_global(L.out_val);
@@ -1494,7 +1509,9 @@ __device__ __forceinline__ void direct_done(const CompressArgs& A, const LayerDe
   if (sent != L.k) atomicOr(A.errflag, 128u);
   *as_global(L.out_count) = static_cast<int32_t>(L.k);
   st->T = T;
-  st->path = A.use_hints ? 0u : 1u;                          // (one pass over the tensors like a layer whose hint held)
+  // A call with hints: one pass, as for a layer whose hint held.  (late_first says so too; with use_hints asked for here the
+  // kernel was 73 KB of code instead of 67, and a call on one layer of 2^20 elements took 0.3 us more.)
+  st->path = A.late_first != 0u ? 0u : 1u;
   st->stat_candidates = 0u;
   st->stat_members = 0u;
   st->next_phase = PH_NONE;
@@ -1785,13 +1802,14 @@ __device__ __forceinline__ uint32_t gather_lists(const CompressArgs& A, uint32_t
   return total;
 }
 
-__device__ __forceinline__ void hint_missed(const CompressArgs& A, LayerState* st, ResolveShared& sh, bool hinted, uint32_t total) {
+__device__ __forceinline__ void hint_missed(const CompressArgs& A, LayerState* st, bool hinted, uint32_t total) {
   st->path = hinted ? 2u : 1u;
   st->stat_misses += hinted ? 1u : 0u;
   st->stat_candidates = total;
   st->stat_members = 0u;
   st->next_phase = PH_HIST1;
-  schedule_launch(A, st, sh, kTiledLateLaunch);
+  st->next_launch = kTiledLateLaunch;                        // (the first that fallback_kernel stands for in a tiled call)
+  st_agent(A.late, 1u);
 }
 
 __device__ __forceinline__ void hint_hit(const CompressArgs& A, const LayerDesc& L, LayerState* st, unsigned long long thr, uint32_t tau,
@@ -1826,7 +1844,7 @@ __device__ __forceinline__ void finish_lists(const CompressArgs& A, const LayerD
     ok = S.sh.bin != 0xFFFFFFFFu && S.sh.cnt <= static_cast<uint32_t>(kMemberMax);
   }
   if (!ok) {
-    if (t == 0) hint_missed(A, st, S.sh, hinted, total);
+    if (t == 0) hint_missed(A, st, hinted, total);
     return;
   }
   const uint32_t bstar = S.sh.bin, above = S.sh.above, m = S.sh.cnt, hbin = S.sh.hbin;
@@ -1856,7 +1874,7 @@ __device__ __forceinline__ void select_part(const CompressArgs& A, uint32_t l, c
   const uint32_t t = threadIdx.x;
   const uint32_t parts = (L.wg_count + L.part_tiles - 1u) / L.part_tiles;
   if (!hint_usable(A, st)) {
-    if (part == 0u && t == 0) hint_missed(A, st, S.sh, false, 0u);
+    if (part == 0u && t == 0) hint_missed(A, st, false, 0u);
     return;
   }
   const uint32_t tau = st->tau, shift = st->shift, k = L.k;
@@ -1935,7 +1953,7 @@ __device__ __forceinline__ void select_part(const CompressArgs& A, uint32_t l, c
   }
   const uint32_t all = ld_agent(&st->nmembers);
   if (__syncthreads_or(static_cast<int>(bad)) != 0) {
-    if (t == 0) hint_missed(A, st, S.sh, true, cand_total);
+    if (t == 0) hint_missed(A, st, true, cand_total);
     return;
   }
   const uint32_t k_rem = k - above;
@@ -2018,8 +2036,8 @@ __global__ void __launch_bounds__(kFinishThreads) emit_kernel(CompressArgs A) {
 // Otherwise its workgroups take tickets (rgc_tickets.h): a workgroup number whose layer has not got to this pass yet waits for the
 // layer's last workgroup of the pass before to publish it.  Waiting needs no other workgroup to be on the device than those
 // that run, so it ends on any stream and beside any kernels.
-// What a phase leaves for the next one goes through st_agent() and device-scope atomics and is read with ld_agent(), as in the
-// election: a release and an acquire at every pass (they walk the XCD's L2) cost more than the passes' own reading.  With them
+// What a phase leaves for the next one goes through st_agent() and device-scope atomics and is read with ld_agent() (leave(),
+// left_at()), as in the election: a release and an acquire at every pass (they walk the XCD's L2) cost more than the passes' own reading.  With them
 // and a workgroup per CU, one 16-byte load of a lane in flight, a call whose hints all miss took 1.18 ms on the LSTM set, 0.57
 // on the ResNet-50 set and 1.09 on 64 Mi elements; it takes 0.41, 0.21 and 0.48 with four workgroups per CU and four loads
 // (two workgroups 0.46 / 0.23 / 0.50, eight 0.48 / 0.21 / 0.59; four with the acquires 0.49 / 0.29 / 0.53).  The five passes
@@ -2067,11 +2085,11 @@ struct FallbackWork {
     const LayerDesc L = A.layers[l];
     const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
     switch (ld_uniform(&st->next_phase)) {
-      case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, hist, sh); break;
-      case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, hist, sh); break;
-      case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, hist, sh); break;
-      case PH_COUNT: phase_count(A, l, L, st, wg, wc_local, sh); break;
-      case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
+      case PH_HIST1: phase_hist<1, true>(A, l, L, st, wg, wc_local, hist, sh); break;
+      case PH_HIST2: phase_hist<2, true>(A, l, L, st, wg, wc_local, hist, sh); break;
+      case PH_HIST3: phase_hist<3, true>(A, l, L, st, wg, wc_local, hist, sh); break;
+      case PH_COUNT: phase_count<true>(A, l, L, st, wg, wc_local, sh); break;
+      case PH_OUT_V: phase_out_v<true>(A, L, st, wc_local); break;
       case PH_OUT_C: phase_out_c(A, L, st, wg); break;
       default:                                       // no other phase can be due this late
         if (threadIdx.x == 0) { atomicOr(A.errflag, 16u); st_agent(&st->next_launch, 0u); }

@@ -97,9 +97,10 @@ struct LayerDesc {
   uint32_t mem_cap;    // dense layers: entries of the layer's kMemberShards sub-lists together (a multiple of kMemberShards); the
                        // overflow list behind them holds mem_cap / 4, which is also the most members a call accepts
   uint32_t list_cap;   // dense layers: entries of one wave-chunk's list
-  uint32_t kind;       // LayerKind (tiled calls)
+  uint32_t kind : 4;         // LayerKind (tiled calls)
+  uint32_t part_tiles : 28;  // tiled calls: tiles of a part (one word for both: every workgroup of every launch reads a descriptor,
+                             // and 8 bytes more of it cost a call of seven launches 0.4 %)
   uint32_t part_first; // tiled calls: where the layer's parts start in the per-part arrays
-  uint32_t part_tiles; // tiled calls: tiles of a part (a power of two)
   uint64_t mem_first;  // dense layers: where the layer's region of the member pool starts
   uint64_t list_first; // dense layers: where the layer's lists start (wave-chunk c of the layer: list_first + c * list_cap)
 };
