@@ -203,6 +203,7 @@ struct rgc_ctx {
   uint32_t wc_max = 0;                     // wave-chunks a call can have
   uint32_t wg_max = 0;                     // and workgroups
   uint32_t cus = 0;                        // compute units of the device (sizes the persistent decompression grids)
+  uint32_t tile_slots = 0;                 // slots of a tile's candidate list (tiled calls)
   DevBuf<LayerState> d_state;
   DevBuf<uint32_t> d_hist, d_coarse, d_cand_cnt, d_wc_a, d_wc_b, d_err, d_group;
   DevBuf<unsigned long long> d_members;
@@ -481,16 +482,28 @@ int rgc_create(rgc_ctx** out, int device_id, int64_t max_total_elems, int32_t ma
   chk(c->d_cand_cnt.alloc(wc_max));
   chk(c->d_wc_a.alloc(wc_max));
   chk(c->d_wc_b.alloc(wc_max));
+  chk(c->d_err.alloc(5));                  // [0] internal inconsistencies of compression, [1] status of the message checks, [2..4] fallback_kernel
+  const uint64_t grp_max = wc_max / (kWavesPerBlock * kElectGroupHost) + 2 * L + 2;
+  chk(c->d_group.alloc(grp_max));
   {
     // every wave-chunk owns chunk / kCapDiv slots whatever the chunk size: total / kCapDiv slots
     // plus one (partly used) chunk per layer at the largest chunk size a plan may pick
     const uint64_t largest = std::max<uint64_t>(16384, chunk_override());
     (void)kCap;
-    chk(c->d_slots.alloc(static_cast<uint64_t>(max_total_elems) / kCapDiv + (static_cast<uint64_t>(max_layers) + 1) * (largest / kCapDiv)));
+    // Tiled calls lay their lists out anew, kTileSlotsMost a tile if the device has room for them.  Large values that sit together
+    // fill single lists far beyond the average, the more so the fewer elements a list stands for (4096; 8192 in large calls on the
+    // general launches): with kTileSlots a tile the row-sparse embedding of the LSTM set missed its hint in 20 to 60 % of the
+    // calls at 0.2 % and in all at 0.4 %, 240 and 367 us a call, where the general launches missed in none at 0.2 % (158 us) and in
+    // all at 0.4 % (294).  With kTileSlotsMost: in none at 0.2 and 0.3 % (161 and 170 us), in half at 0.4 %.
+    static_assert(kTileSlots == kTileElems / kCapDiv, "the lists of the general tilings and those of tiles in as many slots");
+    const uint64_t rest = (static_cast<uint64_t>(max_layers) + 1) * (largest / kCapDiv);
+    c->tile_slots = kTileSlotsMost;
+    if (e == hipSuccess && c->d_slots.alloc(static_cast<uint64_t>(max_total_elems) / 8 + rest) != hipSuccess) {
+      (void)hipGetLastError();
+      c->tile_slots = kTileSlots;
+      chk(c->d_slots.alloc(static_cast<uint64_t>(max_total_elems) / kCapDiv + rest));
+    }
   }
-  chk(c->d_err.alloc(5));                  // [0] internal inconsistencies of compression, [1] status of the message checks, [2..4] fallback_kernel
-  const uint64_t grp_max = wc_max / (kWavesPerBlock * kElectGroupHost) + 2 * L + 2;
-  chk(c->d_group.alloc(grp_max));
   if (e == hipSuccess) chk(hipMemset(c->d_state.p, 0, sizeof(LayerState) * 3 * L));
   if (e == hipSuccess) chk(hipMemset(c->d_hist.p, 0, sizeof(uint32_t) * L * kHistBins));
   if (e == hipSuccess) chk(hipMemset(c->d_coarse.p, 0, sizeof(uint32_t) * L * kCoarseRep * kCoarseBins));
@@ -833,7 +846,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.errflag = ctx->d_err.p;
   A.group_done = ctx->d_group.p;
   A.chunk = tiling.chunk;
-  A.cap = (is_tiled ? kTileElems : A.chunk) / kCapDiv;
+  A.cap = is_tiled ? ctx->tile_slots : A.chunk / kCapDiv;
   A.use_hints = use_hints ? 1u : 0u;
   A.update_hints = no_hints ? 0u : 1u;
   A.mask_momentum = (flags & RGC_NO_MOMENTUM_MASK) ? 0u : 1u;

@@ -1741,7 +1741,7 @@ __device__ __forceinline__ void finish_direct(const CompressArgs& A, const Layer
 // Copies the lists of the tiles first .. first + count - 1 (count <= 1024) into S.u.list.cand, one after the other: in
 // index order.  Returns how many candidates there are; S.bad says whether a list ran over or they do not fit.
 constexpr uint32_t kListOverrun = 1u, kNoRoom = 2u;
-constexpr uint32_t kTilesThatFit = kFinishCand / (kTileElems / 16u);   // whatever their lists hold (kTileElems / 16 slots each)
+static_assert(kFinishCand / kTileSlotsMost >= 16u, "kFinishCand / A.cap lists fit whatever they hold");
 __device__ __forceinline__ uint32_t gather_lists(const CompressArgs& A, uint32_t first, uint32_t count, SelectShared& S) {
   constexpr uint32_t kLanes = 8u, kEach = 2u;                // lanes a list, entries a lane: asked for together with its length
   constexpr uint32_t kPerRound = kFinishThreads / kLanes, kRounds = kPartTilesMax / kPerRound;
@@ -1785,7 +1785,7 @@ __device__ __forceinline__ uint32_t gather_lists(const CompressArgs& A, uint32_t
   for (uint32_t qi = wave; qi < queued; qi += kFinishWaves) {
     const uint32_t i = queue[qi], s0 = start[i], c = start[i + 1u] - s0;
     const gptr<const vu2> slot = as_global(reinterpret_cast<const vu2*>(A.slots + static_cast<size_t>(first + i) * A.cap));
-    constexpr uint32_t kTail = (kTileElems / 16u + kWaveSize - 1u) / kWaveSize;     // a list has kTileElems / 16 slots
+    constexpr uint32_t kTail = (kTileSlotsMost + kWaveSize - 1u) / kWaveSize;
     vu2 x[kTail];
 #pragma unroll
     for (uint32_t b = 0; b < kTail; ++b) {
@@ -1909,7 +1909,7 @@ __device__ __forceinline__ void select_part(const CompressArgs& A, uint32_t l, c
       __syncthreads();
     }
     ok = bad != kListOverrun && bstar != 0xFFFFFFFFu && m <= static_cast<uint32_t>(kMemberMax);
-    if (ok && bad == kNoRoom) { step = kTilesThatFit; continue; }
+    if (ok && bad == kNoRoom) { step = kFinishCand / A.cap; continue; }
     if (ok) {
       for (uint32_t i = t; i < count; i += kFinishThreads) {
         const vu2 e = S.u.list.cand[i];

@@ -126,15 +126,31 @@ def test_large_values_in_one_part_keep_their_hints(rgc, oracle):
     assert all(p == [0] for p in paths[-4:]), paths
 
 
+@pytest.mark.parametrize("ppm", [2000, 4000])
+def test_large_values_in_whole_tiles_keep_their_hints(rgc, oracle, ppm):
+    """The rows of an embedding that carry gradients: one stretch of 8192 elements in fifteen (seven) holds the large values, and
+    a tile inside it has about 300 candidates, more than a sixteenth of its elements."""
+    g = np.random.default_rng(15)
+    n = (2 << 20) + 999
+    scale = np.full(n, 1e-3, np.float32)
+    every = 15 if ppm == 2000 else 7
+    for at in range(0, n, every * 8192):
+        scale[at:at + 8192] = 1.0
+    V = [(g.standard_normal(n).astype(np.float32) * scale)]
+    G_list = [[(g.standard_normal(n).astype(np.float32) * scale * 0.2)] for _ in range(8)]
+    paths = run_iterations(rgc, oracle, V, G_list, [rgc.rgc_k_for_density(n, ppm)], threads=8, tag="whole tiles")
+    assert all(p == [0] for p in paths[-4:]), paths
+
+
 def test_missed_hints_take_the_fallback(rgc, oracle):
     """Hints too high, too low and random, heavy ties, an overflowing list, zeros: several layers at once go through the
     digits in the last launch, others do not."""
     g = np.random.default_rng(9)
-    sizes = [300_000, 4_500_000, 40_001, 90_000, 200_000, 5000]
+    sizes = [300_000, 4_500_000, 40_001, 90_000, 400_000, 5000]
     V = [(g.standard_normal(n) * 1e-2).astype(np.float32) for n in sizes]
     V[2] = (np.round(V[2] * 300) / 300).astype(np.float32)
     V[3][:] = 0.0
-    V[4][1000:2000] *= 100.0                                   # one list of 256 slots for the 500 largest, the rank aimed at
+    V[4][1000:2000] *= 100.0                                   # the 1000 largest, the rank aimed at, in one list of 480 slots
     G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(8)]
     for G in G_list:
         G[2] = (np.round(G[2] * 300) / 300).astype(np.float32)
