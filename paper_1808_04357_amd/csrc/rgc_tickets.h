@@ -12,15 +12,15 @@
 namespace rgc {
 
 struct TicketOrder {
-  uint32_t units, per_ticket;   // a ticket: this many consecutive units
+  uint32_t units;
   uint32_t slices, passes;      // tickets of a pass, passes
 };
 
-// Passes of about `wanted` tickets each.
+// Passes of at most `wanted` tickets each.  A ticket's units lie `slices` apart: those of one layer, which may be the only one with
+// anything to do, go to as many tickets as it has units.
 constexpr TicketOrder ticket_order(uint32_t units, uint32_t wanted, uint32_t passes) {
   const uint32_t most = wanted < 1u ? 1u : wanted;
-  const uint32_t per = units < 1u ? 1u : (units + most - 1u) / most;
-  return TicketOrder{units, per, (units + per - 1u) / per, passes};
+  return TicketOrder{units, units < 1u ? 1u : units < most ? units : most, passes};
 }
 
 // What a layer publishes: the launch number it is due at, with kLastPass if no other follows.  Launch numbers below the first
@@ -40,9 +40,7 @@ constexpr Due due_at(uint32_t published, uint32_t launch, uint32_t first) {
 template <typename Work>
 constexpr void run_tickets(const TicketOrder& o, uint32_t first, Work& work) {
   for (uint32_t t = work.take(); t < o.slices * o.passes; t = work.take()) {
-    const uint32_t begin = t % o.slices * o.per_ticket;
-    const uint32_t end = o.units - begin < o.per_ticket ? o.units : begin + o.per_ticket;
-    for (uint32_t u = begin; u < end; ++u) work.unit(u, first + t / o.slices);
+    for (uint32_t u = t % o.slices; u < o.units; u += o.slices) work.unit(u, first + t / o.slices);
   }
 }
 
