@@ -871,7 +871,6 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
       dense_ok = false;
     }
   }
-  A.dense_ok = dense_ok ? 1u : 0u;
   const bool dense = dense_ok && A.use_hints;
   A.slots2 = ctx->d_slots2.p;
   A.slots_u = ctx->d_slots_u.p;
@@ -887,10 +886,9 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.grad_scale = grad_scale;
   A.m = momentum;
   A.launch = 1;
-  // Dense layers that have a hint are streamed by a kernel of their own and skipped by accumulate_kernel (both
-  // decide from the same state, which neither changes before its layer is done).  They are ranked at launch 2 and
-  // written at launch 3 by lists_kernel; one whose hint misses has its residual put right at launch 2, where it
-  // also starts on the five passes.
+  // In a call with dense layers and hints, collect_kernel streams every layer, and lists_kernel takes launches 2 and 3 (a dense
+  // layer is ranked at 2 and written at 3; one whose hint misses has its residual put right at launch 2, where it also starts
+  // on the five passes).
   A.late = ctx->d_err.p + 2;
   if (A.use_hints) {
     A.late_first = is_tiled ? kTiledLateLaunch : kFirstLateLaunch;
@@ -898,8 +896,8 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   }
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));
   if (is_tiled) RGC_HIP(launch_tiles(A, num_wgs, stream));
+  else if (dense) RGC_HIP(launch_collect(A, num_wgs, stream));
   else RGC_HIP(launch_accumulate(A, num_wgs, stream));
-  if (dense) RGC_HIP(launch_collect(A, num_wgs, stream));
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));
   if (is_tiled) {
     RGC_HIP(launch_select(A, tiling.parts, stream));
@@ -918,8 +916,8 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
         break;
       }
       A.launch = static_cast<uint32_t>(launch);
-      RGC_HIP(launch_phase(A, num_wgs, stream));
       if (dense && launch <= 3) RGC_HIP(launch_lists(A, num_wgs, stream));
+      else RGC_HIP(launch_phase(A, num_wgs, stream));
     }
   }
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_compress));

@@ -419,7 +419,7 @@ __device__ __forceinline__ void stage_hist(uint32_t* g, uint32_t* lds) {
 // sh.{hbin,hcum,hcnt} (bin = ~0 when the total stays below the wanted count); returns the total.
 // Kept light on registers: this code shares a kernel with the streaming loop.
 template <uint32_t kThreads = kBlockThreads>
-__device__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t want_k, uint32_t want_h,
+__device__ __forceinline__ uint32_t locate_from_top(const uint32_t* lds, uint32_t bins, uint32_t want_k, uint32_t want_h,
                                     ResolveShared& sh) {
   const uint32_t t = threadIdx.x;
   const uint32_t per = bins >= kThreads ? bins / kThreads : 1u;
@@ -690,7 +690,7 @@ __device__ __forceinline__ void scan_chunks(uint32_t* a, uint32_t* b, uint32_t c
 // it; hist holds 3 * 256 words.
 static_assert(kBlockThreads == 256, "one thread per histogram bin");   // (PH_SEL also counts on hist holding 3 * kBlockThreads words)
 template <uint32_t kThreads = kBlockThreads>
-__device__ unsigned long long select_kth_largest(const unsigned long long* v, uint32_t m, uint32_t kk,
+__device__ __forceinline__ unsigned long long select_kth_largest(const unsigned long long* v, uint32_t m, uint32_t kk,
                                                  uint32_t* hist, ResolveShared& sh) {
   const uint32_t t = threadIdx.x, lane = lane_id();
   const unsigned long long v0 = v[0];
@@ -768,17 +768,12 @@ __device__ __forceinline__ unsigned long long composite(uint32_t key, uint32_t i
 }  // namespace
 
 // =================================================================== launch 1: streaming pass
+namespace {
+
+// One workgroup of a layer that has no hint or one for the short lists.  lds_hist holds kHistBins words.
 template <bool kNt>
-__global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs A) {
-  __shared__ uint32_t lds_hist[kHistBins];
-  __shared__ ResolveShared sh;
-  // (every other call walks through the tensors from the end: see streaming_direction() in rgc_api.cpp)
-  const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
-  const uint32_t l = A.wg2layer[wg];
-  const LayerDesc L = A.layers[l];
-  LayerState* st = A.state + l;
-  const bool hinted = hint_usable(A, st);
-  if (A.dense_ok && L.dense && hinted && st->dense_skip == 0u) return;     // collect_kernel has this layer
+__device__ __forceinline__ void accumulate_layer(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
+                                                 bool hinted, uint32_t* lds_hist, ResolveShared& sh) {
   const bool collect = hinted && L.hintable;
   // the same LDS array serves as 4096-bin digit histogram (hint-free) or 1024-bin coarse one
   const uint32_t lds_bins = collect ? static_cast<uint32_t>(kCoarseBins) : static_cast<uint32_t>(kHistBins);
@@ -832,8 +827,122 @@ __global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs 
   }
 }
 
+}  // namespace
+
+template <bool kNt>
+__global__ void __launch_bounds__(kBlockThreads) accumulate_kernel(CompressArgs A) {
+  __shared__ uint32_t lds_hist[kHistBins];
+  __shared__ ResolveShared sh;
+  // (every other call walks through the tensors from the end: see streaming_direction() in rgc_api.cpp)
+  const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  const uint32_t l = A.wg2layer[wg];
+  const LayerDesc L = A.layers[l];
+  LayerState* st = A.state + l;
+  accumulate_layer<kNt>(A, l, L, st, wg, hint_usable(A, st), lds_hist, sh);
+}
+
 // =================================================================== launches 2..6: phases
 namespace {
+
+// The members of a dense layer: kMemberLists lists in global memory (region + s * shard_cap, n[s] entries; the last
+// one, for what the others could not hold, is longer), which other workgroups filled with device-scope stores.
+// A thread asks for one value of every list at a time, so that their round trips overlap.
+struct MemberLists {
+  const unsigned long long* region;
+  uint32_t shard_cap;
+  const uint32_t* first;  // [kMemberLists + 1], in LDS: running number of each list's first member; [kMemberLists] = all
+};
+
+template <typename F>
+__device__ __forceinline__ void for_each_member(const MemberLists& M, F&& f) {
+  // one step takes the i-th member of every list: kMemberLists independent loads of a thread in flight
+  uint32_t n[kMemberLists], nmax = 0u;
+#pragma unroll
+  for (uint32_t s = 0; s < kMemberLists; ++s) {
+    n[s] = M.first[s + 1] - M.first[s];
+    nmax = n[s] > nmax ? n[s] : nmax;
+  }
+  for (uint32_t i = threadIdx.x; i < nmax; i += kBlockThreads) {
+    unsigned long long x[kMemberLists];
+#pragma unroll
+    for (uint32_t s = 0; s < kMemberLists; ++s)
+      x[s] = i < n[s] ? __hip_atomic_load(&M.region[static_cast<size_t>(s) * M.shard_cap + i], __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT)
+                      : 0ull;
+#pragma unroll
+    for (uint32_t s = 0; s < kMemberLists; ++s)
+      if (i < n[s]) f(x[s]);
+  }
+}
+
+// select_kth_largest() for such members (there may be more of them than the LDS holds): the same radix
+// selection, every digit one more pass over the values.  `any` is one of the values.  hist holds 3 * 256 words.
+__device__ __forceinline__ unsigned long long select_kth_largest_global(const MemberLists& M, unsigned long long any, uint32_t kk,
+                                                        uint32_t* hist, ResolveShared& sh) {
+  const uint32_t t = threadIdx.x, lane = lane_id();
+  const unsigned long long v0 = any;
+  unsigned long long diff = 0ull;
+  for_each_member(M, [&](unsigned long long x) { diff |= x ^ v0; });
+  int top = diff ? 63 - __clzll(static_cast<long long>(diff)) : -1;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const int other = __shfl_xor(top, o);
+    top = other > top ? other : top;
+  }
+  if (lane == 0) sh.scan[t >> 6] = static_cast<uint32_t>(top + 1);
+  hist[t] = 0u; hist[256u + t] = 0u; hist[512u + t] = 0u;
+  __syncthreads();
+  {
+    const uint32_t a = sh.scan[0], b = sh.scan[1], c = sh.scan[2], d = sh.scan[3];
+    const uint32_t ab = a > b ? a : b, cd = c > d ? c : d;
+    top = static_cast<int>(ab > cd ? ab : cd) - 1;
+  }
+  if (top < 0) return v0;                                   // a single value
+  int shift = (top >> 3) << 3;
+  unsigned long long prefix = shift == 56 ? 0ull : (v0 & (~0ull << (shift + 8)));
+  for (uint32_t pass = 0;; ++pass, shift -= 8) {
+    uint32_t* const H = hist + (pass % 3u) * 256u;
+    const unsigned long long himask = shift == 56 ? 0ull : (~0ull << (shift + 8));
+    for_each_member(M, [&](unsigned long long x) {
+      if ((x & himask) == prefix) atomicAdd(&H[static_cast<uint32_t>(x >> shift) & 255u], 1u);
+    });
+    __syncthreads();
+    hist[((pass + 2u) % 3u) * 256u + t] = 0u;
+    const uint32_t h0 = H[4u * lane], h1 = H[4u * lane + 1u], h2 = H[4u * lane + 2u], h3 = H[4u * lane + 3u];
+    const uint32_t mine = h0 + h1 + h2 + h3;
+    const uint32_t incl = wave_incl_scan(mine);
+    const uint32_t higher = wave_total(incl) - incl;
+    const bool here = higher < kk && kk <= higher + mine;
+    uint32_t bin = 0, above = 0, cnt = 0;
+    if (here) {
+      uint32_t a = higher;
+      if (kk <= a + h3) { bin = 3u; cnt = h3; }
+      else { a += h3; if (kk <= a + h2) { bin = 2u; cnt = h2; }
+      else { a += h2; if (kk <= a + h1) { bin = 1u; cnt = h1; }
+      else { a += h1; bin = 0u; cnt = h0; } } }
+      bin += 4u * lane;
+      above = a;
+    }
+    const unsigned long long who = __ballot(here);          // exactly one lane when 1 <= kk <= values in scope
+    const int src = who ? static_cast<int>(__ffsll(static_cast<long long>(who))) - 1 : 0;
+    bin = static_cast<uint32_t>(__shfl(static_cast<int>(bin), src));
+    above = static_cast<uint32_t>(__shfl(static_cast<int>(above), src));
+    cnt = static_cast<uint32_t>(__shfl(static_cast<int>(cnt), src));
+    prefix |= static_cast<unsigned long long>(bin) << shift;
+    kk -= above;
+    if (shift == 0) return prefix;                          // the composites are distinct: this is the value itself
+    if (cnt <= 1u) break;
+  }
+  // one value is left under these leading bytes: whoever holds it tells the others
+  const unsigned long long lomask = ~0ull << shift;
+  for_each_member(M, [&](unsigned long long x) {
+    if ((x & lomask) == prefix) { sh.hbin = static_cast<uint32_t>(x); sh.hcum = static_cast<uint32_t>(x >> 32); }
+  });
+  __syncthreads();
+  const unsigned long long r = (static_cast<unsigned long long>(sh.hcum) << 32) | sh.hbin;
+  __syncthreads();
+  return r;
+}
 
 // PH_RESTORE, a dense layer whose hint missed: the entries its streaming pass masked on the strength of the hint
 // (keys from the expected k-th key upwards) get their accumulated value and their velocity back from the wave-chunk's
@@ -1026,8 +1135,10 @@ __device__ __forceinline__ void phase_out_v(const CompressArgs& A, const LayerDe
 // Hinted path: every wave looks at its own candidate list; candidates of the coarse bin that
 // holds the k-th key become "members" (ranked exactly by the last workgroup), candidates of
 // higher bins are counted as certainly selected.
+// sortbuf holds kRoom members; should there be more (kRoom < kMemberMax: lists_kernel), they are ranked where they are.
+template <uint32_t kRoom>
 __device__ __forceinline__ void phase_sel(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
-                          unsigned long long* sortbuf, uint32_t* sel_hist, ResolveShared& sh) {
+                          unsigned long long* sortbuf, uint32_t* sel_hist, uint32_t* shard_first, ResolveShared& sh) {
   // The lists are short (a few dozen entries), so this phase is a chain of dependent loads per
   // workgroup and little else: one workgroup in A.list_group takes the lists of that many
   // workgroups, with the loads of all of them in flight together; the others leave at once.
@@ -1109,10 +1220,20 @@ __device__ __forceinline__ void phase_sel(const CompressArgs& A, uint32_t l, con
       if (g < groups) gsum[j] = ld_agent(&A.wc_b[L.wc_first + g]);
     }
   }
-  for (uint32_t i = threadIdx.x; i < m; i += kBlockThreads)
-    sortbuf[i] = __hip_atomic_load(&members[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  const unsigned long long thr = select_kth_largest(sortbuf, m, k_rem, sel_hist, sh);
+  auto member = [&](uint32_t i) { return __hip_atomic_load(&members[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  unsigned long long thr;
+  const bool here = kRoom >= static_cast<uint32_t>(kMemberMax) || m <= kRoom;
+  if (here) {
+    for (uint32_t i = threadIdx.x; i < m; i += kBlockThreads) sortbuf[i] = member(i);
+    __syncthreads();
+    thr = select_kth_largest(sortbuf, m, k_rem, sel_hist, sh);
+  } else {
+    // (as kMemberLists consecutive pieces of the one list they form)
+    const uint32_t each = (m + kMemberLists - 1u) / kMemberLists;
+    if (threadIdx.x <= kMemberLists) shard_first[threadIdx.x] = threadIdx.x * each < m ? threadIdx.x * each : m;
+    __syncthreads();
+    thr = select_kth_largest_global(MemberLists{members, each, shard_first}, member(0), k_rem, sel_hist, sh);
+  }
   __syncthreads();                                  // every wave is done with the selection's histograms
   if (in_lds) {
     sel_hist[threadIdx.x] = 0u; sel_hist[kBlockThreads + threadIdx.x] = 0u; sel_hist[2u * kBlockThreads + threadIdx.x] = 0u;
@@ -1120,8 +1241,9 @@ __device__ __forceinline__ void phase_sel(const CompressArgs& A, uint32_t l, con
   }
   // members not below thr are selected: credit them to their wave-chunks (and to the chunks' groups)
   for (uint32_t i = threadIdx.x; i < m; i += kBlockThreads) {
-    if (sortbuf[i] < thr) continue;
-    const uint32_t idx = 0xFFFFFFFFu - static_cast<uint32_t>(sortbuf[i] & 0xFFFFFFFFull);
+    const unsigned long long x = here ? sortbuf[i] : member(i);
+    if (x < thr) continue;
+    const uint32_t idx = 0xFFFFFFFFu - static_cast<uint32_t>(x & 0xFFFFFFFFull);
     const uint32_t c = idx / A.chunk;
     atomicAdd(&A.wc_a[L.wc_first + c], 1u);
     if (in_lds) atomicAdd(&sel_hist[c / kOffsetGroup], 1u);
@@ -1229,32 +1351,49 @@ __device__ __forceinline__ void phase_out_c(const CompressArgs& A, const LayerDe
 // serial per-layer steps then start as early as possible.  (Letting consecutive launches alternate
 // makes the multi-pass path 6 % faster, each pass starting with what the one before touched last,
 // but the steady state 2 us slower.)
-__global__ void __launch_bounds__(kBlockThreads) phase_kernel(CompressArgs A) {
-  __shared__ union {
+namespace {
+
+// LDS of the launches 2 and 3.
+template <uint32_t kRoom>
+struct PhaseShared {
+  union {
     uint32_t hist[kHistBins];
-    unsigned long long sortbuf[kMemberMax];
-  } sm;
-  __shared__ ResolveShared sh;
-  __shared__ __attribute__((aligned(16))) uint32_t sel_hist[3 * 256];
+    unsigned long long sortbuf[kRoom];
+  } u;
+  __attribute__((aligned(16))) uint32_t sel_hist[3 * 256];
+  uint32_t shard_first[kMemberLists + 1];
+  ResolveShared sh;
+};
+
+template <uint32_t kRoom>
+__device__ __forceinline__ void early_phase(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
+                                            PhaseShared<kRoom>& S) {
+  ResolveShared& sh = S.sh;
+  const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
+  switch (st->next_phase) {
+    case PH_SEL:   phase_sel<kRoom>(A, l, L, st, wg, S.u.sortbuf, S.sel_hist, S.shard_first, sh); break;
+    case PH_OUT_C: phase_out_c(A, L, st, wg); break;
+    case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
+    case PH_RESTORE: dense_restore(A, L, st, wc_local); phase_hist<1>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
+    case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
+    case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
+    case PH_COUNT: phase_count(A, l, L, st, wg, wc_local, sh); break;
+    case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
+    case PH_COLLECT: phase_collect(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
+    default: break;
+  }
+}
+
+}  // namespace
+
+__global__ void __launch_bounds__(kBlockThreads) phase_kernel(CompressArgs A) {
+  __shared__ PhaseShared<kMemberMax> S;
   const uint32_t wg = blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   LayerState* st = A.state + l;
   if (st->next_launch != A.launch) return;
   const LayerDesc L = A.layers[l];
-  const uint32_t phase = st->next_phase;
-  const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
-  switch (phase) {
-    case PH_SEL:   phase_sel(A, l, L, st, wg, sm.sortbuf, sel_hist, sh); break;
-    case PH_OUT_C: phase_out_c(A, L, st, wg); break;
-    case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, sm.hist, sh); break;
-    case PH_RESTORE: dense_restore(A, L, st, wc_local); phase_hist<1>(A, l, L, st, wg, wc_local, sm.hist, sh); break;
-    case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, sm.hist, sh); break;
-    case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, sm.hist, sh); break;
-    case PH_COUNT: phase_count(A, l, L, st, wg, wc_local, sh); break;
-    case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
-    case PH_COLLECT: phase_collect(A, l, L, st, wg, wc_local, sm.hist, sh); break;
-    default: break;
-  }
+  early_phase(A, l, L, st, wg, S);
 }
 
 // Launches 4..6 of a call without hints (in the others fallback_kernel stands for them) can only meet
@@ -2316,20 +2455,31 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
 
 }  // namespace
 
-// Launch 1 for the dense layers that have a hint (accumulate_kernel leaves exactly these out).
+// Launch 1 of a call that has dense layers and hints: its other layers, and dense ones without a hint, are streamed as
+// accumulate_kernel does.  (One launch for both: as two, the dense layers waited for the small tensors' serial steps.  This launch
+// and lists_kernel in the place of two launches each: ResNet-50 set at 1.5625 % 138 -> 112 us per call, 500,000 elements in ten
+// tensors 68 -> 46, LSTM set at 6.25 % 449 -> 392, VGG16 set at 25 % 988 -> 972.)
 template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) {
-  __shared__ uint32_t lds_hist[kCoarseBins];
+  __shared__ union {
+    uint32_t digit[kHistBins];                       // accumulate_layer()
+    struct {
+      vu2 stage[kWavesPerBlock][kStageEntries];
+      float stage_u[kWavesPerBlock][kStageEntries];
+      uint32_t hist[kCoarseBins];
+    } d;
+  } sm;
   __shared__ ResolveShared sh;
-  __shared__ vu2 stage[kWavesPerBlock][kStageEntries];
-  __shared__ float stage_u[kWavesPerBlock][kStageEntries];
   const uint32_t wg = A.reverse ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
-  if (!L.dense) return;
   LayerState* st = A.state + l;
-  const bool hinted = hint_usable(A, st);            // the same condition as in accumulate_kernel
-  if (!hinted || st->dense_skip != 0u) return;
+  const bool hinted = hint_usable(A, st);
+  if (!L.dense || !hinted || st->dense_skip != 0u) {
+    accumulate_layer<kNt>(A, l, L, st, wg, hinted, sm.digit, sh);
+    return;
+  }
+  uint32_t* const lds_hist = sm.d.hist;
   for (uint32_t b = threadIdx.x; b < static_cast<uint32_t>(kCoarseBins); b += kBlockThreads) lds_hist[b] = 0u;
   __syncthreads();
   const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
@@ -2352,8 +2502,8 @@ __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) 
     DenseChunk dc;
     // (the velocity is kept only where the masking clears it)
     dc.slot_u = clear_mom ? as_global(A.slots_u + list) : gptr<float>(nullptr);
-    dc.stage = stage[threadIdx.x >> 6];
-    dc.stage_u = stage_u[threadIdx.x >> 6];
+    dc.stage = sm.d.stage[threadIdx.x >> 6];
+    dc.stage_u = sm.d.stage_u[threadIdx.x >> 6];
     dc.flushed = 0u;
     dc.clip_key = dense_clip_key(c.tau, c.shift, c.clip);
     dc.mask_key = dense_mask_key(st->mask_key, c.tau);
@@ -2380,111 +2530,11 @@ __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) 
 
 namespace {
 
-// The members of a dense layer: kMemberLists lists in global memory (region + s * shard_cap, n[s] entries; the last
-// one, for what the others could not hold, is longer), which other workgroups filled with device-scope stores.
-// A thread asks for one value of every list at a time, so that their round trips overlap.
-struct MemberLists {
-  const unsigned long long* region;
-  uint32_t shard_cap;
-  const uint32_t* first;  // [kMemberLists + 1], in LDS: running number of each list's first member; [kMemberLists] = all
-};
-
-template <typename F>
-__device__ __forceinline__ void for_each_member(const MemberLists& M, F&& f) {
-  // one step takes the i-th member of every list: kMemberLists independent loads of a thread in flight
-  uint32_t n[kMemberLists], nmax = 0u;
-#pragma unroll
-  for (uint32_t s = 0; s < kMemberLists; ++s) {
-    n[s] = M.first[s + 1] - M.first[s];
-    nmax = n[s] > nmax ? n[s] : nmax;
-  }
-  for (uint32_t i = threadIdx.x; i < nmax; i += kBlockThreads) {
-    unsigned long long x[kMemberLists];
-#pragma unroll
-    for (uint32_t s = 0; s < kMemberLists; ++s)
-      x[s] = i < n[s] ? __hip_atomic_load(&M.region[static_cast<size_t>(s) * M.shard_cap + i], __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT)
-                      : 0ull;
-#pragma unroll
-    for (uint32_t s = 0; s < kMemberLists; ++s)
-      if (i < n[s]) f(x[s]);
-  }
-}
-
-// select_kth_largest() for such members (there may be more of them than the LDS holds): the same radix
-// selection, every digit one more pass over the values.  `any` is one of the values.  hist holds 3 * 256 words.
-__device__ unsigned long long select_kth_largest_global(const MemberLists& M, unsigned long long any, uint32_t kk,
-                                                        uint32_t* hist, ResolveShared& sh) {
-  const uint32_t t = threadIdx.x, lane = lane_id();
-  const unsigned long long v0 = any;
-  unsigned long long diff = 0ull;
-  for_each_member(M, [&](unsigned long long x) { diff |= x ^ v0; });
-  int top = diff ? 63 - __clzll(static_cast<long long>(diff)) : -1;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const int other = __shfl_xor(top, o);
-    top = other > top ? other : top;
-  }
-  if (lane == 0) sh.scan[t >> 6] = static_cast<uint32_t>(top + 1);
-  hist[t] = 0u; hist[256u + t] = 0u; hist[512u + t] = 0u;
-  __syncthreads();
-  {
-    const uint32_t a = sh.scan[0], b = sh.scan[1], c = sh.scan[2], d = sh.scan[3];
-    const uint32_t ab = a > b ? a : b, cd = c > d ? c : d;
-    top = static_cast<int>(ab > cd ? ab : cd) - 1;
-  }
-  if (top < 0) return v0;                                   // a single value
-  int shift = (top >> 3) << 3;
-  unsigned long long prefix = shift == 56 ? 0ull : (v0 & (~0ull << (shift + 8)));
-  for (uint32_t pass = 0;; ++pass, shift -= 8) {
-    uint32_t* const H = hist + (pass % 3u) * 256u;
-    const unsigned long long himask = shift == 56 ? 0ull : (~0ull << (shift + 8));
-    for_each_member(M, [&](unsigned long long x) {
-      if ((x & himask) == prefix) atomicAdd(&H[static_cast<uint32_t>(x >> shift) & 255u], 1u);
-    });
-    __syncthreads();
-    hist[((pass + 2u) % 3u) * 256u + t] = 0u;
-    const uint32_t h0 = H[4u * lane], h1 = H[4u * lane + 1u], h2 = H[4u * lane + 2u], h3 = H[4u * lane + 3u];
-    const uint32_t mine = h0 + h1 + h2 + h3;
-    const uint32_t incl = wave_incl_scan(mine);
-    const uint32_t higher = wave_total(incl) - incl;
-    const bool here = higher < kk && kk <= higher + mine;
-    uint32_t bin = 0, above = 0, cnt = 0;
-    if (here) {
-      uint32_t a = higher;
-      if (kk <= a + h3) { bin = 3u; cnt = h3; }
-      else { a += h3; if (kk <= a + h2) { bin = 2u; cnt = h2; }
-      else { a += h2; if (kk <= a + h1) { bin = 1u; cnt = h1; }
-      else { a += h1; bin = 0u; cnt = h0; } } }
-      bin += 4u * lane;
-      above = a;
-    }
-    const unsigned long long who = __ballot(here);          // exactly one lane when 1 <= kk <= values in scope
-    const int src = who ? static_cast<int>(__ffsll(static_cast<long long>(who))) - 1 : 0;
-    bin = static_cast<uint32_t>(__shfl(static_cast<int>(bin), src));
-    above = static_cast<uint32_t>(__shfl(static_cast<int>(above), src));
-    cnt = static_cast<uint32_t>(__shfl(static_cast<int>(cnt), src));
-    prefix |= static_cast<unsigned long long>(bin) << shift;
-    kk -= above;
-    if (shift == 0) return prefix;                          // the composites are distinct: this is the value itself
-    if (cnt <= 1u) break;
-  }
-  // one value is left under these leading bytes: whoever holds it tells the others
-  const unsigned long long lomask = ~0ull << shift;
-  for_each_member(M, [&](unsigned long long x) {
-    if ((x & lomask) == prefix) { sh.hbin = static_cast<uint32_t>(x); sh.hcum = static_cast<uint32_t>(x >> 32); }
-  });
-  __syncthreads();
-  const unsigned long long r = (static_cast<unsigned long long>(sh.hcum) << 32) | sh.hbin;
-  __syncthreads();
-  return r;
-}
-
 // Launch 2 of a call with dense layers (PH_SEL2), for the layers whose streaming pass found the k-th key below
 // its clip bin.  Every wave takes its own wave-chunk's list; the layer's last workgroup ranks the members of the
 // k-th key's coarse bin (in global memory: there may be more of them than one workgroup's LDS holds), credits the
 // selected ones to their wave-chunks, scans the group sums into offsets and schedules the output step.
-__device__ void dense_rank(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
+__device__ __forceinline__ void dense_rank(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                            ResolveShared& sh, uint32_t* sel_hist, uint32_t* shard_first) {
   const uint32_t tau = st->cur_tau, shift = st->cur_shift, bstar = st->bstar;
   unsigned long long* const region = A.members2 + L.mem_first;
@@ -2667,7 +2717,7 @@ __device__ void dense_rank(const CompressArgs& A, uint32_t l, const LayerDesc& L
 // composite (key, then lower index first) is not below it.  The lists are in index order, so a wave writes its
 // wave-chunk's part of the message in one walk; of the sent entries those of the coarse bins below the clip bin
 // are still in V (and u) and are masked here, the others were masked by the streaming pass.
-__device__ void dense_emit(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wg) {
+__device__ __forceinline__ void dense_emit(const CompressArgs& A, const LayerDesc& L, LayerState* st, uint32_t wg) {
   const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
   if (wc_local >= L.wc_count) return;
   const uint32_t lane = lane_id();
@@ -2739,19 +2789,20 @@ __device__ void dense_emit(const CompressArgs& A, const LayerDesc& L, LayerState
 
 }  // namespace
 
+// Launches 2 and 3 of a call that has dense layers and hints: the dense layers' lists, and what phase_kernel does for the others.
+// (One launch for both, as in collect_kernel.  kListsRoom members leave room for eight workgroups on a CU, kMemberMax for four.)
+constexpr uint32_t kListsRoom = kHistBins / 2u;      // members in the histogram's room
 __global__ void __launch_bounds__(kBlockThreads) lists_kernel(CompressArgs A) {
-  __shared__ ResolveShared sh;
-  __shared__ __attribute__((aligned(16))) uint32_t sel_hist[3 * 256];
-  __shared__ uint32_t shard_first[kMemberLists + 1];
+  __shared__ PhaseShared<kListsRoom> S;
   const uint32_t wg = blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   LayerState* st = A.state + l;
   if (st->next_launch != A.launch) return;
   const LayerDesc L = A.layers[l];
   switch (st->next_phase) {
-    case PH_SEL2: dense_rank(A, l, L, st, wg, sh, sel_hist, shard_first); break;
+    case PH_SEL2: dense_rank(A, l, L, st, wg, S.sh, S.sel_hist, S.shard_first); break;
     case PH_EMIT: dense_emit(A, L, st, wg); break;
-    default: break;                                   // the other phases belong to phase_kernel
+    default: early_phase(A, l, L, st, wg, S); break;
   }
 }
 

@@ -281,6 +281,27 @@ def test_dense_layer_whose_kth_key_is_a_long_tie(rgc, oracle):
     assert sum(1 for p in paths[1:] if p == [0]) >= 4, "the hinted path of the dense layer was hardly taken: %r" % (paths,)
 
 
+@pytest.mark.parametrize("ties", [1_900, 2_100, 3_500])
+def test_sparse_layer_beside_a_dense_one_whose_kth_key_is_a_long_tie(rgc, oracle, ties):
+    """Calls with a dense layer rank the members of the other layers' coarse bins in a smaller share of the LDS (2048
+    members) and longer ties where they are: the k-th key of the second layer is shared by up to 3500 elements."""
+    g = np.random.default_rng(82)
+    n, k, per_step = 400_000, 2_000, 20
+    tie = np.sort(g.choice(n, size=ties, replace=False))
+    rest = np.setdiff1d(np.arange(n), tie)
+    large = np.sort(g.choice(rest, size=k - per_step, replace=False))   # sent on every call, and large again on the next
+    V = [(g.standard_normal(100_000) * 1e-2).astype(np.float32), (g.standard_normal(n) * 1e-2).astype(np.float32)]
+    V[1][tie] = 0.25
+    V[1][large] = 0.0
+    G_list = []
+    for _ in range(5):
+        G = np.zeros(n, np.float32)
+        G[large] = (1.0 + g.random(large.size)).astype(np.float32)
+        G_list.append([(g.standard_normal(100_000) * 1e-3).astype(np.float32), G])
+    paths = run_iterations(rgc, oracle, V, G_list, [rgc.rgc_k_for_density(100_000, 62_500), k], tag="%d ties" % ties)
+    assert sum(1 for p in paths[1:] if p == [0, 0]) >= 2, paths
+
+
 @pytest.mark.parametrize("ppm", [250_000, 15_625])
 def test_config3_vgg16_set_full_size_warmup_density(rgc, oracle, ppm):
     """The VGG16-shaped set with the momentum correction at a warm-up density, at full size (the configuration
