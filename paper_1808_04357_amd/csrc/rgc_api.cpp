@@ -661,8 +661,12 @@ int plan_for_layers(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_layers, h
 // that: VGG16 set, three contexts in turn, 520.4 us alternating, 522.0 always ascending.  Smaller
 // layer sets do better in ascending order (largest layers first).
 constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
-uint32_t streaming_direction(const CompressPlan* plan, uint64_t call) {
-  return (plan->write_bytes > kMemorySideCacheBytes) ? static_cast<uint32_t>(call & 1u) : 0u;
+// A call with dense layers (`lists`) writes long lists, which the ranking launch reads next, in ascending order: where they may not all
+// stay in the cache, the streaming pass always descends, so that the ranking meets the latest first, and the launch after it
+// descends again.  With the listed velocities stored past the cache (nothing reads them unless a hint misses) the ranking
+// takes 105 us on the VGG16 set at 25 % where it took 137 (direction alone 123), the call 952 instead of 988.
+uint32_t streaming_direction(const CompressPlan* plan, uint64_t call, bool lists) {
+  return (plan->write_bytes > kMemorySideCacheBytes) ? static_cast<uint32_t>((call & 1u) | (lists ? 1u : 0u)) : 0u;
 }
 
 // Whether the streaming pass reads and writes V and u past the memory-side cache (nontemporal accesses, as it has always
@@ -717,7 +721,7 @@ int rgc_clip_coefficient(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_laye
     RGC_HIP(ctx->d_norm_part.alloc(ctx->wg_max * kExactWordsPerPart));
   CompressArgs A{};
   fill_plan_args(ctx, plan, A);
-  A.reverse = streaming_direction(plan, ctx->compress_calls) ^ 1u;   // against the direction of the compression call to come
+  A.reverse = streaming_direction(plan, ctx->compress_calls, plan->any_dense && !plan->tileable) ^ 1u;   // against the direction of the compression call to come
   const float threshold = static_cast<float>(static_cast<double>(max_norm) / std::sqrt(static_cast<double>(num_workers)));
   RGC_HIP(launch_clip_coefficient(A, plan->general.workgroups, threshold, coefficient, stream));
   return RGC_OK;
@@ -877,7 +881,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.members2 = ctx->d_members2.p;
   A.shard_cnt = ctx->d_shards.p;
   A.past_cache = stream_past_cache(plan, A.use_hints == 0u);
-  A.reverse = streaming_direction(plan, ctx->compress_calls);
+  A.reverse = streaming_direction(plan, ctx->compress_calls, dense);
   ++ctx->compress_calls;
   ctx->compressed_since_decompress = true;
   A.nesterov = (flags & RGC_NESTEROV) ? 1u : 0u;

@@ -2317,7 +2317,7 @@ __device__ __forceinline__ void flush_staged(Collector& c, DenseChunk& dc, uint3
   const uint32_t lane = lane_id();
   if (lane < n) {
     c.slot[dc.flushed + lane] = dc.stage[from + lane];
-    if (dc.slot_u != nullptr) dc.slot_u[dc.flushed + lane] = dc.stage_u[from + lane];
+    if (dc.slot_u != nullptr) __builtin_nontemporal_store(dc.stage_u[from + lane], &dc.slot_u[dc.flushed + lane]);   // (read only after a miss)
   }
 }
 
@@ -2794,7 +2794,7 @@ __device__ __forceinline__ void dense_emit(const CompressArgs& A, const LayerDes
 constexpr uint32_t kListsRoom = kHistBins / 2u;      // members in the histogram's room
 __global__ void __launch_bounds__(kBlockThreads) lists_kernel(CompressArgs A) {
   __shared__ PhaseShared<kListsRoom> S;
-  const uint32_t wg = blockIdx.x;
+  const uint32_t wg = A.reverse && A.launch == 3u ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   LayerState* st = A.state + l;
   if (st->next_launch != A.launch) return;

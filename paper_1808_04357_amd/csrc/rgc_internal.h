@@ -193,7 +193,7 @@ struct CompressArgs {
   uint32_t late_last;
   uint32_t sign_xor;     // selection key: see key_of() (0 / 0x80000000: which sign bit keeps an element in the ranking)
   uint32_t sign_filter;  // 0: every element ranks by magnitude; ~0: elements of the other sign rank last (key 0)
-  uint32_t reverse;      // the streaming pass takes its workgroups in descending order
+  uint32_t reverse;      // the streaming pass takes its workgroups in descending order (and the last pass over dense layers' lists)
   uint32_t past_cache;   // the streaming pass reads and writes residual and velocity past the memory-side cache
   uint32_t nesterov;     // momentum correction in its Nesterov form: u = m (u + g), a = (V + u) + g
   uint32_t list_group;   // workgroups' worth of candidate lists one workgroup of PH_SEL / PH_OUT_C takes (1 or 4)
