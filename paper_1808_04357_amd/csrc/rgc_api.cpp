@@ -83,18 +83,26 @@ HintAim hint_aim(uint64_t n, uint64_t k, uint32_t chunk, uint32_t cap) {
   h.target = 2 * k + h.margin;                                             // rank the next threshold is aimed at
   const uint64_t per_chunk = (h.target * chunk + h.span - 1) / h.span;     // expected per wave-chunk
   // The candidates between the threshold aimed at and the k-th key fall into several hundred coarse
-  // bins, and the one bin that holds the k-th key must fit the member list: beyond about a million
-  // selected entries per layer it would not, and the hint would miss on every call.
-  h.hintable = 2 * per_chunk + 16 <= cap && k <= static_cast<uint64_t>(kMemberMax) * 256u;
+  // bins (256 at least), and the one bin that holds the k-th key must fit the member list: beyond 700,000
+  // selected entries per layer it may not.  (With the line at k = 2^20 the VGG16 set at 1 %, k = 1,027,605 in its largest
+  // tensor, missed on most calls: 1110 us, 645 with that tensor on the dense path.)
+  h.hintable = 2 * per_chunk + 16 <= cap && h.target - k <= static_cast<uint64_t>(kMemberMax) * 256u;
   return h;
 }
 
 // Whether a call on this list can be a tiled one (see tile_kernel): every layer either is small enough to need no hint
-// or has one that its lists (as many slots per element as those of the general tiling's smallest chunk) can hold.
-bool tileable(const rgc_layer* layers, int32_t L) {
+// or has one that its lists (as many slots per element as those of the general tiling's smallest chunk) can hold.  A call of
+// at most kTiledDenseElems elements counts on all the slots a tile's list has (`slots`): densities up to 2.2 % are tiled there.
+// In larger calls the layers that the general tiling's lists cannot hold are dense ones, whose streaming pass masks what is sent
+// where a tiled call writes isolated zeros.  At 1.5625 %, dense / tiled, us per call: 0.5 M elements in ten tensors 47.5 / 29.9,
+// 2 M in one 47.6 / 33.3, 4 M in one 51.3 / 43.2, 6 M in ten 65.3 / 54.2, 8 M in one 61.5 / 63.5, 16 M in ten 75.3 / 86.5, with a
+// velocity 8 M 71.5 / 63.9, 16 M 112 / 108, 24 M 150 / 158.
+constexpr uint64_t kTiledDenseElems = 7ull << 20;
+bool tileable(const rgc_layer* layers, int32_t L, uint64_t total, uint32_t slots) {
   for (int32_t l = 0; l < L; ++l) {
     if (layers[l].n <= static_cast<int64_t>(kDirectMax)) continue;
-    if (!hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileElems, kTileElems / kCapDiv).hintable) return false;
+    const uint32_t cap = total <= kTiledDenseElems ? slots : kTileSlots;
+    if (!hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileElems, cap).hintable) return false;
   }
   return true;
 }
@@ -246,8 +254,7 @@ uint32_t part_tiles(uint32_t tiles, uint64_t n, uint64_t target) {
 }
 
 // Fills `desc` (one entry per layer); the workgroups are handed out in the given order of the layers.
-Tiling cut_layers(const rgc_layer* layers, const std::vector<int32_t>& order, uint32_t kChunk, bool tiled, LayerDesc* desc) {
-  const uint32_t kCap = (tiled ? kTileElems : kChunk) / kCapDiv;
+Tiling cut_layers(const rgc_layer* layers, const std::vector<int32_t>& order, uint32_t kChunk, uint32_t kCap, bool tiled, LayerDesc* desc) {
   const uint32_t list_span = tiled ? kTileElems : kChunk;     // elements one candidate list stands for
   uint32_t parts = 0;
   uint32_t wc = 0, wg = 0, grp = 0;
@@ -337,11 +344,12 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
                    [&](int32_t a, int32_t b) { return layers[a].n > layers[b].n; });
   int64_t total_elems = 0;
   for (int32_t l = 0; l < L; ++l) total_elems += layers[l].n;
-  P.tileable = tileable(layers, L);
+  P.tileable = tileable(layers, L, static_cast<uint64_t>(total_elems), ctx->tile_slots);
+  const uint32_t chunk = chunk_for(total_elems);
   // the general tiling, and behind it in the same tables the one of tiled calls
   std::vector<LayerDesc> desc(static_cast<size_t>(L) * (P.tileable ? 2u : 1u));
-  Tiling general = cut_layers(layers, order, chunk_for(total_elems), false, desc.data());
-  Tiling tiled = P.tileable ? cut_layers(layers, order, kTileChunk, true, desc.data() + L) : Tiling{};
+  Tiling general = cut_layers(layers, order, chunk, chunk / kCapDiv, false, desc.data());
+  Tiling tiled = P.tileable ? cut_layers(layers, order, kTileChunk, ctx->tile_slots, true, desc.data() + L) : Tiling{};
   if (general.wave_chunks > ctx->wc_max || tiled.workgroups > ctx->wc_max) return RGC_ENOMEM;
   const size_t wgs = static_cast<size_t>(general.workgroups) + tiled.workgroups;
   const size_t map_words = (wgs + 1u) / 2u * 2u;                          // the table of parts behind it holds pairs of words

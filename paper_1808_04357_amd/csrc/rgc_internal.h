@@ -183,6 +183,9 @@ struct CompressArgs {
   uint32_t chunk;        // elements per wave-chunk (multiple of 256)
   uint32_t cap;          // candidate slots per wave-chunk
   uint32_t use_hints;
+  uint32_t nesterov;     // momentum correction in its Nesterov form: u = m (u + g), a = (V + u) + g
+                         // (here, not at the end: with `parts` 4 bytes further to the front the compiler makes select_kernel 73 KB of
+                         // code instead of 68, and every call of small layers takes 0.2 us more)
   uint32_t update_hints;
   uint32_t mask_momentum;
   float m;
@@ -195,7 +198,6 @@ struct CompressArgs {
   uint32_t sign_filter;  // 0: every element ranks by magnitude; ~0: elements of the other sign rank last (key 0)
   uint32_t reverse;      // the streaming pass takes its workgroups in descending order (and the last pass over dense layers' lists)
   uint32_t past_cache;   // the streaming pass reads and writes residual and velocity past the memory-side cache
-  uint32_t nesterov;     // momentum correction in its Nesterov form: u = m (u + g), a = (V + u) + g
   uint32_t list_group;   // workgroups' worth of candidate lists one workgroup of PH_SEL / PH_OUT_C takes (1 or 4)
   const float* grad_scale;   // device word every gradient element is multiplied with first, or null
   ExactParts norm_parts; // [workgroups] parts of the sum of squares (clipping coefficient only)

@@ -112,6 +112,19 @@ def test_densities_up_to_one_percent_keep_their_hints(rgc, oracle, ppm, momentum
     assert all(p[:4] == [0, 0, 0, 0] for p in paths[-4:]), paths
 
 
+@pytest.mark.parametrize("ppm", [12_500, 15_625, 22_000])
+@pytest.mark.parametrize("sizes", [[(1 << 20) + 77_777, 4096 * 40, 33_000, 300], [(7 << 20) - 40_000, 40_000], [(7 << 20) - 40_000, 40_001]])
+def test_densities_up_to_two_percent_in_calls_of_up_to_seven_million_elements(rgc, oracle, ppm, sizes):
+    """Tiled up to 7 Mi elements (the first two lists), dense layers above (the third)."""
+    g = np.random.default_rng(16)
+    ks = [rgc.rgc_k_for_density(n, ppm) for n in sizes]
+    V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    U = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(5)]
+    paths = run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9, threads=8, tag="%d ppm" % ppm)
+    assert any(p[0] == 0 for p in paths[1:]), paths
+
+
 def test_large_values_in_one_part_keep_their_hints(rgc, oracle):
     """The frequent rows of an embedding come first: nearly all candidates of a layer of seven parts lie in the first of them,
     more than one step holds, though no list runs over."""
