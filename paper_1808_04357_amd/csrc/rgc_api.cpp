@@ -787,6 +787,8 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   A.slots = ctx->d_slots.p;
   A.cap = plan->general.chunk / kCapDiv;
   A.hist = ctx->d_hist.p;
+  A.state = ctx->d_state.p;
+  A.group_done = ctx->d_group.p;
   A.moments = ctx->d_moments.p;
   A.chunk = plan->general.chunk;
   A.search = (flags & RGC_THRESHOLD_SEARCH) ? 1u : 0u;

@@ -225,7 +225,9 @@ struct ThresholdArgs {
   uint32_t* listed;         // [wave-chunks] elements above the threshold (kept; more than cap: list incomplete)
   uint2* slots;             // [wave-chunks][cap] (float bits, index) of the elements above a reused threshold
   uint32_t cap;             // list slots per wave-chunk
-  uint32_t* hist;           // [layers][kHistBins], the first 1024 bins of each are used
+  uint32_t* hist;           // [layers][kHistBins]: four copies of a histogram of 1024 bins
+  LayerState* state;        // [layers] and
+  uint32_t* group_done;     // [election groups]: the counters of "last workgroup of the layer"
   ThresholdMoments* moments;  // [layers]
   uint32_t chunk;           // elements per wave-chunk
   uint32_t search;          // 1: Algorithm 3 finds the thresholds; 0: they are given

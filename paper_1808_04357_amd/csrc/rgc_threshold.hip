@@ -31,6 +31,7 @@ namespace rgc {
 namespace {
 
 constexpr uint32_t kSteps = 1024;   // 1 / epsilon of the search: ratios are multiples of 2^-10
+constexpr uint32_t kHistReps = static_cast<uint32_t>(kHistBins) / kSteps;   // copies of a histogram of that many bins
 
 typedef uint32_t vu2 __attribute__((ext_vector_type(2)));   // a listed element: (float bits, index)
 
@@ -420,13 +421,72 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(Thresh
     A.moments[l] = M;
   }
   uint32_t* hist = A.hist + static_cast<size_t>(l) * kHistBins;
-  for (uint32_t b = threadIdx.x; b < kSteps; b += kBlockThreads) hist[b] = 0u;
+  for (uint32_t b = threadIdx.x; b < kHistReps * kSteps; b += kBlockThreads) hist[b] = 0u;
+}
+
+// ------------------------------------------------------------------ the threshold search (Section 2.1, Algorithm 3)
+// The layer's histogram is complete; the number of elements above T(j) is the number of elements in the bins j .. 1023.
+struct SearchShared {
+  uint32_t above[kSteps + 1];
+  uint32_t scan[kWavesPerBlock];
+  uint32_t last;
+};
+__device__ __forceinline__ void search_threshold(const ThresholdArgs& A, uint32_t l, const LayerDesc& L, SearchShared& S) {
+  uint32_t* hist = A.hist + static_cast<size_t>(l) * kHistBins;
+  // suffix sums: thread t owns the bins 1023 - 4t and the three below (and leaves them zero: the exact path, which
+  // shares the array, expects it cleared)
+  constexpr uint32_t kPer = kSteps / kBlockThreads;
+  uint32_t v[kHistReps][kPer], h[kPer], mine = 0u;
+#pragma unroll
+  for (uint32_t r = 0; r < kHistReps; ++r)
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) v[r][i] = ld_agent(&hist[r * kSteps + kSteps - 1u - (threadIdx.x * kPer + i)]);
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    h[i] = 0u;
+#pragma unroll
+    for (uint32_t r = 0; r < kHistReps; ++r) {
+      h[i] += v[r][i];
+      hist[r * kSteps + kSteps - 1u - (threadIdx.x * kPer + i)] = 0u;
+    }
+    mine += h[i];
+  }
+  uint32_t total;
+  uint32_t run = block_excl_scan(mine, S.scan, total);
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) { run += h[i]; S.above[kSteps - 1u - (threadIdx.x * kPer + i)] = run; }
+  __syncthreads();
+  if (threadIdx.x == 0u) {
+    // The search interval of Algorithm 3 starts as [0, 1] and is halved until it is 2^-10 wide, so its ends and
+    // midpoints are the multiples j / 1024 and the bisection can run on the integers j: [lo, hi] starts as
+    // [0, 1024], every midpoint is exact, and at most ten thresholds T(j) are tried.  More than k but fewer than
+    // 2k elements above T(j) end the search; k or fewer mean the threshold has to come down (hi = j), otherwise up.
+    ThresholdMoments M = A.moments[l];
+    const unsigned long long k = L.k;
+    uint32_t lo = 0u, hi = kSteps, counts = 0u;
+    float thr = 0.0f;
+    while (hi - lo > 1u) {
+      const uint32_t j = lo + (hi - lo) / 2u;
+      thr = threshold_at(M.mean, M.span, j);
+      const unsigned long long nnz = S.above[j];
+      ++counts;
+      if (nnz > k && nnz < 2ull * k) break;
+      if (nnz <= k) hi = j; else lo = j;
+    }
+    *as_global(A.thresholds + l) = thr;
+    A.moments[l].counts_taken = counts;
+    if (M.lists && thr < M.listed_above) A.moments[l].lists = 0u;   // (the lists know that 2k or more exceed it, not which)
+  }
 }
 
 // ------------------------------------------------------------------ histogram over the candidate thresholds
+// kHistReps copies of a layer's histogram: its workgroups mostly add to the same few bins, and atomics on one address take their
+// turns (LSTM set, this launch with one copy HIST1 us, with four HIST4).  The layer's last workgroup runs the search (as a launch
+// of its own it took 5.4 us).
 template <bool kReverse>
 __global__ void __launch_bounds__(kBlockThreads) threshold_histogram_kernel(ThresholdArgs A) {
   __shared__ uint32_t lds_hist[kSteps];
+  __shared__ SearchShared search;
   const uint32_t wg = (kReverse != (A.reverse != 0u)) ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
@@ -453,63 +513,12 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_histogram_kernel(Thre
   });
   if (below) atomicAdd(&lds_hist[0], below);
   __syncthreads();
-  uint32_t* hist = A.hist + static_cast<size_t>(l) * kHistBins;
+  uint32_t* hist = A.hist + static_cast<size_t>(l) * kHistBins + (wg % kHistReps) * kSteps;
   for (uint32_t b = threadIdx.x; b < kSteps; b += kBlockThreads) {
     const uint32_t c = lds_hist[b];
     if (c) atomicAdd(&hist[b], c);
   }
-}
-
-// ------------------------------------------------------------------ the threshold search (Section 2.1, Algorithm 3)
-// One workgroup per layer; the number of elements above T(j) is the number of elements in the bins j .. 1023.
-__global__ void __launch_bounds__(kBlockThreads) threshold_search_kernel(ThresholdArgs A) {
-  __shared__ uint32_t above[kSteps + 1];
-  __shared__ uint32_t part[kBlockThreads];
-  const uint32_t l = blockIdx.x;
-  const LayerDesc L = A.layers[l];
-  uint32_t* hist = A.hist + static_cast<size_t>(l) * kHistBins;
-  // suffix sums: thread t owns the bins 4t .. 4t+3 (and leaves them zero: the exact path, which
-  // shares the array, expects it cleared)
-  constexpr uint32_t kPer = kSteps / kBlockThreads;
-  uint32_t h[kPer], mine = 0u;
-#pragma unroll
-  for (uint32_t i = 0; i < kPer; ++i) {
-    h[i] = hist[threadIdx.x * kPer + i];
-    hist[threadIdx.x * kPer + i] = 0u;
-    mine += h[i];
-  }
-  part[threadIdx.x] = mine;
-  __syncthreads();
-  if (threadIdx.x == 0u) {
-    uint32_t run = 0u;
-    for (int t = kBlockThreads - 1; t >= 0; --t) { const uint32_t v = part[t]; part[t] = run; run += v; }   // bins of higher threads
-  }
-  __syncthreads();
-  uint32_t run = part[threadIdx.x];
-#pragma unroll
-  for (int i = static_cast<int>(kPer) - 1; i >= 0; --i) { run += h[i]; above[threadIdx.x * kPer + static_cast<uint32_t>(i)] = run; }
-  __syncthreads();
-  if (threadIdx.x == 0u) {
-    // The search interval of Algorithm 3 starts as [0, 1] and is halved until it is 2^-10 wide, so its ends and
-    // midpoints are the multiples j / 1024 and the bisection can run on the integers j: [lo, hi] starts as
-    // [0, 1024], every midpoint is exact, and at most ten thresholds T(j) are tried.  More than k but fewer than
-    // 2k elements above T(j) end the search; k or fewer mean the threshold has to come down (hi = j), otherwise up.
-    ThresholdMoments M = A.moments[l];
-    const unsigned long long k = L.k;
-    uint32_t lo = 0u, hi = kSteps, counts = 0u;
-    float thr = 0.0f;
-    while (hi - lo > 1u) {
-      const uint32_t j = lo + (hi - lo) / 2u;
-      thr = threshold_at(M.mean, M.span, j);
-      const unsigned long long nnz = above[j];
-      ++counts;
-      if (nnz > k && nnz < 2ull * k) break;
-      if (nnz <= k) hi = j; else lo = j;
-    }
-    *as_global(A.thresholds + l) = thr;
-    A.moments[l].counts_taken = counts;
-    if (M.lists && thr < M.listed_above) A.moments[l].lists = 0u;   // (the lists know that 2k or more exceed it, not which)
-  }
+  if (last_block_of_layer(&A.state[l].done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &search.last)) search_threshold(A, l, L, search);
 }
 
 // ------------------------------------------------------------------ count, offsets, emit
@@ -531,7 +540,8 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_count_kernel(Threshol
   if (lane_id() == 0u) A.counts[p.wc] = total;
 }
 
-// One workgroup per layer: the wave-chunk counts become the wave-chunks' first output positions.
+// One workgroup per layer: the wave-chunk counts become the wave-chunks' first output positions.  (By the last workgroup of the
+// layer in the launch before: LSTM set 17.2 us instead of 4.6 + 4.6.)
 __global__ void __launch_bounds__(kBlockThreads) threshold_offsets_kernel(ThresholdArgs A) {
   __shared__ uint32_t lds_scan[kWavesPerBlock];
   const uint32_t l = blockIdx.x;
@@ -636,8 +646,6 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
     hipLaunchKernelGGL(threshold_moments_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_histogram_kernel<true>, dim3(num_wgs), block, 0, s, a);
-    RGC_LAUNCHED();
-    hipLaunchKernelGGL(threshold_search_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_count_kernel<false>, dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
