@@ -309,3 +309,19 @@ def test_validate_flag_reports_bad_messages(rgc, oracle):
     status, _ = run(bad, rgc.RGC_OVERWRITE)
     assert status == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("workers,per_tile", [(1, 8), (3, 40), (128, 8), (128, 120), (129, 8), (256, 60)])
+def test_add_to_what_is_there_at_tile_ends(rgc, oracle, workers, per_tile):
+    """The values added to are read before a tile's colliding positions are summed: whole tiles, one more element, a tail of four,
+    an odd length, few and far too many collisions."""
+    g = np.random.default_rng(workers + per_tile)
+    sizes = [8192, 2 * 8192 + 1, 8192 + 4, 3, 20_001, 5 * 8192]
+    counts = [max(1, n * per_tile // 8192) for n in sizes]
+    idx, val = random_messages(g, sizes, workers, counts)
+    init = [g.standard_normal(n).astype(np.float32) for n in sizes]
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    for misalign in (0, 1):
+        got = gpu_decompress(rgc, ctx, idx, val, sizes, 0.25, dense_init=init, misalign=misalign)
+        compare("add w%d misalign %d" % (workers, misalign), got, oracle_all(oracle, idx, val, sizes, 0.25, init))
+    ctx.close()
