@@ -91,20 +91,29 @@ HintAim hint_aim(uint64_t n, uint64_t k, uint32_t chunk, uint32_t cap) {
 }
 
 // Whether a call on this list can be a tiled one (see tile_kernel): every layer either is small enough to need no hint
-// or has one that its lists (as many slots per element as those of the general tiling's smallest chunk) can hold.  A call of
-// at most kTiledDenseElems elements counts on all the slots a tile's list has (`slots`): densities up to 2.2 % are tiled there.
-// In larger calls the layers that the general tiling's lists cannot hold are dense ones, whose streaming pass masks what is sent
-// where a tiled call writes isolated zeros.  At 1.5625 %, dense / tiled, us per call: 0.5 M elements in ten tensors 47.5 / 29.9,
-// 2 M in one 47.6 / 33.3, 4 M in one 51.3 / 43.2, 6 M in ten 65.3 / 54.2, 8 M in one 61.5 / 63.5, 16 M in ten 75.3 / 86.5, with a
-// velocity 8 M 71.5 / 63.9, 16 M 112 / 108, 24 M 150 / 158.
-constexpr uint64_t kTiledDenseElems = 7ull << 20;
-bool tileable(const rgc_layer* layers, int32_t L, uint64_t total, uint32_t slots) {
+// or has one that lists of `slots` entries a tile can hold.
+bool tileable(const rgc_layer* layers, int32_t L, uint32_t slots) {
   for (int32_t l = 0; l < L; ++l) {
     if (layers[l].n <= static_cast<int64_t>(kDirectMax)) continue;
-    const uint32_t cap = total <= kTiledDenseElems ? slots : kTileSlots;
-    if (!hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileElems, cap).hintable) return false;
+    if (!hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileElems, slots).hintable) return false;
   }
   return true;
+}
+// A tiled call counts on kTileSlots a list, as many per element as the lists of the general tiling's smallest chunk have.  A call of
+// at most kTiledDenseElems elements counts on all the slots a list has, densities up to 2.2 % are tiled there.
+// In larger calls the layers that the general tiling's lists cannot hold are dense ones, whose streaming pass masks what is sent
+// where a tiled call writes isolated zeros.  At 1.5625 %, dense / tiled, us per call: 0.5 M elements in ten tensors 44 / 20,
+// 2 M in one 47 / 33, 4 M in one 52 / 42, 6 M in ten 55 / 47.5, 8 M in one 61.5 / 63.5, 16 M in ten 75.3 / 86.5; with a velocity
+// 4 M 58 / 46, 8 M 71.5 / 63.9, 16 M 112 / 108, 24 M 150 / 158 (so with a velocity the line could lie at twice as many; it does not).
+// That is where the values lie anywhere.  Where the large ones sit in few rows they overfill these lists, on every call, and a
+// tiled call has nothing but the five passes then, where a dense layer goes without its hint for a while: one row in twenty ten times
+// as large, 4 Mi elements 85 / 122, 0.5 Mi at 2 % 62 / 79.  Nothing the host knows tells the two apart, so the device does: after
+// kMissRun calls on end in which a layer's hint missed it leaves the call's number in host memory (CompressArgs::missing), and from
+// the first call that finds it there the list takes the general launches, until its hints are reset (87 and 67 us over the first forty calls).  A call that is being recorded takes
+// them too, since nobody looks at that number on a replay.
+constexpr uint64_t kTiledDenseElems = 7ull << 20;
+bool counts_on_long_lists(const rgc_layer* layers, int32_t L, uint64_t total, uint32_t slots) {
+  return total <= kTiledDenseElems && !tileable(layers, L, kTileSlots) && tileable(layers, L, slots);
 }
 constexpr int kPlanCache = 8;
 constexpr uint32_t kElectGroupHost = 32;   // = kElectGroup of the kernels (workgroups per election group)
@@ -183,6 +192,7 @@ struct CompressPlan {
   uint64_t write_bytes = 0;                // what the streaming pass writes (V, and u where there is one)
   uint32_t max_k = 0;                      // the largest k of the list
   bool tileable = false;                   // a call on this list can be a tiled one ...
+  bool long_lists = false;                 // ... which counts on more than kTileSlots a list
   bool tiled_needs_hints = false;          // ... if there are hints
   bool any_dense = false;                  // some layer is streamed by collect_kernel when it has a hint
   uint64_t last_use = 0;
@@ -234,6 +244,9 @@ struct rgc_ctx {
   // them from call to call): bank b uses the layer states [b * max_layers, (b + 1) * max_layers).
   std::vector<std::pair<int64_t, int32_t>> hint_sig[3];   // (n, k) per layer slot the hints belong to
   bool hints_reset[3] = {true, true, true};
+  uint32_t hint_calls[3] = {0, 0, 0};      // calls so far, and the number of the first one on the present list of (n, k)
+  uint32_t hint_first[3] = {0, 0, 0};
+  PinnedBuf missing;                       // [3] see CompressArgs::missing (allocated with the first plan that counts on long lists)
   int last_bank = 0;
   int32_t last_layers = 0;
   DecompressPlan dplan;
@@ -344,7 +357,12 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
                    [&](int32_t a, int32_t b) { return layers[a].n > layers[b].n; });
   int64_t total_elems = 0;
   for (int32_t l = 0; l < L; ++l) total_elems += layers[l].n;
-  P.tileable = tileable(layers, L, static_cast<uint64_t>(total_elems), ctx->tile_slots);
+  P.long_lists = counts_on_long_lists(layers, L, static_cast<uint64_t>(total_elems), ctx->tile_slots);
+  P.tileable = P.long_lists || tileable(layers, L, kTileSlots);
+  if (P.long_lists && ctx->missing.p == nullptr) {
+    RGC_HIP(ctx->missing.ensure(3 * sizeof(uint32_t)));
+    std::memset(ctx->missing.p, 0, 3 * sizeof(uint32_t));
+  }
   const uint32_t chunk = chunk_for(total_elems);
   // the general tiling, and behind it in the same tables the one of tiled calls
   std::vector<LayerDesc> desc(static_cast<size_t>(L) * (P.tileable ? 2u : 1u));
@@ -554,6 +572,7 @@ int rgc_destroy(rgc_ctx* ctx) {
   ctx->d_norm_part.release();
   ctx->d_mean_part.release();
   ctx->d_moments.release();
+  ctx->missing.release();                  // (the frees above have waited for the kernels that may write to it)
   for (auto* v : {&ctx->ev_compress, &ctx->ev_decompress, &ctx->ev_pool})
     for (hipEvent_t e : *v) (void)hipEventDestroy(e);
   delete ctx;
@@ -704,6 +723,19 @@ uint32_t stream_past_cache(const CompressPlan* plan, bool again) {
 // 119 / 108, 213 / 172.
 constexpr uint64_t kSampleElems = 8ull << 20;
 
+// Whether a call that counts on long lists takes the general launches nevertheless.  (Only the device writes the words; one
+// written too late to be seen here is seen by the next call.)
+bool long_lists_missing(const rgc_ctx* ctx, int bank, hipStream_t stream) {
+  const uint32_t seen = __atomic_load_n(static_cast<const uint32_t*>(ctx->missing.p) + bank, __ATOMIC_RELAXED);
+  if (seen != 0u && seen - ctx->hint_first[bank] < 0x80000000u) return true;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return status != hipStreamCaptureStatusNone;
+}
+
 void fill_plan_args(rgc_ctx* ctx, const CompressPlan* plan, CompressArgs& A) {
   A.layers = plan->d_layers;
   A.wg2layer = plan->d_wg2layer;
@@ -840,7 +872,10 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   const bool no_hints = (flags & RGC_NO_HINTS) != 0;
 
   const bool use_hints = sig_same && !no_hints;
-  const bool is_tiled = plan->tileable && (use_hints || !plan->tiled_needs_hints);
+  const uint32_t call = ++ctx->hint_calls[bank];
+  if (!no_hints && !sig_same) ctx->hint_first[bank] = call;
+  const bool missing = plan->long_lists && long_lists_missing(ctx, bank, stream);
+  const bool is_tiled = plan->tileable && (use_hints || !plan->tiled_needs_hints) && !missing;
   const Tiling& tiling = is_tiled ? plan->tiled : plan->general;
   const uint32_t num_wgs = tiling.workgroups;
   CompressArgs A{};
@@ -867,7 +902,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   // The lists of dense layers are allocated by the first call that shows the context a plan with such layers (or one
   // that needs longer lists; hipFree waits for the kernels that may still use the old ones).  Without them (the device
   // is short of memory) those layers simply take the hint-free path, as they would on a first call.
-  bool dense_ok = plan->any_dense && !plan->tileable;   // (such a list needs them neither with hints nor without)
+  bool dense_ok = plan->any_dense && (!plan->tileable || plan->long_lists);   // (other tiled lists need them neither with hints nor without)
   if (dense_ok && (ctx->d_slots2.n < plan->general.list_entries || ctx->d_members2.n < plan->general.member_entries || !ctx->d_shards.p)) {
     const uint64_t want = plan->general.list_entries * (sizeof(uint2) + sizeof(float)) + plan->general.member_entries * sizeof(unsigned long long);
     const bool capped = ctx->optional_scratch_cap >= 0 && want > static_cast<uint64_t>(ctx->optional_scratch_cap);
@@ -885,7 +920,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
       dense_ok = false;
     }
   }
-  const bool dense = dense_ok && A.use_hints;
+  const bool dense = dense_ok && A.use_hints && !is_tiled;
   A.slots2 = ctx->d_slots2.p;
   A.slots_u = ctx->d_slots_u.p;
   A.members2 = ctx->d_members2.p;
@@ -900,6 +935,10 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.grad_scale = grad_scale;
   A.m = momentum;
   A.launch = 1;
+  if (plan->long_lists && !missing) {
+    A.call = call;
+    A.missing = static_cast<uint32_t*>(ctx->missing.p) + bank;
+  }
   // In a call with dense layers and hints, collect_kernel streams every layer, and lists_kernel takes launches 2 and 3 (a dense
   // layer is ranked at 2 and written at 3; one whose hint misses has its residual put right at launch 2, where it also starts
   // on the five passes).

@@ -554,6 +554,13 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
           st->T_prev = Th;
         }
       }
+      if constexpr (kInFallback) {
+        if (A.missing != nullptr && st->path == 2u) {
+          st->miss_run = st->last_miss + 1u == A.call ? st->miss_run + 1u : 1u;
+          st->last_miss = A.call;
+          if (st->miss_run >= kMissRun) __hip_atomic_store(A.missing, A.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+      }
     }
     leave<kInFallback>(&st->hint_pending, pend);
     schedule_launch<kInFallback>(A, st, sh, cur_launch + 1u);

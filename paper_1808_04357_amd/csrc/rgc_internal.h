@@ -74,6 +74,9 @@ enum LayerKind : uint32_t {
   kLayerDirect = 2,    // at most kDirectMax elements: ended by one workgroup from the residual itself, needs no hint
 };
 constexpr uint32_t kListsTargetMax = kFinishCand / 2;
+// A tiled call that counts on more than kTileSlots a list goes back to the general launches for good after a layer's hint has
+// missed in this many calls on end: see counts_on_long_lists() in rgc_api.cpp.
+constexpr uint32_t kMissRun = 3;
 constexpr uint32_t kEmitLaunch = 3;                // tile_kernel is 1, select_kernel 2
 constexpr uint32_t kTiledLateLaunch = 4;           // a missed hint: the first digit, in fallback_kernel
 
@@ -143,6 +146,9 @@ struct LayerState {
   uint32_t cur_mask_key;
   uint32_t mask_key;         // dense layers: where the k-th key of the next call is expected; its streaming pass masks the candidates
                              // from here upwards at once and the output step puts right what that got wrong
+  // tiled calls that count on long lists (speed only)
+  uint32_t last_miss;        // CompressArgs::call of the last call in which the hint missed
+  uint32_t miss_run;         // calls on end, up to that one, in which it did
 };
 
 // Where the kernels of an exactly rounded sum leave their parts (one per workgroup): the running sum
@@ -201,6 +207,8 @@ struct CompressArgs {
   uint32_t list_group;   // workgroups' worth of candidate lists one workgroup of PH_SEL / PH_OUT_C takes (1 or 4)
   const float* grad_scale;   // device word every gradient element is multiplied with first, or null
   ExactParts norm_parts; // [workgroups] parts of the sum of squares (clipping coefficient only)
+  uint32_t call;         // number of this call among those of its hints
+  uint32_t* missing;     // null, or host memory that learns `call` when a layer's hint has missed in kMissRun calls on end
 };
 
 // ---------------------------------------------------------------- threshold binary search selection

@@ -125,6 +125,27 @@ def test_densities_up_to_two_percent_in_calls_of_up_to_seven_million_elements(rg
     assert any(p[0] == 0 for p in paths[1:]), paths
 
 
+def test_row_sparse_layer_at_a_warmup_density_stops_missing(rgc, oracle):
+    """One row in twenty carries ten times larger values and overfills the tiles' lists on every call: after three misses on end
+    the call takes the general launches, where a miss costs the layer at least one call without its hint (1 + 3 + 20 / 2 at most,
+    of 24 calls)."""
+    g = np.random.default_rng(17)
+    rows, cols = 1024, 512
+    n = rows * cols
+    held = g.permutation(rows)[: rows // 4]
+
+    def fill(s, which):
+        scale = np.zeros((rows, 1), np.float32)
+        scale[which] = 10.0
+        return ((g.standard_normal((rows, cols)) * s).astype(np.float32) * scale).reshape(n)
+
+    V = [fill(5e-3, held)]
+    G_list = [[fill(1e-3, g.permutation(held)[: rows // 20])] for _ in range(24)]
+    paths = run_iterations(rgc, oracle, V, G_list, [rgc.rgc_k_for_density(n, 20_000)], tag="row-sparse")
+    assert paths[1:4] == [[2], [2], [2]], paths       # (the case is the one described)
+    assert sum(p == [2] for p in paths) <= 14, paths
+
+
 def test_large_values_in_one_part_keep_their_hints(rgc, oracle):
     """The frequent rows of an embedding come first: nearly all candidates of a layer of seven parts lie in the first of them,
     more than one step holds, though no list runs over."""

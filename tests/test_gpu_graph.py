@@ -71,3 +71,38 @@ def test_compress_and_decompress_replayed_from_a_graph(rgc, oracle):
             check(t, "graph")
     assert ctx.last_paths(len(sizes), s)[0] == 0      # the large layer reached the hinted one-pass path
     ctx.close()
+
+
+def test_calls_that_count_on_long_lists_replayed_between_eager_ones(rgc, oracle):
+    """At 1.2 to 2.2 % a recorded call takes the general launches and an eager one the tiled ones: each goes on from the hints
+    that the other left."""
+    import torch
+    g = np.random.default_rng(2719)
+    sizes = [300_000, 70_013, 5_000]
+    ks = [rgc.rgc_k_for_density(n, 20_000) for n in sizes]
+    V0 = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    U0 = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+    dev = GpuLayers(rgc, V0, ks, U0)
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    Vh = [v.copy() for v in V0]
+    Uh = [u.copy() for u in U0]
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        graph = None
+        for t, replayed in enumerate([0, 1, 1, 1, 0, 0, 1, 0, 1, 1]):
+            G = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+            if replayed and graph is None:
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=s):
+                    rgc.rgc_compress_layers(ctx, dev.layers, 0.9, 0, s)
+            dev.set_grads(G)
+            if replayed:
+                graph.replay()
+            else:
+                rgc.rgc_compress_layers(ctx, dev.layers, 0.9, 0, s)
+            s.synchronize()
+            ref = oracle_step(oracle, G, Vh, ks, U=Uh, m=0.9)
+            assert_layers_equal("step %d %s" % (t, "replayed" if replayed else "eager"), ks, dev.results(), ref, Vh, Uh)
+            ctx.last_error(s)
+    ctx.close()
