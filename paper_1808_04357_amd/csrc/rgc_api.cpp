@@ -936,6 +936,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.m = momentum;
   A.launch = 1;
   if (plan->long_lists && !missing) {
+    A.aims = plan->d_layers + num_layers;
     A.call = call;
     A.missing = static_cast<uint32_t*>(ctx->missing.p) + bank;
   }

@@ -474,7 +474,8 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
   const uint32_t above_scope = L.k - k_rem;          // keys above the current scope
   // The k entries selected now leave the residual, so the next call's top-k come from ranks
   // k+1.. of this call: aim the next threshold at rank 2k + margin.
-  const uint32_t target = L.target;
+  const uint32_t target = A.aims != nullptr ? A.aims[l].target : L.target;
+  const uint32_t cmax = A.aims != nullptr ? A.aims[l].cmax : L.cmax;
   const uint32_t pending = (kLevel == 1) ? 1u : left_at<kInFallback>(&st->hint_pending);
   const uint32_t prefix = (kLevel == 1) ? 0u : left_at<kInFallback>(&st->prefix);
   stage_hist<kBins, 1u, kInFallback>(A.hist + static_cast<size_t>(l) * kHistBins, lds);
@@ -493,7 +494,7 @@ __device__ __forceinline__ void resolve_digit(const CompressArgs& A, uint32_t l,
     if (pend == 1u) {
       if (sh.hbin == 0xFFFFFFFFu) {          // the whole layer holds fewer keys than the target rank
         leave<kInFallback>(&st->tau_next, 0u); pend = 2u;
-      } else if (hcum <= L.cmax) {
+      } else if (hcum <= cmax) {
         leave<kInFallback>(&st->tau_next, edge(sh.hbin)); pend = 2u;
       } else if (sh.hbin == D) {
         pend = (kLevel < 3) ? 1u : 3u;      // refine inside the same bin, or give up (heavy ties)

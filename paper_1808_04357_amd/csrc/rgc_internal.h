@@ -207,6 +207,8 @@ struct CompressArgs {
   uint32_t list_group;   // workgroups' worth of candidate lists one workgroup of PH_SEL / PH_OUT_C takes (1 or 4)
   const float* grad_scale;   // device word every gradient element is multiplied with first, or null
   ExactParts norm_parts; // [workgroups] parts of the sum of squares (clipping coefficient only)
+  const LayerDesc* aims; // null, or [layers] the descriptors whose `target` and `cmax` the multi-pass path aims the next hint at: those
+                         // of the tiling that the next call is expected to take, where the two differ
   uint32_t call;         // number of this call among those of its hints
   uint32_t* missing;     // null, or host memory that learns `call` when a layer's hint has missed in kMissRun calls on end
 };
