@@ -23,8 +23,9 @@
  * allocates device tables and uploads them; a repeated call with the same descriptors only
  * launches kernels (rgc_message_means, rgc_clip_coefficient and rgc_compress_layers_threshold
  * also allocate a scratch array on their first use, and so does rgc_compress_layers for layers
- * that select more than about 1.2 % of their elements or more than 2^20 entries).  After one eager call of the same function
- * with the same descriptors, rgc_compress_layers (and its _scaled and _threshold forms),
+ * that select more than about 1.2 % of their elements, more than 2^20 entries, or more than 699,050
+ * entries if they have a velocity or these are more than one element in 300).  After one eager call
+ * of the same function with the same descriptors, rgc_compress_layers (and its _scaled and _threshold forms),
  * rgc_message_means, rgc_clip_coefficient and rgc_decompress_accumulate may therefore be
  * recorded into a HIP graph on a capturing stream and replayed: all that changes
  * from step to step (residual, velocity, hints, per-layer state) is device memory.  The calls

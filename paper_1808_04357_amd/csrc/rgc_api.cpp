@@ -69,24 +69,31 @@ uint32_t chunk_for(int64_t total) {
 // Smallest chunk any call may use: the scratch is sized for it.
 uint32_t chunk_smallest() { return chunk_override() ? std::min(chunk_override(), kChunkSmallest) : kChunkSmallest; }
 
-// The threshold hint of a layer of n elements that sends k: the rank it is aimed at, for lists of `cap` slots per
+// The threshold hint of a layer: the rank it is aimed at, for lists of `cap` slots per
 // wave-chunk of `chunk` elements, and whether those lists can hold it.
 struct HintAim {
   uint64_t margin, target, span;
   bool hintable;
 };
-HintAim hint_aim(uint64_t n, uint64_t k, uint32_t chunk, uint32_t cap) {
+HintAim hint_aim(const rgc_layer& layer, uint32_t chunk, uint32_t cap) {
+  const uint64_t n = static_cast<uint64_t>(layer.n), k = static_cast<uint64_t>(layer.k);
   HintAim h;
   h.margin = std::max<uint64_t>(k / 2, 32);
   if (n <= chunk) h.margin = std::min<uint64_t>(h.margin, std::max<uint64_t>(cap / 4, 8));   // one list holds it all
   h.span = std::max<uint64_t>(n, chunk);
   h.target = 2 * k + h.margin;                                             // rank the next threshold is aimed at
   const uint64_t per_chunk = (h.target * chunk + h.span - 1) / h.span;     // expected per wave-chunk
-  // The candidates between the threshold aimed at and the k-th key fall into several hundred coarse
-  // bins (256 at least), and the one bin that holds the k-th key must fit the member list: beyond 700,000
-  // selected entries per layer it may not.  (With the line at k = 2^20 the VGG16 set at 1 %, k = 1,027,605 in its largest
-  // tensor, missed on most calls: 1110 us, 645 with that tensor on the dense path.)
-  h.hintable = 2 * per_chunk + 16 <= cap && h.target - k <= static_cast<uint64_t>(kMemberMax) * 256u;
+  // The candidates between the threshold aimed at and the k-th key fall into several hundred coarse bins (256 at least), and
+  // the one bin that holds the k-th key must fit the member list: with more than 699,050 entries sent it may not, and the hint
+  // misses (VGG16 set at 1 %, k = 1,027,605 in its largest tensor: on most calls, 1110 us, 645 with that tensor on the dense path).
+  // Up to k = 2^20 it mostly does once the threshold has settled, and a layer without a velocity that sends at most one element in 300 is the
+  // better for it.  One such layer, us per call, one pass / dense, settled and over the first 280 calls with their misses: 720 M
+  // elements 0.1 % 1510 / 1800, 1615 / 1840; 1000 M 0.1 % 2110 / 2520, 2410 / 2550; 400 M 0.2 % 900 / 1025, 931 / 1035; 270 M 0.3 % 630 /
+  // 697, 660 / 703; beyond, 100 M 0.8 % 297 / 287, 321 / 288.  With a velocity the misses come in series (200 M 0.4 % 31 of 40 calls, 400 M
+  // 0.2 % 35, 1000 M 0.1 % 37, 2000 M 0.05 % 38): over 280 calls 2060 / 1690 at 0.2 %, 5440 / 4060 at 0.1 %, 9830 / 8460 at 0.05 %.
+  const uint64_t most = static_cast<uint64_t>(kMemberMax) * 256u;
+  const bool fits = h.target - k <= most || (layer.momentum == nullptr && 300u * k <= n && k <= most);
+  h.hintable = 2 * per_chunk + 16 <= cap && fits;
   return h;
 }
 
@@ -95,7 +102,7 @@ HintAim hint_aim(uint64_t n, uint64_t k, uint32_t chunk, uint32_t cap) {
 bool tileable(const rgc_layer* layers, int32_t L, uint32_t slots) {
   for (int32_t l = 0; l < L; ++l) {
     if (layers[l].n <= static_cast<int64_t>(kDirectMax)) continue;
-    if (!hint_aim(static_cast<uint64_t>(layers[l].n), static_cast<uint64_t>(layers[l].k), kTileElems, slots).hintable) return false;
+    if (!hint_aim(layers[l], kTileElems, slots).hintable) return false;
   }
   return true;
 }
@@ -294,7 +301,7 @@ Tiling cut_layers(const rgc_layer* layers, const std::vector<int32_t>& order, ui
     d.mem_first = 0;
     // speed-hint policy: aim the threshold at rank 2k + margin of this call, accept up to cmax
     const uint64_t k = d.k;
-    const HintAim aim = hint_aim(d.n, k, list_span, kCap);
+    const HintAim aim = hint_aim(in, list_span, kCap);
     const uint64_t margin = aim.margin, span = aim.span, target = aim.target;
     d.hintable = aim.hintable ? 1u : 0u;
     d.kind = d.n <= kDirectMax ? kLayerDirect

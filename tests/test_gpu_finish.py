@@ -179,6 +179,44 @@ def test_hint_after_a_miss_is_aimed_like_one_after_a_hit(rgc):
     ctx.close()
 
 
+@pytest.mark.parametrize("velocity,path", [(False, 0), (True, 1)])
+def test_layer_that_sends_many_of_very_many_elements(rgc, velocity, path):
+    """720,000 of 240 million entries: without a velocity the layer is on the one-pass path, with one it is a dense layer, which has
+    no hint where the optional scratch is not to be had.  The results are those of calls without hints."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(19)
+    n, k = 240_000_000, 720_000
+    G = torch.empty(n, device="cuda")
+
+    def buffers():
+        oi = torch.empty(k, dtype=torch.int32, device="cuda")
+        ov = torch.empty(k, dtype=torch.float32, device="cuda")
+        oc = torch.zeros(1, dtype=torch.int32, device="cuda")
+        V = torch.empty(n, device="cuda").normal_(0.0, 5e-3, generator=gen)
+        U = torch.empty(n, device="cuda").normal_(0.0, 1e-3, generator=gen) if velocity else None
+        return V, U, oi, ov, oc
+
+    sides = [buffers(), buffers()]
+    sides[1][0].copy_(sides[0][0])
+    if velocity:
+        sides[1][1].copy_(sides[0][1])
+    lists = [rgc.LayerList([G], [V], [k], [oi], [ov], oc, [U] if velocity else None) for V, U, oi, ov, oc in sides]
+    ctxs = [rgc.Context(n, 1), rgc.Context(n, 1)]
+    ctxs[0].limit_optional_scratch(0)
+    paths = []
+    for _ in range(6):
+        G.normal_(0.0, 1e-3, generator=gen)
+        for ctx, layers, flags in zip(ctxs, lists, (0, rgc.RGC_NO_HINTS)):
+            rgc.rgc_compress_layers(ctx, layers, 0.9, flags, torch.cuda.current_stream())
+        paths.append(ctxs[0].last_paths(1)[0])
+        for name, a, b in zip(("residual", "velocity", "indices", "values", "count"), *sides):
+            assert a is None or torch.equal(a.view(torch.int32), b.view(torch.int32)), name
+    assert paths.count(path) >= (5 if path == 1 else 2) and paths[0] == 1, paths
+    for ctx in ctxs:
+        ctx.close()
+
+
 def test_large_values_in_one_part_keep_their_hints(rgc, oracle):
     """The frequent rows of an embedding come first: nearly all candidates of a layer of seven parts lie in the first of them,
     more than one step holds, though no list runs over."""
