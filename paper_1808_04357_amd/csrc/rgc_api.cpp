@@ -696,9 +696,8 @@ int plan_for_layers(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_layers, h
 // layer sets do better in ascending order (largest layers first).
 constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
 // A call with dense layers (`lists`) writes long lists, which the ranking launch reads next, in ascending order: where they may not all
-// stay in the cache, the streaming pass always descends, so that the ranking meets the latest first, and the launch after it
-// descends again.  With the listed velocities stored past the cache (nothing reads them unless a hint misses) the ranking
-// takes 105 us on the VGG16 set at 25 % where it took 137 (direction alone 123), the call 952 instead of 988.
+// stay in the cache, the streaming pass always descends, so that the ranking meets the latest first, and the output step
+// descends again (see lists_kernel).
 uint32_t streaming_direction(const CompressPlan* plan, uint64_t call, bool lists) {
   return (plan->write_bytes > kMemorySideCacheBytes) ? static_cast<uint32_t>((call & 1u) | (lists ? 1u : 0u)) : 0u;
 }

@@ -2799,10 +2799,17 @@ __device__ __forceinline__ void dense_emit(const CompressArgs& A, const LayerDes
 
 // Launches 2 and 3 of a call that has dense layers and hints: the dense layers' lists, and what phase_kernel does for the others.
 // (One launch for both, as in collect_kernel.  kListsRoom members leave room for eight workgroups on a CU, kMemberMax for four.)
+// Where the output step reads the lists from the end (see streaming_direction() in rgc_api.cpp), it does so only if the largest layer is
+// at it: the largest layers come first otherwise, and one on the five passes whose equal keys meet on few bins, at the end, is all
+// that runs then.  (LSTM set at 6.25 %, this launch in a call whose hints miss 93 us, always from the end 150, in the call after
+// it 67 and 135; the calls 735 / 787 and 622 / 686, at 25 % with its embedding's hint missing now and then 605 / 664.  VGG16 set at 25 %:
+// 946 both ways, 956 with every layer's workgroups reversed among themselves.)  Nothing in this launch makes a layer's phase PH_EMIT or changes
+// it from that, so all workgroups see the same.
 constexpr uint32_t kListsRoom = kHistBins / 2u;      // members in the histogram's room
 __global__ void __launch_bounds__(kBlockThreads) lists_kernel(CompressArgs A) {
   __shared__ PhaseShared<kListsRoom> S;
-  const uint32_t wg = A.reverse && A.launch == 3u ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  const bool descend = A.reverse != 0u && A.launch == 3u && (A.state + A.wg2layer[0])->next_phase == PH_EMIT;
+  const uint32_t wg = descend ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
   const uint32_t l = A.wg2layer[wg];
   LayerState* st = A.state + l;
   if (st->next_launch != A.launch) return;

@@ -302,6 +302,23 @@ def test_sparse_layer_beside_a_dense_one_whose_kth_key_is_a_long_tie(rgc, oracle
     assert sum(1 for p in paths[1:] if p == [0, 0]) >= 2, paths
 
 
+def test_output_steps_from_either_end_beside_layers_whose_hint_missed(rgc, oracle):
+    """A dense call that writes more than the memory-side cache holds, with the largest layer, the other one or both on the five
+    passes after a jump of the gradient."""
+    g = np.random.default_rng(83)
+    sizes = [33_600_000, 300_001]
+    ks = [rgc.rgc_k_for_density(n, 20_000) for n in sizes]
+    V = [(g.standard_normal(n, dtype=np.float32) * np.float32(1e-2)) for n in sizes]
+    U = [(g.standard_normal(n, dtype=np.float32) * np.float32(1e-3)) for n in sizes]
+    base = [(g.standard_normal(n, dtype=np.float32) * np.float32(1e-3)) for n in sizes]
+    G_list = []
+    for first, second in [(1, 1), (1, 1), (1, 1), (1, 1), (300, 1), (1, 1), (1, 1), (1, 1), (1, 300), (1, 1), (1, 1)]:
+        G_list.append([b * np.float32(f) for b, f in zip(base, (first, second))])
+    paths = run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9, threads=16, tag="either end")
+    assert paths[4][0] == 2 and paths[8][1] == 2, paths        # (the jumps miss)
+    assert any(p[0] == 0 for p in paths) and any(p[1] == 0 for p in paths), paths
+
+
 @pytest.mark.parametrize("ppm", [250_000, 15_625])
 def test_config3_vgg16_set_full_size_warmup_density(rgc, oracle, ppm):
     """The VGG16-shaped set with the momentum correction at a warm-up density, at full size (the configuration
