@@ -1382,13 +1382,10 @@ __device__ __forceinline__ void early_phase(const CompressArgs& A, uint32_t l, c
     case PH_SEL:   phase_sel<kRoom>(A, l, L, st, wg, S.u.sortbuf, S.sel_hist, S.shard_first, sh); break;
     case PH_OUT_C: phase_out_c(A, L, st, wg); break;
     case PH_HIST1: phase_hist<1>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
-    case PH_RESTORE: dense_restore(A, L, st, wc_local); phase_hist<1>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
     case PH_HIST2: phase_hist<2>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
     case PH_HIST3: phase_hist<3>(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
-    case PH_COUNT: phase_count(A, l, L, st, wg, wc_local, sh); break;
-    case PH_OUT_V: phase_out_v(A, L, st, wc_local); break;
     case PH_COLLECT: phase_collect(A, l, L, st, wg, wc_local, S.u.hist, sh); break;
-    default: break;
+    default: if (threadIdx.x == 0) atomicOr(A.errflag, 16u); break;   // no other phase can be due this early
   }
 }
 
@@ -2817,6 +2814,12 @@ __global__ void __launch_bounds__(kBlockThreads) lists_kernel(CompressArgs A) {
   switch (st->next_phase) {
     case PH_SEL2: dense_rank(A, l, L, st, wg, S.sh, S.sel_hist, S.shard_first); break;
     case PH_EMIT: dense_emit(A, L, st, wg); break;
+    case PH_RESTORE: {
+      const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);
+      dense_restore(A, L, st, wc_local);
+      phase_hist<1>(A, l, L, st, wg, wc_local, S.u.hist, S.sh);
+      break;
+    }
     default: early_phase(A, l, L, st, wg, S); break;
   }
 }
