@@ -11,7 +11,7 @@
 //  * tiled calls (tile_kernel and what follows it): one pass over G/V that lists, tile by tile, the elements whose magnitude key
 //    is >= a cached threshold tau; the exact k-th key is found among them.  Layers of up to 2^15 elements need no tau.
 //    Every layer of the call must be of one of these two kinds;
-//  * hinted, in calls with dense layers: the same lists from accumulate_kernel's looping waves, with a coarse histogram of
+//  * hinted, in calls with dense layers: the same lists from looping waves (accumulate_layer()), with a coarse histogram of
 //    (key - tau), ranked by PH_SEL and written by PH_OUT_C;
 //  * dense layers (warm-up densities) with a tau: collect_kernel and lists_kernel;
 //  * multi-pass radix select, without tau: three histogram passes over 12+12+7 key bits give the exact k-th key T and the
@@ -2265,7 +2265,7 @@ __global__ void __launch_bounds__(kBlockThreads, 4) fallback_kernel(CompressArgs
 // At the densities of a warm-up period (Section 2.5: 25 %, 6.25 %, 1.5625 % before 0.1 %) the candidate
 // lists of the one-pass path cannot hold every element from the hinted threshold upwards, and masking the
 // sent entries out of the residual one by one afterwards would dirty most cache lines of V and u a second
-// time.  Such a layer ("dense"), once it has a hint, is streamed by a kernel of its own:
+// time.  Such a layer ("dense"), once it has a hint, is streamed otherwise than the call's other layers:
 //  1. collect_kernel reads G, V (, u), computes the accumulated values and lists EVERY candidate
 //     (key >= tau) in the wave-chunk's list, in index order (lists of the layer's own, long enough for twice
 //     the expected number).  The hint also says where the k-th key is expected (mask_key): the pass writes +0
@@ -2322,7 +2322,9 @@ __device__ __forceinline__ void flush_staged(Collector& c, DenseChunk& dc, uint3
   const uint32_t lane = lane_id();
   if (lane < n) {
     c.slot[dc.flushed + lane] = dc.stage[from + lane];
-    if (dc.slot_u != nullptr) __builtin_nontemporal_store(dc.stage_u[from + lane], &dc.slot_u[dc.flushed + lane]);   // (read only after a miss)
+    // (past the cache, of which the lists need all: the ranking does not read them, the output step and a miss those of masked entries
+    // that are not sent.  VGG16 set at 25 %, plain / this way: ranking 122 / 108 us, output step 166 / 170, call 963 / 946)
+    if (dc.slot_u != nullptr) __builtin_nontemporal_store(dc.stage_u[from + lane], &dc.slot_u[dc.flushed + lane]);
   }
 }
 
@@ -2462,8 +2464,8 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
 
 // Launch 1 of a call that has dense layers and hints: its other layers, and dense ones without a hint, are streamed as
 // accumulate_kernel does.  (One launch for both: as two, the dense layers waited for the small tensors' serial steps.  This launch
-// and lists_kernel in the place of two launches each: ResNet-50 set at 1.5625 % 138 -> 112 us per call, 500,000 elements in ten
-// tensors 68 -> 46, LSTM set at 6.25 % 449 -> 392, VGG16 set at 25 % 988 -> 972.)
+// and lists_kernel in the place of two launches each: ResNet-50 set at 1.5625 % 139 -> 113 us per call, 500,000 elements in ten
+// tensors 48 -> 43.5, LSTM set at 6.25 % 443 -> 386, VGG16 set at 25 % 870 -> 856.)
 template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) {
   __shared__ union {
@@ -2795,7 +2797,8 @@ __device__ __forceinline__ void dense_emit(const CompressArgs& A, const LayerDes
 }  // namespace
 
 // Launches 2 and 3 of a call that has dense layers and hints: the dense layers' lists, and what phase_kernel does for the others.
-// (One launch for both, as in collect_kernel.  kListsRoom members leave room for eight workgroups on a CU, kMemberMax for four.)
+// (One launch for both, as in collect_kernel.  kListsRoom members leave LDS for eight workgroups on a CU, of which the registers allow
+// six; kMemberMax would leave it for four.)
 // Where the output step reads the lists from the end (see streaming_direction() in rgc_api.cpp), it does so only if the largest layer is
 // at it: the largest layers come first otherwise, and one on the five passes whose equal keys meet on few bins, at the end, is all
 // that runs then.  (LSTM set at 6.25 %, this launch in a call whose hints miss 93 us, always from the end 150, in the call after

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace rgc {
@@ -55,16 +56,17 @@ constexpr uint32_t kFinishThreads = 1024, kFinishWaves = kFinishThreads / kWaveS
 constexpr uint32_t kDirectMaxLog2 = 15, kDirectMax = 1u << kDirectMaxLog2;
 constexpr uint32_t kTileChunk = 1024;              // elements per wave
 constexpr uint32_t kTileElems = kTileChunk * kWavesPerBlock;
-constexpr uint32_t kTileSlots = kTileElems / 16;   // slots that a call on tiles counts on for each tile's list ...
-constexpr uint32_t kTileSlotsMost = 480;           // ... and what the lists have where the device has room: see rgc_create()
+constexpr uint32_t kTileSlots = kTileElems / 16;   // slots that a large call on tiles counts on for each tile's list ...
+constexpr uint32_t kTileSlotsMost = 480;           // ... and what the lists have where the device has room (see rgc_create()): small calls count
+                                                   // on all of them (see counts_on_long_lists() in rgc_api.cpp)
                                                    // (with 512 all lists begin 4 KiB apart: ResNet-50 set 70.0 us, 69.6 this way)
 static_assert(kTileSlotsMost % 2u == 0 && kTileSlotsMost <= kTileElems / 8, "16-byte aligned lists; an eighth of the elements is allocated");
 constexpr uint32_t kFinishCand = 12288;            // candidates in LDS
 constexpr uint32_t kPartTilesMax = 1024;           // lists gather_lists() can take
 // A larger layer's parts: kPartTiles tiles (2^20 elements, 2,600 candidates at 0.1 %), at higher densities half as many and again
 // until about kPartCand candidates are expected of each, but never more than kPartsMax parts.  A part's candidates are one
-// workgroup's work: at 1 % the ResNet-50 set takes 97 us per call, with parts of 2^20 elements whatever the density 122 (2 Mi +
-// 0.6 Mi elements: 34 and 69; lines of 3072 and 6144 candidates: within 6 us of this one).
+// workgroup's work: at 1 % the ResNet-50 set takes 103 us per call, with parts of 2^20 elements whatever the density 143 (2 Mi +
+// 0.6 Mi elements: 35 and 84; lines of 3072 and 6144 candidates: within 6 us of this one).
 constexpr uint32_t kPartTiles = 256, kPartsMax = 2048, kPartCand = 4096;
 static_assert(static_cast<uint64_t>(kPartsMax) * kPartTiles * kTileElems >= (1ull << 31), "any layer has at most kPartsMax parts");
 enum LayerKind : uint32_t {
@@ -190,8 +192,6 @@ struct CompressArgs {
   uint32_t cap;          // candidate slots per wave-chunk
   uint32_t use_hints;
   uint32_t nesterov;     // momentum correction in its Nesterov form: u = m (u + g), a = (V + u) + g
-                         // (here, not at the end: with `parts` 4 bytes further to the front the compiler makes select_kernel 73 KB of
-                         // code instead of 68, and every call of small layers takes 0.2 us more)
   uint32_t update_hints;
   uint32_t mask_momentum;
   float m;
@@ -212,6 +212,10 @@ struct CompressArgs {
   uint32_t call;         // number of this call among those of its hints
   uint32_t* missing;     // null, or host memory that learns `call` when a layer's hint has missed in kMissRun calls on end
 };
+// With one of the 4-byte fields between `errflag` and `parts` moved behind them (the others then end 4 bytes earlier, a gap before
+// `parts`) the compiler makes select_kernel 73 KB of code instead of 68, and every call of small layers takes 0.2 us more: whoever
+// changes that block looks at the size.
+static_assert(offsetof(CompressArgs, launch) == 156 && offsetof(CompressArgs, parts) == 160, "select_kernel's code depends on these");
 
 // ---------------------------------------------------------------- threshold binary search selection
 struct ThresholdMoments {   // per layer, written by the moments kernel
@@ -323,8 +327,8 @@ int fail_hip(hipError_t e, const char* what);
 
 // kernel launchers (defined in the .hip files)
 hipError_t launch_accumulate(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);
-hipError_t launch_collect(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);   // streaming pass of the dense layers
-hipError_t launch_lists(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);     // their ranking and output steps
+hipError_t launch_collect(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);   // streaming pass of a call with dense layers and hints
+hipError_t launch_lists(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);     // its launches 2 and 3
 hipError_t launch_phase(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);
 hipError_t launch_tiles(const CompressArgs& a, uint32_t num_wgs, hipStream_t s);        // streaming pass of a tiled call
 hipError_t launch_select(const CompressArgs& a, uint32_t num_parts, hipStream_t s);

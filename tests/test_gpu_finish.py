@@ -97,8 +97,8 @@ def test_reported_paths_of_small_layers(rgc, oracle, sizes):
     assert all(p == [1] * len(sizes) for p in paths), paths
 
 
-# a full part (2^20 elements) has more than the 12288 candidates of one step from about 0.47 % on; 11,700 ppm is about the most a
-# tile's list is long enough for
+# a full part (2^20 elements) has more than the 12288 candidates of one step from about 0.47 % on; 11,700 ppm is about the most that
+# calls of more than 7 Mi elements count on a tile's list for
 @pytest.mark.parametrize("ppm", [4000, 5000, 8000, 10_000, 11_500])
 @pytest.mark.parametrize("momentum", [False, True])
 def test_densities_up_to_one_percent_keep_their_hints(rgc, oracle, ppm, momentum):
@@ -115,14 +115,36 @@ def test_densities_up_to_one_percent_keep_their_hints(rgc, oracle, ppm, momentum
 @pytest.mark.parametrize("ppm", [12_500, 15_625, 22_000])
 @pytest.mark.parametrize("sizes", [[(1 << 20) + 77_777, 4096 * 40, 33_000, 300], [(7 << 20) - 40_000, 40_000], [(7 << 20) - 40_000, 40_001]])
 def test_densities_up_to_two_percent_in_calls_of_up_to_seven_million_elements(rgc, oracle, ppm, sizes):
-    """Tiled up to 7 Mi elements (the first two lists), dense layers above (the third)."""
+    """Tiled up to 7 Mi elements (the first two lists), dense layers above (the third), which have no hint where the optional
+    scratch is not to be had; a tiled call needs none.  With it, both keep their hints."""
     g = np.random.default_rng(16)
     ks = [rgc.rgc_k_for_density(n, ppm) for n in sizes]
     V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
     U = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
-    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(5)]
-    paths = run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9, threads=8, tag="%d ppm" % ppm)
-    assert any(p[0] == 0 for p in paths[1:]), paths
+    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(8)]
+    tiled = sum(sizes) <= 7 << 20
+    for limit in (0, -1):
+        ctx = rgc.Context(sum(sizes), len(sizes))
+        ctx.limit_optional_scratch(limit)
+        paths = run_iterations(rgc, oracle, V, G_list, ks, U0=U, m=0.9, ctx=ctx, threads=8, tag="%d ppm, limit %d" % (ppm, limit))
+        ctx.close()
+        hinted = [l for l, n in enumerate(sizes) if n > 32768]
+        want = 0 if tiled or limit < 0 else 1
+        assert all(p[l] == want for p in paths[-3:] for l in hinted), paths
+
+
+def test_most_that_large_calls_count_on_a_list_for(rgc, oracle):
+    """More than 7 Mi elements at 11,500 ppm, with lists that need no optional scratch."""
+    g = np.random.default_rng(20)
+    sizes = [(7 << 20) - 5, 300_000, 60_001]
+    ks = [rgc.rgc_k_for_density(n, 11_500) for n in sizes]
+    V = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+    G_list = [[(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes] for _ in range(6)]
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    ctx.limit_optional_scratch(0)
+    paths = run_iterations(rgc, oracle, V, G_list, ks, ctx=ctx, threads=8, tag="11,500 ppm")
+    ctx.close()
+    assert all(p == [0, 0, 0] for p in paths[-3:]), paths
 
 
 def test_row_sparse_layer_at_a_warmup_density_stops_missing(rgc, oracle):
