@@ -116,8 +116,10 @@ bool tileable(const rgc_layer* layers, int32_t L, uint32_t slots) {
 // tiled call has nothing but the five passes then, where a dense layer goes without its hint for a while: one row in twenty ten times
 // as large, 4 Mi elements 85 / 122, 0.5 Mi at 2 % 62 / 79.  Nothing the host knows tells the two apart, so the device does: after
 // kMissRun calls on end in which a layer's hint missed it leaves the call's number in host memory (CompressArgs::missing), and from
-// the first call that finds it there the list takes the general launches, until its hints are reset (87 and 67 us over the first forty calls).  A call that is being recorded takes
-// them too, since nobody looks at that number on a replay.
+// the first call that finds it there the list takes the general launches, until its hints are reset (87 and 67 us over the first forty
+// calls).  Nobody looks at that number on a replay: a call that is being recorded takes the general launches, unless kProvenCalls calls
+// on the list have been made without one.
+constexpr uint32_t kProvenCalls = 8;
 constexpr uint64_t kTiledDenseElems = 7ull << 20;
 bool counts_on_long_lists(const rgc_layer* layers, int32_t L, uint64_t total, uint32_t slots) {
   return total <= kTiledDenseElems && !tileable(layers, L, kTileSlots) && tileable(layers, L, slots);
@@ -730,11 +732,12 @@ uint32_t stream_past_cache(const CompressPlan* plan, bool again) {
 // 119 / 108, 213 / 172.
 constexpr uint64_t kSampleElems = 8ull << 20;
 
-// Whether a call that counts on long lists takes the general launches nevertheless.  (Only the device writes the words; one
-// written too late to be seen here is seen by the next call.)
-bool long_lists_missing(const rgc_ctx* ctx, int bank, hipStream_t stream) {
+// Whether call number `call`, which counts on long lists, takes the general launches nevertheless.  (Only the device writes the words;
+// one written too late to be seen here is seen by the next call.)
+bool long_lists_missing(const rgc_ctx* ctx, int bank, uint32_t call, hipStream_t stream) {
   const uint32_t seen = __atomic_load_n(static_cast<const uint32_t*>(ctx->missing.p) + bank, __ATOMIC_RELAXED);
   if (seen != 0u && seen - ctx->hint_first[bank] < 0x80000000u) return true;
+  if (call - ctx->hint_first[bank] >= kProvenCalls) return false;
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
     (void)hipGetLastError();
@@ -881,7 +884,7 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   const bool use_hints = sig_same && !no_hints;
   const uint32_t call = ++ctx->hint_calls[bank];
   if (!no_hints && !sig_same) ctx->hint_first[bank] = call;
-  const bool missing = plan->long_lists && long_lists_missing(ctx, bank, stream);
+  const bool missing = plan->long_lists && long_lists_missing(ctx, bank, call, stream);
   const bool is_tiled = plan->tileable && (use_hints || !plan->tiled_needs_hints) && !missing;
   const Tiling& tiling = is_tiled ? plan->tiled : plan->general;
   const uint32_t num_wgs = tiling.workgroups;

@@ -73,15 +73,27 @@ def test_compress_and_decompress_replayed_from_a_graph(rgc, oracle):
     ctx.close()
 
 
-def test_calls_that_count_on_long_lists_replayed_between_eager_ones(rgc, oracle):
-    """At 1.2 to 2.2 % a recorded call takes the general launches and an eager one the tiled ones: each goes on from the hints
-    that the other left."""
+@pytest.mark.parametrize("row_sparse", [False, True])
+@pytest.mark.parametrize("eager_first", [1, 5, 9])
+def test_calls_that_count_on_long_lists_replayed_between_eager_ones(rgc, oracle, row_sparse, eager_first):
+    """At 1.2 to 2.2 % an eager call is tiled until large values in few rows have made the hints miss three times on end, a
+    recorded one only after more eager calls than that without: each goes on from the hints that the others left."""
     import torch
     g = np.random.default_rng(2719)
-    sizes = [300_000, 70_013, 5_000]
+    rows, cols = 600, 512
+    sizes = [rows * cols, 70_013, 5_000]
     ks = [rgc.rgc_k_for_density(n, 20_000) for n in sizes]
-    V0 = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
-    U0 = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+    scale = np.ones((rows, 1), np.float32)
+    if row_sparse:
+        scale[:] = 0.0
+        scale[g.permutation(rows)[: rows // 20]] = 10.0
+
+    def draw(s):
+        out = [(g.standard_normal(n) * s).astype(np.float32) for n in sizes]
+        out[0] = (out[0].reshape(rows, cols) * scale).reshape(-1)
+        return out
+
+    V0, U0 = draw(5e-3), draw(1e-3)
     dev = GpuLayers(rgc, V0, ks, U0)
     ctx = rgc.Context(sum(sizes), len(sizes))
     Vh = [v.copy() for v in V0]
@@ -90,8 +102,8 @@ def test_calls_that_count_on_long_lists_replayed_between_eager_ones(rgc, oracle)
     torch.cuda.synchronize()
     with torch.cuda.stream(s):
         graph = None
-        for t, replayed in enumerate([0, 1, 1, 1, 0, 0, 1, 0, 1, 1]):
-            G = [(g.standard_normal(n) * 1e-3).astype(np.float32) for n in sizes]
+        for t, replayed in enumerate([0] * eager_first + [1, 1, 1, 0, 0, 1, 0, 1, 1]):
+            G = draw(1e-3)
             if replayed and graph is None:
                 graph = torch.cuda.CUDAGraph()
                 with torch.cuda.graph(graph, stream=s):
