@@ -699,8 +699,8 @@ int plan_for_layers(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_layers, h
 constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
 // A call with dense layers (`lists`) writes long lists, which the ranking launch reads next, in ascending order: where they may not all
 // stay in the cache, the streaming pass always descends, so that the ranking meets the latest first, and the output step
-// descends again (see lists_kernel).  With the velocities stored past the cache (see flush_staged()): VGG16 set at 25 % 856 -> 835 us,
-// the ranking 137 -> 108.
+// descends again (see lists_kernel).  VGG16 set at 25 %, us per call: 938 -> 927, with the velocities stored past the cache too (see
+// flush_staged()) 911, the ranking 137 -> 109; at 6.25 % 704, 707 and 698, at 1.5625 % 638, 642 and 641.
 uint32_t streaming_direction(const CompressPlan* plan, uint64_t call, bool lists) {
   return (plan->write_bytes > kMemorySideCacheBytes) ? static_cast<uint32_t>((call & 1u) | (lists ? 1u : 0u)) : 0u;
 }

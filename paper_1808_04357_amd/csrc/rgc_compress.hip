@@ -2323,7 +2323,7 @@ __device__ __forceinline__ void flush_staged(Collector& c, DenseChunk& dc, uint3
   if (lane < n) {
     c.slot[dc.flushed + lane] = dc.stage[from + lane];
     // (past the cache, of which the lists need all: the ranking does not read them, the output step and a miss those of masked entries
-    // that are not sent.  VGG16 set at 25 %, plain / this way: ranking 122 / 108 us, output step 166 / 170, call 963 / 946)
+    // that are not sent.  VGG16 set at 25 %, plain / this way: ranking 122 / 108 us, output step 166 / 170, call 927 / 911)
     if (dc.slot_u != nullptr) __builtin_nontemporal_store(dc.stage_u[from + lane], &dc.slot_u[dc.flushed + lane]);
   }
 }
@@ -2464,8 +2464,8 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
 
 // Launch 1 of a call that has dense layers and hints: its other layers, and dense ones without a hint, are streamed as
 // accumulate_kernel does.  (One launch for both: as two, the dense layers waited for the small tensors' serial steps.  This launch
-// and lists_kernel in the place of two launches each: ResNet-50 set at 1.5625 % 139 -> 113 us per call, 500,000 elements in ten
-// tensors 48 -> 43.5, LSTM set at 6.25 % 443 -> 386, VGG16 set at 25 % 870 -> 856.)
+// and lists_kernel in the place of two launches each: ResNet-50 set at 1.5625 % 140 -> 114 us per call, 500,000 elements in ten
+// tensors 52 -> 45, LSTM set at 6.25 % 502 -> 445, VGG16 set at 25 % 948 -> 937.)
 template <bool kNt>
 __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) {
   __shared__ union {
@@ -2803,7 +2803,7 @@ __device__ __forceinline__ void dense_emit(const CompressArgs& A, const LayerDes
 // at it: the largest layers come first otherwise, and one on the five passes whose equal keys meet on few bins, at the end, is all
 // that runs then.  (LSTM set at 6.25 %, this launch in a call whose hints miss 93 us, always from the end 150, in the call after
 // it 67 and 135; the calls 735 / 787 and 622 / 686, at 25 % with its embedding's hint missing now and then 605 / 664.  VGG16 set at 25 %:
-// 946 both ways, 956 with every layer's workgroups reversed among themselves.)  Nothing in this launch makes a layer's phase PH_EMIT or changes
+// no change, and 10 us more with every layer's workgroups reversed among themselves.)  Nothing in this launch makes a layer's phase PH_EMIT or changes
 // it from that, so all workgroups see the same.
 constexpr uint32_t kListsRoom = kHistBins / 2u;      // members in the histogram's room
 __global__ void __launch_bounds__(kBlockThreads) lists_kernel(CompressArgs A) {
