@@ -650,6 +650,20 @@ bool same_messages(const std::vector<rgc_msg>& key, const rgc_msg* msgs, size_t 
   return true;
 }
 
+// Positions a decompression tile (its logarithm).  A worker has 17 to 32 of its entries in registers; a tile that holds more of them
+// fetches the rest from memory one round trip after the other, and has more colliding positions than rows.  A smaller tile in turn
+// pays the steps of a tile more often, 512 threads more dearly than 256.  us per call with 2048 / 4096 / 8192 positions, 20 M
+// elements: 8 workers 0.2 % 45 / 22 / 31, 0.4 % 47 / 30 / 66, 0.8 % 70 / 68 / 136, 6 % 947 / 995 / 2979; 64 workers 0.05 % 48 / 24 / 24,
+// 0.2 % 54 / 28 / 39, 0.4 % 59 / 44 / 92; 128 workers 0.05 % 67 / 42 / 27, 0.2 % 78 / 50 / 52, 0.4 % 85 / 113 / 135; 200 workers
+// 0.2 % 150 / 91 / 123, 10 M elements 0.4 % 95 / 124 / 157.  At 0.1 % and up to 64 workers it is the number of workgroups: ten tensors
+// of 2 M elements 8.7 / 7.8 / 8.9, ResNet-50 set (26 M) - / 25.9 / 26.9, 64 M - / 59 / 55.
+uint32_t tile_log_for(int64_t elements, int64_t entries, int32_t workers) {
+  if (workers < 1 || workers > static_cast<int32_t>(kFastWorkersMax)) return kTileShift;
+  const double per = static_cast<double>(entries) * kTile / (static_cast<double>(elements) * workers);   // entries of a worker in 8192 positions
+  if (workers <= static_cast<int32_t>(kFewWorkers)) return per > 64.0 ? 11 : per > 11.0 || elements < (int64_t(32) << 20) ? 12 : 13;
+  return per > 22.0 ? 11 : per > 13.0 ? 12 : 13;
+}
+
 // Checks a layer list and finds (or builds) its plan.  On success *out is the plan and the device
 // of the context is current.
 int plan_for_layers(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_layers, hipStream_t stream,
@@ -1108,9 +1122,13 @@ int rgc_decompress_accumulate(rgc_ctx* ctx, const rgc_msg* msgs, int32_t num_wor
     P.valid = false;
     // geometry
     std::vector<uint32_t> layer_tiles(num_layers), layer_col(num_layers);
+    int64_t elements = 0, entries = 0;
+    for (int32_t l = 0; l < num_layers; ++l) elements += n[l];
+    for (size_t i = 0; i < NM; ++i) entries += msgs[i].count;
+    const uint32_t tile_log = tile_log_for(elements, entries, num_workers);
     uint64_t tiles = 0, stride = 0;
     for (int32_t l = 0; l < num_layers; ++l) {
-      layer_tiles[l] = static_cast<uint32_t>((n[l] + kTile - 1) >> kTileShift);
+      layer_tiles[l] = static_cast<uint32_t>((n[l] + (1 << tile_log) - 1) >> tile_log);
       layer_col[l] = static_cast<uint32_t>(stride);
       tiles += layer_tiles[l];
       stride += layer_tiles[l] + 1u;
@@ -1184,6 +1202,7 @@ int rgc_decompress_accumulate(rgc_ctx* ctx, const rgc_msg* msgs, int32_t num_wor
     A.num_layers = static_cast<uint32_t>(num_layers);
     A.num_tiles = static_cast<uint32_t>(tiles);
     A.num_blocks = static_cast<uint32_t>(nb);
+    A.tile_log = tile_log;
     P.key_msgs.resize(NM);
     for (size_t i = 0; i < NM; ++i) {
       rgc_msg c{};

@@ -1,7 +1,7 @@
 // gfx950 kernels of the decompression step (RedSync, Section 2.3: after the Allgather every
 // node adds the N gathered sparse messages into a dense array).
 //
-// Tile ownership: one workgroup owns kTile consecutive positions of one dense buffer, adds every
+// Tile ownership: one workgroup owns a tile of consecutive positions of one dense buffer, adds every
 // worker's entries that fall into the tile and writes the tile once (scaled).  Entries of one
 // worker are unique inside a tile, so positions hit by a single worker need no ordering: the
 // first entry to reach a position stores its value there.  A position hit by several workers
@@ -43,7 +43,7 @@ typedef float vf4a __attribute__((ext_vector_type(4)));
 struct TileGeom {          // one tile, derived arithmetically from its layer
   float* dense;            // start of the tile
   uint32_t first;          // layer-local index of its first position
-  uint32_t len;            // positions in it (<= kTile)
+  uint32_t len;            // positions in it
   uint32_t row;            // its table entry inside a worker's row; row + 1 closes it
   uint32_t layer;
 };
@@ -57,12 +57,25 @@ __device__ __forceinline__ uint32_t layer_of_tile(const DecompressArgs& A, uint3
   return lo;
 }
 
+// The same by a whole wave, at 64 layers at once: one round trip for up to 64 layers, two for up to 4096.
+__device__ __forceinline__ uint32_t layer_of_tile_wave(const DecompressArgs& A, uint32_t tile_id) {
+  uint32_t lo = 0, hi = A.num_layers;
+  while (hi - lo > 1u) {
+    const uint32_t step = (hi - lo + 63u) / 64u, at = lo + lane_id() * step;
+    const bool not_above = at < hi && A.layers[at].tile_base <= tile_id;
+    lo += (popc64(__builtin_amdgcn_ballot_w64(not_above)) - 1u) * step;      // at least one: lane 0
+    hi = lo + step < hi ? lo + step : hi;
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
+template <uint32_t kLog = static_cast<uint32_t>(kTileShift)>
 __device__ __forceinline__ TileGeom tile_geom(const DecompressLayer& L, uint32_t layer, uint32_t tile_id) {
   TileGeom g;
   const uint32_t t = tile_id - L.tile_base;
-  g.first = t << kTileShift;
+  g.first = t << kLog;
   g.dense = L.dense + g.first;
-  g.len = (L.n - g.first) < static_cast<uint32_t>(kTile) ? (L.n - g.first) : static_cast<uint32_t>(kTile);
+  g.len = (L.n - g.first) < (1u << kLog) ? (L.n - g.first) : (1u << kLog);
   g.row = L.row_base + t;
   g.layer = layer;
   return g;
@@ -374,8 +387,9 @@ struct FastGeom {
 };
 
 // seen / cb / nq exist twice: tile i uses set i & 1 while the other set is being cleared.
-template <uint32_t kMaxWorkers>
+template <uint32_t kMaxWorkers, uint32_t kLog>
 struct alignas(16) FastLds {
+  static constexpr uint32_t kTile = 1u << kLog, kWords = kTile / 32u;
   float acc[kTile];                          // the tile; all zero between tiles
   float rows[kRows * FastGeom<kMaxWorkers>::kRowStride];   // per colliding position one slot per worker; all +0 between tiles
   uint32_t seen[2][kWords];                  // positions hit at all
@@ -386,9 +400,10 @@ struct alignas(16) FastLds {
   uint8_t qmap[kTile];                       // the row of a colliding position (valid where cb is set)
   uint8_t who[kTile];                        // the worker whose entry reached a position first (valid where seen is set)
 };
-static_assert(sizeof(FastLds<kFastWorkers>) <= 80 * 1024, "two 8-wave workgroups per CU");
-static_assert(sizeof(FastLds<kFastWorkersMax>) <= 160 * 1024 && kFastWorkersMax <= 256u, "one 16-wave workgroup per CU; worker numbers are bytes");
-static_assert(kWords % 64u == 0u, "a wave scans the colliding-position bitmap, a whole number of words per lane");
+static_assert(sizeof(FastLds<kFastWorkers, 13>) <= 80 * 1024, "two 8-wave workgroups per CU");
+static_assert(sizeof(FastLds<kFewWorkers, 12>) <= 53 * 1024 && sizeof(FastLds<kFewWorkers, 13>) <= 80 * 1024, "three and two 4-wave workgroups per CU");
+static_assert(sizeof(FastLds<kFastWorkersMax, 13>) <= 160 * 1024 && kFastWorkersMax <= 256u, "one 16-wave workgroup per CU; worker numbers are bytes");
+static_assert(FastLds<64, 11>::kWords % 64u == 0u, "a wave scans the colliding-position bitmap, a whole number of words per lane");
 static_assert(kRows <= 64 && kRows < 256, "one wave adds the rows; row numbers are bytes");
 
 // threadIdx.x behind a veil: what is derived from it is recomputed where it is used instead of
@@ -446,21 +461,32 @@ __device__ __forceinline__ uint32_t quad_lane0(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x00, 0xF, 0xF, true));  // quad_perm [0,0,0,0]
 }
 
+constexpr int kRawBuffer = 0x00027000;   // fourth word of a buffer descriptor: 32-bit elements, addressed by bytes
+constexpr int kNonTemporal = 2;          // cache policy of a buffer access: the "nt" bit
+
+// All of this wave's loads and stores have arrived.
+__device__ __forceinline__ void wait_for_memory() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
 }  // namespace
 
 // A workgroup owns a contiguous range of tiles and walks through it once.  Four neighbouring lanes
 // serve one worker and keep a window of its message in registers: two blocks of 16 consecutive
 // entries (block b in slot b & 1, four entries per lane), so that a block comes from memory once,
-// as one 64-byte piece per array, and serves the four or so tiles its entries fall into.  E is
+// as one 64-byte piece per array, and serves the tiles its entries fall into.  E is
 // the number of the worker's entries that lie before the current tile; the window is the two
 // blocks starting at the one that holds entry E, and the blocks that enter it are loaded while
 // the tile is being finished.  There is no per-tile offset table: E starts from a binary search
 // at the first tile of a layer and then advances by what each tile consumes.
-template <uint32_t kMaxWorkers, bool kStreamMsgs, bool kOneValue, bool kAdd>
+template <uint32_t kMaxWorkers, uint32_t kLog, bool kStreamMsgs, bool kOneValue, bool kAdd>
 __global__ void __launch_bounds__(FastGeom<kMaxWorkers>::kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 decompress_tiles_kernel(DecompressArgs A) {
   constexpr uint32_t kFastThreads = FastGeom<kMaxWorkers>::kThreads, kRowStride = FastGeom<kMaxWorkers>::kRowStride;
-  __shared__ FastLds<kMaxWorkers> S;
+  constexpr uint32_t kTile = 1u << kLog, kWords = kTile / 32u;
+  // With few messages a tile is little more than its stores, and fewer of them in flight are faster: VGG16 set, waiting for the
+  // tile's stores / not, us per call: 4 workers 110 / 124, 8 workers 103 / 118, 24 workers 107 / 112 (512 threads, 128 workers: 199 / 193);
+  // with one or two workers, waiting twice a tile / once / not: 109 / 120 / 127.
+  constexpr bool kWaitForStores = kMaxWorkers == kFewWorkers;
+  __shared__ FastLds<kMaxWorkers, kLog> S;
   const uint32_t tid = threadIdx.x;
   const uint32_t N = A.num_workers;                    // 1 .. kMaxWorkers (the host checks)
   // this workgroup's tiles: a contiguous piece of its XCD's contiguous range
@@ -488,11 +514,14 @@ decompress_tiles_kernel(DecompressArgs A) {
   typedef uint32_t vu4 __attribute__((ext_vector_type(4), aligned(4)));
   typedef float vf4u __attribute__((ext_vector_type(4), aligned(4)));
 
-  uint32_t tile_id = t_first;
-  while (tile_id < t_last) {
+  uint32_t tile_id = t_first, layer = 0;
+  if (tile_id < t_last) layer = layer_of_tile_wave(A, tile_id);
+  for (; tile_id < t_last; ++layer) {
     // ---- a run of this workgroup's tiles inside one layer
-    const uint32_t layer = layer_of_tile(A, tile_id);
-    const DecompressLayer L = A.layers[layer];
+    DecompressLayer L = A.layers[layer];
+    L.tile_base = __builtin_amdgcn_readfirstlane(L.tile_base);   // (the same in all lanes)
+    L.tiles = __builtin_amdgcn_readfirstlane(L.tiles);
+    L.n = __builtin_amdgcn_readfirstlane(L.n);
     const uint32_t run_end = (L.tile_base + L.tiles) < t_last ? (L.tile_base + L.tiles) : t_last;
 
     uint32_t my_count = 0;
@@ -519,7 +548,7 @@ decompress_tiles_kernel(DecompressArgs A) {
     // layer needs no search.
     uint32_t E = 0;
     {
-      const uint32_t target = (tile_id - L.tile_base) << kTileShift;
+      const uint32_t target = (tile_id - L.tile_base) << kLog;
       uint32_t lo = 0, hi = target != 0u ? my_count : 0u;   // idx[lo - 1] < target <= idx[hi]
       while (__builtin_amdgcn_ballot_w64(lo < hi) != 0ull) {
         const uint32_t span = hi - lo;                       // the same in the four lanes of a quad
@@ -539,60 +568,51 @@ decompress_tiles_kernel(DecompressArgs A) {
       E = lo;
     }
 
-    // the window: slot s holds block have[s] (kNone: nothing), this lane its entries 4q .. 4q+3
-    uint32_t b_idx[2][4];
-    float b_val[2][4];
-    uint32_t have[2] = {kNone, kNone};
-#pragma unroll
-    for (uint32_t sl = 0; sl < 2u; ++sl)
-#pragma unroll
-      for (uint32_t r = 0; r < 4u; ++r) { b_idx[sl][r] = kNone; b_val[sl][r] = 0.0f; }
+    // the window: slot s holds block have<s> (kNone: nothing), this lane its entries 4q .. 4q+3.  Four registers each that a load
+    // writes at once: entry by entry the compiler copies them on arrival, and waits for that before it stores the tile.
+    vu4 i0 = {kNone, kNone, kNone, kNone}, i1 = i0;
+    vf4u v0 = {0.0f, 0.0f, 0.0f, 0.0f}, v1 = v0;
+    uint32_t have0 = kNone, have1 = kNone;
     // Bring the blocks that hold entries E .. (two blocks) into their slots; entries past the
     // end of the message read as index kNone, which no tile contains.
-    auto fill_window = [&]() {
-      const uint32_t bc = E >> 4;
-#pragma unroll
-      for (uint32_t sl = 0; sl < 2u; ++sl) {
-        const uint32_t want = bc + ((sl ^ bc) & 1u);
-        if (want != have[sl]) {
-          have[sl] = want;
-          const uint32_t at = want * 16u + 4u * q;
-          if (at + 4u <= my_count) {
-            // Streaming loads when the caller alternates compression and decompression: what the
-            // memory-side cache holds of the compression's tensors is worth more to the next call than
-            // the other half of this 128-byte line, which then comes from DRAM again four tiles later.
-            // (a template parameter, not a run-time flag: merged into one branch-free load the two
-            // flavours would lose the hint)
-            vu4 qi;
-            vf4u qv;
-            if constexpr (kStreamMsgs) {
-              qi = __builtin_nontemporal_load(reinterpret_cast<gptr<const vu4>>(my_idx + at));
-              if constexpr (!kOneValue) qv = __builtin_nontemporal_load(reinterpret_cast<gptr<const vf4u>>(my_val + at));
-            } else {
-              qi = *reinterpret_cast<gptr<const vu4>>(my_idx + at);
-              if constexpr (!kOneValue) qv = *reinterpret_cast<gptr<const vf4u>>(my_val + at);
-            }
-            if constexpr (kOneValue) qv = vf4u{my_one, my_one, my_one, my_one};
-            b_idx[sl][0] = qi.x; b_idx[sl][1] = qi.y; b_idx[sl][2] = qi.z; b_idx[sl][3] = qi.w;
-            b_val[sl][0] = qv.x; b_val[sl][1] = qv.y; b_val[sl][2] = qv.z; b_val[sl][3] = qv.w;
-          } else {
-#pragma unroll
-            for (uint32_t r = 0; r < 4u; ++r) {
-              b_idx[sl][r] = kNone;
-              b_val[sl][r] = 0.0f;
-              if (at + r < my_count) {
-                b_idx[sl][r] = static_cast<uint32_t>(my_idx[at + r]);
-                b_val[sl][r] = value_at(at + r);
-              }
-            }
-          }
+    auto fill_slot = [&](vu4& bi, vf4u& bv, uint32_t& have, uint32_t want) {
+      const uint32_t at = want * 16u + 4u * q;
+      const bool need = want != have, whole = at + 4u <= my_count;
+      have = want;
+      if (need && whole) {
+        // Streaming loads when the caller alternates compression and decompression: what the
+        // memory-side cache holds of the compression's tensors is worth more to the next call than
+        // the other half of this 128-byte line, which then comes from DRAM again four tiles later.
+        // (a template parameter, not a run-time flag: merged into one branch-free load the two
+        // flavours would lose the hint)
+        if constexpr (kStreamMsgs) {
+          bi = __builtin_nontemporal_load(reinterpret_cast<gptr<const vu4>>(my_idx + at));
+          if constexpr (!kOneValue) bv = __builtin_nontemporal_load(reinterpret_cast<gptr<const vf4u>>(my_val + at));
+        } else {
+          bi = *reinterpret_cast<gptr<const vu4>>(my_idx + at);
+          if constexpr (!kOneValue) bv = *reinterpret_cast<gptr<const vf4u>>(my_val + at);
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(need && !whole) != 0ull) {     // a message's last block
+        if (need && !whole) {
+          bi = vu4{kNone, kNone, kNone, kNone};
+          if (at < my_count) { bi.x = static_cast<uint32_t>(my_idx[at]); bv.x = value_at(at); }
+          if (at + 1u < my_count) { bi.y = static_cast<uint32_t>(my_idx[at + 1u]); bv.y = value_at(at + 1u); }
+          if (at + 2u < my_count) { bi.z = static_cast<uint32_t>(my_idx[at + 2u]); bv.z = value_at(at + 2u); }
         }
       }
     };
+    auto fill_window = [&]() {
+      const uint32_t bc = E >> 4;
+      fill_slot(i0, v0, have0, bc + (bc & 1u));
+      fill_slot(i1, v1, have1, bc + ((bc & 1u) ^ 1u));
+    };
+    if constexpr (kOneValue) v0 = v1 = vf4u{my_one, my_one, my_one, my_one};
     fill_window();
+    wait_for_memory();
 
     for (; tile_id < run_end; ++tile_id, par ^= 1u) {
-      const TileGeom g = tile_geom(L, layer, tile_id);
+      const TileGeom g = tile_geom<kLog>(L, layer, tile_id);
       uint32_t* const seen = S.seen[par];
       uint32_t* const cb = S.cb[par];
       // ---- mark the positions hit, and those hit again; whoever finds a position hit for the
@@ -615,16 +635,43 @@ decompress_tiles_kernel(DecompressArgs A) {
       };
       uint32_t mine = 0;                           // entries of this lane inside the tile
       uint32_t last_in = 0;                        // the window's last entry is inside the tile
-      uint32_t late = 0;                           // bit 4*sl+r: that window entry was not the first at its position
+      uint32_t late = 0;                           // bit r (4+r): this lane's r-th entry of the first sixteen (of the others) was not the first at its position
+      // The first sixteen entries from E on: a lane has four of them, each either in the block that holds E or, before E's place
+      // in it, in the next one.  Looking at both blocks' entries one by one instead takes twice the instructions for the same hits.
+      const uint32_t o = E & 15u;
+      const bool odd = ((E >> 4) & 1u) != 0u;      // slot of the block that holds E
+      auto window = [&](uint32_t r, bool second, uint32_t& i, float& v) {
+        const bool in0 = ((4u * q + r >= o) != odd) != second;
+        i = in0 ? i0[r] : i1[r];
+        v = in0 ? v0[r] : v1[r];
+      };
+      uint32_t c_idx[4];
+      float c_val[4];
 #pragma unroll
-      for (uint32_t sl = 0; sl < 2u; ++sl) {
+      for (uint32_t r = 0; r < 4u; ++r) {
+        window(r, false, c_idx[r], c_val[r]);
+        const uint32_t p = c_idx[r] - g.first;
+        if (p < g.len) {
+          if (mark(p, c_val[r])) late |= 1u << r;
+          ++mine;
+        }
+      }
+      const bool full = quad_sum(mine) == 16u;     // only then the rest of the window can lie in the tile
+      const bool any_full = __builtin_amdgcn_ballot_w64(full) != 0ull;
+      uint32_t x_idx[4];
+      float x_val[4];
+#pragma unroll
+      for (uint32_t r = 0; r < 4u; ++r) { x_idx[r] = kNone; x_val[r] = 0.0f; }
+      if (any_full) {
 #pragma unroll
         for (uint32_t r = 0; r < 4u; ++r) {
-          const uint32_t p = b_idx[sl][r] - g.first;
+          window(r, true, x_idx[r], x_val[r]);
+          if (!full) x_idx[r] = kNone;
+          const uint32_t p = x_idx[r] - g.first;
           if (p < g.len) {
-            if (mark(p, b_val[sl][r])) late |= 1u << (4u * sl + r);
+            if (mark(p, x_val[r])) late |= 16u << r;
             ++mine;
-            if (r == 3u && q == 3u && have[sl] == (E >> 4) + 1u) last_in = 1u;
+            if (r == 3u && q == 3u) last_in = 1u;  // the window's last entry: its second block's
           }
         }
       }
@@ -640,20 +687,22 @@ decompress_tiles_kernel(DecompressArgs A) {
           ++mine;
         }
       }
-      const uint32_t consumed = quad_sum(mine);
+      // the tile's entries are used up: move the window on; its new blocks arrive while the tile is finished
+      E += quad_sum(mine);
+      fill_window();
       // What the tile is added to, well before it is needed (us per call, late / early: VGG16 set, 128 messages 304 / 284, ResNet-50
       // set, 256 messages 115 / 105, 16 messages 64 / 56; 5 M elements, 200 messages of 0.4 %, whose tiles overfill the rows, 106 / 107.5).
-      constexpr uint32_t kOut = static_cast<uint32_t>(kTile) / (4u * kFastThreads);
-      const bool vec = ((reinterpret_cast<uintptr_t>(g.dense) & 15u) == 0u) && ((g.len & 3u) == 0u);
+      constexpr uint32_t kOut = kTile > 4u * kFastThreads ? kTile / (4u * kFastThreads) : 1u;
+      // The dense buffer is read and written with bounds-checked accesses that leave out what lies behind the tile's last whole 16
+      // bytes: every wave issues the same number of stores for every tile, so the next tile's wait for its messages, asked for
+      // before them, does not have to wait for them too (loads and stores share one counter, in order).
+      const auto out = __builtin_amdgcn_make_buffer_rsrc(g.dense, 0, static_cast<int>((g.len & ~3u) * 4u), kRawBuffer);
       [[maybe_unused]] vf4a old[kOut];
       if constexpr (kAdd) {
-        if (vec) {
-          const gptr<const vf4a> d4 = as_global(reinterpret_cast<const vf4a*>(g.dense));
-          const uint32_t t = fresh_tid();
+        const uint32_t t = fresh_tid();
 #pragma unroll
-          for (uint32_t j = 0; j < kOut; ++j)
-            if (4u * (t + j * kFastThreads) < g.len) old[j] = d4[t + j * kFastThreads];
-        }
+        for (uint32_t j = 0; j < kOut; ++j)
+          old[j] = __builtin_bit_cast(vf4a, __builtin_amdgcn_raw_buffer_load_b128(out, static_cast<int>(16u * (t + j * kFastThreads)), 0, 0));
       }
       __syncthreads();
       const uint32_t nq = S.nq[par];
@@ -697,11 +746,15 @@ decompress_tiles_kernel(DecompressArgs A) {
         uint32_t first = g.first;
         asm volatile("" : "+s"(first));          // recompute the positions here rather than keep (and spill) them
 #pragma unroll
-        for (uint32_t sl = 0; sl < 2u; ++sl) {
+        for (uint32_t r = 0; r < 4u; ++r) {
+          const uint32_t p = c_idx[r] - first;
+          if (p < g.len) f(p, c_val[r]);
+        }
+        if (any_full) {
 #pragma unroll
           for (uint32_t r = 0; r < 4u; ++r) {
-            const uint32_t p = b_idx[sl][r] - first;
-            if (p < g.len) f(p, b_val[sl][r]);
+            const uint32_t p = x_idx[r] - first;
+            if (p < g.len) f(p, x_val[r]);
           }
         }
         if (more) {
@@ -745,8 +798,6 @@ decompress_tiles_kernel(DecompressArgs A) {
           sum_rows(nq - d0 < kRows ? nq - d0 : kRows);
           __syncthreads();
         }
-        E += consumed;
-        fill_window();
       } else {
         // ---- positions hit once are final; the entries that came later put their value into their
         // worker's slot of the position's row
@@ -756,14 +807,12 @@ decompress_tiles_kernel(DecompressArgs A) {
             uint32_t first = g.first;
             asm volatile("" : "+s"(first));        // recompute the positions here rather than keep (and spill) them
 #pragma unroll
-            for (uint32_t sl = 0; sl < 2u; ++sl) {
+            for (uint32_t r = 0; r < 4u; ++r)
+              if ((late >> r) & 1u) S.rows[static_cast<uint32_t>(S.qmap[c_idx[r] - first]) * kRowStride + my_slot] = c_val[r];
+            if (any_full) {
 #pragma unroll
-              for (uint32_t r = 0; r < 4u; ++r) {
-                if ((late >> (4u * sl + r)) & 1u) {
-                  const uint32_t p = b_idx[sl][r] - first;
-                  S.rows[static_cast<uint32_t>(S.qmap[p]) * kRowStride + my_slot] = b_val[sl][r];
-                }
-              }
+              for (uint32_t r = 0; r < 4u; ++r)
+                if ((late >> (4u + r)) & 1u) S.rows[static_cast<uint32_t>(S.qmap[x_idx[r] - first]) * kRowStride + my_slot] = x_val[r];
             }
           }
           if (more) {                              // beyond the window: whoever is on a colliding position (a first arrival twice: harmless)
@@ -775,41 +824,38 @@ decompress_tiles_kernel(DecompressArgs A) {
           }
           __syncthreads();
         }
-        // the tile's entries are used up: move the window on; its new blocks arrive while the tile is finished
-        E += consumed;
-        fill_window();
-        if (nq != 0u) sum_rows(nq);
       }
+      if (nq != 0u && nq <= kRows) sum_rows(nq);
       // ---- write the tile (scaled) and leave its accumulator cleared
-      const uint32_t out_tid = fresh_tid();
-      if (vec) {
-        const gptr<vf4a> d4 = as_global(reinterpret_cast<vf4a*>(g.dense));
-        vf4a* const acc4 = reinterpret_cast<vf4a*>(S.acc);
+      const uint32_t out_tid = fresh_tid(), rest = g.len & 3u;
+      vf4a* const acc4 = reinterpret_cast<vf4a*>(S.acc);
 #pragma unroll
-        for (uint32_t j = 0; j < kOut; ++j) {
-          const uint32_t i4 = out_tid + j * kFastThreads;
-          if (4u * i4 < g.len) {
-            const vf4a a = acc4[i4];
-            acc4[i4] = vf4a{0.0f, 0.0f, 0.0f, 0.0f};
-            vf4a o;
-            o.x = __fmul_rn(a.x, A.scale); o.y = __fmul_rn(a.y, A.scale);
-            o.z = __fmul_rn(a.z, A.scale); o.w = __fmul_rn(a.w, A.scale);
-            if constexpr (kAdd) {
-              o.x = __fadd_rn(old[j].x, o.x); o.y = __fadd_rn(old[j].y, o.y);
-              o.z = __fadd_rn(old[j].z, o.z); o.w = __fadd_rn(old[j].w, o.w);
+      for (uint32_t j = 0; j < kOut; ++j) {
+        const uint32_t i4 = out_tid + j * kFastThreads;
+        if (kTile >= 4u * kFastThreads || i4 < kTile / 4u) {
+          const vf4a a = acc4[i4];
+          acc4[i4] = vf4a{0.0f, 0.0f, 0.0f, 0.0f};
+          vf4a o;
+          o.x = __fmul_rn(a.x, A.scale); o.y = __fmul_rn(a.y, A.scale);
+          o.z = __fmul_rn(a.z, A.scale); o.w = __fmul_rn(a.w, A.scale);
+          if constexpr (kAdd) {
+            o.x = __fadd_rn(old[j].x, o.x); o.y = __fadd_rn(old[j].y, o.y);
+            o.z = __fadd_rn(old[j].z, o.z); o.w = __fadd_rn(old[j].w, o.w);
+          }
+          // written once, not read here again: keep it from pushing the message lines out of the L2
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vu4l, o), out, static_cast<int>(16u * i4), 0, kNonTemporal);
+          if (kWaitForStores && N <= 2u && (j & 3u) == 3u) wait_for_memory();
+          if (rest != 0u && i4 == g.len / 4u) {
+            const gptr<float> d = as_global(g.dense) + 4u * i4;
+            for (uint32_t r = 0; r < rest; ++r) {
+              float v = r == 0u ? o.x : r == 1u ? o.y : o.z;
+              if constexpr (kAdd) v = __fadd_rn(d[r], __fmul_rn(r == 0u ? a.x : r == 1u ? a.y : a.z, A.scale));
+              d[r] = v;
             }
-            __builtin_nontemporal_store(o, &d4[i4]);       // written once, not read here again: keep it from pushing the message lines out of the L2
           }
         }
-      } else {
-        const gptr<float> d = as_global(g.dense);
-        for (uint32_t i = out_tid; i < g.len; i += kFastThreads) {
-          float o = __fmul_rn(S.acc[i], A.scale);
-          S.acc[i] = 0.0f;
-          if constexpr (kAdd) o = __fadd_rn(d[i], o);
-          d[i] = o;
-        }
       }
+      if constexpr (kWaitForStores) wait_for_memory();
       __syncthreads();                             // the next tile's first arrivals write into the accumulator that this one has just cleared
     }
   }
@@ -874,19 +920,19 @@ static uint32_t resident_grid(const void* kernel, uint32_t threads, uint32_t cus
   return g < 8u ? 8u : g;
 }
 
-template <uint32_t kMaxWorkers>
+template <uint32_t kMaxWorkers, uint32_t kLog>
 static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint32_t cus8, hipStream_t s) {
   static std::atomic<uint32_t> per_cu{0};              // workgroups per CU; a property of the code object
   constexpr uint32_t threads = FastGeom<kMaxWorkers>::kThreads;
   uint32_t per = per_cu.load(std::memory_order_relaxed);
   if (per == 0) {
-    per = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<kMaxWorkers, false, false, false>), threads, 8u) / 8u;
+    per = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<kMaxWorkers, kLog, false, false, false>), threads, 8u) / 8u;
     per_cu.store(per, std::memory_order_relaxed);
   }
   const uint32_t grid = want < per * cus8 ? want : per * cus8;
   using Kernel = void (*)(DecompressArgs);
-#define RGC_TILES(add) {decompress_tiles_kernel<kMaxWorkers, false, false, add>, decompress_tiles_kernel<kMaxWorkers, true, false, add>, \
-                        decompress_tiles_kernel<kMaxWorkers, false, true, add>, decompress_tiles_kernel<kMaxWorkers, true, true, add>}
+#define RGC_TILES(add) {decompress_tiles_kernel<kMaxWorkers, kLog, false, false, add>, decompress_tiles_kernel<kMaxWorkers, kLog, true, false, add>, \
+                        decompress_tiles_kernel<kMaxWorkers, kLog, false, true, add>, decompress_tiles_kernel<kMaxWorkers, kLog, true, true, add>}
   static constexpr Kernel kernels[2][4] = {RGC_TILES(false), RGC_TILES(true)};   // (in one kernel for both, calls that overwrite took 4 % more)
 #undef RGC_TILES
   const Kernel kernel = kernels[a.add_to_dst ? 1 : 0][(a.one_value ? 2u : 0u) + (a.stream_msgs ? 1u : 0u)];
@@ -894,11 +940,21 @@ static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint
   return hipGetLastError();
 }
 
+template <uint32_t kMaxWorkers>
+static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint32_t cus8, hipStream_t s) {
+  switch (a.tile_log) {
+    case 11: return launch_fast_tiles<kMaxWorkers, 11>(a, want, cus8, s);
+    case 12: return launch_fast_tiles<kMaxWorkers, 12>(a, want, cus8, s);
+    default: return launch_fast_tiles<kMaxWorkers, 13>(a, want, cus8, s);
+  }
+}
+
 hipError_t launch_decompress_tiles(const DecompressArgs& a, hipStream_t s) {
   if (a.num_tiles == 0) return hipSuccess;
   const uint32_t want = ((a.num_tiles + 7u) / 8u) * 8u;
   const uint32_t cus8 = a.cus < 8u ? 8u : (a.cus / 8u) * 8u;
-  if (a.num_workers >= 1u && a.num_workers <= kFastWorkers) return launch_fast_tiles<kFastWorkers>(a, want, cus8, s);
+  if (a.num_workers >= 1u && a.num_workers <= kFewWorkers) return launch_fast_tiles<kFewWorkers>(a, want, cus8, s);
+  if (a.num_workers > kFewWorkers && a.num_workers <= kFastWorkers) return launch_fast_tiles<kFastWorkers>(a, want, cus8, s);
   if (a.num_workers > kFastWorkers && a.num_workers <= kFastWorkersMax) return launch_fast_tiles<kFastWorkersMax>(a, want, cus8, s);
   static std::atomic<uint32_t> per_cu_generic{0};
   uint32_t per = per_cu_generic.load(std::memory_order_relaxed);

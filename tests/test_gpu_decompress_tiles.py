@@ -1,0 +1,46 @@
+"""GPU parity of the decompression around the sizes of its tiles and the densities that choose them (bit equality)."""
+import numpy as np
+import pytest
+
+from test_gpu_decompress import compare, gpu_decompress, oracle_all, random_messages
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rgc():
+    import paper_1808_04357_amd as m
+    return m
+
+
+# entries of a worker in 8192 positions: 2048 above 64 and 22, 4096 above 11 and 13 (and in small calls of up to 64 workers), else 8192
+@pytest.mark.parametrize("add", [False, True])
+@pytest.mark.parametrize("per_8192", [5, 12, 20, 40, 90])
+@pytest.mark.parametrize("workers", [1, 3, 64, 65, 128, 130])
+def test_tile_edges(rgc, oracle, workers, per_8192, add):
+    """Layers that end at, just before and just behind a tile of each size, with ends of 1 to 3 elements behind the last
+    whole 16 bytes, on unaligned buffers; the same from tiles of 8192 positions in a call that is not small."""
+    g = np.random.default_rng(1000 * workers + per_8192)
+    sizes = [1, 3, 2047, 2048, 2049, 4095, 4098, 8189, 8192, 8195, 2 * 8192 + 1, 5 * 2048 - 2]
+    counts = [max(1, n * per_8192 // 8192) for n in sizes]
+    hot = [g.choice(n, size=max(1, n // 300), replace=False) for n in sizes]
+    idx, val = random_messages(g, sizes, workers, counts, hot)
+    init = [g.standard_normal(n).astype(np.float32) for n in sizes] if add else None
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    got = gpu_decompress(rgc, ctx, idx, val, sizes, 0.7, init, misalign=per_8192 % 4)
+    compare("%d workers, %d" % (workers, per_8192), got, oracle_all(oracle, idx, val, sizes, 0.7, init))
+    ctx.close()
+
+
+@pytest.mark.parametrize("workers", [2, 7])
+def test_large_tiles_for_few_workers(rgc, oracle, workers):
+    """From 32 Mi elements on the messages of few workers are added in tiles of 8192 positions, too."""
+    g = np.random.default_rng(workers)
+    sizes = [(32 << 20) + 8189, 8193]
+    pos = np.sort(g.choice(sizes[0], size=30_000, replace=False)).astype(np.int32)
+    idx = [[pos[g.random(pos.size) < 0.8], np.arange(w, 8193, 700, dtype=np.int32)] for w in range(workers)]
+    val = [[g.standard_normal(i.size).astype(np.float32) for i in row] for row in idx]
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    got = gpu_decompress(rgc, ctx, idx, val, sizes, 1.0 / workers, None, misalign=1)
+    compare("%d workers" % workers, got, oracle_all(oracle, idx, val, sizes, 1.0 / workers, None))
+    ctx.close()
