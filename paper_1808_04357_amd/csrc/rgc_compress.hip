@@ -854,7 +854,7 @@ namespace {
 
 // The members of a dense layer: kMemberLists lists in global memory (region + s * shard_cap, n[s] entries; the last
 // one, for what the others could not hold, is longer), which other workgroups filled with device-scope stores.
-// A thread asks for one value of every list at a time, so that their round trips overlap.
+// A thread asks for one value of every list at a time, so that their round trips overlap; f gets a value, its list and its number in it.
 struct MemberLists {
   const unsigned long long* region;
   uint32_t shard_cap;
@@ -879,7 +879,7 @@ __device__ __forceinline__ void for_each_member(const MemberLists& M, F&& f) {
                       : 0ull;
 #pragma unroll
     for (uint32_t s = 0; s < kMemberLists; ++s)
-      if (i < n[s]) f(x[s]);
+      if (i < n[s]) f(x[s], s, i);
   }
 }
 
@@ -890,7 +890,7 @@ __device__ __forceinline__ unsigned long long select_kth_largest_global(const Me
   const uint32_t t = threadIdx.x, lane = lane_id();
   const unsigned long long v0 = any;
   unsigned long long diff = 0ull;
-  for_each_member(M, [&](unsigned long long x) { diff |= x ^ v0; });
+  for_each_member(M, [&](unsigned long long x, uint32_t, uint32_t) { diff |= x ^ v0; });
   int top = diff ? 63 - __clzll(static_cast<long long>(diff)) : -1;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -911,7 +911,7 @@ __device__ __forceinline__ unsigned long long select_kth_largest_global(const Me
   for (uint32_t pass = 0;; ++pass, shift -= 8) {
     uint32_t* const H = hist + (pass % 3u) * 256u;
     const unsigned long long himask = shift == 56 ? 0ull : (~0ull << (shift + 8));
-    for_each_member(M, [&](unsigned long long x) {
+    for_each_member(M, [&](unsigned long long x, uint32_t, uint32_t) {
       if ((x & himask) == prefix) atomicAdd(&H[static_cast<uint32_t>(x >> shift) & 255u], 1u);
     });
     __syncthreads();
@@ -943,7 +943,7 @@ __device__ __forceinline__ unsigned long long select_kth_largest_global(const Me
   }
   // one value is left under these leading bytes: whoever holds it tells the others
   const unsigned long long lomask = ~0ull << shift;
-  for_each_member(M, [&](unsigned long long x) {
+  for_each_member(M, [&](unsigned long long x, uint32_t, uint32_t) {
     if ((x & lomask) == prefix) { sh.hbin = static_cast<uint32_t>(x); sh.hcum = static_cast<uint32_t>(x >> 32); }
   });
   __syncthreads();
@@ -2537,12 +2537,14 @@ __global__ void __launch_bounds__(kBlockThreads) collect_kernel(CompressArgs A) 
 
 namespace {
 
+constexpr uint32_t kListsRoom = kHistBins / 2u;      // members in the histogram's room
+
 // Launch 2 of a call with dense layers (PH_SEL2), for the layers whose streaming pass found the k-th key below
 // its clip bin.  Every wave takes its own wave-chunk's list; the layer's last workgroup ranks the members of the
 // k-th key's coarse bin (in global memory: there may be more of them than one workgroup's LDS holds), credits the
 // selected ones to their wave-chunks, scans the group sums into offsets and schedules the output step.
 __device__ __forceinline__ void dense_rank(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
-                           ResolveShared& sh, uint32_t* sel_hist, uint32_t* shard_first) {
+                           ResolveShared& sh, unsigned long long* sortbuf, uint32_t* sel_hist, uint32_t* shard_first) {
   const uint32_t tau = st->cur_tau, shift = st->cur_shift, bstar = st->bstar;
   unsigned long long* const region = A.members2 + L.mem_first;
   const uint32_t shard_cap = L.mem_cap / kMemberShards, spill_cap = L.mem_cap / 4u;
@@ -2651,15 +2653,30 @@ __device__ __forceinline__ void dense_rank(const CompressArgs& A, uint32_t l, co
     atomicAdd(&A.wc_b[L.wc_first + ((wg - L.wg_first) * kWavesPerBlock) / kOffsetGroup], sh.hcnt);
   if (!last_block_of_layer(&st->done, A.group_done + L.grp_first, wg - L.wg_first, L.wg_count, &sh.flag)) return;
 
-  if (threadIdx.x == 0) {
-    uint32_t run = 0;
-    for (uint32_t s = 0; s < kMemberLists; ++s) {
-      const uint32_t c = ld_agent(&A.shard_cnt[(static_cast<size_t>(l) * kMemberLists + s) * kShardStride]);
-      const uint32_t cap = s < kMemberShards ? shard_cap : spill_cap;
-      shard_first[s] = run;
-      run += c < cap ? c : cap;
+  // From here on one workgroup works alone and every round trip to memory counts: the lists' lengths and the groups' sums (as in
+  // phase_sel) are asked for together, and members that fit the LDS are fetched once.  (Length after length by one thread, ranking and
+  // crediting straight from memory in every case, and the credits added to the sums in memory before those are scanned: this launch
+  // 25 us on the ResNet-50 set at 1.5625 %, 16 this way; 20 and 12 on 1 M elements at 25 %.)
+  const uint32_t groups = (L.wc_count + kOffsetGroup - 1u) / kOffsetGroup;
+  const bool in_lds = groups <= 3u * kBlockThreads;
+  uint32_t gsum[3] = {0u, 0u, 0u};
+  if (in_lds) {
+#pragma unroll
+    for (uint32_t j = 0; j < 3u; ++j) {
+      const uint32_t g = 3u * threadIdx.x + j;
+      if (g < groups) gsum[j] = ld_agent(&A.wc_b[L.wc_first + g]);
     }
-    shard_first[kMemberLists] = run;
+  }
+  static_assert(kMemberLists < kWaveSize, "a lane per list");
+  if (wave == 0) {
+    uint32_t c = 0;
+    if (lane < kMemberLists) {
+      c = ld_agent(&A.shard_cnt[(static_cast<size_t>(l) * kMemberLists + lane) * kShardStride]);
+      const uint32_t cap = lane < kMemberShards ? shard_cap : spill_cap;
+      c = c < cap ? c : cap;
+    }
+    const uint32_t incl = wave_incl_scan(c);
+    if (lane <= kMemberLists) shard_first[lane] = incl - c;
   }
   __syncthreads();
   const uint32_t m = shard_first[kMemberLists];
@@ -2669,35 +2686,61 @@ __device__ __forceinline__ void dense_rank(const CompressArgs& A, uint32_t l, co
     return;   // cannot happen when the histogram and the lists agree; leave the layer unscheduled
   }
   MemberLists M{region, shard_cap, shard_first};
-  unsigned long long any = 0ull;
-  for (uint32_t s = 0; s < kMemberLists; ++s)
-    if (shard_first[s + 1] != shard_first[s]) { any = __hip_atomic_load(&region[static_cast<size_t>(s) * shard_cap], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
-  const unsigned long long thr = select_kth_largest_global(M, any, k_rem, sel_hist, sh);
+  const bool here = m <= kListsRoom;
+  unsigned long long thr;
+  if (here) {
+    for_each_member(M, [&](unsigned long long x, uint32_t s, uint32_t i) { sortbuf[shard_first[s] + i] = x; });
+    __syncthreads();
+    thr = select_kth_largest(sortbuf, m, k_rem, sel_hist, sh);
+  } else {
+    unsigned long long any = 0ull;
+    for (uint32_t s = 0; s < kMemberLists; ++s)
+      if (shard_first[s + 1] != shard_first[s]) { any = __hip_atomic_load(&region[static_cast<size_t>(s) * shard_cap], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
+    thr = select_kth_largest_global(M, any, k_rem, sel_hist, sh);
+  }
   // members not below thr are selected: credit them to their wave-chunks and to the chunks' groups
   // (the groups' credits are counted in LDS where the groups fit, as in PH_SEL: their counters share a few cache lines)
-  const uint32_t groups = (L.wc_count + kOffsetGroup - 1u) / kOffsetGroup;
-  const bool in_lds = groups <= 3u * kBlockThreads;
   __syncthreads();                                  // every wave is done with the selection's histograms
   if (in_lds) {
     sel_hist[threadIdx.x] = 0u; sel_hist[kBlockThreads + threadIdx.x] = 0u; sel_hist[2u * kBlockThreads + threadIdx.x] = 0u;
     __syncthreads();
   }
-  for_each_member(M, [&](unsigned long long x) {
+  auto credit = [&](unsigned long long x) {
     if (x < thr) return;
     const uint32_t idx = 0xFFFFFFFFu - static_cast<uint32_t>(x & 0xFFFFFFFFull);
     const uint32_t c = idx / A.chunk;
     atomicAdd(&A.wc_a[L.wc_first + c], 1u);
     if (in_lds) atomicAdd(&sel_hist[c / kOffsetGroup], 1u);
     else atomicAdd(&A.wc_b[L.wc_first + c / kOffsetGroup], 1u);
-  });
-  __syncthreads();
-  if (in_lds) {
-    for (uint32_t g = threadIdx.x; g < groups; g += kBlockThreads)
-      if (sel_hist[g] != 0u) atomicAdd(&A.wc_b[L.wc_first + g], sel_hist[g]);
+  };
+  if (here) {
+    for (uint32_t i = threadIdx.x; i < m; i += kBlockThreads) credit(sortbuf[i]);
+  } else {
+    for_each_member(M, [&](unsigned long long x, uint32_t, uint32_t) { credit(x); });
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the credits are device-scope atomics
-  __syncthreads();
-  scan_chunks(A.wc_b + L.wc_first, nullptr, groups, 0u, false, sh.scan, &sh.cnt);
+  if (in_lds) {
+    __syncthreads();
+    uint32_t v[3], mine = 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < 3u; ++j) {
+      const uint32_t g = 3u * threadIdx.x + j;
+      v[j] = g < groups ? gsum[j] + sel_hist[g] : 0u;
+      mine += v[j];
+    }
+    uint32_t total;
+    uint32_t ex = block_excl_scan(mine, sh.scan, total);
+#pragma unroll
+    for (uint32_t j = 0; j < 3u; ++j) {
+      const uint32_t g = 3u * threadIdx.x + j;
+      if (g < groups) A.wc_b[L.wc_first + g] = ex;
+      ex += v[j];
+    }
+    if (threadIdx.x == 0) sh.cnt = total;
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the credits are device-scope atomics
+    __syncthreads();
+    scan_chunks(A.wc_b + L.wc_first, nullptr, groups, 0u, false, sh.scan, &sh.cnt);
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     if (sh.cnt != L.k) atomicOr(A.errflag, 64u);
@@ -2805,7 +2848,6 @@ __device__ __forceinline__ void dense_emit(const CompressArgs& A, const LayerDes
 // it 67 and 135; the calls 735 / 787 and 622 / 686, at 25 % with its embedding's hint missing now and then 605 / 664.  VGG16 set at 25 %:
 // no change, and 10 us more with every layer's workgroups reversed among themselves.)  Nothing in this launch makes a layer's phase PH_EMIT or changes
 // it from that, so all workgroups see the same.
-constexpr uint32_t kListsRoom = kHistBins / 2u;      // members in the histogram's room
 __global__ void __launch_bounds__(kBlockThreads) lists_kernel(CompressArgs A) {
   __shared__ PhaseShared<kListsRoom> S;
   const bool descend = A.reverse != 0u && A.launch == 3u && (A.state + A.wg2layer[0])->next_phase == PH_EMIT;
@@ -2815,7 +2857,7 @@ __global__ void __launch_bounds__(kBlockThreads) lists_kernel(CompressArgs A) {
   if (st->next_launch != A.launch) return;
   const LayerDesc L = A.layers[l];
   switch (st->next_phase) {
-    case PH_SEL2: dense_rank(A, l, L, st, wg, S.sh, S.sel_hist, S.shard_first); break;
+    case PH_SEL2: dense_rank(A, l, L, st, wg, S.sh, S.u.sortbuf, S.sel_hist, S.shard_first); break;
     case PH_EMIT: dense_emit(A, L, st, wg); break;
     case PH_RESTORE: {
       const uint32_t wc_local = (wg - L.wg_first) * kWavesPerBlock + (threadIdx.x >> 6);

@@ -115,7 +115,9 @@ __device__ __forceinline__ bool last_block_of_layer(uint32_t* layer_done, uint32
     if (atomicAdd(&group_done[grp], 1u) + 1u == in_grp) {
       st_agent(&group_done[grp], 0u);
       if (again_soon) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if (atomicAdd(layer_done, 1u) + 1u == groups) {
+      if (groups == 1u) {
+        last = true;                               // (a round trip less for layers of one group)
+      } else if (atomicAdd(layer_done, 1u) + 1u == groups) {
         st_agent(layer_done, 0u);
         last = true;
       }
