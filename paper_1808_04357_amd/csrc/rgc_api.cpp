@@ -60,14 +60,25 @@ constexpr uint32_t chunk_override() { return 0u; }
 
 // Elements per wave-chunk for a call over `total` elements.  Larger chunks mean fewer per-chunk
 // counters for the per-layer serial steps, smaller ones more workgroups to fill 256 CUs.
-uint32_t chunk_for(int64_t total) {
+// A call that is never tiled (`dense`) streams every step with these chunks, and a small one is then bound by the rounds of a wave's
+// loop, on a device it does not fill.  With 1024 / 2048 / 4096, us per call: 0.5 M elements in ten tensors 25 % 32 / 36 / 44, in a hundred
+// 6.25 % 43 / 32 / 37 (short lists miss more hints), 1.5 M in ten 25 % 40.0 / 39.4 / 46.6, in a hundred 6.25 % 64 / 34 / 40, 3 M in ten
+// 25 % 46.0 / 46.1 / 50.0, 6 M in twenty 65 / 54 / 57, 6.25 % 60.1 / 48.7 / 49.1; beyond, 8192 / 2048: 7.6 M in 97 6.25 % 58.6 / 60.3, 12 M
+// in one 96 / 101, 25 M in ten 106 / 119.
+constexpr int64_t kLargeCall = int64_t(8) << 20;
+constexpr uint32_t kChunkDense = 2048;
+uint32_t chunk_for(int64_t total, bool dense) {
   if (chunk_override()) return chunk_override();
-  if (total >= (int64_t(8) << 20)) return 8192;
-  return kChunkSmallest;
+  if (total >= kLargeCall) return 8192;
+  return dense ? kChunkDense : kChunkSmallest;
 }
 
-// Smallest chunk any call may use: the scratch is sized for it.
-uint32_t chunk_smallest() { return chunk_override() ? std::min(chunk_override(), kChunkSmallest) : kChunkSmallest; }
+// Wave-chunks that a call over at most `total` elements in one tensor may have, whichever size it gets: the scratch is sized for it.
+uint64_t chunks_most(int64_t total) {
+  const uint64_t smallest = chunk_override() ? std::min(chunk_override(), kChunkSmallest) : kChunkSmallest;
+  const uint64_t dense = chunk_override() ? smallest : kChunkDense, n = static_cast<uint64_t>(total);
+  return std::max((n + smallest - 1) / smallest, (std::min<uint64_t>(n, kLargeCall) + dense - 1) / dense);
+}
 
 // The threshold hint of a layer: the rank it is aimed at, for lists of `cap` slots per
 // wave-chunk of `chunk` elements, and whether those lists can hold it.
@@ -372,7 +383,7 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     RGC_HIP(ctx->missing.ensure(3 * sizeof(uint32_t)));
     std::memset(ctx->missing.p, 0, 3 * sizeof(uint32_t));
   }
-  const uint32_t chunk = chunk_for(total_elems);
+  const uint32_t chunk = chunk_for(total_elems, !P.tileable);
   // the general tiling, and behind it in the same tables the one of tiled calls
   std::vector<LayerDesc> desc(static_cast<size_t>(L) * (P.tileable ? 2u : 1u));
   Tiling general = cut_layers(layers, order, chunk, chunk / kCapDiv, false, desc.data());
@@ -502,8 +513,7 @@ int rgc_create(rgc_ctx** out, int device_id, int64_t max_total_elems, int32_t ma
   }
   c->max_total = max_total_elems;
   c->max_layers = max_layers;
-  const uint32_t kChunk = chunk_smallest(), kCap = kChunk / kCapDiv;
-  const uint64_t wc_max = static_cast<uint64_t>((max_total_elems + kChunk - 1) / kChunk) + static_cast<uint64_t>(max_layers);
+  const uint64_t wc_max = chunks_most(max_total_elems) + static_cast<uint64_t>(max_layers);
   if (wc_max > 0x7FFFFFFFull) return RGC_ENOMEM;
   c->wc_max = static_cast<uint32_t>(wc_max);
   c->wg_max = static_cast<uint32_t>(wc_max / kWavesPerBlock + static_cast<uint64_t>(max_layers) + 1);
@@ -524,7 +534,6 @@ int rgc_create(rgc_ctx** out, int device_id, int64_t max_total_elems, int32_t ma
     // every wave-chunk owns chunk / kCapDiv slots whatever the chunk size: total / kCapDiv slots
     // plus one (partly used) chunk per layer at the largest chunk size a plan may pick
     const uint64_t largest = std::max<uint64_t>(16384, chunk_override());
-    (void)kCap;
     // Tiled calls lay their lists out anew, kTileSlotsMost a tile if the device has room for them.  Large values that sit together
     // fill single lists far beyond the average, the more so the fewer elements a list stands for (4096; 8192 in large calls on the
     // general launches): with kTileSlots a tile the row-sparse embedding of the LSTM set missed its hint in 20 to 60 % of the
