@@ -168,49 +168,18 @@ __device__ __forceinline__ void stream_chunk(const LayerDesc& L, uint32_t begin,
   uint32_t zeros = 0;
   uint32_t base = begin;
   {
-    const uint32_t nfull = (end - begin) / kGroupElems;
-    const gcvf4 G4 = as_vec(L.grad + begin);
+    const uint32_t nfull = __builtin_amdgcn_readfirstlane((end - begin) / kGroupElems);
     const gvf4 V4 = as_vec(L.resid + begin);
     const gvf4 U4 = kMom ? as_vec(L.mom + begin) : nullptr;
-    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;   // 16-byte loads in flight per lane: 6, 8 or 12
-    uint32_t g = 0;
-    for (; g + kUnroll <= nfull; g += kUnroll) {
-      vf4 gv[kUnroll], vv[kUnroll], uv[kUnroll];
-#pragma unroll
-      for (uint32_t t = 0; t < kUnroll; ++t) {
-        const uint32_t o = (g + t) * kWaveSize + lane;
-        gv[t] = __builtin_nontemporal_load(&G4[o]);
-        vv[t] = stream_load<kNt>(V4 + o);
-        if constexpr (kMom) uv[t] = stream_load<kNt>(U4 + o);
-      }
-#pragma unroll
-      for (uint32_t t = 0; t < kUnroll; ++t) {
-        const uint32_t o = (g + t) * kWaveSize + lane;
-        const float gg[4] = {gv[t].x, gv[t].y, gv[t].z, gv[t].w};
-        const float vvv[4] = {vv[t].x, vv[t].y, vv[t].z, vv[t].w};
-        float uu[4] = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (kMom) { uu[0] = uv[t].x; uu[1] = uv[t].y; uu[2] = uv[t].z; uu[3] = uv[t].w; }
-        float a[4];
-        accum4<kMom, kNest>(gg, vvv, uu, m, a);
-        stream_store<kNt>(V4 + o, vf4{a[0], a[1], a[2], a[3]});
-        if constexpr (kMom) stream_store<kNt>(U4 + o, vf4{uu[0], uu[1], uu[2], uu[3]});
-        consume<kTake>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
-      }
-    }
-    for (; g < nfull; ++g) {
-      const uint32_t o = g * kWaveSize + lane;
-      const vf4 gq = __builtin_nontemporal_load(&G4[o]);
-      const vf4 vq = stream_load<kNt>(V4 + o);
-      const float gg[4] = {gq.x, gq.y, gq.z, gq.w};
-      const float vvv[4] = {vq.x, vq.y, vq.z, vq.w};
-      float uu[4] = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (kMom) { const vf4 uq = stream_load<kNt>(U4 + o); uu[0] = uq.x; uu[1] = uq.y; uu[2] = uq.z; uu[3] = uq.w; }
+    stream_groups<kNt, kMom, 4>(as_vec(L.grad + begin), V4, U4, nfull,
+                                [&](const float (&gg)[4], const float (&vv)[4], float (&uu)[4], uint32_t o, auto&& next) {
       float a[4];
-      accum4<kMom, kNest>(gg, vvv, uu, m, a);
+      accum4<kMom, kNest>(gg, vv, uu, m, a);
+      next();
       stream_store<kNt>(V4 + o, vf4{a[0], a[1], a[2], a[3]});
       if constexpr (kMom) stream_store<kNt>(U4 + o, vf4{uu[0], uu[1], uu[2], uu[3]});
       consume<kTake>(a, 4u, begin + o * 4u, c, lds_hist, zeros);
-    }
+    });
     base = begin + nfull * kGroupElems;
   }
   // the ragged tail, a word at a time
@@ -2378,18 +2347,14 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
   const uint32_t lane = lane_id();
   uint32_t base = begin;
   {
-    const uint32_t nfull = (end - begin) / kGroupElems;
-    const gcvf4 G4 = as_vec(L.grad + begin);
+    const uint32_t nfull = __builtin_amdgcn_readfirstlane((end - begin) / kGroupElems);
     const gvf4 V4 = as_vec(L.resid + begin);
     const gvf4 U4 = kMom ? as_vec(L.mom + begin) : nullptr;
-    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;
-    auto group = [&](const vf4& gq, const vf4& vq, const vf4& uq, uint32_t o) __attribute__((always_inline)) {
-      const float gg[4] = {gq.x, gq.y, gq.z, gq.w};
-      const float vvv[4] = {vq.x, vq.y, vq.z, vq.w};
-      float uu[4] = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (kMom) { uu[0] = uq.x; uu[1] = uq.y; uu[2] = uq.z; uu[3] = uq.w; }
+    stream_groups<kNt, kMom, 1>(as_vec(L.grad + begin), V4, U4, nfull,
+                                [&](const float (&gg)[4], const float (&vv)[4], float (&uu)[4], uint32_t o, auto&& next) {
       float a[4];
-      accum4<kMom, kNest>(gg, vvv, uu, m, a);
+      accum4<kMom, kNest>(gg, vv, uu, m, a);
+      next();
       dc.overflow = dc.overflow || (c.count + 4u * kWaveSize > c.cap);
       uint32_t key[4];
       bool masked[4];
@@ -2399,28 +2364,7 @@ __device__ __forceinline__ void stream_chunk_dense(const LayerDesc& L, uint32_t 
         stream_store<kNt>(U4 + o, vf4{(masked[0] && clear_mom) ? 0.0f : uu[0], (masked[1] && clear_mom) ? 0.0f : uu[1],
                                       (masked[2] && clear_mom) ? 0.0f : uu[2], (masked[3] && clear_mom) ? 0.0f : uu[3]});
       if (!dc.overflow) list_dense(a, uu, key, 4u, begin + o * 4u, c, dc);
-    };
-    uint32_t g = 0;
-    for (; g + kUnroll <= nfull; g += kUnroll) {
-      vf4 gv[kUnroll], vv[kUnroll], uv[kUnroll];
-#pragma unroll
-      for (uint32_t t = 0; t < kUnroll; ++t) {
-        const uint32_t o = (g + t) * kWaveSize + lane;
-        gv[t] = __builtin_nontemporal_load(&G4[o]);
-        vv[t] = stream_load<kNt>(V4 + o);
-        if constexpr (kMom) uv[t] = stream_load<kNt>(U4 + o);
-      }
-#pragma unroll
-      for (uint32_t t = 0; t < kUnroll; ++t) group(gv[t], vv[t], uv[t], (g + t) * kWaveSize + lane);
-    }
-    for (; g < nfull; ++g) {
-      const uint32_t o = g * kWaveSize + lane;
-      const vf4 gq = __builtin_nontemporal_load(&G4[o]);
-      const vf4 vq = stream_load<kNt>(V4 + o);
-      vf4 uq = vf4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (kMom) uq = stream_load<kNt>(U4 + o);
-      group(gq, vq, uq, o);
-    }
+    });
     base = begin + nfull * kGroupElems;
   }
   // the ragged tail, a word at a time

@@ -478,7 +478,7 @@ __device__ __forceinline__ void wait_for_memory() { __builtin_amdgcn_s_waitcnt(0
 // the tile is being finished.  There is no per-tile offset table: E starts from a binary search
 // at the first tile of a layer and then advances by what each tile consumes.
 template <uint32_t kMaxWorkers, uint32_t kLog, bool kStreamMsgs, bool kOneValue, bool kAdd>
-__global__ void __launch_bounds__(FastGeom<kMaxWorkers>::kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ void __launch_bounds__(FastGeom<kMaxWorkers>::kThreads) __attribute__((amdgpu_waves_per_eu(kMaxWorkers == kFewWorkers && kLog == 13u ? 2 : 4, 4)))
 decompress_tiles_kernel(DecompressArgs A) {
   constexpr uint32_t kFastThreads = FastGeom<kMaxWorkers>::kThreads, kRowStride = FastGeom<kMaxWorkers>::kRowStride;
   constexpr uint32_t kTile = 1u << kLog, kWords = kTile / 32u;

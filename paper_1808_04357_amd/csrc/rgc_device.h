@@ -181,6 +181,40 @@ __device__ __forceinline__ void accum4(const float (&g)[4], const float (&v)[4],
   }
 }
 
+// The whole groups of 256 elements of a wave's stretch, which begins at the three pointers (`U4` only with a velocity), kAhead groups
+// ahead: f(g, v, u, o, next) gets a lane's four elements of a group, which are number 4 o .. 4 o + 3 of the stretch, and calls next(), which asks
+// for the group kAhead further on, when it has read them and before it stores anything.  Loads and stores share one counter, in
+// order, so a wait for loads that were issued after stores would be a wait for the stores too.  (Four groups' loads, then their work and
+// stores, then the next four, against this with kAhead = 1 / 2 / 4, us per call: dense layers, whose lists leave them little room, ResNet-50
+// set at 1.5625 % 102.9 / 96.2 / 100.1 / -, VGG16 set at 25 % 913 / 901 / 899 / -; thresholds reused, LSTM set 167.7 / 167.9 / 166.6 /
+// 163.5, searched, 126 M elements at 0.4 % 384 / 386 / 382 / 376; without hints, LSTM set 337 / 349 / 342 / 334.)
+template <bool kNt, bool kMom, uint32_t kAhead, typename F>
+__device__ __forceinline__ void stream_groups(gcvf4 G4, gvf4 V4, gvf4 U4, uint32_t groups, F&& f) {
+  const uint32_t lane = lane_id();
+  vf4 g[kAhead], v[kAhead], u[kAhead];
+  auto load = [&](uint32_t t, uint32_t at) __attribute__((always_inline)) {
+    const uint32_t o = at * kWaveSize + lane;
+    g[t] = __builtin_nontemporal_load(&G4[o]);
+    v[t] = stream_load<kNt>(V4 + o);
+    if constexpr (kMom) u[t] = stream_load<kNt>(U4 + o);
+  };
+#pragma unroll
+  for (uint32_t t = 0; t < kAhead; ++t)
+    if (t < groups) load(t, t);
+  for (uint32_t g0 = 0; g0 < groups; g0 += kAhead) {
+#pragma unroll
+    for (uint32_t t = 0; t < kAhead; ++t) {
+      const uint32_t at = g0 + t;
+      if (at < groups) {
+        const float gg[4] = {g[t].x, g[t].y, g[t].z, g[t].w}, vv[4] = {v[t].x, v[t].y, v[t].z, v[t].w};
+        float uu[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (kMom) { uu[0] = u[t].x; uu[1] = u[t].y; uu[2] = u[t].z; uu[3] = u[t].w; }
+        f(gg, vv, uu, at * kWaveSize + lane, [&]() __attribute__((always_inline)) { if (at + kAhead < groups) load(t, at + kAhead); });
+      }
+    }
+  }
+}
+
 // The zeros that mask a sent entry out of the residual (and the velocity) are isolated 4-byte
 // writes, one cache line in a thousand.  Left dirty in the caches they are written to DRAM one
 // by one while the next streaming pass runs and cost it about a tenth of its bandwidth; stored

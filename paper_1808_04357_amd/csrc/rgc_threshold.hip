@@ -132,8 +132,7 @@ __device__ __forceinline__ void for_listed(const ThresholdArgs& A, const Place& 
 }
 
 // The accumulate of Algorithm 1 over [begin, end) of a layer (same arithmetic as the exact path:
-// accum4), handing every group of accumulated values to f.  Whole groups are
-// taken four (two with a velocity) at a time, all their loads issued before the first use.
+// accum4), handing every group of accumulated values to f.
 template <bool kNt, bool kMom, bool kNest, typename F>
 __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t begin, uint32_t end, const AccumRule& rule, F&& f) {
   const gptr<const float> G = as_global(L.grad);
@@ -142,66 +141,41 @@ __device__ __forceinline__ void accumulate_groups(const LayerDesc& L, uint32_t b
   const uint32_t lane = lane_id();
   uint32_t base = begin;
   {
-    constexpr uint32_t kUnroll = kMom && !kNt ? 2u : 4u;
-    for (; base + kUnroll * kGroupElems <= end; base += kUnroll * kGroupElems) {
-      vf4 gq[kUnroll], vq[kUnroll], uq[kUnroll];
-#pragma unroll
-      for (uint32_t t = 0; t < kUnroll; ++t) {
-        const uint32_t idx0 = base + t * kGroupElems + lane * 4u;
-        gq[t] = __builtin_nontemporal_load(as_vec(L.grad + idx0));
-        vq[t] = stream_load<kNt>(as_vec(L.resid + idx0));
-        if constexpr (kMom) uq[t] = stream_load<kNt>(as_vec(L.mom + idx0));
-      }
-#pragma unroll
-      for (uint32_t t = 0; t < kUnroll; ++t) {
-        const uint32_t idx0 = base + t * kGroupElems + lane * 4u;
-        const float g[4] = {gq[t].x, gq[t].y, gq[t].z, gq[t].w};
-        const float v[4] = {vq[t].x, vq[t].y, vq[t].z, vq[t].w};
-        float u[4] = {0.f, 0.f, 0.f, 0.f}, a[4];
-        if constexpr (kMom) { u[0] = uq[t].x; u[1] = uq[t].y; u[2] = uq[t].z; u[3] = uq[t].w; }
-        accum4<kMom, kNest>(g, v, u, rule, a);
-        stream_store<kNt>(as_vec(L.resid + idx0), vf4{a[0], a[1], a[2], a[3]});
-        if constexpr (kMom) stream_store<kNt>(as_vec(L.mom + idx0), vf4{u[0], u[1], u[2], u[3]});
-        f(a, 4u, idx0);
-      }
-    }
+    const uint32_t groups = __builtin_amdgcn_readfirstlane((end - begin) / kGroupElems);
+    const gvf4 V4 = as_vec(L.resid + begin);
+    const gvf4 U4 = kMom ? as_vec(L.mom + begin) : nullptr;
+    stream_groups<kNt, kMom, 4>(as_vec(L.grad + begin), V4, U4, groups,
+                                [&](const float (&g)[4], const float (&v)[4], float (&u)[4], uint32_t o, auto&& next) {
+      float a[4];
+      accum4<kMom, kNest>(g, v, u, rule, a);
+      next();
+      stream_store<kNt>(V4 + o, vf4{a[0], a[1], a[2], a[3]});
+      if constexpr (kMom) stream_store<kNt>(U4 + o, vf4{u[0], u[1], u[2], u[3]});
+      f(a, 4u, begin + 4u * o);
+    });
+    base = begin + groups * kGroupElems;
   }
   for (; base < end; base += kGroupElems) {
     const uint32_t idx0 = base + lane * 4u;
     float g[4] = {0.f, 0.f, 0.f, 0.f}, v[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f}, a[4];
-    if (base + kGroupElems <= end) {
-      const vf4 gq = __builtin_nontemporal_load(as_vec(L.grad + idx0));
-      const vf4 vq = *as_vec(L.resid + idx0);
-      g[0] = gq.x; g[1] = gq.y; g[2] = gq.z; g[3] = gq.w;
-      v[0] = vq.x; v[1] = vq.y; v[2] = vq.z; v[3] = vq.w;
-      if constexpr (kMom) {
-        const vf4 uq = *as_vec(L.mom + idx0);
-        u[0] = uq.x; u[1] = uq.y; u[2] = uq.z; u[3] = uq.w;
-      }
-      accum4<kMom, kNest>(g, v, u, rule, a);
-      stream_store<kNt>(as_vec(L.resid + idx0), vf4{a[0], a[1], a[2], a[3]});
-      if constexpr (kMom) stream_store<kNt>(as_vec(L.mom + idx0), vf4{u[0], u[1], u[2], u[3]});
-      f(a, 4u, idx0);
-    } else {
-      const uint32_t nvalid = idx0 < end ? ((end - idx0) < 4u ? (end - idx0) : 4u) : 0u;
+    const uint32_t nvalid = idx0 < end ? ((end - idx0) < 4u ? (end - idx0) : 4u) : 0u;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (static_cast<uint32_t>(j) < nvalid) {
-          g[j] = G[idx0 + j];
-          v[j] = V[idx0 + j];
-          if constexpr (kMom) u[j] = U[idx0 + j];
-        }
+    for (int j = 0; j < 4; ++j) {
+      if (static_cast<uint32_t>(j) < nvalid) {
+        g[j] = G[idx0 + j];
+        v[j] = V[idx0 + j];
+        if constexpr (kMom) u[j] = U[idx0 + j];
       }
-      accum4<kMom, kNest>(g, v, u, rule, a);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (static_cast<uint32_t>(j) < nvalid) {
-          V[idx0 + j] = a[j];
-          if constexpr (kMom) U[idx0 + j] = u[j];
-        }
-      }
-      f(a, nvalid, idx0);
     }
+    accum4<kMom, kNest>(g, v, u, rule, a);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (static_cast<uint32_t>(j) < nvalid) {
+        V[idx0 + j] = a[j];
+        if constexpr (kMom) U[idx0 + j] = u[j];
+      }
+    }
+    f(a, nvalid, idx0);
   }
 }
 
