@@ -208,6 +208,7 @@ struct CompressPlan {
   hipEvent_t uploaded = nullptr;    // recorded after the uploads
   uint64_t tensor_bytes = 0;               // gradients, residuals and velocities together
   uint64_t total_elems = 0;
+  uint32_t max_workgroups = 0;             // of a layer, in the general tiling
   uint64_t listable_elems = 0;             // elements of the layers that a searching threshold call can list the largest of
   uint64_t write_bytes = 0;                // what the streaming pass writes (V, and u where there is one)
   uint32_t max_k = 0;                      // the largest k of the list
@@ -433,6 +434,7 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
   P.listable_elems = 0;
   P.total_elems = static_cast<uint64_t>(total_elems);
   P.max_k = 0;
+  P.max_workgroups = 0;
   P.any_dense = false;
   P.tiled_needs_hints = false;
   for (int32_t l = 0; l < L; ++l) {
@@ -443,6 +445,7 @@ int build_compress_plan(rgc_ctx* ctx, CompressPlan& P, const rgc_layer* layers, 
     if (threshold_listable(static_cast<uint32_t>(layers[l].n), static_cast<uint32_t>(layers[l].k)))
       P.listable_elems += static_cast<uint64_t>(layers[l].n);
     P.max_k = std::max(P.max_k, static_cast<uint32_t>(layers[l].k));
+    P.max_workgroups = std::max(P.max_workgroups, desc[l].wg_count);
   }
   P.valid = true;
   return RGC_OK;
@@ -847,6 +850,7 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   A.grad_scale = grad_scale;
   A.sum_parts = exact_parts_at(ctx->d_norm_part.p, ctx->wg_max);
   A.part_max = reinterpret_cast<float*>(ctx->d_wc_b.p);
+  A.wg_counts = ctx->d_wc_b.p;
   A.counts = ctx->d_wc_a.p;
   A.listed = ctx->d_cand_cnt.p;
   A.slots = ctx->d_slots.p;
@@ -858,6 +862,7 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   A.chunk = plan->general.chunk;
   A.search = (flags & RGC_THRESHOLD_SEARCH) ? 1u : 0u;
   A.sampled = plan->listable_elems >= kSampleElems ? 1u : 0u;
+  A.scanned = plan->max_workgroups > kOffsetsWgs ? 1u : 0u;
   A.mask_momentum = (flags & RGC_NO_MOMENTUM_MASK) ? 0u : 1u;
   A.nesterov = (flags & RGC_NESTEROV) ? 1u : 0u;
   A.m = momentum;

@@ -235,7 +235,8 @@ struct ThresholdArgs {
   const float* grad_scale;  // device word every gradient element is multiplied with first, or null
   ExactParts sum_parts;     // [workgroups] parts of the sum of |a|
   float* part_max;          // [workgroups] partial maxima of |a|
-  uint32_t* counts;         // [wave-chunks] elements above the threshold, then first output positions
+  uint32_t* counts;         // [wave-chunks] elements above the threshold (then first output positions, if `scanned`)
+  uint32_t* wg_counts;      // [workgroups] elements above the threshold (the memory of part_max, which is no longer needed then)
   uint32_t* listed;         // [wave-chunks] elements above the threshold (kept; more than cap: list incomplete)
   uint2* slots;             // [wave-chunks][cap] (float bits, index) of the elements above a reused threshold
   uint32_t cap;             // list slots per wave-chunk
@@ -246,12 +247,17 @@ struct ThresholdArgs {
   uint32_t chunk;           // elements per wave-chunk
   uint32_t search;          // 1: Algorithm 3 finds the thresholds; 0: they are given
   uint32_t sampled;         // searching call: a sample says what the streaming pass lists (0: it lists nothing)
+  uint32_t scanned;         // some layer has more than kOffsetsWgs workgroups: the counts are scanned by a launch of their own
   uint32_t past_cache;      // the first pass reads and writes residual and velocity past the memory-side cache
   uint32_t reverse;         // the first pass takes its workgroups in descending order (and every pass after it the other way)
   uint32_t mask_momentum;
   uint32_t nesterov;
   float m;
 };
+
+// Up to this many workgroups a layer, every workgroup that writes a part of the message adds the counts of those before it up by itself
+// (268 M elements; 32 KB each at most, 16 on average.  In a layer of 2^31 elements that would be 131 KB each, 8.6 GB together.)
+constexpr uint32_t kOffsetsWgs = 8192;
 
 // The sample of a searching threshold call: kPieceElems elements from each of up to kSampleThreads places of a layer, and the
 // magnitude that threshold_sample_rank() of them exceed.  Lists hold one element in 16 and single ones several times the

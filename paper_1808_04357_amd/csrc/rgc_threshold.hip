@@ -21,9 +21,10 @@
 //
 // Launches of one call (same workgroup -> layer -> wave-chunk decomposition as the exact path):
 //   search:  sample  ->  accumulate (+ partial sums and maxima of |a|, lists)  ->  moments  ->  histogram  ->  search
-//            ->  count  ->  offsets  ->  emit
-//   reuse:   accumulate (+ the elements above the given threshold, listed per wave-chunk)  ->  offsets
+//            ->  count  ->  emit
+//   reuse:   accumulate (+ the elements above the given threshold, listed per wave-chunk)
 //            ->  emit from the lists
+//   and a launch that scans the counts of very large layers before emit
 #include "rgc_exact.h"
 
 namespace rgc {
@@ -185,6 +186,18 @@ __device__ __forceinline__ float wave_max(float x) {
   return x;
 }
 
+// The workgroup's elements above the threshold, from its waves' counts (every thread of a wave has its wave's).
+__device__ __forceinline__ void leave_wg_count(const ThresholdArgs& A, uint32_t wg, uint32_t count, uint32_t* wave_counts) {
+  if (lane_id() == 0u) wave_counts[threadIdx.x >> 6] = count;
+  __syncthreads();
+  if (threadIdx.x == 0u) {
+    uint32_t sum = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < kWavesPerBlock; ++w) sum += wave_counts[w];
+    A.wg_counts[wg] = sum;
+  }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ sample (a search follows)
@@ -283,6 +296,7 @@ template <bool kNt, bool kSearch, bool kReverse>
 __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(ThresholdArgs A) {
   __shared__ ExactShared sh;
   __shared__ float wave_mx[kWavesPerBlock];
+  __shared__ uint32_t wave_counts[kWavesPerBlock];
   if constexpr (kSearch) {
     exact_shared_init(sh);
     __syncthreads();
@@ -293,9 +307,9 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
   const Place p = place_of(A, L, l, wg);
   ExactAcc acc{0.0, 0.0, 0u};
   float mx = 0.0f;
+  uint32_t cnt = 0u;                        // elements above the magnitude so far, the same in every lane
   if (p.begin != p.end) {
     const float thr = !kSearch ? *as_global(A.thresholds + l) : A.sampled ? A.moments[l].listed_above : __uint_as_float(0x7F800000u);
-    uint32_t cnt = 0u;                      // elements above it so far, the same in every lane
     const gptr<vu2> slot = as_global(reinterpret_cast<vu2*>(A.slots + static_cast<size_t>(p.wc) * A.cap));
     auto take = [&](const float (&a)[4], uint32_t nvalid, uint32_t idx0) {
       if constexpr (kSearch) {
@@ -347,6 +361,8 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
       for (int w = 1; w < kWavesPerBlock; ++w) bm = fmaxf(bm, wave_mx[w]);
       A.part_max[wg] = bm;
     }
+  } else {
+    leave_wg_count(A, wg, cnt, wave_counts);
   }
 }
 
@@ -355,7 +371,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_accumulate_kernel(Thr
 // maximum, stores mean, max and max - mean, and clears the layer's histogram for the pass that follows.
 __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(ThresholdArgs A) {
   __shared__ ExactShared sh;
-  __shared__ float redm[kBlockThreads];
+  __shared__ float wave_mx[kWavesPerBlock];
   __shared__ uint32_t scan[kWavesPerBlock];
   exact_shared_init(sh);
   __syncthreads();
@@ -364,10 +380,16 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(Thresh
   ExactPair acc;
   float mx = 0.0f;
   exact_take_parts(acc, A.sum_parts, L.wg_first, L.wg_count, sh);
-  for (uint32_t i = threadIdx.x; i < L.wg_count; i += kBlockThreads) mx = fmaxf(mx, A.part_max[L.wg_first + i]);
+  constexpr uint32_t kItems = 8;          // independent loads in flight per thread
+  for (uint32_t base = threadIdx.x; base < L.wg_count; base += kItems * kBlockThreads) {
+    float v[kItems];
+#pragma unroll
+    for (uint32_t j = 0; j < kItems; ++j) v[j] = base + j * kBlockThreads < L.wg_count ? A.part_max[L.wg_first + base + j * kBlockThreads] : 0.0f;
+#pragma unroll
+    for (uint32_t j = 0; j < kItems; ++j) mx = fmaxf(mx, v[j]);
+  }
   // what the lists hold: all of them complete, and 2k elements or more together
   uint32_t listed = 0u, bad = 0u;
-  constexpr uint32_t kItems = 8;          // independent loads in flight per thread
   for (uint32_t base = threadIdx.x; base < L.wc_count; base += kItems * kBlockThreads) {
     uint32_t v[kItems];
 #pragma unroll
@@ -378,16 +400,15 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_moments_kernel(Thresh
   uint32_t listed_all;
   (void)block_excl_scan(listed, scan, listed_all);
   bad = __syncthreads_or(static_cast<int>(bad)) ? 1u : 0u;
-  redm[threadIdx.x] = mx;
+  mx = wave_max(mx);
+  if (lane_id() == 0u) wave_mx[threadIdx.x >> 6] = mx;
   const double sum = exact_finish(acc, sh);                 // holds barriers
-  for (uint32_t step = kBlockThreads / 2u; step >= 1u; step >>= 1) {
-    if (threadIdx.x < step) redm[threadIdx.x] = fmaxf(redm[threadIdx.x], redm[threadIdx.x + step]);
-    __syncthreads();
-  }
   if (threadIdx.x == 0u) {
     ThresholdMoments M;
     M.mean = static_cast<float>(sum / static_cast<double>(L.n));
-    M.max = redm[0];
+    M.max = wave_mx[0];
+#pragma unroll
+    for (int w = 1; w < kWavesPerBlock; ++w) M.max = fmaxf(M.max, wave_mx[w]);
     M.span = __fsub_rn(M.max, M.mean);
     M.counts_taken = 0u;
     M.listed_above = A.sampled ? A.moments[l].listed_above : __uint_as_float(0x7F800000u);
@@ -503,7 +524,7 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_count_kernel(Threshol
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   const Place p = place_of(A, L, l, wg);
-  if (p.begin == p.end) return;
+  __shared__ uint32_t wave_counts[kWavesPerBlock];
   const float thr = *as_global(A.thresholds + l);
   uint32_t cnt = 0u;
   if (A.moments[l].lists) for_listed(A, p, [&](const vu2& e, bool in) { cnt += in && fabsf(__uint_as_float(e.x)) > thr ? 1u : 0u; });
@@ -512,11 +533,12 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_count_kernel(Threshol
     for (int j = 0; j < 4; ++j) cnt += (static_cast<uint32_t>(j) < nvalid && fabsf(a[j]) > thr) ? 1u : 0u;
   });
   const uint32_t total = wave_total(wave_incl_scan(cnt));
-  if (lane_id() == 0u) A.counts[p.wc] = total;
+  if (p.begin != p.end && lane_id() == 0u) A.counts[p.wc] = total;
+  leave_wg_count(A, wg, total, wave_counts);
 }
 
-// One workgroup per layer: the wave-chunk counts become the wave-chunks' first output positions.  (By the last workgroup of the
-// layer in the launch before: LSTM set 17.2 us instead of 4.6 + 4.6.)
+// Calls with a layer of more than kOffsetsWgs workgroups, one workgroup per layer: the wave-chunk counts become the wave-chunks' first
+// output positions.  (By the last workgroup of the layer in the launch before: LSTM set 17.2 us instead of 4.6 + 4.6.)
 __global__ void __launch_bounds__(kBlockThreads) threshold_offsets_kernel(ThresholdArgs A) {
   __shared__ uint32_t lds_scan[kWavesPerBlock];
   const uint32_t l = blockIdx.x;
@@ -556,9 +578,41 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_emit_kernel(Threshold
   const uint32_t l = A.wg2layer[wg];
   const LayerDesc L = A.layers[l];
   const Place p = place_of(A, L, l, wg);
-  if (p.begin == p.end) return;
   const uint32_t cap = 2u * L.k;
-  uint32_t out_pos = A.counts[p.wc];
+  uint32_t out_pos = p.begin != p.end ? A.counts[p.wc] : 0u;
+  if (A.scanned == 0u) {
+    // Where this wave's part of the message begins: every workgroup adds the counts of those before it up by itself, sixteen words of a
+    // thread in flight.  (With one workgroup a layer and a launch for that instead, us per call: LSTM set searching 217 / 204, reusing
+    // 163.8 / 160.4, 126 M elements in two tensors 0.4 % 378 / 364, 0.2 M in three 17.8 / 15.9; some 1.5 us of the searching calls'
+    // difference are the moments' sums and maxima.)
+    __shared__ uint32_t sums[kWavesPerBlock], counts[kWavesPerBlock];
+    const uint32_t wave = threadIdx.x >> 6, before = wg - L.wg_first;
+    const gptr<const uint32_t> c = as_global(static_cast<const uint32_t*>(A.wg_counts)) + L.wg_first;
+    constexpr uint32_t kItems = 16;
+    uint32_t sum = 0u;
+    for (uint32_t base = threadIdx.x; base < before; base += kItems * kBlockThreads) {
+      uint32_t v[kItems];
+#pragma unroll
+      for (uint32_t j = 0; j < kItems; ++j) v[j] = base + j * kBlockThreads < before ? c[base + j * kBlockThreads] : 0u;
+#pragma unroll
+      for (uint32_t j = 0; j < kItems; ++j) sum += v[j];
+    }
+    sum = wave_total(wave_incl_scan(sum));
+    if (lane_id() == 0u) { sums[wave] = sum; counts[wave] = out_pos; }
+    __syncthreads();
+    uint32_t first = 0u, all = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < kWavesPerBlock; ++w) {
+      first += sums[w] + (w < wave ? counts[w] : 0u);
+      all += sums[w] + counts[w];
+    }
+    out_pos = first;
+    if (before + 1u == L.wg_count && threadIdx.x == 0u) {
+      *as_global(L.out_count) = static_cast<int32_t>(all < cap ? all : cap);
+      if (A.nnz) *as_global(A.nnz + l) = static_cast<int32_t>(all);
+    }
+  }
+  if (p.begin == p.end) return;
   if (out_pos >= cap) return;                      // the buffer is full: the rest stays in the residual
   const bool clear_mom = (L.mom != nullptr) && A.mask_momentum;
   const gptr<int32_t> out_idx = as_global(L.out_idx);
@@ -624,14 +678,14 @@ hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, u
     RGC_LAUNCHED();
     hipLaunchKernelGGL(threshold_count_kernel<false>, dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
-    hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
+    if (a.scanned) hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL((threshold_emit_kernel<true, true>), dim3(num_wgs), block, 0, s, a);
   } else {
     if (a.past_cache) hipLaunchKernelGGL((threshold_accumulate_kernel<true, false, false>), dim3(num_wgs), block, 0, s, a);
     else hipLaunchKernelGGL((threshold_accumulate_kernel<false, false, false>), dim3(num_wgs), block, 0, s, a);
     RGC_LAUNCHED();
-    hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
+    if (a.scanned) hipLaunchKernelGGL(threshold_offsets_kernel, dim3(num_layers), block, 0, s, a);
     RGC_LAUNCHED();
     hipLaunchKernelGGL((threshold_emit_kernel<true, false>), dim3(num_wgs), block, 0, s, a);
   }
