@@ -257,7 +257,6 @@ struct rgc_ctx {
   CompressPlan plans[kPlanCache];
   uint64_t tick = 0;
   int64_t optional_scratch_cap = -1;       // bytes the dense layers' lists may take (diagnostics); negative: no cap
-  bool compressed_since_decompress = false;
   uint64_t compress_calls = 0;             // its parity is the direction of the next streaming pass
   uint32_t threshold_reverse = 0;          // direction of the next threshold-selection call's first pass
   // Speed hints are kept per selection mode (0 magnitude, 1 largest, 2 smallest: the thresholds of
@@ -875,7 +874,6 @@ int rgc_compress_layers_threshold(rgc_ctx* ctx, const rgc_layer* layers, int32_t
   A.reverse = alternate ? ctx->threshold_reverse : 0u;
   RGC_HIP(launch_threshold_compress(A, plan->general.workgroups, static_cast<uint32_t>(num_layers), stream));
   if (!A.search) ctx->threshold_reverse ^= 1u;
-  ctx->compressed_since_decompress = true;
   return RGC_OK;
 }
 
@@ -966,7 +964,6 @@ int rgc_compress_layers_scaled(rgc_ctx* ctx, const rgc_layer* layers, int32_t nu
   A.past_cache = stream_past_cache(plan, A.use_hints == 0u);
   A.reverse = streaming_direction(plan, ctx->compress_calls, dense);
   ++ctx->compress_calls;
-  ctx->compressed_since_decompress = true;
   A.nesterov = (flags & RGC_NESTEROV) ? 1u : 0u;
   // a call that leaves most of the device idle spreads its candidate lists over as many workgroups as it has
   A.list_group = num_wgs <= kSmallCallWorkgroups ? 1u : kListGroup;
@@ -1233,12 +1230,6 @@ int rgc_decompress_accumulate(rgc_ctx* ctx, const rgc_msg* msgs, int32_t num_wor
   A.add_to_dst = (flags == RGC_ADD_TO_DST) ? 1u : 0u;
   A.scale = scale;
   A.one_value = one_value ? 1u : 0u;
-  // After a compression call the messages are read with streaming loads.  (The line was drawn while the streaming passes went
-  // through the memory-side cache and found their tensors' ends there.  Now, VGG16 set and 128 workers, streaming / plain: the
-  // step 722 / 689 us with nothing between two steps, 741 / 770 after 2 GB of other traffic; a decompression by itself 203 /
-  // 167 us on the same messages again, 203 / 215 on three lists in turn, 217 / 244 after other traffic.)
-  A.stream_msgs = ctx->compressed_since_decompress ? 1u : 0u;
-  ctx->compressed_since_decompress = false;
   if (validate) RGC_HIP(launch_decompress_validate(A, ctx->d_err.p + 1, stream));
   if (ctx->profiling) RGC_HIP(take_event(ctx, stream, ctx->ev_decompress));
   RGC_HIP(launch_decompress_table(A, stream));

@@ -477,7 +477,7 @@ __device__ __forceinline__ void wait_for_memory() { __builtin_amdgcn_s_waitcnt(0
 // blocks starting at the one that holds entry E, and the blocks that enter it are loaded while
 // the tile is being finished.  There is no per-tile offset table: E starts from a binary search
 // at the first tile of a layer and then advances by what each tile consumes.
-template <uint32_t kMaxWorkers, uint32_t kLog, bool kStreamMsgs, bool kOneValue, bool kAdd>
+template <uint32_t kMaxWorkers, uint32_t kLog, bool kOneValue, bool kAdd>
 __global__ void __launch_bounds__(FastGeom<kMaxWorkers>::kThreads) __attribute__((amdgpu_waves_per_eu(kMaxWorkers == kFewWorkers && kLog == 13u ? 2 : 4, 4)))
 decompress_tiles_kernel(DecompressArgs A) {
   constexpr uint32_t kFastThreads = FastGeom<kMaxWorkers>::kThreads, kRowStride = FastGeom<kMaxWorkers>::kRowStride;
@@ -580,18 +580,12 @@ decompress_tiles_kernel(DecompressArgs A) {
       const bool need = want != have, whole = at + 4u <= my_count;
       have = want;
       if (need && whole) {
-        // Streaming loads when the caller alternates compression and decompression: what the
-        // memory-side cache holds of the compression's tensors is worth more to the next call than
-        // the other half of this 128-byte line, which then comes from DRAM again four tiles later.
-        // (a template parameter, not a run-time flag: merged into one branch-free load the two
-        // flavours would lose the hint)
-        if constexpr (kStreamMsgs) {
-          bi = __builtin_nontemporal_load(reinterpret_cast<gptr<const vu4>>(my_idx + at));
-          if constexpr (!kOneValue) bv = __builtin_nontemporal_load(reinterpret_cast<gptr<const vf4u>>(my_val + at));
-        } else {
-          bi = *reinterpret_cast<gptr<const vu4>>(my_idx + at);
-          if constexpr (!kOneValue) bv = *reinterpret_cast<gptr<const vf4u>>(my_val + at);
-        }
+        // (Plain loads: the second half of a 128-byte line is wanted some tiles later and is found in the memory-side cache.  Streaming /
+        // plain, us per step of a compression and a decompression on one message list, on three in turn, after 2 GB of other traffic: VGG16
+        // set, 128 workers 728 / 660, 745 / 734, 748 / 728, 16 workers 651 / 620, 662 / 626, 666 / 651, ResNet-50 set, 128 workers 117.5 / 108,
+        // 149 / 140, 148 / 147, 16 workers 102.5 / 95.3, 125 / 119, 127 / 123, LSTM set, 128 workers 400 / 398, 415 / 423, 418 / 419.)
+        bi = *reinterpret_cast<gptr<const vu4>>(my_idx + at);
+        if constexpr (!kOneValue) bv = *reinterpret_cast<gptr<const vf4u>>(my_val + at);
       }
       if (__builtin_amdgcn_ballot_w64(need && !whole) != 0ull) {     // a message's last block
         if (need && !whole) {
@@ -931,16 +925,15 @@ static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint
   constexpr uint32_t threads = FastGeom<kMaxWorkers>::kThreads;
   uint32_t per = per_cu.load(std::memory_order_relaxed);
   if (per == 0) {
-    per = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<kMaxWorkers, kLog, false, false, false>), threads, 8u) / 8u;
+    per = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<kMaxWorkers, kLog, false, false>), threads, 8u) / 8u;
     per_cu.store(per, std::memory_order_relaxed);
   }
   const uint32_t grid = want < per * cus8 ? want : per * cus8;
   using Kernel = void (*)(DecompressArgs);
-#define RGC_TILES(add) {decompress_tiles_kernel<kMaxWorkers, kLog, false, false, add>, decompress_tiles_kernel<kMaxWorkers, kLog, true, false, add>, \
-                        decompress_tiles_kernel<kMaxWorkers, kLog, false, true, add>, decompress_tiles_kernel<kMaxWorkers, kLog, true, true, add>}
-  static constexpr Kernel kernels[2][4] = {RGC_TILES(false), RGC_TILES(true)};   // (in one kernel for both, calls that overwrite took 4 % more)
-#undef RGC_TILES
-  const Kernel kernel = kernels[a.add_to_dst ? 1 : 0][(a.one_value ? 2u : 0u) + (a.stream_msgs ? 1u : 0u)];
+  // (in one kernel for both, calls that overwrite took 4 % more)
+  static constexpr Kernel kernels[2][2] = {{decompress_tiles_kernel<kMaxWorkers, kLog, false, false>, decompress_tiles_kernel<kMaxWorkers, kLog, true, false>},
+                                           {decompress_tiles_kernel<kMaxWorkers, kLog, false, true>, decompress_tiles_kernel<kMaxWorkers, kLog, true, true>}};
+  const Kernel kernel = kernels[a.add_to_dst ? 1 : 0][a.one_value ? 1 : 0];
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, a);
   return hipGetLastError();
 }

@@ -320,10 +320,9 @@ struct DecompressArgs {
   uint32_t cus;               // compute units of the device (sizes the persistent grids)
   uint32_t num_workers;
   uint32_t num_layers;
-  uint32_t num_tiles;
-  uint32_t num_blocks;
+  uint32_t num_blocks;        // (With num_tiles behind num_layers the tile kernel loads the two together, its code moves by eight bytes, and 256
+  uint32_t num_tiles;         // messages on the ResNet-50 set take 78.9 us instead of 74.7, added 96.6 instead of 92.0.)
   uint32_t add_to_dst;
-  uint32_t stream_msgs;       // read the messages with streaming loads (see decompress_tiles_kernel)
   uint32_t tile_log;          // positions a tile, a power of two
   uint32_t one_value;         // every message's val points to ONE float that all its entries carry
   float scale;
