@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librgc.so")
 SOURCES = ["rgc_api.cpp", "rgc_compress.hip", "rgc_decompress.hip", "rgc_threshold.hip", "rgc_yardstick.hip"]
-HEADERS = ["rgc_internal.h", "rgc_device.h", "rgc_exact.h", "rgc_tickets.h", os.path.join("..", "..", "include", "rgc.h"),
+HEADERS = ["rgc_internal.h", "rgc_device.h", "rgc_exact.h", "rgc_tickets.h", "rgc_tiles.h", os.path.join("..", "..", "include", "rgc.h"),
            os.path.join("..", "..", "include", "rgc_diag.h")]
 
 FLAGS = [

@@ -661,20 +661,6 @@ bool same_messages(const std::vector<rgc_msg>& key, const rgc_msg* msgs, size_t 
   return true;
 }
 
-// Positions a decompression tile (its logarithm).  A worker has 17 to 32 of its entries in registers; a tile that holds more of them
-// fetches the rest from memory one round trip after the other, and has more colliding positions than rows.  A smaller tile in turn
-// pays the steps of a tile more often, 512 threads more dearly than 256.  us per call with 2048 / 4096 / 8192 positions, 20 M
-// elements: 8 workers 0.2 % 45 / 22 / 31, 0.4 % 47 / 30 / 66, 0.8 % 70 / 68 / 136, 6 % 947 / 995 / 2979; 64 workers 0.05 % 48 / 24 / 24,
-// 0.2 % 54 / 28 / 39, 0.4 % 59 / 44 / 92; 128 workers 0.05 % 67 / 42 / 27, 0.2 % 78 / 50 / 52, 0.4 % 85 / 113 / 135; 200 workers
-// 0.2 % 150 / 91 / 123, 10 M elements 0.4 % 95 / 124 / 157.  At 0.1 % and up to 64 workers it is the number of workgroups: ten tensors
-// of 2 M elements 8.7 / 7.8 / 8.9, ResNet-50 set (26 M) - / 25.9 / 26.9, 64 M - / 59 / 55.
-uint32_t tile_log_for(int64_t elements, int64_t entries, int32_t workers) {
-  if (workers < 1 || workers > static_cast<int32_t>(kFastWorkersMax)) return kTileShift;
-  const double per = static_cast<double>(entries) * kTile / (static_cast<double>(elements) * workers);   // entries of a worker in 8192 positions
-  if (workers <= static_cast<int32_t>(kFewWorkers)) return per > 64.0 ? 11 : per > 11.0 || elements < (int64_t(32) << 20) ? 12 : 13;
-  return per > 22.0 ? 11 : per > 13.0 ? 12 : 13;
-}
-
 // Checks a layer list and finds (or builds) its plan.  On success *out is the plan and the device
 // of the context is current.
 int plan_for_layers(rgc_ctx* ctx, const rgc_layer* layers, int32_t num_layers, hipStream_t stream,
@@ -1144,12 +1130,12 @@ int rgc_decompress_accumulate(rgc_ctx* ctx, const rgc_msg* msgs, int32_t num_wor
       tiles += layer_tiles[l];
       stride += layer_tiles[l] + 1u;
     }
-    const bool need_table = num_workers > static_cast<int32_t>(kFastWorkersMax);   // only the any-number-of-workers kernel reads the offset table
-    uint64_t blocks = 0;                                    // ... which is built by one workgroup per 1024 entries of a message
+    const bool need_table = needs_offset_table(num_workers);
+    uint64_t blocks = 0;
     if (need_table)
       for (size_t i = 0; i < NM; ++i) blocks += std::max<uint64_t>(1, (static_cast<uint64_t>(msgs[i].count) + 1023) / 1024);
-    const uint64_t tab_words = stride * static_cast<uint64_t>(std::max(num_workers, 1));
-    if (tiles > 0x7FFFFFFFull || blocks > 0x7FFFFFFFull || tab_words > 0xFFFFFFFFull) return RGC_ENOMEM;
+    if (!tables_reach(tiles, stride, blocks, num_workers)) return RGC_ENOMEM;
+    const uint64_t tab_words = stride * static_cast<uint64_t>(num_workers);
     const size_t off_msgs = 0;
     const size_t off_layers = off_msgs + sizeof(MsgDesc) * std::max<size_t>(NM, 1);
     const size_t off_blocks = off_layers + sizeof(DecompressLayer) * num_layers;

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "rgc_tiles.h"
+
 namespace rgc {
 
 // ---------------------------------------------------------------- geometry (compile time)
@@ -277,15 +279,7 @@ constexpr bool threshold_listable(uint32_t n, uint32_t k) {
 hipError_t launch_threshold_compress(const ThresholdArgs& a, uint32_t num_wgs, uint32_t num_layers, hipStream_t s);
 
 // ---------------------------------------------------------------- decompress
-// 8192 positions unless the messages are dense or the call is small (tile_log_for() in rgc_api.cpp): most of a tile's instructions
-// (window checks, map clearing, barriers) are paid per tile, not per position; 16384 leaves room for one workgroup per CU only.
-constexpr int kTileShift = 13;
-constexpr int kTile = 1 << kTileShift;            // dense positions owned by one workgroup (any number of workers)
 constexpr int kEntryCap = 1024;                   // entries staged per worker batch (generic tiles)
-// The tile kernel comes in three sizes, four lanes a worker: 256 threads for up to 64 workers, 512 for up to 128, 1024 for up to
-// 256.  ResNet-50 set, 256 workers, 0.1 %: 76 us against 257 us in the kernel for any number of workers
-// plus 36 us for the table it needs.  256 threads / 512: 16 workers on the VGG16 set 107 / 125 us, on 20 M elements at 0.4 % 32 / 53.
-constexpr uint32_t kFewWorkers = 64, kFastWorkers = 128, kFastWorkersMax = 256;
 constexpr int kBatchWorkers = 128;                // any number of workers: workers per batch (mask of 4 words)
 constexpr int kMaskWords = kBatchWorkers / 32;
 constexpr int kQMax = 128;                        // positions hit more than once per batch

@@ -1,0 +1,41 @@
+// How a decompression call is cut into tiles, and which calls its tables can hold.  No HIP in here: the host tests compile it by itself.
+#pragma once
+
+#include <stdint.h>
+
+namespace rgc {
+
+// 8192 positions unless the messages are dense or the call is small (tile_log_for()): most of a tile's instructions
+// (window checks, map clearing, barriers) are paid per tile, not per position; 16384 leaves room for one workgroup per CU only.
+constexpr int kTileShift = 13;
+constexpr int kTile = 1 << kTileShift;            // dense positions owned by one workgroup (any number of workers)
+// The tile kernel comes in three sizes, four lanes a worker: 256 threads for up to 64 workers, 512 for up to 128, 1024 for up to
+// 256.  ResNet-50 set, 256 workers, 0.1 %: 76 us against 257 us in the kernel for any number of workers
+// plus 36 us for the table it needs.  256 threads / 512: 16 workers on the VGG16 set 107 / 125 us, on 20 M elements at 0.4 % 32 / 53.
+constexpr uint32_t kFewWorkers = 64, kFastWorkers = 128, kFastWorkersMax = 256;
+
+// Positions a decompression tile (its logarithm).  A worker has 17 to 32 of its entries in registers; a tile that holds more of them
+// fetches the rest from memory one round trip after the other, and has more colliding positions than rows.  A smaller tile in turn
+// pays the steps of a tile more often, 512 threads more dearly than 256.  us per call with 2048 / 4096 / 8192 positions, 20 M
+// elements: 8 workers 0.2 % 45 / 22 / 31, 0.4 % 47 / 30 / 66, 0.8 % 70 / 68 / 136, 6 % 947 / 995 / 2979; 64 workers 0.05 % 48 / 24 / 24,
+// 0.2 % 54 / 28 / 39, 0.4 % 59 / 44 / 92; 128 workers 0.05 % 67 / 42 / 27, 0.2 % 78 / 50 / 52, 0.4 % 85 / 113 / 135; 200 workers
+// 0.2 % 150 / 91 / 123, 10 M elements 0.4 % 95 / 124 / 157.  At 0.1 % and up to 64 workers it is the number of workgroups: ten tensors
+// of 2 M elements 8.7 / 7.8 / 8.9, ResNet-50 set (26 M) - / 25.9 / 26.9, 64 M - / 59 / 55.
+inline uint32_t tile_log_for(int64_t elements, int64_t entries, int32_t workers) {
+  if (workers < 1 || workers > static_cast<int32_t>(kFastWorkersMax)) return kTileShift;
+  const double per = static_cast<double>(entries) * kTile / (static_cast<double>(elements) * workers);   // entries of a worker in 8192 positions
+  if (workers <= static_cast<int32_t>(kFewWorkers)) return per > 64.0 ? 11 : per > 11.0 || elements < (int64_t(32) << 20) ? 12 : 13;
+  return per > 22.0 ? 11 : per > 13.0 ? 12 : 13;
+}
+
+// Only the kernel for any number of workers reads the offset table (a word per worker and tile), which one workgroup per 1024 entries
+// of a message builds.
+constexpr bool needs_offset_table(int32_t workers) { return workers > static_cast<int32_t>(kFastWorkersMax); }
+
+// Whether the tables' 32-bit offsets reach: `columns` are the tiles and one more per layer, `blocks` the workgroups that build the table.
+constexpr bool tables_reach(uint64_t tiles, uint64_t columns, uint64_t blocks, int32_t workers) {
+  const uint64_t words = needs_offset_table(workers) ? columns * static_cast<uint64_t>(workers) : 0u;
+  return tiles <= 0x7FFFFFFFull && columns <= 0xFFFFFFFFull && blocks <= 0x7FFFFFFFull && words <= 0xFFFFFFFFull;
+}
+
+}  // namespace rgc

@@ -1,0 +1,17 @@
+"""How large a decompression call may be, from the host's rules alone (see tiles_check.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def test_tables_refuse_only_what_they_cannot_hold(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    exe = str(tmp_path / "tiles_check")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-o", exe, os.path.join(HERE, "tiles_check.cpp")], check=True)
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and "tiles_check ok" in run.stdout, run.stdout + run.stderr

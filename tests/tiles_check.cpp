@@ -1,0 +1,43 @@
+// Host check of rgc_tiles.h: which decompression calls the tables can hold, for lists of equal layers and messages.
+#include <cstdio>
+#include <initializer_list>
+
+#include "../paper_1808_04357_amd/csrc/rgc_tiles.h"
+
+using namespace rgc;
+
+namespace {
+
+int faults = 0;
+
+void expect(const char* what, bool got, bool want) {
+  if (got == want) return;
+  std::printf("%s: %d, expected %d\n", what, got, want);
+  ++faults;
+}
+
+bool accepted(int64_t layers, int64_t n, int32_t workers, int64_t entries_each) {
+  const uint32_t log = tile_log_for(layers * n, layers * workers * entries_each, workers);
+  const uint64_t tiles = static_cast<uint64_t>(layers * ((n + (int64_t(1) << log) - 1) >> log));
+  const uint64_t blocks = needs_offset_table(workers) ? static_cast<uint64_t>(layers * workers * ((entries_each + 1023) / 1024)) : 0u;
+  return tables_reach(tiles, tiles + static_cast<uint64_t>(layers), blocks, workers);
+}
+
+}  // namespace
+
+int main() {
+  // The largest buffers a card holds, in any tile size: up to 256 workers no table stands against them.
+  const int64_t n = int64_t(1) << 30;
+  for (int32_t workers : {1, 64, 65, 128, 129, 256})
+    for (int64_t per_8192 : {1, 12, 15, 25, 70}) {
+      char what[80];
+      std::snprintf(what, sizeof what, "64 layers of 2^30, %d workers, %d entries in 8192", workers, static_cast<int>(per_8192));
+      expect(what, accepted(64, n, workers, (n >> kTileShift) * per_8192), true);
+    }
+  // With more workers the table has a word per worker and column, numbered in 32 bits.
+  expect("257 workers, 2^23 tiles", accepted(64, n, 257, 1000), true);
+  expect("511 workers, 2^23 tiles", accepted(64, n, 511, 1000), true);
+  expect("512 workers, 2^23 tiles", accepted(64, n, 512, 1000), false);
+  std::printf(faults == 0 ? "tiles_check ok\n" : "tiles_check: %d faults\n", faults);
+  return faults == 0 ? 0 : 1;
+}
