@@ -61,23 +61,26 @@ constexpr uint32_t chunk_override() { return 0u; }
 // Elements per wave-chunk for a call over `total` elements.  Larger chunks mean fewer per-chunk
 // counters for the per-layer serial steps, smaller ones more workgroups to fill 256 CUs.
 // A call that is never tiled (`dense`) streams every step with these chunks, and a small one is then bound by the rounds of a wave's
-// loop, on a device it does not fill.  With 1024 / 2048 / 4096, us per call: 0.5 M elements in ten tensors 25 % 32 / 36 / 44, in a hundred
-// 6.25 % 43 / 32 / 37 (short lists miss more hints), 1.5 M in ten 25 % 40.0 / 39.4 / 46.6, in a hundred 6.25 % 64 / 34 / 40, 3 M in ten
-// 25 % 46.0 / 46.1 / 50.0, 6 M in twenty 65 / 54 / 57, 6.25 % 60.1 / 48.7 / 49.1; beyond, 8192 / 2048: 7.6 M in 97 6.25 % 58.6 / 60.3, 12 M
-// in one 96 / 101, 25 M in ten 106 / 119.
-constexpr int64_t kLargeCall = int64_t(8) << 20;
+// loop, on a device it does not fill.  Larger calls have more workgroups than they need with 2048, whose flushes of the histograms and
+// tickets the five passes wait for once hints miss, as they do where the large values sit in few rows.  us per call with 2048 / 4096 / 8192,
+// values that lie anywhere, and in one stretch of 2048 elements of twenty: 0.5 M elements in ten tensors 25 % 34 / 42 / 59, 62 / 88 / 136;
+// 1.5 M in ten 6.25 % 36 / 39 / 50, 70 / 90 / 138; 2 M in one 3 % 36.5 / 39.4 / 50, 67 / 70 / 89; 2.5 M in one 38.9 / 40.3 / 50, 77 / 72 / 90;
+// 3 M in ten 6.25 % 41.4 / 42.2 / 53, 99 / 97 / 144; 4 M in one 45.7 / 44.7 / 54, 115 / 102 / 144; 7.6 M in 97 51.6 / 50.2 / 58.6, 166 / 143 /
+// 156; 12 M in one 79 / 65 / 67, 239 / 207 / 221; 25 M in ten 117 / 109 / 94, 354 / 330 / 328.  (With 1024: 0.5 M in ten 25 % 32, 55, 1.5 M in a
+// hundred 6.25 % 63, 75 where 2048 takes 34, 71: short lists miss more hints.)
+constexpr int64_t kLargeCall = int64_t(8) << 20, kSmallDenseCall = int64_t(2) << 20;
 constexpr uint32_t kChunkDense = 2048;
 uint32_t chunk_for(int64_t total, bool dense) {
   if (chunk_override()) return chunk_override();
   if (total >= kLargeCall) return 8192;
-  return dense ? kChunkDense : kChunkSmallest;
+  return dense && total <= kSmallDenseCall ? kChunkDense : kChunkSmallest;
 }
 
 // Wave-chunks that a call over at most `total` elements in one tensor may have, whichever size it gets: the scratch is sized for it.
 uint64_t chunks_most(int64_t total) {
   const uint64_t smallest = chunk_override() ? std::min(chunk_override(), kChunkSmallest) : kChunkSmallest;
   const uint64_t dense = chunk_override() ? smallest : kChunkDense, n = static_cast<uint64_t>(total);
-  return std::max((n + smallest - 1) / smallest, (std::min<uint64_t>(n, kLargeCall) + dense - 1) / dense);
+  return std::max((n + smallest - 1) / smallest, (std::min<uint64_t>(n, kSmallDenseCall) + dense - 1) / dense);
 }
 
 // The threshold hint of a layer: the rank it is aimed at, for lists of `cap` slots per

@@ -38,6 +38,30 @@ def test_chunk_edges(rgc, oracle, sizes, ppm, momentum):
     ctx.close()
 
 
+@pytest.mark.parametrize("more", [0, 1])
+def test_largest_call_on_short_chunks(rgc, oracle, more):
+    """Calls of 2^21 elements take wave-chunks of 2048 elements, of one more 4096: values anywhere, and in one stretch of twenty."""
+    g = np.random.default_rng(more)
+    sizes = [1_900_001, (1 << 21) - 1_900_001 + more]
+    ks = [rgc.rgc_k_for_density(n, 62_500) for n in sizes]
+    V = [np.zeros(n, np.float32) for n in sizes]
+    dev = GpuLayers(rgc, V, ks)
+    ctx = rgc.Context(sum(sizes), len(sizes))
+    ranked = 0
+    for t in range(8):
+        G = [(g.standard_normal(n) * 5e-3).astype(np.float32) for n in sizes]
+        if t >= 4:
+            G = [x * (g.random(-(-x.size // 2048)) < 0.05).repeat(2048)[:x.size] for x in G]
+        dev.set_grads(G)
+        dev.step(ctx)
+        msgs = oracle_step(oracle, G, V, ks)
+        assert_layers_equal("step %d" % t, ks, dev.results(), msgs, V)
+        ranked += sum(s[0] == 0 and s[2] > 0 for s in ctx.last_stats(len(sizes)))
+    assert ranked >= 2
+    ctx.last_error()
+    ctx.close()
+
+
 @pytest.mark.parametrize("ties", [1500, 2040, 2060, 3000])
 def test_members_in_lds_and_not(rgc, oracle, ties):
     """The k-th key is shared by `ties` elements on every call, and up to 2048 members are ranked in LDS."""
