@@ -21,11 +21,15 @@ constexpr uint32_t kFewWorkers = 64, kFastWorkers = 128, kFastWorkersMax = 256;
 // 0.2 % 54 / 28 / 39, 0.4 % 59 / 44 / 92; 128 workers 0.05 % 67 / 42 / 27, 0.2 % 78 / 50 / 52, 0.4 % 85 / 113 / 135; 200 workers
 // 0.2 % 150 / 91 / 123, 10 M elements 0.4 % 95 / 124 / 157.  At 0.1 % and up to 64 workers it is the number of workgroups: ten tensors
 // of 2 M elements 8.7 / 7.8 / 8.9, ResNet-50 set (26 M) - / 25.9 / 26.9, 64 M - / 59 / 55.
+// From 65 workers on, where 4096 and 8192 positions meet moves with the workers, whose entries collide: entries of each in 8192 positions,
+// us with 4096 / 8192, ResNet-50 set: 65 workers 13.9 48.1 / 42.7, 16.4 51.1 / 48.2, 20.5 54.6 / 64.2; 100 workers 13.9 54.8 / 48.7, 16.4
+// 56.4 / 60.2; 128 workers 13.9 59.1 / 52.6, 16.4 61.9 / 64.7; 160 workers 13.9 96 / 86, 15.6 99 / 111; 200 workers 11.5 106 / 78, 13.9 108 / 103,
+// 16.4 112 / 158; 256 workers 11.5 119 / 101, 13.9 123 / 165; VGG16 set, 65 workers 16.4 208 / 194.
 inline uint32_t tile_log_for(int64_t elements, int64_t entries, int32_t workers) {
   if (workers < 1 || workers > static_cast<int32_t>(kFastWorkersMax)) return kTileShift;
   const double per = static_cast<double>(entries) * kTile / (static_cast<double>(elements) * workers);   // entries of a worker in 8192 positions
   if (workers <= static_cast<int32_t>(kFewWorkers)) return per > 64.0 ? 11 : per > 11.0 || elements < (int64_t(32) << 20) ? 12 : 13;
-  return per > 22.0 ? 11 : per > 13.0 ? 12 : 13;
+  return per > 22.0 ? 11 : per > 18.4 - workers / 48.0 ? 12 : 13;
 }
 
 // Only the kernel for any number of workers reads the offset table (a word per worker and tile), which one workgroup per 1024 entries

@@ -13,7 +13,7 @@ def rgc():
     return m
 
 
-# entries of a worker in 8192 positions: 2048 above 64 and 22, 4096 above 11 and 13 (and in small calls of up to 64 workers), else 8192
+# entries of a worker in 8192 positions: 2048 above 64 and 22, 4096 above 11 and 13 to 17 (and in small calls of up to 64 workers), else 8192
 @pytest.mark.parametrize("add", [False, True])
 @pytest.mark.parametrize("per_8192", [5, 12, 20, 40, 90])
 @pytest.mark.parametrize("workers", [1, 3, 64, 65, 128, 130])

@@ -1,4 +1,4 @@
-"""How large a decompression call may be, from the host's rules alone (see tiles_check.cpp)."""
+"""How large a decompression call may be and which tiles it gets, from the host's rules alone (see tiles_check.cpp)."""
 import os
 import shutil
 import subprocess
@@ -8,7 +8,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-def test_tables_refuse_only_what_they_cannot_hold(tmp_path):
+def test_tables_and_tile_sizes(tmp_path):
     if shutil.which("g++") is None:
         pytest.skip("no g++")
     exe = str(tmp_path / "tiles_check")

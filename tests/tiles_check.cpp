@@ -38,6 +38,15 @@ int main() {
   expect("257 workers, 2^23 tiles", accepted(64, n, 257, 1000), true);
   expect("511 workers, 2^23 tiles", accepted(64, n, 511, 1000), true);
   expect("512 workers, 2^23 tiles", accepted(64, n, 512, 1000), false);
+  // Where tiles of 4096 positions begin to be the faster ones (entries of a worker in 8192 positions).
+  const struct { int32_t workers; double at_13, at_12; } lines[] = {{65, 16.4, 20.5}, {80, 15.6, 18.8}, {96, 15.6, 17.2}, {112, 15.5, 17.2}, {128, 13.9, 16.4},
+                                                                    {144, 13.9, 17.2}, {160, 13.9, 15.6}, {180, 13.9, 15.6}, {200, 12.3, 16.4}, {256, 11.5, 13.9}};
+  for (const auto& l : lines) {
+    char what[80];
+    std::snprintf(what, sizeof what, "%d workers, tiles of 8192 at %.1f and of 4096 at %.1f", l.workers, l.at_13, l.at_12);
+    const auto log = [&](double per) { return tile_log_for(int64_t(100) << 20, static_cast<int64_t>(per * 12800.0 * l.workers), l.workers); };
+    expect(what, log(l.at_13) == 13 && log(l.at_12) == 12, true);
+  }
   std::printf(faults == 0 ? "tiles_check ok\n" : "tiles_check: %d faults\n", faults);
   return faults == 0 ? 0 : 1;
 }
