@@ -1202,7 +1202,10 @@ int rgc_decompress_accumulate(rgc_ctx* ctx, const rgc_msg* msgs, int32_t num_wor
     A.num_layers = static_cast<uint32_t>(num_layers);
     A.num_tiles = static_cast<uint32_t>(tiles);
     A.num_blocks = static_cast<uint32_t>(nb);
-    A.tile_log = tile_log;
+    A.tile_log = static_cast<uint16_t>(tile_log);
+    A.wait_after = 0;
+    if (const uint32_t at_once = stores_at_once(elements, entries, num_workers, tile_log))
+      for (uint32_t j = at_once - 1u; j < 16u; j += at_once) A.wait_after = static_cast<uint16_t>(A.wait_after | (1u << j));
     P.key_msgs.resize(NM);
     for (size_t i = 0; i < NM; ++i) {
       rgc_msg c{};

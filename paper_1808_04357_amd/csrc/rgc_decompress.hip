@@ -477,14 +477,15 @@ __device__ __forceinline__ void wait_for_memory() { __builtin_amdgcn_s_waitcnt(0
 // blocks starting at the one that holds entry E, and the blocks that enter it are loaded while
 // the tile is being finished.  There is no per-tile offset table: E starts from a binary search
 // at the first tile of a layer and then advances by what each tile consumes.
-template <uint32_t kMaxWorkers, uint32_t kLog, bool kOneValue, bool kAdd>
+template <uint32_t kMaxWorkers, uint32_t kLog, bool kPaced, bool kOneValue, bool kAdd>
 __global__ void __launch_bounds__(FastGeom<kMaxWorkers>::kThreads) __attribute__((amdgpu_waves_per_eu(kMaxWorkers == kFewWorkers && kLog == 13u ? 2 : 4, 4)))
 decompress_tiles_kernel(DecompressArgs A) {
   constexpr uint32_t kFastThreads = FastGeom<kMaxWorkers>::kThreads, kRowStride = FastGeom<kMaxWorkers>::kRowStride;
   constexpr uint32_t kTile = 1u << kLog, kWords = kTile / 32u;
   // With few messages a tile is little more than its stores, and fewer of them in flight are faster: VGG16 set, waiting for the
   // tile's stores / not, us per call: 4 workers 110 / 124, 8 workers 103 / 118, 24 workers 107 / 112 (512 threads, 128 workers: 199 / 193);
-  // with one or two workers, waiting twice a tile / once / not: 109 / 120 / 127.
+  // with one or two workers, waiting twice a tile / once / not: 109 / 120 / 127.  Where few entries meet a large dense buffer the host
+  // says after which stores to wait (kPaced, stores_at_once() in rgc_tiles.h).
   constexpr bool kWaitForStores = kMaxWorkers == kFewWorkers;
   __shared__ FastLds<kMaxWorkers, kLog> S;
   const uint32_t tid = threadIdx.x;
@@ -843,7 +844,7 @@ decompress_tiles_kernel(DecompressArgs A) {
           }
           // written once, not read here again: keep it from pushing the message lines out of the L2
           __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vu4l, o), out, static_cast<int>(16u * i4), 0, kNonTemporal);
-          if (kWaitForStores && N <= 2u && (j & 3u) == 3u) wait_for_memory();
+          if (kPaced ? ((A.wait_after >> j) & 1u) != 0u : kWaitForStores && N <= 2u && (j & 3u) == 3u) wait_for_memory();
           if (rest != 0u && i4 == g.len / 4u) {
             const gptr<float> d = as_global(g.dense) + 4u * i4;
             for (uint32_t r = 0; r < rest; ++r) {
@@ -854,7 +855,7 @@ decompress_tiles_kernel(DecompressArgs A) {
           }
         }
       }
-      if constexpr (kWaitForStores) wait_for_memory();
+      if constexpr (kWaitForStores && !kPaced) wait_for_memory();
       __syncthreads();                             // the next tile's first arrivals write into the accumulator that this one has just cleared
     }
   }
@@ -919,20 +920,21 @@ static uint32_t resident_grid(const void* kernel, uint32_t threads, uint32_t cus
   return g < 8u ? 8u : g;
 }
 
-template <uint32_t kMaxWorkers, uint32_t kLog>
+template <uint32_t kMaxWorkers, uint32_t kLog, bool kPaced = false>
 static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint32_t cus8, hipStream_t s) {
   static std::atomic<uint32_t> per_cu{0};              // workgroups per CU; a property of the code object
   constexpr uint32_t threads = FastGeom<kMaxWorkers>::kThreads;
   uint32_t per = per_cu.load(std::memory_order_relaxed);
   if (per == 0) {
-    per = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<kMaxWorkers, kLog, false, false>), threads, 8u) / 8u;
+    per = resident_grid(reinterpret_cast<const void*>(decompress_tiles_kernel<kMaxWorkers, kLog, kPaced, false, false>), threads, 8u) / 8u;
     per_cu.store(per, std::memory_order_relaxed);
   }
   const uint32_t grid = want < per * cus8 ? want : per * cus8;
   using Kernel = void (*)(DecompressArgs);
   // (in one kernel for both, calls that overwrite took 4 % more)
-  static constexpr Kernel kernels[2][2] = {{decompress_tiles_kernel<kMaxWorkers, kLog, false, false>, decompress_tiles_kernel<kMaxWorkers, kLog, true, false>},
-                                           {decompress_tiles_kernel<kMaxWorkers, kLog, false, true>, decompress_tiles_kernel<kMaxWorkers, kLog, true, true>}};
+  static constexpr Kernel kernels[2][2] = {
+      {decompress_tiles_kernel<kMaxWorkers, kLog, kPaced, false, false>, decompress_tiles_kernel<kMaxWorkers, kLog, kPaced, true, false>},
+      {decompress_tiles_kernel<kMaxWorkers, kLog, false, false, true>, decompress_tiles_kernel<kMaxWorkers, kLog, false, true, true>}};
   const Kernel kernel = kernels[a.add_to_dst ? 1 : 0][a.one_value ? 1 : 0];
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, a);
   return hipGetLastError();
@@ -940,6 +942,9 @@ static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint
 
 template <uint32_t kMaxWorkers>
 static hipError_t launch_fast_tiles(const DecompressArgs& a, uint32_t want, uint32_t cus8, hipStream_t s) {
+  // (the combinations that stores_at_once() asks for; calls that add are not paced: 66 M elements, 8 workers 0.01 % 97 us, paced 107)
+  if constexpr (kMaxWorkers == kFewWorkers) if (a.wait_after != 0u && a.tile_log == 12u) return launch_fast_tiles<kMaxWorkers, 12, true>(a, want, cus8, s);
+  if constexpr (kMaxWorkers <= kFastWorkers) if (a.wait_after != 0u && a.tile_log == 13u) return launch_fast_tiles<kMaxWorkers, 13, true>(a, want, cus8, s);
   switch (a.tile_log) {
     case 11: return launch_fast_tiles<kMaxWorkers, 11>(a, want, cus8, s);
     case 12: return launch_fast_tiles<kMaxWorkers, 12>(a, want, cus8, s);

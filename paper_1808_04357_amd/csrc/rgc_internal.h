@@ -317,7 +317,8 @@ struct DecompressArgs {
   uint32_t num_blocks;        // (With num_tiles behind num_layers the tile kernel loads the two together, its code moves by eight bytes, and 256
   uint32_t num_tiles;         // messages on the ResNet-50 set take 78.9 us instead of 74.7, added 96.6 instead of 92.0.)
   uint32_t add_to_dst;
-  uint32_t tile_log;          // positions a tile, a power of two
+  uint16_t tile_log;          // positions a tile, a power of two
+  uint16_t wait_after;        // bit j: a lane waits for its stores after its j-th one of a tile (0: no rule; see stores_at_once())
   uint32_t one_value;         // every message's val points to ONE float that all its entries carry
   float scale;
 };

@@ -32,6 +32,23 @@ inline uint32_t tile_log_for(int64_t elements, int64_t entries, int32_t workers)
   return per > 22.0 ? 11 : per > 18.4 - workers / 48.0 ? 12 : 13;
 }
 
+// How many 16-byte stores a lane of the tile kernel has under way before it waits for them (0: as the kernel does without such a rule).
+// Where a tile is little more than its stores and the dense buffers outgrow the memory-side cache, the memory takes them the faster the
+// fewer come at once, down to what keeps it busy, and that depends on the time the tile's entries take.  us without the rule / with 1 / 2 /
+// 4 / 8 stores, VGG16 set: 3 workers 0.02 % (5 entries of all workers in 8192 positions) 121 / 112 / 117 / 121 / 123, 16 workers 0.01 % (13)
+// 123 / 118 / 108 / 121 / 123, 4 workers 0.05 % (16) 120 / 125 / 111 / 104 / 111, 16 workers 0.02 % (26) 121 / 124 / 109 / 104 / 117, 64 workers
+// 0.01 % (52) 122 / 131 / 116 / 108 / 115, 8 workers 0.1 % (66) 103 / 131 / 117 / 110 / 106; tiles of 4096, 2 workers 0.2 % (33) 125 / 111 /
+// 121 / 125; from 65 workers on 65 of 0.01 % (53) 131 / 111 / 119 / 124, 128 of 0.01 % (105) 132 / 129 / 122 / 118, 100 of 0.02 % (164) 109 / 129 /
+// 122 / 118.  66 M elements: 16 workers 0.02 % 66 / 64 / 58 / 65.  Smaller buffers, without / with the rule: 50 M elements, 4 workers 0.05 %
+// 48.2 / 45.8, 2 workers 47.2 / 47.3, 44 M 41.3 / 42.9, 41.7 / 44.4, 36 M 33.8 / 36.4, 34.6 / 37.7.
+inline uint32_t stores_at_once(int64_t elements, int64_t entries, int32_t workers, uint32_t tile_log) {
+  if (elements < (int64_t(48) << 20) || workers < 1 || workers > static_cast<int32_t>(kFastWorkers)) return 0;
+  const double in_8192 = static_cast<double>(entries) * kTile / static_cast<double>(elements);   // entries of all workers in 8192 positions
+  if (workers > static_cast<int32_t>(kFewWorkers)) return tile_log != 13 || in_8192 > 120.0 ? 0 : in_8192 > 90.0 ? 2 : 1;
+  if (tile_log == 12) return in_8192 > 40.0 ? 0 : 1;
+  return tile_log != 13 || in_8192 < 4.5 || in_8192 > 60.0 ? 0 : in_8192 > 30.0 ? 4 : in_8192 > 9.0 ? 2 : 1;
+}
+
 // Only the kernel for any number of workers reads the offset table (a word per worker and tile), which one workgroup per 1024 entries
 // of a message builds.
 constexpr bool needs_offset_table(int32_t workers) { return workers > static_cast<int32_t>(kFastWorkersMax); }

@@ -47,6 +47,16 @@ int main() {
     const auto log = [&](double per) { return tile_log_for(int64_t(100) << 20, static_cast<int64_t>(per * 12800.0 * l.workers), l.workers); };
     expect(what, log(l.at_13) == 13 && log(l.at_12) == 12, true);
   }
+  // Stores at once, by the entries of all workers in 8192 positions: 0 where a tile is not paced.
+  const struct { int64_t elements; int32_t workers; double in_8192; uint32_t log, want; } paces[] = {
+      {64 << 20, 3, 4.0, 13, 0}, {64 << 20, 3, 5.0, 13, 1}, {64 << 20, 16, 13.0, 13, 2}, {64 << 20, 64, 52.0, 13, 4}, {64 << 20, 64, 66.0, 13, 0},
+      {64 << 20, 2, 33.0, 12, 1}, {64 << 20, 3, 49.0, 12, 0}, {64 << 20, 1, 33.0, 11, 0}, {64 << 20, 65, 53.0, 13, 1}, {64 << 20, 128, 105.0, 13, 2},
+      {64 << 20, 100, 164.0, 13, 0}, {64 << 20, 129, 53.0, 13, 0}, {48 << 20, 3, 5.0, 13, 1}, {(48 << 20) - 1, 3, 5.0, 13, 0}, {0, 1, 0.0, 13, 0}};
+  for (const auto& p : paces) {
+    char what[80];
+    std::snprintf(what, sizeof what, "%d workers, %.0f entries in 8192 of %lld", p.workers, p.in_8192, static_cast<long long>(p.elements));
+    expect(what, stores_at_once(p.elements, static_cast<int64_t>(p.in_8192 * static_cast<double>(p.elements) / kTile), p.workers, p.log) == p.want, true);
+  }
   std::printf(faults == 0 ? "tiles_check ok\n" : "tiles_check: %d faults\n", faults);
   return faults == 0 ? 0 : 1;
 }
