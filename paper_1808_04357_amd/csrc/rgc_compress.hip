@@ -2485,8 +2485,8 @@ constexpr uint32_t kListsRoom = kHistBins / 2u;      // members in the histogram
 
 // Launch 2 of a call with dense layers (PH_SEL2), for the layers whose streaming pass found the k-th key below
 // its clip bin.  Every wave takes its own wave-chunk's list; the layer's last workgroup ranks the members of the
-// k-th key's coarse bin (in global memory: there may be more of them than one workgroup's LDS holds), credits the
-// selected ones to their wave-chunks, scans the group sums into offsets and schedules the output step.
+// k-th key's coarse bin (in the LDS up to kListsRoom of them, more of them in global memory), credits the selected ones
+// to their wave-chunks, scans the group sums into offsets and schedules the output step.
 __device__ __forceinline__ void dense_rank(const CompressArgs& A, uint32_t l, const LayerDesc& L, LayerState* st, uint32_t wg,
                            ResolveShared& sh, unsigned long long* sortbuf, uint32_t* sel_hist, uint32_t* shard_first) {
   const uint32_t tau = st->cur_tau, shift = st->cur_shift, bstar = st->bstar;

@@ -457,10 +457,6 @@ __device__ __forceinline__ uint32_t quad_sum(uint32_t v) {
   return v;
 }
 
-__device__ __forceinline__ uint32_t quad_lane0(uint32_t v) {
-  return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x00, 0xF, 0xF, true));  // quad_perm [0,0,0,0]
-}
-
 constexpr int kRawBuffer = 0x00027000;   // fourth word of a buffer descriptor: 32-bit elements, addressed by bytes
 constexpr int kNonTemporal = 2;          // cache policy of a buffer access: the "nt" bit
 

@@ -186,8 +186,8 @@ __device__ __forceinline__ void accum4(const float (&g)[4], const float (&v)[4],
 // for the group kAhead further on, when it has read them and before it stores anything.  Loads and stores share one counter, in
 // order, so a wait for loads that were issued after stores would be a wait for the stores too.  (Four groups' loads, then their work and
 // stores, then the next four, against this with kAhead = 1 / 2 / 4, us per call: dense layers, whose lists leave them little room, ResNet-50
-// set at 1.5625 % 102.9 / 96.2 / 100.1 / -, VGG16 set at 25 % 913 / 901 / 899 / -; thresholds reused, LSTM set 167.7 / 167.9 / 166.6 /
-// 163.5, searched, 126 M elements at 0.4 % 384 / 386 / 382 / 376; without hints, LSTM set 337 / 349 / 342 / 334.)
+// set at 1.5625 % 102.9 / 96.2 / 100.1 / -, VGG16 set at 25 % 913 / 901 / 899 / -, where its runs differ by as much; thresholds reused, LSTM
+// set 167.7 / 167.9 / 166.6 / 163.5, searched, 126 M elements at 0.4 % 384 / 386 / 382 / 376; without hints, LSTM set 337 / 349 / 342 / 334.)
 template <bool kNt, bool kMom, uint32_t kAhead, typename F>
 __device__ __forceinline__ void stream_groups(gcvf4 G4, gvf4 V4, gvf4 U4, uint32_t groups, F&& f) {
   const uint32_t lane = lane_id();

@@ -258,7 +258,9 @@ struct ThresholdArgs {
 };
 
 // Up to this many workgroups a layer, every workgroup that writes a part of the message adds the counts of those before it up by itself
-// (268 M elements; 32 KB each at most, 16 on average.  In a layer of 2^31 elements that would be 131 KB each, 8.6 GB together.)
+// (268 M elements; 32 KB each at most, 16 on average.  In a layer of 2^31 elements that would be 131 KB each, 8.6 GB together.)  The
+// line is a cautious one: a launch that scans / adding, us, thresholds reused and searched: 66 M elements 166 / 157, 206 / 198; 265 M 610 / 580,
+// 707 / 676; beyond it 300 M 689 / 657, 796 / 766; 1000 M 2424 / 2223, 2619 / 2506.
 constexpr uint32_t kOffsetsWgs = 8192;
 
 // The sample of a searching threshold call: kPieceElems elements from each of up to kSampleThreads places of a layer, and the
@@ -317,11 +319,12 @@ struct DecompressArgs {
   uint32_t num_blocks;        // (With num_tiles behind num_layers the tile kernel loads the two together, its code moves by eight bytes, and 256
   uint32_t num_tiles;         // messages on the ResNet-50 set take 78.9 us instead of 74.7, added 96.6 instead of 92.0.)
   uint32_t add_to_dst;
-  uint16_t tile_log;          // positions a tile, a power of two
+  uint16_t tile_log;          // logarithm of the positions a tile
   uint16_t wait_after;        // bit j: a lane waits for its stores after its j-th one of a tile (0: no rule; see stores_at_once())
   uint32_t one_value;         // every message's val points to ONE float that all its entries carry
   float scale;
 };
+static_assert(offsetof(DecompressArgs, num_blocks) == 48 && offsetof(DecompressArgs, num_tiles) == 52, "the tile kernel's code depends on these");
 
 // Records the text of a failed HIP call for rgc_strerror and returns RGC_EHIP (defined with the host API).
 int fail_hip(hipError_t e, const char* what);

@@ -582,9 +582,8 @@ __global__ void __launch_bounds__(kBlockThreads) threshold_emit_kernel(Threshold
   uint32_t out_pos = p.begin != p.end ? A.counts[p.wc] : 0u;
   if (A.scanned == 0u) {
     // Where this wave's part of the message begins: every workgroup adds the counts of those before it up by itself, sixteen words of a
-    // thread in flight.  (With one workgroup a layer and a launch for that instead, us per call: LSTM set searching 217 / 204, reusing
-    // 163.8 / 160.4, 126 M elements in two tensors 0.4 % 378 / 364, 0.2 M in three 17.8 / 15.9; some 1.5 us of the searching calls'
-    // difference are the moments' sums and maxima.)
+    // thread in flight.  (With one workgroup a layer and a launch for that instead, us per call, thresholds reused and searched: 66 M elements in
+    // one tensor 165.9 / 157.5, 206.2 / 198.3, 134 M 315 / 294, 373 / 359, 400 M in four 915 / 879, 1044 / 1015.)
     __shared__ uint32_t sums[kWavesPerBlock], counts[kWavesPerBlock];
     const uint32_t wave = threadIdx.x >> 6, before = wg - L.wg_first;
     const gptr<const uint32_t> c = as_global(static_cast<const uint32_t*>(A.wg_counts)) + L.wg_first;

@@ -198,9 +198,8 @@ def test_config5_full_size(rgc, oracle):
     print("  oracle", flush=True)
     ref = oracle_all(oracle, idx, val, sizes, 1.0 / 128)
     compare("C5", got, ref)
-    # The benchmark's step decompresses right after a compression call on the same context, and the
-    # library then reads the messages with streaming loads (another instantiation of the tile kernel):
-    # the same messages once more in that configuration.
+    # The benchmark's step decompresses right after a compression call on the same context: the same messages
+    # once more in that position.
     import torch
     dev = torch.device("cuda:0")
     n, k = 1000, 1

@@ -70,3 +70,24 @@ def test_layers_whose_lists_may_not_do(rgc, oracle, filler, law, listed):
     for t in range(3):
         r.step([draw(0.05), (g.standard_normal(200_000) * 0.1).astype(np.float32), filler[1][:more]], search=True)
     r.close()
+
+
+@pytest.mark.parametrize("clustered", [False, True])
+@pytest.mark.parametrize("ppm", [30_000, 62_500, 250_000])
+def test_small_lists_of_dense_layers(rgc, oracle, ppm, clustered):
+    """Small calls that no tiled call can take: wave-chunks of 2048 elements with 128 slots each, which hold what lies above a reused
+    threshold, or run over (everywhere at the higher densities, where the values sit together at all)."""
+    g = np.random.default_rng(ppm + clustered)
+    sizes = [2047, 2049, 8193, 300_001, 700_001]
+    ks = [rgc.rgc_k_for_density(n, ppm) for n in sizes]
+
+    def draw(s):
+        a = [(g.standard_normal(n) * s).astype(np.float32) for n in sizes]
+        if clustered:
+            a = [x * np.where(g.random(-(-x.size // 2048)) < 0.1, np.float32(20.0), np.float32(1.0)).repeat(2048)[:x.size] for x in a]
+        return a
+
+    r = Runner(rgc, oracle, draw(1.0), ks, U0=draw(0.1), m=0.9, misalign=1, tag="threshold small")
+    for search in (True, False, True, False):
+        r.step(draw(0.05), search=search)
+    r.close()
